@@ -219,3 +219,104 @@ def tolerance(case):
     if case["dtype"] == "bf16":
         return {"rel": 1e-2 if case["d"] == 128 else 7e-3}
     return {"rel": 5e-6 if case["op"] == "softmax" else 1.5e-6}
+
+
+def _chunked64(Q, K, V, dO, lam, C, L):
+    """Causal linear attention of one document in 64 bits, [G,n,d] tensors: O, the states before each slot of L
+    tokens, dQ, dK, dV (chunks of C tokens, one state carried from chunk to chunk).  lam: [G] factors, or None."""
+    G, n, d = Q.shape
+    T = -(-n // C)
+    a = torch.arange(C, device=Q.device, dtype=torch.float64)
+    lam = torch.ones(G, dtype=torch.float64, device=Q.device) if lam is None else lam
+    pw = lam[:, None] ** torch.arange(C + 1, device=Q.device)                       # [G,C+1]
+    W = torch.tril(lam[:, None, None] ** (a[:, None] - a[None, :]).clamp(min=0))[:, None]
+    up = lambda x: None if x is None else torch.nn.functional.pad(x, (0, 0, 0, T * C - n)).view(G, T, C, d)
+    Q, K, V, dO = up(Q), up(K), up(V), up(dO)
+    tr = lambda x: x.transpose(-1, -2).contiguous()
+    down = lambda x: x.reshape(G, T * C, d)[:, :n]
+
+    def carry(M, order):
+        out, S = torch.empty_like(M), torch.zeros_like(M[:, 0])
+        for t in order:
+            out[:, t] = S
+            S = pw[:, C, None, None] * S + M[:, t]
+        return out
+    S = carry(tr(K * pw[:, :C].flip(1)[:, None, :, None]) @ V, range(T))
+    grow = pw[:, 1:][:, None, :, None]
+    O = down((W * (Q @ tr(K))) @ V + grow * (Q @ S))
+    P = S[:, ::L // C]
+    if dO is None:
+        return O, P
+    R = carry(tr(Q * pw[:, :C][:, None, :, None]) @ dO, range(T - 1, -1, -1))
+    fall = pw[:, 1:].flip(1)[:, None, :, None]
+    dQ = down((W * (dO @ tr(V))) @ K + grow * (dO @ tr(S)))
+    del S
+    dK = down((tr(W) * (V @ tr(dO))) @ Q + fall * (V @ tr(R)))
+    return O, P, dQ, dK, down((tr(W) * (K @ tr(Q))) @ dO + fall * (K @ R))
+
+
+def _softmax64(Q, K, V, dO, causal, q0):
+    """Softmax attention of one document in 64 bits, [n,d] queries at positions q0.. against [N,d] keys:
+    O, log-sum-exp, dQ, dK, dV, in blocks of 2048 queries."""
+    (n, d), N = Q.shape, K.shape[0]
+    O, lse = torch.empty_like(Q), Q.new_empty(n)
+    dQ, dK, dV = (torch.zeros_like(x) for x in (Q, K, V))
+    for i in range(0, n, 2048):
+        j = min(n, i + 2048)
+        m = q0 + j if causal else N
+        s = (Q[i:j] @ K[:m].T).div_(math.sqrt(d))
+        if causal:
+            at = torch.arange(q0 + i, q0 + j, device=Q.device)
+            s.masked_fill_(torch.arange(m, device=Q.device)[None] > at[:, None], -math.inf)
+        lse[i:j] = torch.logsumexp(s, 1)
+        p = s.sub_(lse[i:j, None]).exp_()
+        O[i:j] = p @ V[:m]
+        if dO is not None:
+            g = dO[i:j]
+            dV[:m] += p.T @ g
+            ds = (g @ V[:m].T).sub_((g * O[i:j]).sum(1, keepdim=True)).mul_(p).div_(math.sqrt(d))
+            dQ[i:j] = ds @ K[:m]
+            dK[:m] += ds.T @ Q[i:j]
+    return (O, lse) if dO is None else (O, lse, dQ, dK, dV)
+
+
+def exact(case, seed):
+    """What run() returns, from the definitions in 64 bits with torch alone."""
+    c = case
+    s = prepare(c, seed)
+    B, H, G, N = c["B"], c["H"], c["B"] * c["H"], c["N"]
+    Q, K, V, dO = (s[n].double().view(G, -1, c["d"]) if n in s else None for n in ("Q", "K", "V", "dO"))
+    cu = [0, N] if not c["docs"] else [int(x) for x in _offsets(c)]
+    part = lambda x, g, lo, hi: None if x is None else x[g, lo:hi]
+    if c["op"] == "softmax":
+        heads = []
+        for g in range(G):
+            docs = []
+            for lo, hi in zip(cu[:-1], cu[1:]):
+                ql, qh = (0, c["q_len"]) if c["q_len"] else (lo, hi)
+                docs.append(_softmax64(Q[g, ql:qh], K[g, lo:hi], V[g, lo:hi], part(dO, g, ql, qh), c["causal"],
+                                       N - c["q_len"] if c["q_len"] else 0))
+            heads.append([torch.cat(x) for x in zip(*docs)])
+        return tuple(torch.stack(x).view((B, H) + x[0].shape) for x in zip(*heads))
+    if c["op"] == "nomask":
+        tr = lambda x: x.transpose(-1, -2).contiguous()
+        L, outs = c["L"] or c["C"], []
+        for lo, hi in zip(cu[:-1], cu[1:]):
+            q, k, v, g = (part(x, slice(None), lo, hi) for x in (Q, K, V, dO))
+            S = tr(k) @ v
+            out = [q @ S, S[:, None].expand(-1, -(-(hi - lo) // L), -1, -1)]
+            if g is not None:
+                R = tr(q) @ g
+                out += [g @ tr(S), v @ tr(R), k @ R]
+            outs.append(out)
+    else:
+        lam = None
+        if c["decay"]:
+            lam = torch.from_numpy((1.0 - 2.0 ** (-5.0 - np.arange(H))).astype(np.float32)).cuda().double().repeat(B)
+        outs = [_chunked64(*(part(x, slice(None), lo, hi) for x in (Q, K, V, dO)), lam, c["C"], c["L"] or c["C"])
+                for lo, hi in zip(cu[:-1], cu[1:])]
+    out = [torch.cat(x, 1) for x in zip(*outs)]
+    if c["serial"]:
+        del out[1]
+    out = [x.reshape((B, H) + x.shape[1:]) for x in out]
+    return out[0] if len(out) == 1 else tuple(out)
