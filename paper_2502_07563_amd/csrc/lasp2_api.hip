@@ -186,6 +186,21 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
     return (int)ws;
 }
 
+// Slots per walk of the split-plane kernels, `nprob` workgroups per walk.  They work on chunks of 128
+// rows: slots that leave chunks partly empty (one state per 64 tokens, say) are taken two, four or
+// eight at a time while that still gives every CU a workgroup, and P is read at the first only.  (d = 32, fp32,
+// 64-token slots: forward pass 123 -> 92 us.)
+int pick_planes_slots(const Geom& g, const int32_t* cu_host, int nprob)
+{
+    int ws = 1;
+    while (ws < 8 && g.L * ws < 512 && (g.L * ws) % 128 != 0) {
+        const Geom w = regroup(g, cu_host, 2 * ws);
+        if (w.T_s == g.T_s || (int64_t)w.G * w.T_s * nprob < cu_count()) break;
+        ws *= 2;
+    }
+    return ws;
+}
+
 // (backward, equal sequences: two rounds of 16 384-token walks beat eight of 4 096 by 2 % at config 3 -
 // the states kernel writes fewer states; ragged documents do best at 4 096)
 constexpr int64_t kWalkTargetFwd = 2048, kWalkTargetBwd = 16384, kWalkTargetBwdPacked = 4096;
@@ -212,7 +227,7 @@ hipError_t run_states(const Geom& g, int dtype, const void* K, const void* V, fl
                       int anchor_start, hipStream_t st)
 {
     if (mfma_path_supported(g, dtype)) return launch_states_mfma(g, K, V, M, anchor_start, st);
-    return launch_states_generic(g, dtype, K, V, M, anchor_start, st);
+    return launch_states_planes(g, dtype, K, V, M, anchor_start, st);
 }
 
 // What lasp2_attn_bwd and lasp2_attn_bwd_noalloc have in common: the checks that need no
@@ -268,7 +283,7 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     return LASP2_OK;
 }
 
-int run_attn_bwd(const BwdPlan& pl, int dtype, const void* Q, const void* K, const void* V, const void* dO,
+int run_attn_bwd(const BwdPlan& pl, int dtype, const int32_t* cu_host, const void* Q, const void* K, const void* V, const void* dO,
                  const float* P, void* dQ, void* dK, void* dV, float* dR, hipStream_t st)
 {
     const Geom& g = pl.gw;
@@ -287,16 +302,8 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const void* Q, const void* K, con
         unsigned* pace = dR ? reinterpret_cast<unsigned*>(reinterpret_cast<char*>(dR) + states_bytes(g)) : nullptr;
         return from_hip(launch_attn_bwd_mfma(g, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, pace, dQ, dK, dV, st));
     }
-    // dQ: the forward problem with (dO, V, K) in the roles of (Q, K, V); its state is
-    // V^T K = (K^T V)^T, i.e. the cached prefix read transposed.
-    e = launch_attn_generic(g, dtype, dO, V, K, P, dQ, 1, 0, st);
-    if (e != hipSuccess) return LASP2_ERR_LAUNCH;
-    // dV: anti-causal problem with (K, Q, dO); state dM_{t+1:T} = sum Q^T dO.
-    e = launch_attn_generic(g, dtype, K, Q, dO, dR, dV, 0, 1, st);
-    if (e != hipSuccess) return LASP2_ERR_LAUNCH;
-    // dK: anti-causal problem with (V, dO, Q); state dO^T Q = dM^T.
-    e = launch_attn_generic(g, dtype, V, dO, Q, dR, dK, 1, 1, st);
-    return from_hip(e);
+    const Geom gp = regroup(g, cu_host, pick_planes_slots(g, cu_host, 3));
+    return from_hip(launch_attn_bwd_planes(gp, dtype, Q, K, V, dO, P, dR, dQ, dK, dV, st));
 }
 
 // Scratch of lasp2_attn_bwd_noalloc: device memory that belongs to the loaded library itself, one
@@ -404,7 +411,8 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
         const Geom gw = regroup(g, desc->cu_seqlens_host, pick_walk_slots(g, desc->cu_seqlens_host, cu_count(), kWalkTargetFwd));
         return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
     }
-    return from_hip(launch_attn_generic(g, desc->dtype, Q, K, V, P, O, 0, 0, st));
+    const Geom gp = regroup(g, desc->cu_seqlens_host, pick_planes_slots(g, desc->cu_seqlens_host, 1));
+    return from_hip(launch_attn_fwd_planes(gp, desc->dtype, Q, K, V, P, O, st));
 }
 
 int lasp2_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,
@@ -416,7 +424,7 @@ int lasp2_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
     if (rc != LASP2_OK) return rc;
     if (pl.empty) return LASP2_OK;
     if (pl.need_states && workspace_bytes < pl.need) return LASP2_ERR_WORKSPACE;
-    return run_attn_bwd(pl, desc->dtype, Q, K, V, dO, P, dQ, dK, dV,
+    return run_attn_bwd(pl, desc->dtype, desc->cu_seqlens_host, Q, K, V, dO, P, dQ, dK, dV,
                         pl.need_states ? static_cast<float*>(workspace) : nullptr, (hipStream_t)stream);
 }
 
@@ -435,7 +443,7 @@ int lasp2_attn_bwd_noalloc(const lasp2_desc_t* desc, const void* Q, const void* 
     }
     // Nothing in the array has to start at zero: the states kernel writes every slot's state
     // before the combine and the attention kernels read any of it.
-    return run_attn_bwd(pl, desc->dtype, Q, K, V, dO, P, dQ, dK, dV, dR, (hipStream_t)stream);
+    return run_attn_bwd(pl, desc->dtype, desc->cu_seqlens_host, Q, K, V, dO, P, dQ, dK, dV, dR, (hipStream_t)stream);
 }
 
 int lasp2_state_total(const lasp2_desc_t* desc, const float* M, float* S, void* stream)

@@ -151,17 +151,16 @@ inline int cu_count()
 
 // ---- launchers implemented in the kernel files (return hipGetLastError()) ----
 
-// Plain fp32-FMA kernels, any supported (dtype, d, C).
+// Split-plane matrix-core kernels (kernels_planes.hip), any supported (dtype, d, C).
 // anchor_start (decay only): weights lam^(token - slot start) instead of lam^(slot end - token).
-hipError_t launch_states_generic(const Geom& g, int dtype, const void* K, const void* V,
-                                 float* M, int anchor_start, hipStream_t st);
-// out = [(A Bk^T) (.) mask] Cv + A * state, state += Bk^T Cv chunk by chunk.
-//   reverse = 0: causal mask, chunks walked first to last, state = prefix;
-//   reverse = 1: anti-causal mask (j >= i), chunks walked last to first, state = suffix.
-//   transpose_state: the d x d slot state is read transposed.
-hipError_t launch_attn_generic(const Geom& g, int dtype, const void* A, const void* Bk,
-                               const void* Cv, const float* state, void* out,
-                               int transpose_state, int reverse, hipStream_t st);
+hipError_t launch_states_planes(const Geom& g, int dtype, const void* K, const void* V,
+                                float* M, int anchor_start, hipStream_t st);
+hipError_t launch_attn_fwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V,
+                                  const float* P, void* O, hipStream_t st);
+// dR: EXCLUSIVE suffix states of Q^T dO; P, dR NULL: zero (every document a single slot)
+hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V,
+                                  const void* dO, const float* P, const float* dR, void* dQ, void* dK,
+                                  void* dV, hipStream_t st);
 // inclusive = 0: P[s] excludes M[s] (the public entry point); 1: P[s] includes it.
 hipError_t launch_state_prefix(const Geom& g, const float* M, float* P, int reverse, int inclusive,
                                hipStream_t st);

@@ -1,0 +1,93 @@
+"""The split-plane matrix-core kernels (fp32, and bf16 with d < 128) where their tiling can go wrong: lengths around
+the 32-token tiles and 128-row chunks, slots taken several at a time, slots cut into segments, every head
+size, packed documents, and values whose bf16 planes matter.
+
+Tolerance, fp32: every product carries a relative error below 2^-24 and sums of n terms in fp32 a few times
+2^-24 sqrt(n); n <= 2048 here, so 1e-6 of the row norm is ten times what rounding gives, and a lost middle
+plane (2^-9) or low plane (2^-17 = 8e-6) fails.  bf16: outputs are rounded to 2^-9, 4e-3 of a row at most."""
+import numpy as np
+import pytest
+
+from tests.util import host_inputs, rel_l2, to_device, to_host
+
+pytestmark = pytest.mark.gpu
+LIMIT = {"f32": 1e-6, "bf16": 4e-3}
+
+
+@pytest.fixture(scope="module")
+def oracle():
+    import oracle as o
+    return o
+
+
+def _want(oracle, x, bounds, lam, H):
+    """Definition in 64 bits, document by document."""
+    parts = []
+    for a, b in zip(bounds[:-1], bounds[1:]):
+        t = {n: v[:, a:b].astype(np.float64) for n, v in x.items()}
+        d = np.arange(b - a)[:, None] - np.arange(b - a)[None]
+        w = np.tril(np.ones((b - a, b - a)))[None] if lam is None else np.where(d >= 0, np.float64(lam)[:, None, None] ** np.maximum(d, 0), 0.0)
+        if lam is not None:
+            w = np.tile(w, (x["Q"].shape[0] // H, 1, 1))
+        s = (t["Q"] @ t["K"].transpose(0, 2, 1)) * w
+        g = (t["dO"] @ t["V"].transpose(0, 2, 1)) * w
+        parts.append((s @ t["V"], g @ t["K"], g.transpose(0, 2, 1) @ t["Q"], s.transpose(0, 2, 1) @ t["dO"]))
+    return [np.concatenate(p, axis=1) for p in zip(*parts)]
+
+
+def _run(oracle, dtype, B, H, N, d, C, L, cu=None, lam=None, seed=5):
+    from paper_2502_07563_amd import binding as bd
+    x = host_inputs(seed, B * H, N, d, dtype)
+    p = bd.Problem(B, H, N, d, C, L, dtype, cu, decay=lam)
+    t = {n: to_device(v, B, H, dtype) for n, v in x.items()}
+    O, P = bd.forward(p, t["Q"], t["K"], t["V"])
+    dQ, dK, dV, _ = bd.backward(p, t["Q"], t["K"], t["V"], t["dO"], P)
+    want = _want(oracle, x, [0, N] if cu is None else list(cu), lam, H)
+    for name, got, ref in zip(("O", "dQ", "dK", "dV"), (O, dQ, dK, dV), want):
+        err = rel_l2(to_host(got), ref)
+        assert err <= LIMIT[dtype], (name, dtype, B, H, N, d, C, L, err)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 16), ("bf16", 32), ("bf16", 64)])
+@pytest.mark.parametrize("lam", [None, 0.97, 1e-3])
+def test_tile_edges(oracle, dtype, d, lam):
+    """Lengths on both sides of a tile (32), a stage (64) and a chunk (128); slots shorter than a chunk, taken
+    several at a time or not; a slot cut into segments (few workgroups, L = 1024)."""
+    f = None if lam is None else np.array([lam, 1.0], dtype=np.float32)
+    for N, C, L in ((1, 1, 0), (31, 32, 0), (33, 64, 0), (129, 128, 0), (255, 64, 0), (300, 50, 0), (1100, 64, 1024)):
+        _run(oracle, dtype, 1, 2, N, d, C, L, lam=f)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 32), ("f32", 128), ("bf16", 64)])
+def test_packed_documents_and_merged_slots(oracle, dtype, d):
+    lens = [64, 1, 127, 128, 129, 65, 300, 31]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    _run(oracle, dtype, 1, 2, int(cu[-1]), d, 64, 64, cu=cu)
+    # enough groups that 64-token slots are taken two at a time
+    _run(oracle, dtype, 16, 16, 200, d, 64, 64)
+    cu = np.array([0, 70, 200, 391], dtype=np.int32)
+    _run(oracle, dtype, 1, 256, 391, d, 32, 32, cu=cu, lam=np.full(256, 0.9, dtype=np.float32))
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 32), ("f32", 128)])
+def test_rows_that_the_mask_keeps_from_a_nan_stay_finite(dtype, d):
+    """A NaN in V at token j reaches O at j and later, one in dO and Q the rows of dV and dK at j and before:
+    not the other rows of the tile it lies in."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    N, j = 400, 177
+    x = {n: to_device(v, 1, 2, dtype) for n, v in host_inputs(9, 2, N, d, dtype).items()}
+    p = bd.Problem(1, 2, N, d, 128, 0, dtype)
+    good, P = bd.forward(p, x["Q"], x["K"], x["V"])
+    V = x["V"].clone()
+    V[:, :, j, 3] = float("nan")
+    O, _ = bd.forward(p, x["Q"], x["K"], V)
+    assert torch.isfinite(O[:, :, :j]).all() and torch.isnan(O[:, :, j:, 3]).all()
+    assert rel_l2(to_host(O[:, :, :j]), to_host(good[:, :, :j])) <= LIMIT[dtype]
+    dO = x["dO"].clone()
+    dO[:, :, j, 3] = float("inf")
+    _, gk, gv, _ = bd.backward(p, x["Q"], x["K"], x["V"], x["dO"], P)
+    _, dK, dV, _ = bd.backward(p, x["Q"], x["K"], x["V"], dO, P)
+    assert torch.isfinite(dV[:, :, j + 1:]).all() and not torch.isfinite(dV[:, :, :j + 1, 3]).any()
+    assert torch.isfinite(dK[:, :, j + 1:]).all()
+    assert rel_l2(to_host(dV[:, :, j + 1:]), to_host(gv[:, :, j + 1:])) <= LIMIT[dtype]
