@@ -1,0 +1,604 @@
+// Softmax attention on the matrix cores for the shapes kernels_softmax.hip does not take (fp32 of any head
+// size, bf16 with d < 128).  All products go through split planes (planes.h): scores, probabilities and
+// their gradients have fp32 accuracy whatever the input type.
+//
+// One scheme serves the three kernels.  A wave owns 32 rows (queries, or keys for dK and dV), a row per lane, its
+// operands in registers; the partner rows pass through LDS in stages.  Scores are formed transposed, so
+// the row statistics are per-lane scalars and the probabilities are the next product's operand as they
+// stand.  The waves of a workgroup are QW row tiles times KW shares of the partner rows, whose results are
+// merged at the end: 4 x 1 when such workgroups fill the device; 2 x 4 otherwise, where the longest causal
+// row sets the time.  The two row tiles are then mirrored (tile i with the i-th from the end), and a SIMD
+// has one wave of each, so that every workgroup has the same number of tiles.
+// Bounds: vector instructions - in fp32 the splits of the stages (five and a half per element) and of the scores -
+// and the matrix products beside them (six bf16 ones per fp32 one).
+#include "planes.h"
+
+#include <algorithm>
+
+namespace lasp2 {
+namespace {
+
+constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+
+template <typename T, int D, int QW_, int KW_>
+struct SmCfg {
+    static constexpr int NP = planes_of<T>::n, DP = D < 32 ? 32 : D, NT = DP / 32, KS = D / 16, QW = QW_, KW = KW_, THR = 64 * QW * KW;
+    static constexpr int ROWS = 32 * KW < 64 && !(NP == 3 && D == 128) ? 64 : 32 * KW;   // partner rows per stage
+    typedef PairStage<T, D, DP, ROWS, THR> Stage;
+    static constexpr bool own_lds = NP == 3 && D == 64 && KW == 4;   // dK, dV: own rows in LDS
+    static constexpr int MERGE = (KW - 1) * QW * 64 * 4;      // bytes per merged register
+    static constexpr int lds(int merged, int extra)            // stage, or the merge of `merged` registers per lane
+    {
+        return Stage::BYTES + extra > merged * MERGE ? Stage::BYTES + extra : merged * MERGE;
+    }
+};
+
+// First row of wave tile qw of workgroup bx (tiles of 32 of `rows` rows; a start at or past `rows`: none).
+template <int QW>
+__device__ __forceinline__ int tile_row(int bx, int qw, int rows, bool mirrored)
+{
+    if (QW != 2 || !mirrored) return 32 * (bx * QW + qw);
+    const int tiles = (rows + 31) / 32, last = tiles - 1 - bx;
+    return 32 * (qw == 0 ? last : last == bx ? tiles : bx);
+}
+
+// First row of the workgroup's tiles and the one past its last.
+template <int QW>
+__device__ __forceinline__ void wg_rows(int bx, int rows, bool mirrored, int& r0, int& r1)
+{
+    const bool m = QW == 2 && mirrored;
+    r0 = m ? 32 * bx : 32 * QW * bx;
+    r1 = min(rows, m ? 32 * ((rows + 31) / 32 - bx) : 32 * QW * (bx + 1));
+}
+
+// Document of token i: [lo, hi).
+__device__ __forceinline__ void doc_of(const Geom& g, int i, int& lo, int& hi)
+{
+    lo = 0;
+    hi = g.N;
+    if (g.n_seqs == 0) return;
+    int a = 0, b = g.n_seqs;   // cu[a] <= i < cu[b]
+    while (b - a > 1) {
+        const int m = (a + b) >> 1;
+        if (g.cu[m] <= i) a = m; else b = m;
+    }
+    lo = g.cu[a];
+    hi = g.cu[a + 1];
+}
+
+// keys of query token i
+__device__ __forceinline__ void keys_of(const Geom& g, int i, int causal, int& lo, int& hi)
+{
+    doc_of(g, i, lo, hi);
+    if (causal) hi = i + 1;
+}
+
+// the share's query tokens that see key j
+__device__ __forceinline__ void queries_of(const Geom& g, int j, int causal, int& lo, int& hi)
+{
+    doc_of(g, j, lo, hi);
+    if (causal) lo = j;
+    lo = max(lo, g.q0);
+    hi = min(hi, g.q0 + g.qn);
+}
+
+// s = X_tile . own rows: lane = own row, accumulator rows = the 32 partner rows at `tile`
+template <int DP, int KS, int NP>
+__device__ __forceinline__ f32x16 scores(const char* tile, int plane_bytes, const bf16x8 (&own)[KS][NP], int l32, int h)
+{
+    f32x16 s = zero16();
+    if constexpr (NP > 1) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            bf16x8 k[NP];
+            row_frag<DP>(tile, plane_bytes, l32, 2 * ks + h, k);
+            s = mm<1, 2>(k, own[ks], s);
+        }
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        bf16x8 k[1];
+        row_frag<DP>(tile, plane_bytes, l32, 2 * ks + h, k);
+        s = mm<0, 0>(k, own[ks], s);
+    }
+    return s;
+}
+
+// the same with the own rows in LDS too
+template <int DP, int KS, int NP>
+__device__ __forceinline__ f32x16 scores(const char* tile, int plane_bytes, const char* own, int own_plane, int l32, int h)
+{
+    f32x16 s = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        bf16x8 k[NP], o[NP];
+        row_frag<DP>(tile, plane_bytes, l32, 2 * ks + h, k);
+        row_frag<DP>(own, own_plane, l32, 2 * ks + h, o);
+        s = mm<1, 2>(k, o, s);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        bf16x8 k[1], o[1];
+        row_frag<DP>(tile, plane_bytes, l32, 2 * ks + h, k);
+        row_frag<DP>(own, own_plane, l32, 2 * ks + h, o);
+        s = mm<0, 0>(k, o, s);
+    }
+    return s;
+}
+
+// acc[nt] (lane = own row, rows = columns of X) += X_tile^T . p over the 32 partner rows
+template <int DP, int NP>
+__device__ __forceinline__ void accumulate(f32x16 (&acc)[DP / 32], const char* tile, int plane_bytes, const f32x16& p, int lane)
+{
+    bf16x8 f[2][3];
+    acc_frag(p, 0, f[0]);
+    acc_frag(p, 8, f[1]);
+#pragma unroll
+    for (int nt = 0; nt < DP / 32; ++nt) {
+        bf16x8 x[2][NP];
+        col_frag<DP>(tile, plane_bytes, 0, 32 * nt, lane, x[0]);
+        col_frag<DP>(tile, plane_bytes, 16, 32 * nt, lane, x[1]);
+        const f32x16 low = mm<1, 2>(x[1], f[1], mm<1, 2>(x[0], f[0], zero16()));
+        acc[nt] = mm<0, 0>(x[1], f[1], mm<0, 0>(x[0], f[0], acc[nt] + low));
+    }
+}
+
+__device__ __forceinline__ void store4(float* p, const float (&x)[4])
+{
+    const f32x4 v = {x[0], x[1], x[2], x[3]};
+    *reinterpret_cast<f32x4*>(p) = v;
+}
+__device__ __forceinline__ void store4(__hip_bfloat16* p, const float (&x)[4])
+{
+    const u32x2 v = {pack2(x[0], x[1]), pack2(x[2], x[3])};
+    *reinterpret_cast<u32x2*>(p) = v;
+}
+
+// row of out (D elements) from a transposed accumulator, times f
+template <typename T, int D>
+__device__ __forceinline__ void store_row(T* row, const f32x16 (&acc)[(D < 32 ? 32 : D) / 32], float f, int h)
+{
+#pragma unroll
+    for (int nt = 0; nt < (D < 32 ? 32 : D) / 32; ++nt)
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) {
+            const int c = 32 * nt + acc_row(v) + 4 * h;
+            const float x[4] = {acc[nt][v] * f, acc[nt][v + 1] * f, acc[nt][v + 2] * f, acc[nt][v + 3] * f};
+            if (c < D) store4(row + c, x);
+        }
+}
+
+template <typename T, int D, int KS, int NP>
+__device__ __forceinline__ void load_rows(bf16x8 (&f)[KS][NP], const T* row, bool ok, int h)
+{
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) to_planes(load8(row + 16 * ks + 8 * h, ok), f[ks]);
+}
+
+template <typename T, int D, int QW, int KW>
+__global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K,
+                                                                  const T* __restrict__ V, T* __restrict__ O,
+                                                                  float* __restrict__ LSE, int causal)
+{
+    typedef SmCfg<T, D, QW, KW> Cf;
+    typedef typename Cf::Stage Stage;
+    constexpr int NP = Cf::NP, DP = Cf::DP, NT = Cf::NT, KS = Cf::KS, ROWS = Cf::ROWS;
+    extern __shared__ __align__(16) char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
+    const int qw = w / KW, kw = w % KW, grp = blockIdx.y;
+    const bool mirrored = causal && g.n_seqs == 0;
+    const int bx = mirrored ? blockIdx.x : gridDim.x - 1 - blockIdx.x;   // longest rows first (causal)
+    const int wr = tile_row<QW>(bx, qw, g.qn, mirrored), row = wr + l32;
+    int r0, r1;
+    wg_rows<QW>(bx, g.qn, mirrored, r0, r1);
+    const size_t kbase = (size_t)grp * (size_t)g.N * D, qbase = (size_t)grp * (size_t)g.qn * D;
+    const bool valid = row < g.qn;
+    int lo = 0, hi = 0;
+    if (valid) keys_of(g, g.q0 + row, causal, lo, hi);
+    // the wave's and the workgroup's key ranges: both ends grow with the query
+    int wlo = 0, whi = 0, klo, khi, t;
+    if (wr < g.qn) {
+        keys_of(g, g.q0 + wr, causal, wlo, t);
+        keys_of(g, g.q0 + min(wr + 31, g.qn - 1), causal, t, whi);
+    }
+    keys_of(g, g.q0 + r0, causal, klo, t);
+    keys_of(g, g.q0 + r1 - 1, causal, t, khi);
+
+    const unsigned span = (unsigned)max(hi - lo, 0);   // a partner row x counts if (unsigned)(x - lo) < span
+    bf16x8 q[KS][NP];
+    load_rows<T, D>(q, Q + qbase + (size_t)row * D, valid, h);
+    const float c = rsqrtf((float)D) * kLog2e;
+    float m = -INFINITY, l = 0.f;      // m: of the whole row, l: of this lane's half of the keys
+    f32x16 acc[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = zero16();
+
+    Stage st;
+    st.fetch(K + kbase, V + kbase, klo, khi, tid);
+    for (int k0 = klo; k0 < khi; k0 += ROWS) {
+        if (k0 > klo) __syncthreads();
+        st.put(smem, tid);
+        if (k0 + ROWS < khi) st.fetch(K + kbase, V + kbase, k0 + ROWS, khi, tid);
+        __syncthreads();
+#pragma unroll 1
+        for (int u = kw; u < ROWS / 32; u += KW) {
+            const int t0 = k0 + 32 * u;
+            if (t0 >= whi || t0 + 32 <= wlo) continue;
+            const char* kt = smem + u * 64 * DP;
+            f32x16 s = scores<DP, KS, NP>(kt, Stage::PLANE, q, l32, h);
+            float mx = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                s[v] = (unsigned)(t0 + 4 * h - lo + acc_row(v)) < span ? s[v] * c : -INFINITY;
+                mx = fmaxf(mx, s[v]);
+            }
+            mx = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)));
+            const float mu = mx == -INFINITY ? 0.f : mx;
+            const float alpha = __builtin_amdgcn_exp2f(m - mu);
+            m = mx;
+            float ps = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                s[v] = __builtin_amdgcn_exp2f(s[v] - mu);
+                ps += s[v];
+            }
+            l = fmaf(l, alpha, ps);
+            if (__any(alpha != 1.f)) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[nt] *= alpha;
+            }
+            accumulate<DP, NP>(acc, kt + Stage::TENSOR, Stage::PLANE, s, lane);
+        }
+    }
+    l += __shfl_xor(l, 32, 64);
+    if constexpr (KW > 1) {
+        float* part = reinterpret_cast<float*>(smem) + (((kw - 1) * QW + qw) * (16 * NT + 2)) * 64 + lane;
+        __syncthreads();
+        if (kw > 0) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) part[(16 * nt + v) * 64] = acc[nt][v];
+            part[16 * NT * 64] = m;
+            part[(16 * NT + 1) * 64] = l;
+        }
+        __syncthreads();
+        if (kw > 0) return;
+#pragma unroll 1
+        for (int k = 1; k < KW; ++k) {
+            const float* o = reinterpret_cast<const float*>(smem) + (((k - 1) * QW + qw) * (16 * NT + 2)) * 64 + lane;
+            const float om = o[16 * NT * 64], mn = fmaxf(m, om), mu = mn == -INFINITY ? 0.f : mn;
+            const float fa = __builtin_amdgcn_exp2f(m - mu), fb = __builtin_amdgcn_exp2f(om - mu);
+            l = l * fa + o[(16 * NT + 1) * 64] * fb;
+            m = mn;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[nt][v] = acc[nt][v] * fa + o[(16 * nt + v) * 64] * fb;
+        }
+    }
+    if (!valid) return;
+    store_row<T, D>(O + qbase + (size_t)row * D, acc, 1.f / l, h);
+    if (h == 0) LSE[(size_t)grp * g.qn + row] = fmaf(m, kLn2, logf(l));
+}
+
+// dQ = scale * sum_j dS_j k_j, with dS = P (dO.v - delta), P rebuilt from the log-sum-exp
+template <typename T, int D, int QW, int KW>
+__global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K,
+                                                                     const T* __restrict__ V, const T* __restrict__ dO,
+                                                                     const float* __restrict__ LSE, const float* __restrict__ delta,
+                                                                     T* __restrict__ dQ, int causal)
+{
+    typedef SmCfg<T, D, QW, KW> Cf;
+    typedef typename Cf::Stage Stage;
+    constexpr int NP = Cf::NP, DP = Cf::DP, NT = Cf::NT, KS = Cf::KS, ROWS = Cf::ROWS;
+    extern __shared__ __align__(16) char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
+    const int qw = w / KW, kw = w % KW, grp = blockIdx.y;
+    const bool mirrored = causal && g.n_seqs == 0;
+    const int bx = mirrored ? blockIdx.x : gridDim.x - 1 - blockIdx.x;   // longest rows first (causal)
+    const int wr = tile_row<QW>(bx, qw, g.qn, mirrored), row = wr + l32;
+    int r0, r1;
+    wg_rows<QW>(bx, g.qn, mirrored, r0, r1);
+    const size_t kbase = (size_t)grp * (size_t)g.N * D, qbase = (size_t)grp * (size_t)g.qn * D;
+    const bool valid = row < g.qn;
+    int lo = 0, hi = 0, wlo = 0, whi = 0, klo, khi, t;
+    float lse2 = 0.f, dlt = 0.f;
+    if (valid) {
+        keys_of(g, g.q0 + row, causal, lo, hi);
+        lse2 = LSE[(size_t)grp * g.qn + row] * kLog2e;
+        dlt = delta[(size_t)grp * g.qn + row];
+    }
+    if (wr < g.qn) {
+        keys_of(g, g.q0 + wr, causal, wlo, t);
+        keys_of(g, g.q0 + min(wr + 31, g.qn - 1), causal, t, whi);
+    }
+    keys_of(g, g.q0 + r0, causal, klo, t);
+    keys_of(g, g.q0 + r1 - 1, causal, t, khi);
+
+    const unsigned span = (unsigned)max(hi - lo, 0);
+    bf16x8 q[KS][NP], d[KS][NP];
+    load_rows<T, D>(q, Q + qbase + (size_t)row * D, valid, h);
+    load_rows<T, D>(d, dO + qbase + (size_t)row * D, valid, h);
+    const float scale = rsqrtf((float)D), c = scale * kLog2e;
+    f32x16 acc[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = zero16();
+
+    Stage st;
+    st.fetch(K + kbase, V + kbase, klo, khi, tid);
+    for (int k0 = klo; k0 < khi; k0 += ROWS) {
+        if (k0 > klo) __syncthreads();
+        st.put(smem, tid);
+        if (k0 + ROWS < khi) st.fetch(K + kbase, V + kbase, k0 + ROWS, khi, tid);
+        __syncthreads();
+#pragma unroll 1
+        for (int u = kw; u < ROWS / 32; u += KW) {
+            const int t0 = k0 + 32 * u;
+            if (t0 >= whi || t0 + 32 <= wlo) continue;
+            const char* kt = smem + u * 64 * DP;
+            f32x16 s = scores<DP, KS, NP>(kt, Stage::PLANE, q, l32, h);
+            const f32x16 dp = scores<DP, KS, NP>(kt + Stage::TENSOR, Stage::PLANE, d, l32, h);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c, -lse2)), ds = p * (dp[v] - dlt);
+                s[v] = (unsigned)(t0 + 4 * h - lo + acc_row(v)) < span ? ds : 0.f;
+            }
+            accumulate<DP, NP>(acc, kt, Stage::PLANE, s, lane);
+        }
+    }
+    if constexpr (KW > 1) {
+        __syncthreads();
+        if (kw > 0) {
+            float* part = reinterpret_cast<float*>(smem) + (((kw - 1) * QW + qw) * 16 * NT) * 64 + lane;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) part[(16 * nt + v) * 64] = acc[nt][v];
+        }
+        __syncthreads();
+        if (kw > 0) return;
+#pragma unroll 1
+        for (int k = 1; k < KW; ++k) {
+            const float* o = reinterpret_cast<const float*>(smem) + (((k - 1) * QW + qw) * 16 * NT) * 64 + lane;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[nt][v] += o[(16 * nt + v) * 64];
+        }
+    }
+    if (valid) store_row<T, D>(dQ + qbase + (size_t)row * D, acc, scale, h);
+}
+
+// dV = sum_i P_i dO_i and dK = scale * sum_i dS_i q_i: a key per lane, the share's queries pass through LDS with
+// their log-sum-exp (base 2) and delta.  fp32, d = 64: with two accumulators the own rows' planes (96 registers)
+// do not fit beside the rest at two waves per SIMD.  Eight waves keep them in LDS (158 -> 84 us at
+// 8 x 2003, against spills of 72 registers), four run at one wave per SIMD.
+template <typename T, int D, int QW, int KW>
+__global__ __launch_bounds__(64 * QW * KW, D == 128 || (D == 64 && planes_of<T>::n == 3 && KW == 1) ? 1 : 2) void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K,
+                                                                      const T* __restrict__ V, const T* __restrict__ dO,
+                                                                      const float* __restrict__ LSE, const float* __restrict__ delta,
+                                                                      T* __restrict__ dK, T* __restrict__ dV, int causal)
+{
+    typedef SmCfg<T, D, QW, KW> Cf;
+    typedef typename Cf::Stage Stage;
+    constexpr int NP = Cf::NP, DP = Cf::DP, NT = Cf::NT, KS = Cf::KS, ROWS = Cf::ROWS;
+    extern __shared__ __align__(16) char smem[];
+    constexpr bool OWN_LDS = Cf::own_lds;
+    constexpr int OPLANE = 64 * DP, OTENSOR = NP * OPLANE;        // 32 own rows
+    float* stat = reinterpret_cast<float*>(smem + Stage::BYTES);   // [2][ROWS]
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
+    const int qw = w / KW, kw = w % KW, grp = blockIdx.y;
+    const bool mirrored = causal && g.n_seqs == 0;
+    const int wr = tile_row<QW>(blockIdx.x, qw, g.N, mirrored), row = wr + l32;   // (causal: the first keys have the most queries)
+    int r0, r1;
+    wg_rows<QW>(blockIdx.x, g.N, mirrored, r0, r1);
+    const size_t kbase = (size_t)grp * (size_t)g.N * D, qbase = (size_t)grp * (size_t)g.qn * D;
+    const bool valid = row < g.N;
+    int lo = 0, hi = 0, wlo = 0, whi = 0, ilo, ihi, t;
+    if (valid) queries_of(g, row, causal, lo, hi);
+    if (wr < g.N) {
+        queries_of(g, wr, causal, wlo, t);
+        queries_of(g, min(wr + 31, g.N - 1), causal, t, whi);
+    }
+    queries_of(g, r0, causal, ilo, t);
+    queries_of(g, r1 - 1, causal, t, ihi);
+
+    const unsigned span = (unsigned)max(hi - lo, 0);
+    bf16x8 k[KS][NP], x[KS][NP];
+    char* own = smem + Stage::BYTES + 8 * ROWS + qw * 2 * OTENSOR;
+    if constexpr (OWN_LDS) {
+        // (the tile's KW = 4 waves have a 16-byte chunk of K and V per lane; published by the first stage's barrier)
+        static_assert(!OWN_LDS || 32 * (D / 8) == 64 * KW);
+        const int u = 64 * kw + lane, r = u / (D / 8), ch = u % (D / 8), off = plane_off<DP>(r, ch);
+        const size_t o = kbase + (size_t)(wr + r) * D + 8 * ch;
+        bf16x8 a[NP], b[NP];
+        to_planes(load8(K + o, wr + r < g.N), a);
+        to_planes(load8(V + o, wr + r < g.N), b);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            *reinterpret_cast<bf16x8*>(own + i * OPLANE + off) = a[i];
+            *reinterpret_cast<bf16x8*>(own + OTENSOR + i * OPLANE + off) = b[i];
+        }
+    } else {
+        load_rows<T, D>(k, K + kbase + (size_t)row * D, valid, h);
+        load_rows<T, D>(x, V + kbase + (size_t)row * D, valid, h);
+    }
+    const float scale = rsqrtf((float)D), c = scale * kLog2e;
+    f32x16 ak[NT], av[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) ak[nt] = av[nt] = zero16();
+
+    // rows of Q and dO are counted from the share's first query
+    const T *Qg = Q + qbase, *Dg = dO + qbase;
+    Stage st;
+    float stv = 0.f;   // ROWS <= 128: one value per thread
+    auto fetch = [&](int i0) {
+        st.fetch(Qg, Dg, i0 - g.q0, ihi - g.q0, tid);
+        const int r = tid % ROWS, i = i0 - g.q0 + r;
+        stv = 0.f;
+        if (tid < 2 * ROWS && i0 + r < ihi)
+            stv = tid < ROWS ? LSE[(size_t)grp * g.qn + i] * kLog2e : delta[(size_t)grp * g.qn + i];
+    };
+    if (ilo < ihi) fetch(ilo);
+    for (int i0 = ilo; i0 < ihi; i0 += ROWS) {
+        if (i0 > ilo) __syncthreads();
+        st.put(smem, tid);
+        if (tid < 2 * ROWS) stat[tid] = stv;
+        if (i0 + ROWS < ihi) fetch(i0 + ROWS);
+        __syncthreads();
+#pragma unroll 1
+        for (int u = kw; u < ROWS / 32; u += KW) {
+            const int t0 = i0 + 32 * u;
+            if (t0 >= whi || t0 + 32 <= wlo) continue;
+            const char* qt = smem + u * 64 * DP;
+            f32x16 s, dp;
+            if constexpr (OWN_LDS) {
+                s = scores<DP, KS, NP>(qt, Stage::PLANE, own, OPLANE, l32, h);
+                dp = scores<DP, KS, NP>(qt + Stage::TENSOR, Stage::PLANE, own + OTENSOR, OPLANE, l32, h);
+            } else {
+                s = scores<DP, KS, NP>(qt, Stage::PLANE, k, l32, h);
+                dp = scores<DP, KS, NP>(qt + Stage::TENSOR, Stage::PLANE, x, l32, h);
+            }
+#pragma unroll
+            for (int v = 0; v < 16; v += 4) {
+                const f32x4 ls = *reinterpret_cast<const f32x4*>(stat + 32 * u + acc_row(v) + 4 * h);
+                const f32x4 dl = *reinterpret_cast<const f32x4*>(stat + ROWS + 32 * u + acc_row(v) + 4 * h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool keep = (unsigned)(t0 + 4 * h - lo + acc_row(v + e)) < span;
+                    const float p = __builtin_amdgcn_exp2f(fmaf(s[v + e], c, -ls[e])), ds = p * (dp[v + e] - dl[e]);
+                    s[v + e] = keep ? p : 0.f;
+                    dp[v + e] = keep ? ds : 0.f;
+                }
+            }
+            accumulate<DP, NP>(av, qt + Stage::TENSOR, Stage::PLANE, s, lane);
+            accumulate<DP, NP>(ak, qt, Stage::PLANE, dp, lane);
+        }
+    }
+    if constexpr (KW > 1) {
+        __syncthreads();
+        if (kw > 0) {
+            float* part = reinterpret_cast<float*>(smem) + (((kw - 1) * QW + qw) * 32 * NT) * 64 + lane;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    part[(16 * nt + v) * 64] = ak[nt][v];
+                    part[(16 * (NT + nt) + v) * 64] = av[nt][v];
+                }
+        }
+        __syncthreads();
+        if (kw > 0) return;
+#pragma unroll 1
+        for (int e = 1; e < KW; ++e) {
+            const float* o = reinterpret_cast<const float*>(smem) + (((e - 1) * QW + qw) * 32 * NT) * 64 + lane;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    ak[nt][v] += o[(16 * nt + v) * 64];
+                    av[nt][v] += o[(16 * (NT + nt) + v) * 64];
+                }
+        }
+    }
+    if (!valid) return;
+    store_row<T, D>(dK + kbase + (size_t)row * D, ak, scale, h);
+    store_row<T, D>(dV + kbase + (size_t)row * D, av, 1.f, h);
+}
+
+// Workgroups of four row tiles, unless they fill less than the device twice over: then two tiles and four (fp32
+// with d = 128, whose rows take too many registers for eight waves: two) shares of the partner rows.
+// (fp32, 8 x 2003 x 64, causal, forward: 1 x 4 115 us, 2 x 4 mirrored 57 us.)
+bool split_partners(const Geom& g, int rows) { return (int64_t)g.G * ((rows + 127) / 128) < 2 * (int64_t)cu_count(); }
+
+template <typename T, int D, int QW, int KW>
+hipError_t fwd_TD(const Geom& g, const T* Q, const T* K, const T* V, T* O, float* LSE, int causal, hipStream_t st)
+{
+    typedef SmCfg<T, D, QW, KW> Cf;
+    constexpr int lds = Cf::lds(16 * Cf::NT + 2, 0), R = 32 * Cf::QW;
+    hipError_t e = allow_dynamic_lds<softmax_fwd_planes_kernel<T, D, QW, KW>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((softmax_fwd_planes_kernel<T, D, QW, KW>), dim3((g.qn + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K, V, O, LSE, causal);
+    return hipGetLastError();
+}
+
+template <typename T, int D, int QW, int KW>
+hipError_t dq_TD(const Geom& g, const T* Q, const T* K, const T* V, const T* dO, const float* LSE, const float* delta, T* dQ,
+                 int causal, hipStream_t st)
+{
+    typedef SmCfg<T, D, QW, KW> Cf;
+    constexpr int lds = Cf::lds(16 * Cf::NT, 0), R = 32 * Cf::QW;
+    hipError_t e = allow_dynamic_lds<softmax_bwd_dq_planes_kernel<T, D, QW, KW>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((softmax_bwd_dq_planes_kernel<T, D, QW, KW>), dim3((g.qn + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K, V, dO, LSE,
+                       delta, dQ, causal);
+    return hipGetLastError();
+}
+
+template <typename T, int D, int QW, int KW>
+hipError_t dkv_TD(const Geom& g, const T* Q, const T* K, const T* V, const T* dO, const float* LSE, const float* delta, T* dK,
+                  T* dV, int causal, hipStream_t st)
+{
+    typedef SmCfg<T, D, QW, KW> Cf;
+    constexpr int lds = Cf::lds(32 * Cf::NT, 8 * Cf::ROWS + (Cf::own_lds ? QW * 2 * Cf::NP * 64 * Cf::DP : 0)), R = 32 * Cf::QW;
+    hipError_t e = allow_dynamic_lds<softmax_bwd_dkv_planes_kernel<T, D, QW, KW>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((softmax_bwd_dkv_planes_kernel<T, D, QW, KW>), dim3((g.N + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K, V, dO, LSE,
+                       delta, dK, dV, causal);
+    return hipGetLastError();
+}
+
+template <typename T, int D>
+hipError_t fwd_T(const Geom& g, const void* Q_, const void* K_, const void* V_, void* O_, float* LSE, int causal, hipStream_t st)
+{
+    constexpr int KW = planes_of<T>::n == 3 && D == 128 ? 2 : 4;
+    const T *Q = static_cast<const T*>(Q_), *K = static_cast<const T*>(K_), *V = static_cast<const T*>(V_);
+    T* O = static_cast<T*>(O_);
+    return split_partners(g, g.qn) ? fwd_TD<T, D, 2, KW>(g, Q, K, V, O, LSE, causal, st) : fwd_TD<T, D, 4, 1>(g, Q, K, V, O, LSE, causal, st);
+}
+
+template <typename T, int D>
+hipError_t bwd_T(const Geom& g, const void* Q_, const void* K_, const void* V_, const void* dO_, const float* LSE, const float* delta,
+                 void* dQ_, void* dK_, void* dV_, int causal, hipStream_t st)
+{
+    constexpr int KW = planes_of<T>::n == 3 && D == 128 ? 2 : 4;
+    const T *Q = static_cast<const T*>(Q_), *K = static_cast<const T*>(K_), *V = static_cast<const T*>(V_), *dO = static_cast<const T*>(dO_);
+    T *dQ = static_cast<T*>(dQ_), *dK = static_cast<T*>(dK_), *dV = static_cast<T*>(dV_);
+    if (g.qn > 0) {
+        const hipError_t e = split_partners(g, g.qn) ? dq_TD<T, D, 2, KW>(g, Q, K, V, dO, LSE, delta, dQ, causal, st)
+                                                     : dq_TD<T, D, 4, 1>(g, Q, K, V, dO, LSE, delta, dQ, causal, st);
+        if (e != hipSuccess) return e;
+    }
+    return split_partners(g, g.N) ? dkv_TD<T, D, 2, KW>(g, Q, K, V, dO, LSE, delta, dK, dV, causal, st)
+                                  : dkv_TD<T, D, 4, 1>(g, Q, K, V, dO, LSE, delta, dK, dV, causal, st);
+}
+
+}  // namespace
+
+#define LASP2_FOR_TYPE_AND_SIZE(CALL, ...)                                         \
+    if (dtype == LASP2_F32) switch (g.d) {                                         \
+        case 16: return CALL<float, 16>(__VA_ARGS__);                              \
+        case 32: return CALL<float, 32>(__VA_ARGS__);                              \
+        case 64: return CALL<float, 64>(__VA_ARGS__);                              \
+        default: return CALL<float, 128>(__VA_ARGS__);                             \
+    }                                                                              \
+    switch (g.d) {                                                                 \
+        case 16: return CALL<__hip_bfloat16, 16>(__VA_ARGS__);                     \
+        case 32: return CALL<__hip_bfloat16, 32>(__VA_ARGS__);                     \
+        default: return CALL<__hip_bfloat16, 64>(__VA_ARGS__);                     \
+    }
+
+hipError_t launch_softmax_fwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V, void* O, float* LSE,
+                                     int causal, hipStream_t st)
+{
+    LASP2_FOR_TYPE_AND_SIZE(fwd_T, g, Q, K, V, O, LSE, causal, st)
+}
+
+hipError_t launch_softmax_bwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V, const void* dO,
+                                     const float* LSE, const float* delta, void* dQ, void* dK, void* dV, int causal, hipStream_t st)
+{
+    LASP2_FOR_TYPE_AND_SIZE(bwd_T, g, Q, K, V, dO, LSE, delta, dQ, dK, dV, causal, st)
+}
+
+}  // namespace lasp2

@@ -535,7 +535,7 @@ static int softmax_fwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q
     hipStream_t st = (hipStream_t)stream;
     if (softmax_mfma_supported(g, desc->dtype))
         return from_hip(launch_softmax_fwd_mfma(g, Q, K, V, O, LSE, causal ? 1 : 0, st));
-    return from_hip(launch_softmax_fwd_generic(g, desc->dtype, Q, K, V, O, LSE, causal ? 1 : 0, st));
+    return from_hip(launch_softmax_fwd_planes(g, desc->dtype, Q, K, V, O, LSE, causal ? 1 : 0, st));
 }
 
 static int softmax_bwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q_len, const void* Q,
@@ -564,8 +564,8 @@ static int softmax_bwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
         return from_hip(launch_softmax_bwd_dkv_mfma(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st));
     }
-    return from_hip(launch_softmax_bwd_generic(g, desc->dtype, Q, K, V, dO, LSE, delta, dQ, dK, dV,
-                                               causal ? 1 : 0, st));
+    return from_hip(launch_softmax_bwd_planes(g, desc->dtype, Q, K, V, dO, LSE, delta, dQ, dK, dV,
+                                              causal ? 1 : 0, st));
 }
 
 int lasp2_softmax_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,

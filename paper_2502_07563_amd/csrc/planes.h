@@ -25,15 +25,20 @@ template <> struct planes_of<__hip_bfloat16> { static constexpr int n = 1; };
 
 __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[3])
 {
+    auto lo = [](uint32_t u) { return __builtin_bit_cast(float, u << 16); };
+    auto hi = [](uint32_t u) { return __builtin_bit_cast(float, u & 0xffff0000u); };
+    u32x4 w[3];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const __bf16 hi = (__bf16)x[e];
-        const float r = x[e] - (float)hi;
-        const __bf16 mid = (__bf16)r;
-        p[0][e] = hi;
-        p[1][e] = mid;
-        p[2][e] = (__bf16)(r - (float)mid);
+    for (int e = 0; e < 4; ++e) {   // two at a time: a conversion makes a pair
+        const uint32_t a = pack2(x[2 * e], x[2 * e + 1]);
+        const float r0 = x[2 * e] - lo(a), r1 = x[2 * e + 1] - hi(a);
+        const uint32_t b = pack2(r0, r1);
+        w[0][e] = a;
+        w[1][e] = b;
+        w[2][e] = pack2(r0 - lo(b), r1 - hi(b));
     }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) p[i] = __builtin_bit_cast(bf16x8, w[i]);
 }
 
 // c += the plane products of one k-step (a, b: MFMA operands) whose orders i + j lie in [LO, HI], smallest

@@ -91,3 +91,52 @@ def test_rows_that_the_mask_keeps_from_a_nan_stay_finite(dtype, d):
     assert torch.isfinite(dV[:, :, j + 1:]).all() and not torch.isfinite(dV[:, :, :j + 1, 3]).any()
     assert torch.isfinite(dK[:, :, j + 1:]).all()
     assert rel_l2(to_host(dV[:, :, j + 1:]), to_host(gv[:, :, j + 1:])) <= LIMIT[dtype]
+
+
+def _softmax64(Q, K, V, dO, bounds, causal, q0):
+    """The definition in 64 bits: queries are the tokens q0 .. of N keys, attending inside their document."""
+    n, N, d = Q.shape[1], K.shape[1], Q.shape[2]
+    i, j = np.arange(q0, q0 + n), np.arange(N)
+    doc = lambda t: np.searchsorted(bounds[1:], t, side="right")
+    ok = (doc(i)[:, None] == doc(j)[None]) & ((j[None] <= i[:, None]) | (not causal))
+    s = np.where(ok, (Q @ K.transpose(0, 2, 1)) / np.sqrt(d), -np.inf)
+    m = s.max(axis=2, keepdims=True)
+    e = np.exp(s - m)
+    lse = np.log(e.sum(axis=2)) + m[..., 0]
+    p = e / e.sum(axis=2, keepdims=True)
+    O = p @ V
+    ds = p * (dO @ V.transpose(0, 2, 1) - (dO * O).sum(axis=2, keepdims=True)) / np.sqrt(d)
+    return O, lse, ds @ K, ds.transpose(0, 2, 1) @ Q, p.transpose(0, 2, 1) @ dO
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 16), ("bf16", 32), ("bf16", 64)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_softmax_tile_edges(dtype, d, causal):
+    """Row counts around a tile (32), a stage (64, 128) and an odd number of mirrored tiles; a share of the
+    queries; documents; enough groups for workgroups of four row tiles.  fp32: a probability carries the rounding
+    of its exponent, 2^-24 |score| with scores below 8 here, and a gradient the difference of two such terms."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    limit = {"f32": 3e-6, "bf16": 6e-3}[dtype]
+    cu3 = np.array([0, 33, 34, 300], dtype=np.int32)
+    for G, N, q0, n, cu in ((2, 1, 0, 1, None), (2, 33, 0, 33, None), (3, 96, 0, 96, None), (2, 161, 0, 161, None), (2, 290, 193, 97, None),
+                            (2, 300, 0, 300, cu3), (2, 300, 30, 100, cu3), (256, 150, 0, 150, None), (520, 70, 0, 70, np.array([0, 37, 70], dtype=np.int32))):
+        x = host_inputs(G + N, G, N, d, dtype)
+        x = {k: v * np.float32(2.0) for k, v in x.items()}
+        p = bd.Problem(1, G, N, d, 64, 0, dtype, cu)
+        t = {k: to_device(v, 1, G, dtype) for k, v in x.items()}
+        Q, dO = t["Q"][:, :, q0:q0 + n].contiguous(), t["dO"][:, :, q0:q0 + n].contiguous()
+        nan = lambda like: torch.full_like(like, float("nan"))
+        O, lse, dQ, dK, dV = nan(Q), torch.full((1, G, n), float("nan"), device="cuda"), nan(Q), nan(t["K"]), nan(t["V"])
+        ws = torch.empty(bd.lasp2_softmax_share_workspace_size(p, n), dtype=torch.uint8, device="cuda")
+        bd.lasp2_softmax_fwd_share(p, q0, n, Q, t["K"], t["V"], O, lse, causal)
+        bd.lasp2_softmax_bwd_share(p, q0, n, Q, t["K"], t["V"], O, dO, lse, dQ, dK, dV, ws, causal)
+        x64 = {k: v.astype(np.float64) for k, v in x.items()}
+        want = _softmax64(x64["Q"][:, q0:q0 + n], x64["K"], x64["V"], x64["dO"][:, q0:q0 + n], np.array([0, N]) if cu is None else cu, causal, q0)
+        got = (to_host(O), lse.cpu().numpy()[0].astype(np.float64), to_host(dQ), to_host(dK), to_host(dV))
+        # A row with a single key has dQ = dK = 0, the difference of two sums dO.v that are rounded apart: up to
+        # 2^-23 |dO| |v| |k| / sqrt(d), with |v| |k| / sqrt(d) = 4 / sqrt(d) <= 1 here; 1.5e-7 of |dV| = |dO| is allowed.
+        scale = np.linalg.norm(want[4])
+        for name, a, b in zip(("O", "LSE", "dQ", "dK", "dV"), got, want):
+            err = np.linalg.norm(a - b) / max(np.linalg.norm(b), 0.05 * scale)
+            assert err <= limit, (name, dtype, d, causal, G, N, q0, n, err)
