@@ -68,6 +68,15 @@ def test_bf16_d128(oracle, N, causal):
 
 
 @pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("N,cu", [(31, None), (65, None), (95, None), (129, None), (257, None), (321, None),
+                                  (420, (0, 32, 95, 128, 193, 257, 420))])
+def test_bf16_d128_tile_edges(oracle, N, cu, causal):
+    """One row more or less than the 32-row tiles, the 64-row stages and the query and key blocks; documents that
+    begin and end on and beside the edges of a tile."""
+    _run(oracle, 1, 2, N, 128, "bf16", seed=190 + N, causal=causal, cu=None if cu is None else np.array(cu, np.int32))
+
+
+@pytest.mark.parametrize("causal", [False, True])
 def test_bf16_d128_sharp_scores(oracle, causal):
     """Inputs four times larger: scores of order 16/sqrt(128) * ..., a peaked softmax whose running
     maximum keeps moving."""
