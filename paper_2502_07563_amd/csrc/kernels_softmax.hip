@@ -290,23 +290,13 @@ __global__ __launch_bounds__(SM_NW * 64) void softmax_fwd_mfma_kernel(Geom g, co
 // and values streamed), with the probabilities rebuilt from the stored log-sum-exp instead of
 // an online maximum:  P = exp(s - lse_i), dP = V_tile dO_w^T, dS = P (dP - delta_i) / sqrt(d),
 // dQ^T += K_tile^T dS.  Everything per query is per lane, as in the forward.
-// Four waves of 64 queries, one per SIMD: every operand read from LDS feeds two products.  With 32
-// queries per wave the reads, not the products, set the pace (24 KiB of LDS for 24 MFMAs, about
-// 60 bytes per clock and CU, with or without the vector work).  A block of 64 keys is four units (32
-// keys x 32 queries).  The elements of a unit are computed between the products of the next, its
-// accumulation covers the move of that one's scores out of the accumulation file, and a block's first
-// operands arrive under the accumulation in the block before, behind a barrier that is taken there.
-// 4096 queries against 131072 keys, 16 heads, causal: 5.2 -> 4.1 ms (1.6 PFLOP/s of executed products).
 // =====================================================================================
-constexpr int SD_NW = 4;
-static_assert(SD_NW * 64 == SM_QB, "same query blocks as the forward");
-
-__global__ __launch_bounds__(SD_NW * 64) void softmax_bwd_dq_mfma_kernel(
+__global__ __launch_bounds__(SM_NW * 64) void softmax_bwd_dq_mfma_kernel(
     Geom g, const char* __restrict__ Q, const char* __restrict__ K, const char* __restrict__ V,
     const char* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     char* __restrict__ dQ, int causal, float scale_log2e, float scale)
 {
-    constexpr int NW = SD_NW, DPS = 2 * (16 / NW);
+    constexpr int NW = SM_NW, DPS = 2 * (16 / NW);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* sK = smem;
     char* sV = smem + NSTAGE * STAGE_BYTES;
@@ -333,42 +323,33 @@ __global__ __launch_bounds__(SD_NW * 64) void softmax_bwd_dq_mfma_kernel(
     doc_range(g, r0, blo, tmp);
     doc_range(g, rlast, tmp, bhi);
     if (causal) bhi = rlast + 1;
-    // this lane's two queries, qi and qi + 32: key ranges, and over each tile of 32 queries the keys
-    // that all of them see
-    const int qi = r0 + 64 * w + l32;
-    int lo_i[2], hi_i[2], lo_max[2], hi_min[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const bool valid = qi + 32 * a < qend;
-        lo_i[a] = hi_i[a] = 0;
-        if (valid) {
-            doc_range(g, qi + 32 * a, lo_i[a], hi_i[a]);
-            if (causal) hi_i[a] = qi + 32 * a + 1;
-        }
-        lo_max[a] = __builtin_amdgcn_readfirstlane(wave_max_i(lo_i[a]));
-        hi_min[a] = __builtin_amdgcn_readfirstlane(wave_min_i(hi_i[a]));
+    const int qi = r0 + 32 * w + l32;
+    const bool valid = qi < qend;
+    int lo_i = 0, hi_i = 0;
+    if (valid) {
+        doc_range(g, qi, lo_i, hi_i);
+        if (causal) hi_i = qi + 1;
     }
+    const int lo_min = __builtin_amdgcn_readfirstlane(wave_min_i(valid ? lo_i : g.N));
+    const int lo_max = __builtin_amdgcn_readfirstlane(wave_max_i(valid ? lo_i : 0));
+    const int hi_min = __builtin_amdgcn_readfirstlane(wave_min_i(valid ? hi_i : g.N));
+    const int hi_max = __builtin_amdgcn_readfirstlane(wave_max_i(valid ? hi_i : 0));
 
     const int kb0 = blo / KB, kb1 = (bhi + KB - 1) / KB;
     const int NBK = kb1 - kb0;
-    // The per-lane source offsets are rebuilt at every call from a lane index that the compiler cannot
-    // hoist: kept across the walk they cost registers this kernel does not have.
-    auto lane_here = [&]() __attribute__((always_inline)) {
-        int ln;
-        asm volatile("v_and_b32 %0, 63, %1" : "=v"(ln) : "v"(tid));
-        return ln;
-    };
-    auto issue = [&](int i) __attribute__((always_inline)) {
-        const int ln = lane_here();
-        uint32_t dvo[16 / NW];
+    uint32_t dvo[16 / NW];
 #pragma unroll
-        for (int u = 0; u < 16 / NW; ++u) dvo[u] = dma_lane_off(w * (16 / NW) + u, ln);
+    for (int u = 0; u < 16 / NW; ++u) dvo[u] = dma_lane_off(w * (16 / NW) + u, lane);
+    auto issue = [&](int i) {
         dma_block<NW>(K, V, base, (kb0 + i) * KB, g.N, sK + (i % NSTAGE) * STAGE_BYTES,
-                      sV + (i % NSTAGE) * STAGE_BYTES, w, ln, dvo);
+                      sV + (i % NSTAGE) * STAGE_BYTES, w, lane, dvo);
     };
     issue(0);
     if (NBK > 1) issue(1);
 
+    // lane offsets of the natural and the transposed reads; the other k-steps and column blocks
+    // differ from these only in address bits 5..7, which the row term leaves clear, so they are
+    // derived with one XOR at the point of use instead of being held in registers
     // per-lane LDS addresses inside ring slot 0, first half: natural reads of the K and V tiles
     // (row = key) and transposed reads of the K tile (row = d); slot, half and k-step are added
     // as immediates at the point of use
@@ -393,193 +374,142 @@ __global__ __launch_bounds__(SD_NW * 64) void softmax_bwd_dq_mfma_kernel(
         }
     }
 
-    // this wave's 64 queries and their dO rows as B-operand fragments; zero past the end
-    bf16x8 qf[2][8], gf[2][8];
-    float lse2[2], dlt[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const bool valid = qi + 32 * a < qend;
-        const int row = min(qi + 32 * a, qend - 1) - g.q0;
-        const size_t ro = qbase + (size_t)row * ROWB + 16 * h;
+    // this wave's 32 queries and their dO rows as B-operand fragments; zero past the end
+    bf16x8 qf[8], gf[8];
+    {
+        const size_t ro = qbase + (size_t)(min(qi, qend - 1) - g.q0) * ROWB + 16 * h;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
             const u32x4 z = {0u, 0u, 0u, 0u};
             const u32x4 x = *reinterpret_cast<const u32x4*>(Q + ro + 32 * ks);
             const u32x4 y = *reinterpret_cast<const u32x4*>(dO + ro + 32 * ks);
-            qf[a][ks] = __builtin_bit_cast(bf16x8, valid ? x : z);
-            gf[a][ks] = __builtin_bit_cast(bf16x8, valid ? y : z);
+            qf[ks] = __builtin_bit_cast(bf16x8, valid ? x : z);
+            gf[ks] = __builtin_bit_cast(bf16x8, valid ? y : z);
         }
-        lse2[a] = LSE[(size_t)grp * g.qn + row] * 1.4426950408889634f;   // log2 of the row's sum of exponentials
-        dlt[a] = delta[(size_t)grp * g.qn + row];
     }
-    // Use these here, before the walk: the compiler waits for a loaded value at its first use with
+    const size_t li = (size_t)grp * g.qn + (min(qi, qend - 1) - g.q0);
+    float lse2 = LSE[li] * 1.4426950408889634f;   // log2 of the row's sum of exponentials
+    float dlt = delta[li];
+    // Use both here, before the walk: the compiler waits for a loaded value at its first use with
     // vmcnt(0), and a first use inside the loop would put that wait, which also drains every
     // stage load in flight, into every tile.
-    asm volatile("" : "+v"(lse2[0]), "+v"(dlt[0]), "+v"(lse2[1]), "+v"(dlt[1]));
+    asm volatile("" : "+v"(lse2), "+v"(dlt));
 
-    // products take either file as an operand: the 128 registers of Q and dO live in the accumulation file
+    f32x16 Oacc[4];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int tv = 0; tv < 4; ++tv)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+a"(qf[a][ks]), "+a"(gf[a][ks]));
+        for (int v = 0; v < 16; ++v) Oacc[tv][v] = 0.f;
 
-    f32x16 Oacc[2][4];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int tv = 0; tv < 4; ++tv)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) Oacc[a][tv][v] = 0.f;
-
-    // block n is complete in LDS and every wave has read the last of block n - 1; the loads of block
-    // n + 2 go out
-    auto enter = [&](int n) __attribute__((always_inline)) {
-        if (n + 1 < NBK) wait_vmcnt<DPS>(); else wait_vmcnt<0>();
-        const int k0b = (kb0 + n) * KB;
-        if (k0b + KB > g.N)
-            zero_tail_rows<NW>(k0b, g.N, sK + (n % NSTAGE) * STAGE_BYTES, sV + (n % NSTAGE) * STAGE_BYTES, w, lane_here());
+    // One key block; the ring slot is a compile-time constant (the loop below is unrolled by the
+    // ring length), so every LDS read is a pinned register plus an immediate.
+    auto block = [&](auto stage_c, int bi) {
+        constexpr int ST = decltype(stage_c)::value;
+        char* tK = sK + ST * STAGE_BYTES;
+        char* tV = sV + ST * STAGE_BYTES;
+        const int k0b = (kb0 + bi) * KB;
+        if (bi + 1 < NBK) wait_vmcnt<DPS>(); else wait_vmcnt<0>();
+        if (k0b + KB > g.N) zero_tail_rows<NW>(k0b, g.N, tK, tV, w, lane);
         __syncthreads();
-        if (n + 2 < NBK) issue(n + 2);
-    };
-    bf16x8 kn[8], vn[8];   // natural operands of the tile in work
-    bf16x8 tk[8];          // transposed K operands of the tile that is being accumulated
-    float xs[16], xd[16];  // scores and dP of the unit whose products are done
-    uint32_t p[8];         // its dS, packed
+        if (bi + 2 < NBK) issue(bi + 2);
 
-    // products of a unit, between them the elements of the one before:  P (dP - delta),
-    // P = exp2(scale_log2e s - lse2) (the factor 1/sqrt(d) of dS is applied once, to the finished sum)
-    f32x16 sc, dp;
-    auto products = [&](auto a_c, auto&& loads) __attribute__((always_inline)) {
-        constexpr int a = decltype(a_c)::value, pa = 1 - a;
+        bf16x8 bufA[4], bufB[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const f32x16 z = {};
-            sc = mfma(kn[j], qf[a][j], j ? sc : z);
-            dp = mfma(vn[j], gf[a][j], j ? dp : z);
-            const float e0 = fast_exp2(fmaf(xs[2 * j], scale_log2e, -lse2[pa])) * (xd[2 * j] - dlt[pa]);
-            const float e1 = fast_exp2(fmaf(xs[2 * j + 1], scale_log2e, -lse2[pa])) * (xd[2 * j + 1] - dlt[pa]);
-            p[j] = pack2(e0, e1);
-            pin_vgpr(p[j]);   // here, and not where it is used
-            loads(j);
+        for (int half = 0; half < 2; ++half) {
+            const int k0 = k0b + 32 * half;
+            if (k0 >= hi_max || k0 + 32 <= lo_min) continue;
+            const bool whole = (k0 >= lo_max) && (k0 + 32 <= hi_min);
+            const uint32_t HO = ST * STAGE_BYTES + half * (32 * ROWB);
+            // scores^T = K_tile Q_w^T and dP^T = V_tile dO_w^T (keys x queries)
+            f32x16 sc, dp;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { sc[v] = 0.f; dp[v] = 0.f; }
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) bufA[ks] = lds_read16_u(natK[ks] + HO);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) bufB[ks] = lds_read16_u(natK[ks + 4] + HO);
             SCHED_FENCE();
-        }
-    };
-    // the mask of the elements in p: queries a, keys from k0 (nothing to do in all but the tiles at its edge)
-    auto mask = [&](int k0, auto a_c) __attribute__((always_inline)) {
-        constexpr int a = decltype(a_c)::value;
-        if (k0 >= lo_max[a] && k0 + 32 <= hi_min[a]) return;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int key = k0 + 8 * (j >> 1) + 4 * (lane_here() >> 5) + 2 * (j & 1);
-            p[j] &= (key >= lo_i[a] && key < hi_i[a] ? 0xffffu : 0u) |
-                    (key + 1 >= lo_i[a] && key + 1 < hi_i[a] ? 0xffff0000u : 0u);
-        }
-    };
-    // accumulation of the elements in p; meanwhile the finished unit's scores move to ordinary registers
-    auto accumulate = [&](auto a_c) __attribute__((always_inline)) {
-        constexpr int a = decltype(a_c)::value;
-        asm volatile("" : "+a"(sc), "+a"(dp));   // (not moved earlier, where no product would cover it)
+            for (int ks = 0; ks < 4; ++ks) sc = mfma(bufA[ks], qf[ks], sc);
+            SCHED_FENCE();
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const u32x4 x = {p[4 * (j >> 2)], p[4 * (j >> 2) + 1], p[4 * (j >> 2) + 2], p[4 * (j >> 2) + 3]};
-            Oacc[a][j & 3] = mfma(tk[j], __builtin_bit_cast(bf16x8, x), Oacc[a][j & 3]);
+            for (int ks = 0; ks < 4; ++ks) bufA[ks] = lds_read16_u(natV[ks] + HO);
+            SCHED_FENCE();
 #pragma unroll
-            for (int v = 2 * j; v < 2 * j + 2; ++v) {
-                xs[v] = sc[v];
-                xd[v] = dp[v];
-                asm volatile("" : "+v"(xs[v]), "+v"(xd[v]));
+            for (int ks = 0; ks < 4; ++ks) sc = mfma(bufB[ks], qf[ks + 4], sc);
+            SCHED_FENCE();
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) bufB[ks] = lds_read16_u(natV[ks + 4] + HO);
+            SCHED_FENCE();
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) dp = mfma(bufA[ks], gf[ks], dp);
+            SCHED_FENCE();
+#pragma unroll
+            for (int tv = 0; tv < 4; ++tv) bufA[tv] = lds_read_tr8_u(trK[tv][0] + HO, trK[tv][1] + HO);
+            SCHED_FENCE();
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) dp = mfma(bufB[ks], gf[ks + 4], dp);
+            SCHED_FENCE();
+            // P (dP - delta), P = exp2(scale_log2e s - lse2), zero outside the mask (the factor
+            // 1/sqrt(d) of dS is applied once, to the finished sum)
+            if (whole) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    sc[v] = fast_exp2(fmaf(sc[v], scale_log2e, -lse2)) * (dp[v] - dlt);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int key = k0 + 8 * (v >> 2) + 4 * h + (v & 3);
+                    const float arg = (key >= lo_i && key < hi_i) ? fmaf(sc[v], scale_log2e, -lse2) : -INFINITY;
+                    sc[v] = fast_exp2(arg) * (dp[v] - dlt);
+                }
+            }
+            SCHED_FENCE();
+#pragma unroll
+            for (int tv = 0; tv < 4; ++tv) bufB[tv] = lds_read_tr8_u(trK[tv][0] + (HO + 16 * ROWB), trK[tv][1] + (HO + 16 * ROWB));
+            SCHED_FENCE();
+            {
+                u32x4 pk = {pack2(sc[0], sc[1]), pack2(sc[2], sc[3]), pack2(sc[4], sc[5]), pack2(sc[6], sc[7])};
+                bf16x8 sb = __builtin_bit_cast(bf16x8, pk);
+#pragma unroll
+                for (int tv = 0; tv < 4; ++tv) Oacc[tv] = mfma(bufA[tv], sb, Oacc[tv]);
+            }
+            {
+                u32x4 pk = {pack2(sc[8], sc[9]), pack2(sc[10], sc[11]), pack2(sc[12], sc[13]), pack2(sc[14], sc[15])};
+                bf16x8 sb = __builtin_bit_cast(bf16x8, pk);
+#pragma unroll
+                for (int tv = 0; tv < 4; ++tv) Oacc[tv] = mfma(bufB[tv], sb, Oacc[tv]);
             }
             SCHED_FENCE();
         }
     };
-    std::integral_constant<int, 0> first;
-    std::integral_constant<int, 1> second;
-
-    // One key block; the ring slot is a compile-time constant (the loop below is unrolled by the
-    // ring length), so every LDS read is a pinned register plus an immediate.  Units: (keys 0.., first
-    // queries), (keys 0.., second), (keys 32.., first), (keys 32.., second); the last one is finished
-    // in the next block.
-    auto block = [&](auto stage_c, int bi) __attribute__((always_inline)) {
-        constexpr int ST = decltype(stage_c)::value;
-        constexpr uint32_t SO = ST * STAGE_BYTES, SN = ((ST + 1) % NSTAGE) * STAGE_BYTES, HB = 32 * ROWB;
-        const int k0b = (kb0 + bi) * KB;
-        products(first, [&](int) {});
-        mask(k0b - 32, second);
-        accumulate(second);
-        products(second, [&](int j) __attribute__((always_inline)) {
-            kn[j] = lds_read16_u(natK[j] + (SO + HB));
-            vn[j] = lds_read16_u(natV[j] + (SO + HB));
-            tk[j] = lds_read_tr8_u(trK[j & 3][0] + (SO + (j >> 2) * (16 * ROWB)), trK[j & 3][1] + (SO + (j >> 2) * (16 * ROWB)));
-        });
-        mask(k0b, first);
-        accumulate(first);
-        products(first, [&](int) {});
-        mask(k0b, second);
-        accumulate(second);
-        products(second, [&](int j) __attribute__((always_inline)) {
-            tk[j] = lds_read_tr8_u(trK[j & 3][0] + (SO + HB + (j >> 2) * (16 * ROWB)),
-                                   trK[j & 3][1] + (SO + HB + (j >> 2) * (16 * ROWB)));
-        });
-        mask(k0b + 32, first);
-        if (bi + 1 < NBK) enter(bi + 1);
-        // the next block's first operands (after the last block: bytes of the ring that nothing uses)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            kn[j] = lds_read16_u(natK[j] + SN);
-            vn[j] = lds_read16_u(natV[j] + SN);
-        }
-        SCHED_FENCE();
-        accumulate(first);
-    };
     static_assert(NSTAGE == 3, "the block loop is unrolled by the ring length");
-    enter(0);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        kn[j] = lds_read16_u(natK[j]);
-        vn[j] = lds_read16_u(natV[j]);
-        tk[j] = __builtin_bit_cast(bf16x8, z);   // nothing to finish before the first block
-        xs[2 * j] = xs[2 * j + 1] = -INFINITY;
-        xd[2 * j] = xd[2 * j + 1] = 0.f;
-    }
     for (int bi = 0; bi < NBK; bi += 3) {
         block(std::integral_constant<int, 0>{}, bi);
         if (bi + 1 < NBK) block(std::integral_constant<int, 1>{}, bi + 1);
         if (bi + 2 < NBK) block(std::integral_constant<int, 2>{}, bi + 2);
     }
-    // the last unit
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float e0 = fast_exp2(fmaf(xs[2 * j], scale_log2e, -lse2[1])) * (xd[2 * j] - dlt[1]);
-        const float e1 = fast_exp2(fmaf(xs[2 * j + 1], scale_log2e, -lse2[1])) * (xd[2 * j + 1] - dlt[1]);
-        p[j] = pack2(e0, e1);
-    }
-    mask((kb0 + NBK) * KB - 32, second);
-    accumulate(second);
 
     {
         char* stg = sO + w * 4096;
+        const int rbase = rl0 + 32 * w;
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const int rbase = rl0 + 64 * w + 32 * a;
+        for (int hv = 0; hv < 2; ++hv) {
 #pragma unroll
-            for (int hv = 0; hv < 2; ++hv) {
+            for (int tvv = 0; tvv < 2; ++tvv)
 #pragma unroll
-                for (int tvv = 0; tvv < 2; ++tvv)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const f32x16& o = Oacc[a][2 * hv + tvv];
-                        u32x2 pk = {pack2(o[4 * q] * scale, o[4 * q + 1] * scale),
-                                    pack2(o[4 * q + 2] * scale, o[4 * q + 3] * scale)};
-                        *reinterpret_cast<u32x2*>(stg + l32 * 128 + (((4 * tvv + q) ^ (l32 & 7)) << 4) + 8 * h) = pk;
-                    }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int idx = lane + 64 * i, row = idx >> 3, ch = idx & 7;
-                    const u32x4 v = *reinterpret_cast<const u32x4*>(stg + row * 128 + ((ch ^ (row & 7)) << 4));
-                    if (rbase + row < g.qn)
-                        *reinterpret_cast<u32x4*>(dQ + qbase + (size_t)(rbase + row) * ROWB + 128 * hv + 16 * ch) = v;
+                for (int q = 0; q < 4; ++q) {
+                    const f32x16& o = Oacc[2 * hv + tvv];
+                    u32x2 pk = {pack2(o[4 * q] * scale, o[4 * q + 1] * scale),
+                                pack2(o[4 * q + 2] * scale, o[4 * q + 3] * scale)};
+                    *reinterpret_cast<u32x2*>(stg + l32 * 128 + (((4 * tvv + q) ^ (l32 & 7)) << 4) + 8 * h) = pk;
                 }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int idx = lane + 64 * i, row = idx >> 3, ch = idx & 7;
+                const u32x4 v = *reinterpret_cast<const u32x4*>(stg + row * 128 + ((ch ^ (row & 7)) << 4));
+                if (rbase + row < g.qn)
+                    *reinterpret_cast<u32x4*>(dQ + qbase + (size_t)(rbase + row) * ROWB + 128 * hv + 16 * ch) = v;
             }
         }
     }
@@ -922,7 +852,7 @@ hipError_t launch_softmax_bwd_dq_mfma(const Geom& g, const void* Q, const void* 
                                       const void* dO, const float* LSE, const float* delta, void* dQ,
                                       int causal, hipStream_t st)
 {
-    constexpr int smem = 2 * NSTAGE * STAGE_BYTES + SD_NW * 4096;   // 112 KiB
+    constexpr int smem = 2 * NSTAGE * STAGE_BYTES + SM_NW * 4096;   // 128 KiB
     hipError_t e = allow_dynamic_lds<softmax_bwd_dq_mfma_kernel>(smem);
     if (e != hipSuccess) return e;
     if (g.qn == 0) return hipSuccess;
@@ -930,7 +860,7 @@ hipError_t launch_softmax_bwd_dq_mfma(const Geom& g, const void* Q, const void* 
     const unsigned units = (unsigned)g.G * nqb;
     const unsigned gx = 8u * ((units + 7u) / 8u);
     const float scale = 1.f / sqrtf((float)g.d);
-    hipLaunchKernelGGL(softmax_bwd_dq_mfma_kernel, dim3(gx), dim3(SD_NW * 64), smem, st, g,
+    hipLaunchKernelGGL(softmax_bwd_dq_mfma_kernel, dim3(gx), dim3(SM_NW * 64), smem, st, g,
                        static_cast<const char*>(Q), static_cast<const char*>(K),
                        static_cast<const char*>(V), static_cast<const char*>(dO), LSE, delta,
                        static_cast<char*>(dQ), causal, 1.4426950408889634f * scale, scale);
