@@ -345,7 +345,7 @@ def main():
     bwd_v = [t - pre_ms for t in per_step[seg_names.index("attn_bwd")]]
     wide_f, wide_b = ws_f * Leff > 128, ws_b * Leff > 128
     if not mfma_path:
-        kern_fwd = kern_bwd = "attn_generic_kernel"
+        kern_fwd = kern_bwd = "attn_planes_kernel"
     elif args.decay:
         kern_fwd = "attn_skew_mfma_kernel<decay>" if wide_f else "attn_decay_mfma_kernel<128>"
         kern_bwd = "attn_skew_mfma_kernel<decay>" if wide_b else "attn_decay_mfma_kernel<128>"
