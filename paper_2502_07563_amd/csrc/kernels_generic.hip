@@ -163,28 +163,70 @@ hipError_t rows_state_generic_T(const Geom& g, const T* A, const float* state, T
     }
 }
 
-// delta_i = dO_i . O_i for every row (the row sums the softmax backward needs); one wave-sized
-// group of 64 threads per row.  lse2, when given, receives the row's log-sum-exp times log2(e),
-// the form in which the matrix-core dK/dV kernel subtracts it from base-2 scores.
-template <typename T>
+// delta_i = dO_i . O_i for every row (the row sums the softmax backward needs).  lse2, when given,
+// receives the row's log-sum-exp times log2(e), the form in which the matrix-core dK/dV kernel subtracts
+// it from base-2 scores.  Bound by memory: a lane takes 16 bytes of a row (both tensors are 16-byte
+// aligned and a row is a multiple of that), D * sizeof(T) / 16 lanes a row, and four rows are under way
+// per lane.  (One wave per row and 2-byte loads left most of a wave's work to addresses and shuffles.)
+// Layer forward + backward, 16 heads of 128, us: 8192 tokens of 30 documents, causal 363 -> 340; 8000 causal 1251 ->
+// 1231; 4000 unmasked 656 -> 647; 1000 causal 118.4 -> 117.7.
+constexpr int kDeltaRows = 4;   // rows per lane
+
+template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void softmax_delta_kernel(Geom g, const T* __restrict__ O,
                                                                  const T* __restrict__ dO,
                                                                  const float* __restrict__ LSE,
                                                                  float* __restrict__ delta,
                                                                  float* __restrict__ lse2)
 {
+    constexpr int VE = 16 / (int)sizeof(T), LP = D / VE, RB = kThreads / LP;   // elements and lanes; rows at a time
+    struct alignas(16) Vec { T x[VE]; };
     const size_t rows = (size_t)g.G * (size_t)g.qn;
-    const size_t row = (size_t)blockIdx.x * (kThreads / 64) + threadIdx.x / 64;
-    if (row >= rows) return;
-    const int lane = threadIdx.x % 64;
-    float acc = 0.f;
-    for (int a = lane; a < g.d; a += 64) acc = fmaf(ld(O + row * g.d + a), ld(dO + row * g.d + a), acc);
+    const size_t row0 = (size_t)blockIdx.x * (RB * kDeltaRows) + threadIdx.x / LP;
+    const int part = threadIdx.x % LP;
+    Vec o[kDeltaRows], w[kDeltaRows];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if (lane == 0) {
-        delta[row] = acc;
-        if (lse2) lse2[row] = LSE[row] * 1.4426950408889634f;
+    for (int u = 0; u < kDeltaRows; ++u) {
+        const size_t row = min(row0 + (size_t)(u * RB), rows - 1);   // (past the end: the last row again)
+        o[u] = *reinterpret_cast<const Vec*>(O + row * D + part * VE);
+        w[u] = *reinterpret_cast<const Vec*>(dO + row * D + part * VE);
     }
+#pragma unroll
+    for (int u = 0; u < kDeltaRows; ++u) {
+        float acc = 0.f;
+#pragma unroll
+        for (int v = 0; v < VE; ++v) acc = fmaf(ld(&o[u].x[v]), ld(&w[u].x[v]), acc);
+#pragma unroll
+        for (int m = LP / 2; m > 0; m >>= 1) acc += __shfl_xor(acc, m, 64);
+        const size_t row = row0 + (size_t)(u * RB);
+        if (part == 0 && row < rows) {
+            delta[row] = acc;
+            if (lse2) lse2[row] = LSE[row] * 1.4426950408889634f;
+        }
+    }
+}
+
+template <typename T, int D>
+void softmax_delta_TD(const Geom& g, size_t rows, const T* O, const T* dO, const float* LSE, float* delta, float* lse2,
+                      hipStream_t st)
+{
+    constexpr size_t per = (size_t)(kThreads * 16 / (D * (int)sizeof(T))) * kDeltaRows;
+    hipLaunchKernelGGL((softmax_delta_kernel<T, D>), dim3((unsigned)((rows + per - 1) / per)), dim3(kThreads), 0, st, g,
+                       O, dO, LSE, delta, lse2);
+}
+
+template <typename T>
+hipError_t softmax_delta_T(const Geom& g, size_t rows, const void* O, const void* dO, const float* LSE, float* delta,
+                           float* lse2, hipStream_t st)
+{
+    const T *o = static_cast<const T*>(O), *w = static_cast<const T*>(dO);
+    switch (g.d) {
+        case 16: softmax_delta_TD<T, 16>(g, rows, o, w, LSE, delta, lse2, st); break;
+        case 32: softmax_delta_TD<T, 32>(g, rows, o, w, LSE, delta, lse2, st); break;
+        case 64: softmax_delta_TD<T, 64>(g, rows, o, w, LSE, delta, lse2, st); break;
+        default: softmax_delta_TD<T, 128>(g, rows, o, w, LSE, delta, lse2, st); break;
+    }
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -194,15 +236,8 @@ hipError_t launch_softmax_delta(const Geom& g, int dtype, const void* O, const v
 {
     const size_t rows = (size_t)g.G * (size_t)g.qn;
     if (rows == 0) return hipSuccess;
-    dim3 grid((unsigned)((rows + kThreads / 64 - 1) / (kThreads / 64))), block(kThreads);
-    if (dtype == LASP2_F32)
-        hipLaunchKernelGGL(softmax_delta_kernel<float>, grid, block, 0, st, g, static_cast<const float*>(O),
-                           static_cast<const float*>(dO), LSE, delta, lse2);
-    else
-        hipLaunchKernelGGL(softmax_delta_kernel<__hip_bfloat16>, grid, block, 0, st, g,
-                           static_cast<const __hip_bfloat16*>(O), static_cast<const __hip_bfloat16*>(dO), LSE,
-                           delta, lse2);
-    return hipGetLastError();
+    if (dtype == LASP2_F32) return softmax_delta_T<float>(g, rows, O, dO, LSE, delta, lse2, st);
+    return softmax_delta_T<__hip_bfloat16>(g, rows, O, dO, LSE, delta, lse2, st);
 }
 
 hipError_t launch_state_total(const Geom& g, const float* M, float* S, hipStream_t st)
