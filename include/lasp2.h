@@ -133,17 +133,21 @@ typedef struct lasp2_desc {
 int lasp2_num_slots(const lasp2_desc_t* desc, int64_t* T_s);
 
 /*
- * How many of the caller's slots one workgroup of the bf16, d = 128 attention
- * kernels walks in one go (`backward` = 0: lasp2_attn_fwd, else lasp2_attn_bwd),
- * 1 for every other path.  The state a fused pass carries across a slot
- * boundary is that slot's prefix M_{1:t-1} (the recurrence the prefix sum
- * itself follows), so a walk reads P only at its first slot and the slot length
- * fixes the granularity of the state arrays, not the number or length of the
- * workgroups' walks: the library picks the walk length that keeps the device's
- * CUs busy with the fewest starts (never across a document edge).  Results are
- * the same within the rounding order.  lasp2_attn_bwd builds its dM states per
- * walk.  The environment variable LASP2_WALK_SLOTS (a positive integer, read at
- * every call) overrides the choice; 1 gives one walk per slot.
+ * How many of the caller's slots one workgroup of the attention kernels walks
+ * in one go (`backward` = 0: lasp2_attn_fwd, else lasp2_attn_bwd).  The state a
+ * fused pass carries across a slot boundary is that slot's prefix M_{1:t-1}
+ * (the recurrence the prefix sum itself follows), so a walk reads P only at its
+ * first slot and the slot length fixes the granularity of the state arrays, not
+ * the number or length of the workgroups' walks: the library picks the walk
+ * length that keeps the device's CUs busy with the fewest starts (never across
+ * a document edge).  Results are the same within the rounding order.
+ *   bf16, d = 128 (without decay, or every factor >= 0.35): any L;
+ *     lasp2_attn_bwd builds its dM states per walk.
+ *   Everything else: only where L is not a multiple of the kernels' 128-row
+ *     chunk, so that single slots would leave chunks partly empty; 1 otherwise.
+ *     dM states are built per slot.
+ * The environment variable LASP2_WALK_SLOTS (a positive integer, read at every
+ * call) overrides the choice where there is one; 1 gives one walk per slot.
  */
 int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_walk);
 

@@ -143,6 +143,25 @@ Geom regroup(const Geom& g, const int32_t* cu_host, int ws)
     return w;
 }
 
+int64_t longest_sequence(const Geom& g, const int32_t* cu_host)
+{
+    if (g.n_seqs == 0) return g.N;
+    int64_t m = 0;
+    for (int k = 0; k < g.n_seqs; ++k) m = std::max<int64_t>(m, cu_host[k + 1] - cu_host[k]);
+    return m;
+}
+
+int64_t max_walk_slots(const Geom& g) { return std::max<int64_t>(1, std::min<int64_t>(kMaxWalkTokens / g.L, INT32_MAX / 2)); }
+
+// The environment variable LASP2_WALK_SLOTS (for tests and tuning), clamped; 0 when it is not set to a
+// positive number.
+int forced_walk_slots(const Geom& g)
+{
+    const char* e = getenv("LASP2_WALK_SLOTS");
+    const long v = e ? strtol(e, nullptr, 10) : 0;
+    return v >= 1 ? (int)std::min<int64_t>(v, max_walk_slots(g)) : 0;
+}
+
 // Slots per walk for a launch that runs `par` walks at a time and gains little from walks longer
 // than `target` tokens (measured: the forward launch is flat from about 2 048 tokens on, the
 // backward from about 4 096; starting a walk costs what streaming about a hundred tokens does).
@@ -151,22 +170,13 @@ Geom regroup(const Geom& g, const int32_t* cu_host, int ws)
 //   - Otherwise the shortest walk of at least `target` tokens (a power of two of slots), made
 //     shorter again while the launch would have fewer than two rounds of workgroups: a launch of
 //     one round ends at the pace of its slowest CU, and less than one leaves CUs without work.
-// The environment variable LASP2_WALK_SLOTS, when set to a positive number, overrides the choice
-// (for tests and tuning).
+// LASP2_WALK_SLOTS overrides the choice.
 int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t target)
 {
-    const int64_t longest_seq = [&] {
-        if (g.n_seqs == 0) return (int64_t)g.N;
-        int64_t m = 0;
-        for (int k = 0; k < g.n_seqs; ++k) m = std::max<int64_t>(m, cu_host[k + 1] - cu_host[k]);
-        return m;
-    }();
+    const int64_t longest_seq = longest_sequence(g, cu_host);
     if (g.L >= longest_seq || g.G == 0) return 1;
-    const int64_t ws_max = std::max<int64_t>(1, std::min<int64_t>(kMaxWalkTokens / g.L, INT32_MAX / 2));
-    if (const char* e = getenv("LASP2_WALK_SLOTS")) {
-        const long v = strtol(e, nullptr, 10);
-        if (v >= 1) return (int)std::min<int64_t>(v, ws_max);
-    }
+    const int64_t ws_max = max_walk_slots(g);
+    if (const int v = forced_walk_slots(g)) return v;
     if (par < 1) par = 1;
     const int64_t ws_whole = (longest_seq + g.L - 1) / g.L;   // slots of the longest sequence
     if (g.n_seqs == 0 && ws_whole <= ws_max) {
@@ -189,9 +199,12 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
 // Slots per walk of the split-plane kernels, `nprob` workgroups per walk.  They work on chunks of 128
 // rows: slots that leave chunks partly empty (one state per 64 tokens, say) are taken two, four or
 // eight at a time while that still gives every CU a workgroup, and P is read at the first only.  (d = 32, fp32,
-// 64-token slots: forward pass 123 -> 92 us.)
+// 64-token slots: forward pass 123 -> 92 us.)  Slots of whole chunks gain nothing and are walked one by one.
+// LASP2_WALK_SLOTS overrides the choice where there is one.
 int pick_planes_slots(const Geom& g, const int32_t* cu_host, int nprob)
 {
+    if (g.L % 128 == 0 || g.G == 0 || g.L >= longest_sequence(g, cu_host)) return 1;
+    if (const int v = forced_walk_slots(g)) return v;
     int ws = 1;
     while (ws < 8 && g.L * ws < 512 && (g.L * ws) % 128 != 0) {
         const Geom w = regroup(g, cu_host, 2 * ws);
@@ -350,7 +363,11 @@ int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_
     int rc = make_geom(desc, &g, &empty);
     if (rc != LASP2_OK) return rc;
     *slots_per_walk = 1;
-    if (empty || !mfma_path_supported(g, desc->dtype)) return LASP2_OK;
+    if (empty) return LASP2_OK;
+    if (!mfma_path_supported(g, desc->dtype)) {
+        *slots_per_walk = pick_planes_slots(g, desc->cu_seqlens_host, backward ? 3 : 1);
+        return LASP2_OK;
+    }
     const int wgs = backward ? (g.decay ? 3 : 2) : 1;
     *slots_per_walk = pick_walk_slots(g, desc->cu_seqlens_host, std::max(1, cu_count() / wgs),
                                       backward ? (g.n_seqs ? kWalkTargetBwdPacked : kWalkTargetBwd) : kWalkTargetFwd);

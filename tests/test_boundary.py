@@ -114,6 +114,30 @@ def test_walk_slots_choice(monkeypatch):
     assert B.lib().lasp2_walk_slots(ctypes.byref(_desc()), 0, None) == -1
 
 
+def test_walk_slots_off_the_bf16_d128_path(monkeypatch):
+    """The kernels for fp32, d < 128 and strong decay take slots that leave their 128-row chunks partly empty two,
+    four or eight at a time while every CU gets a workgroup; the query says so, and the override reaches them."""
+    monkeypatch.delenv("LASP2_WALK_SLOTS", raising=False)
+    many = dict(B=16, H=32, N=1000, d=64)
+    lam = (ctypes.c_float * 32)(*([0.2] * 32))
+    decay = dict(decay_host=ctypes.addressof(lam), decay_dev=0x3000)
+    for kw in (dict(), dict(dtype=B.LASP2_BF16), dict(dtype=B.LASP2_BF16, d=128, **decay)):
+        kw = dict(many, **kw)
+        assert _walk(_desc(C=64, **kw)) == (0, 2) and _walk(_desc(C=64, **kw), 1) == (0, 2)
+        assert _walk(_desc(C=16, **kw)) == (0, 8)
+        assert _walk(_desc(C=128, **kw)) == (0, 1)                              # whole chunks
+        assert _walk(_desc(C=64, **dict(kw, B=1, N=100), L=128)) == (0, 1)      # a slot holds the sequence
+    # 2 heads x 400 tokens: 14 slots, 7 walks of two; three workgroups each (backward) do not fill 256 CUs either
+    few = dict(H=2, N=400, d=64, C=64)
+    assert _walk(_desc(**few)) == (0, 1) and _walk(_desc(**few), 1) == (0, 1)
+    # 200 groups x 64-token slots of 128 tokens: 200 walks of two are too few, 600 workgroups enough
+    assert _walk(_desc(B=10, H=20, N=128, d=64, C=64)) == (0, 1) and _walk(_desc(B=10, H=20, N=128, d=64, C=64), 1) == (0, 2)
+    for forced, want in ((1, 1), (3, 3), (1 << 40, (1 << 30) // 64)):
+        monkeypatch.setenv("LASP2_WALK_SLOTS", str(forced))
+        assert _walk(_desc(C=64, **many)) == (0, want) and _walk(_desc(**few), 1) == (0, want)
+        assert _walk(_desc(C=128, **many)) == (0, 1)
+
+
 def test_workspace_size():
     out = ctypes.c_size_t(0)
     d = _desc(B=8, H=32, N=8192, d=128, C=256, dtype=B.LASP2_BF16)

@@ -69,6 +69,19 @@ def test_packed_documents_and_merged_slots(oracle, dtype, d):
     _run(oracle, dtype, 1, 256, 391, d, 32, 32, cu=cu, lam=np.full(256, 0.9, dtype=np.float32))
 
 
+@pytest.mark.parametrize("slots", [1, 3, 100])
+@pytest.mark.parametrize("dtype,d,lam", [("f32", 64, None), ("f32", 16, 0.9), ("bf16", 32, 0.97), ("bf16", 128, 0.2)])
+def test_forced_walk_lengths(oracle, monkeypatch, dtype, d, lam, slots):
+    """LASP2_WALK_SLOTS on these kernels: one slot per walk, walks whose chunks begin inside a slot, a whole document per
+    walk.  (bf16, d = 128: states and scores of three planes, so the bound is that of the output's rounding too.)"""
+    monkeypatch.setenv("LASP2_WALK_SLOTS", str(slots))
+    f = None if lam is None else np.array([lam, 1.0], dtype=np.float32)
+    _run(oracle, dtype, 2, 2, 500, d, 48, 48, lam=f)
+    lens = [47, 300, 1, 97]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    _run(oracle, dtype, 1, 2, int(cu[-1]), d, 32, 96, cu=cu, lam=f)
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 32), ("f32", 128)])
 def test_rows_that_the_mask_keeps_from_a_nan_stay_finite(dtype, d):
     """A NaN in V at token j reaches O at j and later, one in dO and Q the rows of dV and dK at j and before:
