@@ -25,6 +25,12 @@ struct Tiles {
 // lam^e, l2 = log2 lam (the hardware exponential: 1 ulp; results below 2^-126 are zero)
 __device__ __forceinline__ float decay_pow(float e, float l2) { return __builtin_amdgcn_exp2f(e * l2); }
 
+template <typename T> __device__ __forceinline__ void store1(T* p, float x);
+template <> __device__ __forceinline__ void store1(float* p, float x) { *p = x; }
+template <> __device__ __forceinline__ void store1(__hip_bfloat16* p, float x) { *p = __float2bfloat16(x); }
+__device__ __forceinline__ float load1(const float* p) { return *p; }
+__device__ __forceinline__ float load1(const __hip_bfloat16* p) { return __bfloat162float(*p); }
+
 // Rescales the elements of a transposed fetch (tokens r0 + 4h + .., planes.h) by lam^(e0 + de * token):
 // the planes add up to the exact value, the product is an fp32 one and is split again.
 template <int NP>
@@ -72,6 +78,17 @@ __device__ __forceinline__ void state_step(f32x16 (&S)[Tiles<DP / 32>::n], const
     }
 }
 
+// sum over t < n of lam^(e0 + de t) x[t] y[t] in fp32 (columns of row-major arrays with rows of D elements)
+template <typename T>
+__device__ __forceinline__ float state_element(const T* x, const T* y, int D, int n, float l2, int e0, int de)
+{
+    float acc = 0.f;
+#pragma unroll 1
+    for (int t = 0; t < n; ++t)
+        acc = fmaf(exp2f((float)(e0 + de * t) * l2) * load1(x + (size_t)t * D), load1(y + (size_t)t * D), acc);
+    return acc;
+}
+
 // M[slot] = sum over the slot's tokens of (weighted) k^T v; one workgroup per slot.
 template <typename T, int D, bool DECAY>
 __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __restrict__ K, const T* __restrict__ V,
@@ -109,8 +126,19 @@ __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __
         }
     }
     float* m = M + ((size_t)grp * g.T_s + s) * (size_t)(D * D);
+    // Planes make NaN of an infinity and of what rounds to one (planes.h): such a slot is summed again in fp32.
+    float odd = 0.f;
+#pragma unroll
+    for (int t = 0; t < Tiles<NT>::n; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            odd = fmaf(D >= 32 || (acc_row(v) + 4 * (lane >> 5) < D && (lane & 31) < D) ? S[t][v] : 0.f, 0.f, odd);
+    if (__syncthreads_or(odd != 0.f)) {
+        for (int e = tid; e < D * D; e += kThr)
+            m[e] = state_element(K + base + e / D, V + base + e % D, D, len, l2, e0, de);
+        return;
+    }
     if (NT == 1) {
-        __syncthreads();
         float* part = reinterpret_cast<float*>(smem);
 #pragma unroll
         for (int v = 0; v < 16; ++v) part[(w * 16 + v) * 64 + lane] = S[0][v];
@@ -137,12 +165,6 @@ struct PlanesProblem {
 };
 struct PlanesProblems { PlanesProblem p[3]; };
 
-template <typename T> __device__ __forceinline__ void store1(T* p, float x);
-template <> __device__ __forceinline__ void store1(float* p, float x) { *p = x; }
-template <> __device__ __forceinline__ void store1(__hip_bfloat16* p, float x) { *p = __float2bfloat16(x); }
-__device__ __forceinline__ float load1(const float* p) { return *p; }
-__device__ __forceinline__ float load1(const __hip_bfloat16* p) { return __bfloat162float(*p); }
-
 // Tokens per LDS stage: as many of the chunk's 128 as leave room for a second workgroup on the CU
 // (one workgroup with d = 128), with at most 32 registers per thread for the next stage's loads; fp32 with
 // decay and d = 64 has no registers for more than 32.
@@ -154,6 +176,77 @@ struct AttnLds {
     static constexpr int SPLANE = DP * DP * 2;
     static constexpr int BYTES = Stage::BYTES + 3 * SPLANE;
 };
+
+// What attn_planes_kernel computes, in fp32 from the elements as they are, for a workgroup's chunks from `first`
+// on: a row of out per wave, the running state M [D][D] in LDS.  For inputs whose planes are not finite; one
+// such segment takes as long as scalar kernels do.
+template <typename T, int D>
+__device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems& probs, int nprob, int nseg, int cps, int first,
+                                            float* M)
+{
+    int x = blockIdx.x;
+    asm volatile("" : "+s"(x));   // (all of this worked out anew, so that none of it stays in registers through the walk)
+    const PlanesProblem pb = probs.p[x % nprob];
+    x /= nprob;
+    const int tid = threadIdx.x, grp = blockIdx.y;
+    int tok0, len, ps;
+    slot_range(g, x / nseg, tok0, len, ps);
+    const bool rev = pb.reverse != 0;
+    if (rev && g.wslots > 1) ps += (len - 1) / ((int)g.L / g.wslots);
+    const size_t base = ((size_t)grp * (size_t)g.N + tok0) * D;
+    const T* A = static_cast<const T*>(pb.A) + base;
+    const T* Bk = static_cast<const T*>(pb.Bk) + base;
+    const T* Cv = static_cast<const T*>(pb.Cv) + base;
+    T* out = static_cast<T*>(pb.out) + base;
+    const float* state = pb.state ? pb.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) : nullptr;
+    const float l2 = decay_log2(g, grp);
+    const int transpose = pb.transpose, last = min((len + kChunk - 1) / kChunk, (x % nseg + 1) * cps);
+    constexpr int NB = D > 64 ? 2 : 1;
+    const int lane = tid & 63, nch = (len + kChunk - 1) / kChunk;
+#pragma unroll 1
+    for (int e = tid; e < D * D; e += kThr) M[e] = state ? state[transpose ? (e % D) * D + e / D : e] : 0.f;
+#pragma unroll 1
+    for (int ci = 0; ci < last; ++ci) {
+        const int c0 = (rev ? nch - 1 - ci : ci) * kChunk, clen = min(kChunk, len - c0);
+        __syncthreads();   // M is written
+#pragma unroll 1
+        for (int i = ci < first ? clen : tid >> 6; i < clen; i += kThr / 64) {
+            float o[NB], t[NB];
+            const T* ar = A + (size_t)(c0 + i) * D;
+#pragma unroll
+            for (int u = 0; u < NB; ++u) { o[u] = 0.f; t[u] = 0.f; }
+#pragma unroll 1
+            for (int a = 0; a < D; ++a)
+#pragma unroll
+                for (int u = 0; u < NB; ++u) t[u] = fmaf(load1(ar + a), M[a * D + min(lane + 64 * u, D - 1)], t[u]);
+#pragma unroll 1
+            for (int j = rev ? i : 0; j <= (rev ? clen - 1 : i); ++j) {
+                float p = 0.f;
+#pragma unroll
+                for (int u = 0; u < NB; ++u)
+                    if (lane + 64 * u < D)
+                        p = fmaf(load1(ar + lane + 64 * u), load1(Bk + (size_t)(c0 + j) * D + lane + 64 * u), p);
+#pragma unroll
+                for (int k = 32; k > 0; k >>= 1) p += __shfl_xor(p, k, 64);
+                p *= exp2f((float)(rev ? j - i : i - j) * l2);
+#pragma unroll
+                for (int u = 0; u < NB; ++u) o[u] = fmaf(p, load1(Cv + (size_t)(c0 + j) * D + min(lane + 64 * u, D - 1)), o[u]);
+            }
+            const float wi = exp2f((float)(rev ? clen - i : i + 1) * l2);
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (lane + 64 * u < D) store1(out + (size_t)(c0 + i) * D + lane + 64 * u, fmaf(wi, t[u], o[u]));
+        }
+        __syncthreads();   // M has been read
+        if (ci + 1 < last) {
+            const float wc = exp2f((float)clen * l2);
+#pragma unroll 1
+            for (int e = tid; e < D * D; e += kThr)
+                M[e] = fmaf(wc, M[e], state_element(Bk + (size_t)c0 * D + e / D, Cv + (size_t)c0 * D + e % D, D, clen, l2,
+                                                    rev ? 0 : clen - 1, rev ? 1 : -1));
+        }
+    }
+}
 
 // out = [(A Bk^T) (.) mask] Cv + A * state for the rows of one segment of one slot, state += Bk^T Cv from
 // chunk to chunk of 128 rows (causal: first to last; reverse: mask j >= i, last to first).
@@ -226,6 +319,7 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
             }
     }
 
+    int redo = ci1;
     for (int ci = 0; ci < ci1; ++ci) {
         const int c0 = (rev ? nch - 1 - ci : ci) * kChunk, clen = min(kChunk, len - c0);
         const int nsub = (clen + 31) / 32;
@@ -345,58 +439,28 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
         if (!emit) { have_state = true; continue; }
 
         // A non-finite row of Cv would reach, as 0 * inf, the rows of its 32-token tile that the mask
-        // keeps from it.  Such chunks (any non-finite result) are done again row by row.
+        // keeps from it, and planes make NaN of an infinity and of what rounds to one.  Either shows as a
+        // non-finite result (a state that has one makes its whole column so): from that chunk on the
+        // segment is done again in fp32.
         float odd = 0.f;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) odd = fmaf(32 * nt + l32 < D ? acc[nt][v] : 0.f, 0.f, odd);
         if (__syncthreads_or(odd != 0.f)) {
-            for (int i = w; i < clen; i += 4) {
-                constexpr int NB = D > 64 ? 2 : 1;
-                float o[NB], t[NB];
-                const T* ar = A + (size_t)(c0 + i) * D;
-#pragma unroll
-                for (int u = 0; u < NB; ++u) { o[u] = 0.f; t[u] = 0.f; }
-                if (have_state) {
-                    for (int a = 0; a < D; ++a)
-#pragma unroll
-                        for (int u = 0; u < NB; ++u) {
-                            const int b = min(lane + 64 * u, D - 1);
-                            const char* e = snap + plane_off<DP>(b, a >> 3) + (a & 7) * 2;
-                            const float m = ((float)*reinterpret_cast<const __bf16*>(e + 2 * LD::SPLANE) +
-                                             (float)*reinterpret_cast<const __bf16*>(e + LD::SPLANE)) + (float)*reinterpret_cast<const __bf16*>(e);
-                            t[u] = fmaf(load1(ar + a), m, t[u]);
-                        }
-                }
-                for (int j = rev ? i : 0; j <= (rev ? clen - 1 : i); ++j) {
-                    float p = 0.f;
-#pragma unroll
-                    for (int u = 0; u < NB; ++u)
-                        if (lane + 64 * u < D) p = fmaf(load1(ar + lane + 64 * u), load1(Bk + (size_t)(c0 + j) * D + lane + 64 * u), p);
-#pragma unroll
-                    for (int k = 32; k > 0; k >>= 1) p += __shfl_xor(p, k, 64);
-                    if (DECAY) p *= decay_pow((float)(rev ? j - i : i - j), l2);
-#pragma unroll
-                    for (int u = 0; u < NB; ++u) o[u] = fmaf(p, load1(Cv + (size_t)(c0 + j) * D + min(lane + 64 * u, D - 1)), o[u]);
-                }
-                const float wi = DECAY ? decay_pow((float)(rev ? clen - i : i + 1), l2) : 1.f;
-#pragma unroll
-                for (int u = 0; u < NB; ++u)
-                    if (lane + 64 * u < D) store1(out + (size_t)(c0 + i) * D + lane + 64 * u, fmaf(wi, t[u], o[u]));
-            }
-            __syncthreads();   // the snapshot has been read
-        } else {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int i = 32 * w + acc_row(v) + 4 * h, b = 32 * nt + l32;
-                    if (i < clen && b < D) store1(out + (size_t)(c0 + i) * D + b, acc[nt][v]);
-                }
+            redo = ci;
+            break;
         }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int i = 32 * w + acc_row(v) + 4 * h, b = 32 * nt + l32;
+                if (i < clen && b < D) store1(out + (size_t)(c0 + i) * D + b, acc[nt][v]);
+            }
         have_state = true;
     }
+    if (redo < ci1) attn_scalar<T, D>(g, probs, nprob, nseg, cps, redo, reinterpret_cast<float*>(snap));
 }
 
 template <typename T, int D, bool DECAY>

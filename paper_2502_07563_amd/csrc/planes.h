@@ -10,7 +10,8 @@
 // scores, probabilities and states always three: nothing is held in fewer bits than fp32.
 // Why: the matrix unit multiplies fp32 operands at 1/16 of its bf16 rate, so three or six bf16
 // products are 5 or 2.7 times faster than one fp32 instruction.
-// Infinities and NaN stay non-finite (an infinity has no finite remainder, so it may come out as NaN).
+// An infinity, or a finite fp32 value that rounds to one in bf16 (above 3.39e38), has planes that make every
+// sum they enter NaN.
 #ifndef LASP2_PLANES_H
 #define LASP2_PLANES_H
 #include "mfma_tile.h"

@@ -106,6 +106,63 @@ def test_rows_that_the_mask_keeps_from_a_nan_stay_finite(dtype, d):
     assert rel_l2(to_host(dV[:, :, j + 1:]), to_host(gv[:, :, j + 1:])) <= LIMIT[dtype]
 
 
+def _positive_inputs(N, d, dtype, seed):
+    import torch
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator().manual_seed(seed)
+    return {n: (2.0 ** -5 * (0.125 + 0.875 * torch.rand(N, d, generator=gen))).to(tdt) for n in ("Q", "K", "V", "dO")}
+
+
+def _same_range(got, want, tol, what):
+    """Element by element: infinities where |want| is past fp32's range, within tol of the value elsewhere."""
+    import torch
+    got, past = got.double().cpu(), want.abs() > torch.finfo(torch.float32).max
+    assert torch.equal(got[past], torch.sign(want[past]) * float("inf")), what
+    err = ((got - want).abs() / want.abs())[~past]
+    assert bool((err <= tol).all()), (what, err.max().item())
+
+
+@pytest.mark.parametrize("C,L,walk", [(128, 256, ""), (48, 48, "3")])
+@pytest.mark.parametrize("lam", [None, 0.9])
+@pytest.mark.parametrize("dtype,d,value", [(t, d, v) for t, d in (("f32", 16), ("f32", 64), ("f32", 128), ("bf16", 64))
+                                           for v in (float("inf"), -float("inf"), 3.4e38) if t == "f32" or v != 3.4e38])
+def test_infinities_and_values_above_the_largest_bf16(monkeypatch, dtype, d, value, lam, C, L, walk):
+    """One element of K or V is infinite or close to fp32's largest value: chunk states, carried states, outputs and
+    gradients are what sums in fp32 give, in the chunk concerned, the ones after it and the slots after it (walked one by one,
+    or three at a time).  Everything else is positive and below 2^-5, so no sum has terms of both signs or leaves the
+    range by itself.  Bound per element: a sum of n positive terms of d-term scores, (n + d) 2^-24, and the decay's exponent,
+    400 log2(1/0.9) 2^-24; bf16 results 2^-8, half of the last of 8 bits.  (The reference has 1e300 for an infinity: what
+    comes out past fp32's range stands for one.)"""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    monkeypatch.setenv("LASP2_WALK_SLOTS", walk)
+    N, j = 400, 130                                # second chunk of the first walk
+    tol = (N + d + 100) * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0.0)
+    w = torch.ones(N, N, dtype=torch.float64)
+    if lam is not None:
+        i = torch.arange(N)
+        w = float(np.float32(lam)) ** (i[:, None] - i[None]).double()
+    w = w.tril()
+    for name, col in (("K", 3), ("V", 5)):
+        x = _positive_inputs(N, d, dtype, d)
+        x[name][j, col] = value
+        ref = {n: v.double() for n, v in x.items()}
+        if np.isinf(value):
+            ref[name][j, col] = 1e300 if value > 0 else -1e300
+        p = bd.Problem(1, 1, N, d, C, L, dtype, decay=None if lam is None else np.array([lam], dtype=np.float32))
+        t = {n: v.cuda().view(1, 1, N, d) for n, v in x.items()}
+        M = bd.alloc_states(p)
+        bd.lasp2_chunk_states(p, t["K"], t["V"], M)
+        O, P = bd.forward(p, t["Q"], t["K"], t["V"])
+        dQ, dK, dV, _ = bd.backward(p, t["Q"], t["K"], t["V"], t["dO"], P)
+        s, g = w * (ref["Q"] @ ref["K"].T), w * (ref["dO"] @ ref["V"].T)
+        for slot, a in enumerate(range(0, N, L)):
+            b = min(a + L, N)
+            _same_range(M[0, 0, slot], (ref["K"][a:b] * w[b - 1, a:b, None]).T @ ref["V"][a:b], (N + 100) * 2.0 ** -24, ("M", name, slot))
+        for what, a, b in (("O", O, s @ ref["V"]), ("dQ", dQ, g @ ref["K"]), ("dK", dK, g.T @ ref["Q"]), ("dV", dV, s.T @ ref["dO"])):
+            _same_range(a[0, 0], b, tol, (what, name))
+
+
 def _softmax64(Q, K, V, dO, bounds, causal, q0):
     """The definition in 64 bits: queries are the tokens q0 .. of N keys, attending inside their document."""
     n, N, d = Q.shape[1], K.shape[1], Q.shape[2]
