@@ -25,12 +25,6 @@ struct Tiles {
 // lam^e, l2 = log2 lam (the hardware exponential: 1 ulp; results below 2^-126 are zero)
 __device__ __forceinline__ float decay_pow(float e, float l2) { return __builtin_amdgcn_exp2f(e * l2); }
 
-template <typename T> __device__ __forceinline__ void store1(T* p, float x);
-template <> __device__ __forceinline__ void store1(float* p, float x) { *p = x; }
-template <> __device__ __forceinline__ void store1(__hip_bfloat16* p, float x) { *p = __float2bfloat16(x); }
-__device__ __forceinline__ float load1(const float* p) { return *p; }
-__device__ __forceinline__ float load1(const __hip_bfloat16* p) { return __bfloat162float(*p); }
-
 // Rescales the elements of a transposed fetch (tokens r0 + 4h + .., planes.h) by lam^(e0 + de * token):
 // the planes add up to the exact value, the product is an fp32 one and is split again.
 template <int NP>

@@ -175,6 +175,135 @@ __device__ __forceinline__ void load_rows(bf16x8 (&f)[KS][NP], const T* row, boo
     for (int ks = 0; ks < KS; ++ks) to_planes(load8(row + 16 * ks + 8 * h, ok), f[ks]);
 }
 
+// ---- Rows with a non-finite result, once more in fp32, by the row's wave ----
+// A non-finite partner row reaches, as 0 * inf, the rows of its tile that the mask (or their document) keeps from it,
+// and planes make NaN of an infinity and of what rounds to one (planes.h): an infinite key whose scores are -inf has
+// the probability 0.  The sums below are over a row's own partners and the elements as they are.
+
+// The lane, worked out anew, so that it does not stay in a register through the walk before.
+__device__ __forceinline__ int lane_again()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t & 63;
+}
+
+// lanes (h = 0 and 1) of the rows whose accumulators are not all finite, as a mask of rows
+template <int D>
+__device__ __forceinline__ uint32_t odd_rows(const f32x16 (&acc)[(D < 32 ? 32 : D) / 32], float extra, bool valid, int h)
+{
+    float odd = extra * 0.f;
+#pragma unroll
+    for (int nt = 0; nt < (D < 32 ? 32 : D) / 32; ++nt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) odd = fmaf(32 * nt + acc_row(v) + 4 * h < D ? acc[nt][v] : 0.f, 0.f, odd);
+    const unsigned long long m = __ballot(valid && odd != 0.f);
+    return (uint32_t)m | (uint32_t)(m >> 32);
+}
+
+template <typename T, int D>
+__device__ __forceinline__ float dot_row(const T* a, const T* b)
+{
+    float s = 0.f;
+#pragma unroll 4
+    for (int e = 0; e < D; ++e) s = fmaf(load1(a + e), load1(b + e), s);
+    return s;
+}
+
+// o += sum over the block's n rows of X of (lane's coefficient) * row; a lane has the columns lane and lane + 64
+template <typename T, int D>
+__device__ __forceinline__ void add_rows(float (&o)[2], float coef, const T* X, int n, int lane)
+{
+#pragma unroll 1
+    for (int j = 0; j < n; ++j) {
+        const float c = __shfl(coef, j, 64);
+#pragma unroll
+        for (int u = 0; u < (D > 64 ? 2 : 1); ++u) o[u] = fmaf(c, load1(X + (size_t)j * D + min(lane + 64 * u, D - 1)), o[u]);
+    }
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void put_row(T* row, const float (&o)[2], float f, int lane)
+{
+#pragma unroll
+    for (int u = 0; u < (D > 64 ? 2 : 1); ++u)
+        if (lane + 64 * u < D) store1(row + lane + 64 * u, o[u] * f);
+}
+
+// q, o: the row; K, V: of the group; keys [lo, hi)
+template <typename T, int D>
+__device__ __forceinline__ void fwd_row(const T* q, const T* K, const T* V, T* out, float* lse, int lo, int hi, int lane)
+{
+    const float scale = rsqrtf((float)D);
+    float m = -INFINITY, l = 0.f, o[2] = {0.f, 0.f};
+    bool nan = false;                 // a score is: so are the row's sum and every element
+#pragma unroll 1
+    for (int k0 = lo; k0 < hi && !nan; k0 += 64) {
+        const float s = k0 + lane < hi ? dot_row<T, D>(q, K + (size_t)(k0 + lane) * D) * scale : -INFINITY;
+        m = fmaxf(m, s);
+        nan = __any(s != s);
+    }
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) m = fmaxf(m, __shfl_xor(m, k, 64));
+    const float mu = m == -INFINITY ? 0.f : m;
+    if (nan) l = NAN;
+#pragma unroll 1
+    for (int k0 = lo; k0 < hi && !nan; k0 += 64) {
+        const float p = k0 + lane < hi ? expf(dot_row<T, D>(q, K + (size_t)(k0 + lane) * D) * scale - mu) : 0.f;
+        l += p;
+        add_rows<T, D>(o, p, V + (size_t)k0 * D, min(64, hi - k0), lane);
+    }
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) l += __shfl_xor(l, k, 64);
+    put_row<T, D>(out, o, 1.f / l, lane);
+    if (lane == 0) *lse = m + logf(l);
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void dq_row(const T* q, const T* d, const T* K, const T* V, float lse, float dlt, T* out, int lo, int hi,
+                                       int lane)
+{
+    const float scale = rsqrtf((float)D);
+    float o[2] = {0.f, 0.f};
+    bool nan = false;
+#pragma unroll 1
+    for (int k0 = lo; k0 < hi && !nan; k0 += 64) {
+        float ds = 0.f;
+        if (k0 + lane < hi) {
+            const size_t r = (size_t)(k0 + lane) * D;
+            ds = expf(dot_row<T, D>(q, K + r) * scale - lse) * (dot_row<T, D>(d, V + r) - dlt);
+        }
+        nan = __any(ds != ds);
+        add_rows<T, D>(o, ds * scale, K + (size_t)k0 * D, nan ? 0 : min(64, hi - k0), lane);
+    }
+    put_row<T, D>(out, o, nan ? NAN : 1.f, lane);
+}
+
+// k, x: the key's rows of K and V; Q, dO, LSE, delta: of the group's share, queries [lo, hi) counted from its first
+template <typename T, int D>
+__device__ __forceinline__ void dkv_row(const T* k, const T* x, const T* Q, const T* dO, const float* LSE, const float* delta, T* dk,
+                                        T* dv, int lo, int hi, int lane)
+{
+    const float scale = rsqrtf((float)D);
+    float ok[2] = {0.f, 0.f}, ov[2] = {0.f, 0.f};
+    bool nan = false;
+#pragma unroll 1
+    for (int i0 = lo; i0 < hi && !nan; i0 += 64) {
+        float p = 0.f, ds = 0.f;
+        if (i0 + lane < hi) {
+            const size_t r = (size_t)(i0 + lane) * D;
+            p = expf(dot_row<T, D>(k, Q + r) * scale - LSE[i0 + lane]);
+            ds = p * (dot_row<T, D>(x, dO + r) - delta[i0 + lane]);
+        }
+        nan = __any(p != p);
+        const int n = nan ? 0 : min(64, hi - i0);
+        add_rows<T, D>(ok, ds * scale, Q + (size_t)i0 * D, n, lane);
+        add_rows<T, D>(ov, p, dO + (size_t)i0 * D, n, lane);
+    }
+    put_row<T, D>(dk, ok, nan ? NAN : 1.f, lane);
+    put_row<T, D>(dv, ov, nan ? NAN : 1.f, lane);
+}
+
 template <typename T, int D, int QW, int KW>
 __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K,
                                                                   const T* __restrict__ V, T* __restrict__ O,
@@ -277,9 +406,19 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_pl
                 for (int v = 0; v < 16; ++v) acc[nt][v] = acc[nt][v] * fa + o[(16 * nt + v) * 64] * fb;
         }
     }
-    if (!valid) return;
-    store_row<T, D>(O + qbase + (size_t)row * D, acc, 1.f / l, h);
-    if (h == 0) LSE[(size_t)grp * g.qn + row] = fmaf(m, kLn2, logf(l));
+    const float inv = 1.f / l;
+    const int ln = lane_again(), first = __builtin_amdgcn_readfirstlane(row);
+    uint32_t odd = odd_rows<D>(acc, inv, valid, h);
+    if (valid && !((odd >> (ln & 31)) & 1u)) {
+        store_row<T, D>(O + qbase + (size_t)row * D, acc, inv, h);
+        if (h == 0) LSE[(size_t)grp * g.qn + row] = fmaf(m, kLn2, logf(l));
+    }
+    for (; odd; odd &= odd - 1) {
+        const int r = first + __builtin_ctz(odd);
+        keys_of(g, g.q0 + r, causal, klo, khi);
+        fwd_row<T, D>(Q + qbase + (size_t)r * D, K + kbase, V + kbase, O + qbase + (size_t)r * D, LSE + (size_t)grp * g.qn + r, klo, khi,
+                      ln);
+    }
 }
 
 // dQ = scale * sum_j dS_j k_j, with dS = P (dO.v - delta), P rebuilt from the log-sum-exp
@@ -367,7 +506,15 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
                 for (int v = 0; v < 16; ++v) acc[nt][v] += o[(16 * nt + v) * 64];
         }
     }
-    if (valid) store_row<T, D>(dQ + qbase + (size_t)row * D, acc, scale, h);
+    const int ln = lane_again(), first = __builtin_amdgcn_readfirstlane(row);
+    uint32_t odd = odd_rows<D>(acc, 0.f, valid, h);
+    if (valid && !((odd >> (ln & 31)) & 1u)) store_row<T, D>(dQ + qbase + (size_t)row * D, acc, scale, h);
+    for (; odd; odd &= odd - 1) {
+        const int r = first + __builtin_ctz(odd);
+        const size_t o = qbase + (size_t)r * D, i = (size_t)grp * g.qn + r;
+        keys_of(g, g.q0 + r, causal, klo, khi);
+        dq_row<T, D>(Q + o, dO + o, K + kbase, V + kbase, LSE[i], delta[i], dQ + o, klo, khi, ln);
+    }
 }
 
 // dV = sum_i P_i dO_i and dK = scale * sum_i dS_i q_i: a key per lane, the share's queries pass through LDS with
@@ -502,9 +649,18 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 || (D == 64 && planes_of<T>:
                 }
         }
     }
-    if (!valid) return;
-    store_row<T, D>(dK + kbase + (size_t)row * D, ak, scale, h);
-    store_row<T, D>(dV + kbase + (size_t)row * D, av, 1.f, h);
+    const int ln = lane_again(), first = __builtin_amdgcn_readfirstlane(row);
+    uint32_t odd = odd_rows<D>(ak, 0.f, valid, h) | odd_rows<D>(av, 0.f, valid, h);
+    if (valid && !((odd >> (ln & 31)) & 1u)) {
+        store_row<T, D>(dK + kbase + (size_t)row * D, ak, scale, h);
+        store_row<T, D>(dV + kbase + (size_t)row * D, av, 1.f, h);
+    }
+    for (; odd; odd &= odd - 1) {
+        const int r = first + __builtin_ctz(odd);
+        const size_t o = kbase + (size_t)r * D, i = (size_t)grp * g.qn;
+        queries_of(g, r, causal, ilo, ihi);
+        dkv_row<T, D>(K + o, V + o, Qg, Dg, LSE + i, delta + i, dK + o, dV + o, ilo - g.q0, ihi - g.q0, ln);
+    }
 }
 
 // Workgroups of four row tiles, unless they fill less than the device twice over: then two tiles and four (fp32

@@ -102,6 +102,13 @@ __device__ __forceinline__ f32x16 zero16()
     return z;
 }
 
+// one element in global memory
+template <typename T> __device__ __forceinline__ void store1(T* p, float x);
+template <> __device__ __forceinline__ void store1(float* p, float x) { *p = x; }
+template <> __device__ __forceinline__ void store1(__hip_bfloat16* p, float x) { *p = __float2bfloat16(x); }
+__device__ __forceinline__ float load1(const float* p) { return *p; }
+__device__ __forceinline__ float load1(const __hip_bfloat16* p) { return __bfloat162float(*p); }
+
 // 8 consecutive elements in global memory (16-byte aligned), raw, as 16-byte words
 template <typename T> struct raw8;
 template <> struct raw8<float> { u32x4 w[2]; };

@@ -210,3 +210,81 @@ def test_softmax_tile_edges(dtype, d, causal):
         for name, a, b in zip(("O", "LSE", "dQ", "dK", "dV"), got, want):
             err = np.linalg.norm(a - b) / max(np.linalg.norm(b), 0.05 * scale)
             assert err <= limit, (name, dtype, d, causal, G, N, q0, n, err)
+
+
+def _softmax_all(dtype, d, x, causal, cu=None):
+    """O, LSE, dQ, dK, dV as 64-bit host tensors [N, d] ([N])."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    N = x["Q"].shape[0]
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    p = bd.Problem(1, 1, N, d, 64, 0, dtype, cu)
+    Q, K, V, dO = (x[n].to(tdt).cuda().view(1, 1, N, d) for n in ("Q", "K", "V", "dO"))
+    O, dQ, dK, dV = (torch.empty_like(Q) for _ in range(4))
+    lse = torch.empty(1, 1, N, device="cuda")
+    ws = torch.empty(bd.lasp2_softmax_workspace_size(p), dtype=torch.uint8, device="cuda")
+    bd.lasp2_softmax_fwd(p, Q, K, V, O, lse, causal)
+    bd.lasp2_softmax_bwd(p, Q, K, V, O, dO, lse, dQ, dK, dV, ws, causal)
+    return [t[0, 0].double().cpu() for t in (O, lse, dQ, dK, dV)]
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_softmax_rows_that_the_mask_keeps_from_a_nan_stay_finite(dtype, d):
+    """A NaN in V at token j reaches O at j and later in the same document, one in dO (and so in its delta) at token i the
+    rows of dV and dK at i and before: not the other rows of the tile, nor the next document in it."""
+    import torch
+    N, cu = 300, np.array([0, 90, 300], dtype=np.int32)
+    x = {n: 2 * torch.randn(N, d, generator=torch.Generator().manual_seed(ord(n[-1]))) for n in ("Q", "K", "V", "dO")}
+    good = _softmax_all(dtype, d, x, True, cu)
+    limit = {"f32": 1e-5, "bf16": 1e-2}[dtype]     # (four and two times the error of a row allowed above)
+    j = 77                                         # documents meet at 90: both lie in the tile 64 .. 95
+    y = dict(x, V=x["V"].clone())
+    y["V"][j, 3] = float("nan")
+    O, lse, dQ = _softmax_all(dtype, d, y, True, cu)[:3]
+    free = (torch.arange(N) < j) | (torch.arange(N) >= 90)
+    assert torch.isnan(O[~free, 3]).all() and torch.isfinite(O[~free][:, [2, 4]]).all()
+    assert torch.isfinite(lse).all() and torch.isfinite(O[free]).all() and torch.isfinite(dQ[free]).all()
+    assert rel_l2(O[free], good[0][free]) <= limit and rel_l2(dQ[free], good[2][free]) <= limit
+    y = dict(x, dO=x["dO"].clone())
+    y["dO"][95, 3] = float("nan")                  # sixth token of the second document
+    dQ, dK, dV = _softmax_all(dtype, d, y, True, cu)[2:]
+    free = (torch.arange(N) < 90) | (torch.arange(N) > 95)
+    assert torch.isnan(dV[~free, 3]).all() and torch.isnan(dK[~free]).all() and torch.isnan(dQ[95]).all()
+    assert torch.isfinite(dV[free]).all() and torch.isfinite(dK[free]).all() and torch.isfinite(dQ[torch.arange(N) != 95]).all()
+    assert rel_l2(dV[free], good[4][free]) <= limit and rel_l2(dK[free], good[3][free]) <= limit
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_softmax_infinite_keys_and_large_values(dtype, d, causal):
+    """Queries are positive, so a key with an element of -inf has scores of -inf and probability 0: the layer is that
+    without the key, with dK = dV = 0 for it.  fp32: a value of 3.4e38, above
+    the largest bf16, is taken as the finite number that it is."""
+    import torch
+    N, j = 300, 70
+    limit = {"f32": 1e-5, "bf16": 1e-2}[dtype]
+    x = {n: torch.randn(N, d, generator=torch.Generator().manual_seed(ord(n[-1]))) for n in ("Q", "K", "V", "dO")}
+    x["Q"] = x["Q"].abs() + 0.1
+    x["K"][j, 3] = -float("inf")
+    O, lse, dQ, dK, dV = _softmax_all(dtype, d, x, causal)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    r = {n: v.to(tdt).double() for n, v in x.items()}
+    r["K"][j, 3] = -1e9                            # exp of it is 0 in 64 bits too
+    n64 = {n: v.numpy()[None] for n, v in r.items()}
+    want = [torch.from_numpy(t[0]) for t in _softmax64(n64["Q"], n64["K"], n64["V"], n64["dO"], np.array([0, N]), causal, 0)]
+    for what, a, b in (("O", O, want[0]), ("LSE", lse[:, None], want[1][:, None]), ("dV", dV, want[4])):
+        assert rel_l2(a, b) <= limit, what
+    # dS = 0 for the key: 0 * inf in dQ's column 3 for the rows that see it, as in any arithmetic; dK has no such term
+    assert torch.equal(dK[j], torch.zeros(d, dtype=torch.float64)) and torch.equal(dV[j], torch.zeros(d, dtype=torch.float64))
+    cols = [c for c in range(d) if c != 3]
+    assert rel_l2(dQ[:, cols], want[2][:, cols]) <= limit and rel_l2(dK, want[3]) <= limit
+    if dtype == "f32":
+        x["K"][j, 3] = 0.0
+        x["V"][j, 5] = 3.4e38
+        O = _softmax_all(dtype, d, x, causal)[0]
+        n64 = {n: v.double().numpy()[None] for n, v in x.items()}
+        p = _softmax64(n64["Q"], n64["K"], n64["V"], n64["dO"], np.array([0, N]), causal, 0)[0][0]
+        assert torch.isfinite(O).all()
+        assert rel_l2(O[:, 5], p[:, 5]) <= limit
+        cols = [c for c in range(d) if c != 5]
+        assert rel_l2(O[:, cols], p[:, cols]) <= limit
