@@ -1,7 +1,7 @@
 """The small passes between the large kernels, against 64-bit sums.  Prefix and suffix of the states: where the
 walk's batches of eight slots and the documents' borders meet (fewer slots than a batch, one more or less,
-several documents in a batch).  Row sums of the softmax backward: every head size and type, numbers of
-rows beside those of a workgroup."""
+several documents in a batch).  Row sums of the softmax backward, by the
+gradients they enter: every head size and type, numbers of rows beside those of a workgroup."""
 import numpy as np
 import pytest
 import torch
@@ -46,15 +46,27 @@ def test_state_prefix(d, slots, decay, reverse, in_place):
 @pytest.mark.parametrize("d", [16, 32, 64, 128])
 @pytest.mark.parametrize("N", [1, 31, 257])
 def test_softmax_row_sums(dtype, d, N):
+    """dS = P (dP - delta), delta = dO . O: with an O of 64 times the usual size delta is most of dS, so dQ and dK carry its
+    relative error (and that of the other terms) row by row."""
     p = bd.Problem(1, 3, N, d, 64, 0, dtype)
     gen = torch.Generator(device="cuda").manual_seed(N * d)
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
-    Q, K, V, dO = (torch.randn(1, 3, N, d, generator=gen, device="cuda").to(tdt) for _ in range(4))
-    O, dQ, dK, dV = (torch.empty_like(Q) for _ in range(4))
+    Q, K, V, dO, O = (torch.randn(1, 3, N, d, generator=gen, device="cuda").to(tdt) for _ in range(5))
+    dQ, dK, dV = (torch.empty_like(Q) for _ in range(3))
     LSE = torch.empty(1, 3, N, device="cuda")
     ws = torch.full((bd.lasp2_softmax_workspace_size(p) // 4,), float("nan"), device="cuda")
-    bd.lasp2_softmax_fwd(p, Q, K, V, O, LSE, True)
+    bd.lasp2_softmax_fwd(p, Q, K, V, torch.empty_like(Q), LSE, True)
+    O = O * 64
     bd.lasp2_softmax_bwd(p, Q, K, V, O, dO, LSE, dQ, dK, dV, ws, True)
-    terms = (O.double() * dO.double()).view(-1, d)
-    err = (ws[:3 * N].double() - terms.sum(1)).abs()   # the workspace begins with the row sums
-    assert bool((err <= d * 2.0 ** -24 * terms.abs().sum(1)).all())   # d roundings of at most the sum of magnitudes
+    q, k, v, w, o = (x[0].double().cpu() for x in (Q, K, V, dO, O))
+    tr = lambda x: x.transpose(1, 2).contiguous()
+    P = torch.softmax((q @ tr(k) / d ** 0.5).masked_fill(torch.ones(N, N).triu(1).bool(), -float("inf")), 2)
+    size = (w * o).abs().sum(2, keepdim=True)                    # what delta is the sum of
+    ds = P * (w @ tr(v) - (w * o).sum(2, keepdim=True)) / d ** 0.5
+    # Per row, against the row if every delta had the size of its terms: fp32 d 2^-24 for the sum and as much for the
+    # rounded exponent (scores below 2^3) and the sums over N rows; bf16 2^-8 each for P, dS and the result.
+    tol = (2 * d + N) * 2.0 ** -24 if dtype == "f32" else 3 * 2.0 ** -8
+    big = P * size / d ** 0.5
+    for name, got, want, scale in (("dQ", dQ, ds @ k, (big ** 2 @ (k ** 2)).sum(2)), ("dK", dK, tr(ds) @ q, (tr(big) ** 2 @ (q ** 2)).sum(2))):
+        err = (got[0].double().cpu() - want).norm(dim=2)
+        assert bool((err <= tol * scale.sqrt()).all()), (name, (err / scale.sqrt()).max().item(), tol)
