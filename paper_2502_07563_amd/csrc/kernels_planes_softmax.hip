@@ -201,25 +201,62 @@ __device__ __forceinline__ uint32_t odd_rows(const f32x16 (&acc)[(D < 32 ? 32 : 
     return (uint32_t)m | (uint32_t)(m >> 32);
 }
 
+__device__ __forceinline__ float value_of(const raw8<float>& r, int e) { return __builtin_bit_cast(float, (uint32_t)r.w[e / 4][e % 4]); }
+__device__ __forceinline__ float value_of(const raw8<__hip_bfloat16>& r, int e)
+{
+    const uint32_t w = r.w[0][e / 2];
+    return __builtin_bit_cast(float, e % 2 ? w & 0xffff0000u : w << 16);
+}
+
 template <typename T, int D>
 __device__ __forceinline__ float dot_row(const T* a, const T* b)
 {
     float s = 0.f;
 #pragma unroll 4
-    for (int e = 0; e < D; ++e) s = fmaf(load1(a + e), load1(b + e), s);
+    for (int c = 0; c < D; c += 8) {
+        const raw8<T> x = load8(a + c, true), y = load8(b + c, true);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s = fmaf(value_of(x, e), value_of(y, e), s);
+    }
     return s;
 }
 
-// o += sum over the block's n rows of X of (lane's coefficient) * row; a lane has the columns lane and lane + 64
+// o += sum over n rows of X (1 .. 64) of (lane j's coefficient) * row j; a lane has the columns lane and lane + 64
 template <typename T, int D>
 __device__ __forceinline__ void add_rows(float (&o)[2], float coef, const T* X, int n, int lane)
 {
-#pragma unroll 1
-    for (int j = 0; j < n; ++j) {
-        const float c = __shfl(coef, j, 64);
+    constexpr int NU = D > 64 ? 2 : 1;
+    auto row = [&](int j, float (&x)[NU]) {
 #pragma unroll
-        for (int u = 0; u < (D > 64 ? 2 : 1); ++u) o[u] = fmaf(c, load1(X + (size_t)j * D + min(lane + 64 * u, D - 1)), o[u]);
+        for (int u = 0; u < NU; ++u) x[u] = load1(X + (size_t)j * D + min(lane + 64 * u, D - 1));
+    };
+    auto add = [&](int j, const float (&x)[NU]) {
+        const float c = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, coef), j));
+#pragma unroll
+        for (int u = 0; u < NU; ++u) o[u] = fmaf(c, x[u], o[u]);
+    };
+    int j = 0;
+#pragma unroll 1
+    for (; j + 8 <= n; j += 8) {      // (eight rows' loads in flight)
+        float x[8][NU];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) row(j + e, x[e]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) add(j + e, x[e]);
     }
+#pragma unroll 1
+    for (; j < n; ++j) {
+        float x[NU];
+        row(j, x);
+        add(j, x);
+    }
+}
+
+// every column of the row is NaN: it stays so
+template <int D>
+__device__ __forceinline__ bool all_nan(const float (&o)[2])
+{
+    return __all(o[0] != o[0] && (D <= 64 || o[1] != o[1]));
 }
 
 template <typename T, int D>
@@ -230,33 +267,40 @@ __device__ __forceinline__ void put_row(T* row, const float (&o)[2], float f, in
         if (lane + 64 * u < D) store1(row + lane + 64 * u, o[u] * f);
 }
 
-// q, o: the row; K, V: of the group; keys [lo, hi)
+// q, out: the row; K, V: of the group; keys [lo, hi).  known: the row's log-sum-exp, if the walk found a finite one.
 template <typename T, int D>
-__device__ __forceinline__ void fwd_row(const T* q, const T* K, const T* V, T* out, float* lse, int lo, int hi, int lane)
+__device__ __forceinline__ void fwd_row(const T* q, const T* K, const T* V, T* out, float* lse, float known, int lo, int hi, int lane)
 {
     const float scale = rsqrtf((float)D);
-    float m = -INFINITY, l = 0.f, o[2] = {0.f, 0.f};
+    float m = known, l = 1.f, o[2] = {0.f, 0.f};
     bool nan = false;                 // a score is: so are the row's sum and every element
+    const bool all = !(known - known == 0.f);
+    if (all) {
+        m = -INFINITY;
 #pragma unroll 1
-    for (int k0 = lo; k0 < hi && !nan; k0 += 64) {
-        const float s = k0 + lane < hi ? dot_row<T, D>(q, K + (size_t)(k0 + lane) * D) * scale : -INFINITY;
-        m = fmaxf(m, s);
-        nan = __any(s != s);
-    }
+        for (int k0 = lo; k0 < hi && !nan; k0 += 64) {
+            const float s = k0 + lane < hi ? dot_row<T, D>(q, K + (size_t)(k0 + lane) * D) * scale : -INFINITY;
+            m = fmaxf(m, s);
+            nan = __any(s != s);
+        }
 #pragma unroll
-    for (int k = 32; k > 0; k >>= 1) m = fmaxf(m, __shfl_xor(m, k, 64));
+        for (int k = 32; k > 0; k >>= 1) m = fmaxf(m, __shfl_xor(m, k, 64));
+        l = nan ? NAN : 0.f;
+    }
     const float mu = m == -INFINITY ? 0.f : m;
-    if (nan) l = NAN;
 #pragma unroll 1
     for (int k0 = lo; k0 < hi && !nan; k0 += 64) {
         const float p = k0 + lane < hi ? expf(dot_row<T, D>(q, K + (size_t)(k0 + lane) * D) * scale - mu) : 0.f;
-        l += p;
+        if (all) l += p;
         add_rows<T, D>(o, p, V + (size_t)k0 * D, min(64, hi - k0), lane);
+        nan = !all && all_nan<D>(o);
     }
+    if (all) {
 #pragma unroll
-    for (int k = 32; k > 0; k >>= 1) l += __shfl_xor(l, k, 64);
+        for (int k = 32; k > 0; k >>= 1) l += __shfl_xor(l, k, 64);
+    }
     put_row<T, D>(out, o, 1.f / l, lane);
-    if (lane == 0) *lse = m + logf(l);
+    if (lane == 0) *lse = all ? m + logf(l) : known;
 }
 
 template <typename T, int D>
@@ -273,13 +317,14 @@ __device__ __forceinline__ void dq_row(const T* q, const T* d, const T* K, const
             const size_t r = (size_t)(k0 + lane) * D;
             ds = expf(dot_row<T, D>(q, K + r) * scale - lse) * (dot_row<T, D>(d, V + r) - dlt);
         }
-        nan = __any(ds != ds);
-        add_rows<T, D>(o, ds * scale, K + (size_t)k0 * D, nan ? 0 : min(64, hi - k0), lane);
+        add_rows<T, D>(o, ds * scale, K + (size_t)k0 * D, min(64, hi - k0), lane);
+        nan = all_nan<D>(o);
     }
-    put_row<T, D>(out, o, nan ? NAN : 1.f, lane);
+    put_row<T, D>(out, o, 1.f, lane);
 }
 
-// k, x: the key's rows of K and V; Q, dO, LSE, delta: of the group's share, queries [lo, hi) counted from its first
+// k, x: the key's rows of K and V; Q, dO, LSE, delta: of the group's share, queries [lo, hi) counted from its first;
+// dk, dv: where the row goes, or null for a row that is right as it is
 template <typename T, int D>
 __device__ __forceinline__ void dkv_row(const T* k, const T* x, const T* Q, const T* dO, const float* LSE, const float* delta, T* dk,
                                         T* dv, int lo, int hi, int lane)
@@ -293,21 +338,21 @@ __device__ __forceinline__ void dkv_row(const T* k, const T* x, const T* Q, cons
         if (i0 + lane < hi) {
             const size_t r = (size_t)(i0 + lane) * D;
             p = expf(dot_row<T, D>(k, Q + r) * scale - LSE[i0 + lane]);
-            ds = p * (dot_row<T, D>(x, dO + r) - delta[i0 + lane]);
+            if (dk) ds = p * (dot_row<T, D>(x, dO + r) - delta[i0 + lane]);
         }
-        nan = __any(p != p);
-        const int n = nan ? 0 : min(64, hi - i0);
-        add_rows<T, D>(ok, ds * scale, Q + (size_t)i0 * D, n, lane);
-        add_rows<T, D>(ov, p, dO + (size_t)i0 * D, n, lane);
+        const int n = min(64, hi - i0);
+        if (dk) add_rows<T, D>(ok, ds * scale, Q + (size_t)i0 * D, n, lane);
+        if (dv) add_rows<T, D>(ov, p, dO + (size_t)i0 * D, n, lane);
+        nan = (!dk || all_nan<D>(ok)) && (!dv || all_nan<D>(ov));
     }
-    put_row<T, D>(dk, ok, nan ? NAN : 1.f, lane);
-    put_row<T, D>(dv, ov, nan ? NAN : 1.f, lane);
+    if (dk) put_row<T, D>(dk, ok, 1.f, lane);
+    if (dv) put_row<T, D>(dv, ov, 1.f, lane);
 }
 
 template <typename T, int D, int QW, int KW>
-__global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K,
-                                                                  const T* __restrict__ V, T* __restrict__ O,
-                                                                  float* __restrict__ LSE, int causal)
+__global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_planes_kernel(
+    Geom g, const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O, float* __restrict__ LSE,
+    int causal)
 {
     typedef SmCfg<T, D, QW, KW> Cf;
     typedef typename Cf::Stage Stage;
@@ -316,7 +361,11 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_pl
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
     const int qw = w / KW, kw = w % KW, grp = blockIdx.y;
     const bool mirrored = causal && g.n_seqs == 0;
-    const int bx = mirrored ? blockIdx.x : gridDim.x - 1 - blockIdx.x;   // longest rows first (causal)
+    // Order of the workgroups within a group.  Mirrored ones are alike.  Else documents start with their last rows,
+    // which are the longest under a causal mask; one causal sequence (four row tiles) with its first.  The other order
+    // is no better there, because the groups follow one another and the last one's longest workgroup comes late either
+    // way (16 x 4096 x 128 in fp32, us, first rows first | last rows first: forward 903 | 923, backward 3110 | 3029).
+    const int bx = mirrored ? blockIdx.x : gridDim.x - 1 - blockIdx.x;
     const int wr = tile_row<QW>(bx, qw, g.qn, mirrored), row = wr + l32;
     int r0, r1;
     wg_rows<QW>(bx, g.qn, mirrored, r0, r1);
@@ -406,27 +455,26 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_pl
                 for (int v = 0; v < 16; ++v) acc[nt][v] = acc[nt][v] * fa + o[(16 * nt + v) * 64] * fb;
         }
     }
-    const float inv = 1.f / l;
+    const float inv = 1.f / l, lse = fmaf(m, kLn2, logf(l));
     const int ln = lane_again(), first = __builtin_amdgcn_readfirstlane(row);
     uint32_t odd = odd_rows<D>(acc, inv, valid, h);
     if (valid && !((odd >> (ln & 31)) & 1u)) {
         store_row<T, D>(O + qbase + (size_t)row * D, acc, inv, h);
-        if (h == 0) LSE[(size_t)grp * g.qn + row] = fmaf(m, kLn2, logf(l));
+        if (h == 0) LSE[(size_t)grp * g.qn + row] = lse;
     }
     for (; odd; odd &= odd - 1) {
         const int r = first + __builtin_ctz(odd);
         keys_of(g, g.q0 + r, causal, klo, khi);
-        fwd_row<T, D>(Q + qbase + (size_t)r * D, K + kbase, V + kbase, O + qbase + (size_t)r * D, LSE + (size_t)grp * g.qn + r, klo, khi,
-                      ln);
+        fwd_row<T, D>(Q + qbase + (size_t)r * D, K + kbase, V + kbase, O + qbase + (size_t)r * D, LSE + (size_t)grp * g.qn + r,
+                      __shfl(lse, __builtin_ctz(odd), 64), klo, khi, ln);
     }
 }
 
 // dQ = scale * sum_j dS_j k_j, with dS = P (dO.v - delta), P rebuilt from the log-sum-exp
 template <typename T, int D, int QW, int KW>
-__global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K,
-                                                                     const T* __restrict__ V, const T* __restrict__ dO,
-                                                                     const float* __restrict__ LSE, const float* __restrict__ delta,
-                                                                     T* __restrict__ dQ, int causal)
+__global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq_planes_kernel(
+    Geom g, const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
+    const float* __restrict__ LSE, const float* __restrict__ delta, T* __restrict__ dQ, int causal)
 {
     typedef SmCfg<T, D, QW, KW> Cf;
     typedef typename Cf::Stage Stage;
@@ -435,7 +483,7 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
     const int qw = w / KW, kw = w % KW, grp = blockIdx.y;
     const bool mirrored = causal && g.n_seqs == 0;
-    const int bx = mirrored ? blockIdx.x : gridDim.x - 1 - blockIdx.x;   // longest rows first (causal)
+    const int bx = mirrored ? blockIdx.x : gridDim.x - 1 - blockIdx.x;   // as in the forward
     const int wr = tile_row<QW>(bx, qw, g.qn, mirrored), row = wr + l32;
     int r0, r1;
     wg_rows<QW>(bx, g.qn, mirrored, r0, r1);
@@ -520,12 +568,13 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
 // dV = sum_i P_i dO_i and dK = scale * sum_i dS_i q_i: a key per lane, the share's queries pass through LDS with
 // their log-sum-exp (base 2) and delta.  fp32, d = 64: with two accumulators the own rows' planes (96 registers)
 // do not fit beside the rest at two waves per SIMD.  Eight waves keep them in LDS (158 -> 84 us at
-// 8 x 2003, against spills of 72 registers), four run at one wave per SIMD.
+// 8 x 2003, against spills of 72 registers), four run at one wave per SIMD.  fp32, d = 128, spills at one wave per SIMD too
+// (111 registers with two row tiles, 62 with four); against scalar products, 16 x 4096 causal, backward: 16.5 -> 3.1 ms.
 template <typename T, int D, int QW, int KW>
-__global__ __launch_bounds__(64 * QW * KW, D == 128 || (D == 64 && planes_of<T>::n == 3 && KW == 1) ? 1 : 2) void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K,
-                                                                      const T* __restrict__ V, const T* __restrict__ dO,
-                                                                      const float* __restrict__ LSE, const float* __restrict__ delta,
-                                                                      T* __restrict__ dK, T* __restrict__ dV, int causal)
+__global__ __launch_bounds__(64 * QW * KW, D == 128 || (D == 64 && planes_of<T>::n == 3 && KW == 1) ? 1 : 2)
+void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+                                   const T* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
+                                   T* __restrict__ dK, T* __restrict__ dV, int causal)
 {
     typedef SmCfg<T, D, QW, KW> Cf;
     typedef typename Cf::Stage Stage;
@@ -650,16 +699,15 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 || (D == 64 && planes_of<T>:
         }
     }
     const int ln = lane_again(), first = __builtin_amdgcn_readfirstlane(row);
-    uint32_t odd = odd_rows<D>(ak, 0.f, valid, h) | odd_rows<D>(av, 0.f, valid, h);
-    if (valid && !((odd >> (ln & 31)) & 1u)) {
-        store_row<T, D>(dK + kbase + (size_t)row * D, ak, scale, h);
-        store_row<T, D>(dV + kbase + (size_t)row * D, av, 1.f, h);
-    }
-    for (; odd; odd &= odd - 1) {
-        const int r = first + __builtin_ctz(odd);
+    const uint32_t oddk = odd_rows<D>(ak, 0.f, valid, h), oddv = odd_rows<D>(av, 0.f, valid, h);
+    if (valid && !((oddk >> (ln & 31)) & 1u)) store_row<T, D>(dK + kbase + (size_t)row * D, ak, scale, h);
+    if (valid && !((oddv >> (ln & 31)) & 1u)) store_row<T, D>(dV + kbase + (size_t)row * D, av, 1.f, h);
+    for (uint32_t odd = oddk | oddv; odd; odd &= odd - 1) {
+        const int b = __builtin_ctz(odd), r = first + b;
         const size_t o = kbase + (size_t)r * D, i = (size_t)grp * g.qn;
         queries_of(g, r, causal, ilo, ihi);
-        dkv_row<T, D>(K + o, V + o, Qg, Dg, LSE + i, delta + i, dK + o, dV + o, ilo - g.q0, ihi - g.q0, ln);
+        dkv_row<T, D>(K + o, V + o, Qg, Dg, LSE + i, delta + i, (oddk >> b) & 1u ? dK + o : nullptr,
+                      (oddv >> b) & 1u ? dV + o : nullptr, ilo - g.q0, ihi - g.q0, ln);
     }
 }
 
@@ -675,7 +723,8 @@ hipError_t fwd_TD(const Geom& g, const T* Q, const T* K, const T* V, T* O, float
     constexpr int lds = Cf::lds(16 * Cf::NT + 2, 0), R = 32 * Cf::QW;
     hipError_t e = allow_dynamic_lds<softmax_fwd_planes_kernel<T, D, QW, KW>>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((softmax_fwd_planes_kernel<T, D, QW, KW>), dim3((g.qn + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K, V, O, LSE, causal);
+    hipLaunchKernelGGL((softmax_fwd_planes_kernel<T, D, QW, KW>), dim3((g.qn + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K, V,
+                       O, LSE, causal);
     return hipGetLastError();
 }
 
@@ -687,8 +736,8 @@ hipError_t dq_TD(const Geom& g, const T* Q, const T* K, const T* V, const T* dO,
     constexpr int lds = Cf::lds(16 * Cf::NT, 0), R = 32 * Cf::QW;
     hipError_t e = allow_dynamic_lds<softmax_bwd_dq_planes_kernel<T, D, QW, KW>>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((softmax_bwd_dq_planes_kernel<T, D, QW, KW>), dim3((g.qn + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K, V, dO, LSE,
-                       delta, dQ, causal);
+    hipLaunchKernelGGL((softmax_bwd_dq_planes_kernel<T, D, QW, KW>), dim3((g.qn + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K,
+                       V, dO, LSE, delta, dQ, causal);
     return hipGetLastError();
 }
 
@@ -700,8 +749,8 @@ hipError_t dkv_TD(const Geom& g, const T* Q, const T* K, const T* V, const T* dO
     constexpr int lds = Cf::lds(32 * Cf::NT, 8 * Cf::ROWS + (Cf::own_lds ? QW * 2 * Cf::NP * 64 * Cf::DP : 0)), R = 32 * Cf::QW;
     hipError_t e = allow_dynamic_lds<softmax_bwd_dkv_planes_kernel<T, D, QW, KW>>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((softmax_bwd_dkv_planes_kernel<T, D, QW, KW>), dim3((g.N + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K, V, dO, LSE,
-                       delta, dK, dV, causal);
+    hipLaunchKernelGGL((softmax_bwd_dkv_planes_kernel<T, D, QW, KW>), dim3((g.N + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K,
+                       V, dO, LSE, delta, dK, dV, causal);
     return hipGetLastError();
 }
 
@@ -711,7 +760,8 @@ hipError_t fwd_T(const Geom& g, const void* Q_, const void* K_, const void* V_, 
     constexpr int KW = planes_of<T>::n == 3 && D == 128 ? 2 : 4;
     const T *Q = static_cast<const T*>(Q_), *K = static_cast<const T*>(K_), *V = static_cast<const T*>(V_);
     T* O = static_cast<T*>(O_);
-    return split_partners(g, g.qn) ? fwd_TD<T, D, 2, KW>(g, Q, K, V, O, LSE, causal, st) : fwd_TD<T, D, 4, 1>(g, Q, K, V, O, LSE, causal, st);
+    return split_partners(g, g.qn) ? fwd_TD<T, D, 2, KW>(g, Q, K, V, O, LSE, causal, st)
+                                   : fwd_TD<T, D, 4, 1>(g, Q, K, V, O, LSE, causal, st);
 }
 
 template <typename T, int D>
@@ -719,7 +769,8 @@ hipError_t bwd_T(const Geom& g, const void* Q_, const void* K_, const void* V_, 
                  void* dQ_, void* dK_, void* dV_, int causal, hipStream_t st)
 {
     constexpr int KW = planes_of<T>::n == 3 && D == 128 ? 2 : 4;
-    const T *Q = static_cast<const T*>(Q_), *K = static_cast<const T*>(K_), *V = static_cast<const T*>(V_), *dO = static_cast<const T*>(dO_);
+    const T *Q = static_cast<const T*>(Q_), *K = static_cast<const T*>(K_), *V = static_cast<const T*>(V_);
+    const T* dO = static_cast<const T*>(dO_);
     T *dQ = static_cast<T*>(dQ_), *dK = static_cast<T*>(dK_), *dV = static_cast<T*>(dV_);
     if (g.qn > 0) {
         const hipError_t e = split_partners(g, g.qn) ? dq_TD<T, D, 2, KW>(g, Q, K, V, dO, LSE, delta, dQ, causal, st)
