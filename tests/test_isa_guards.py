@@ -296,3 +296,30 @@ def test_states_kernel_store_count_matches_its_wait_arithmetic(isa):
             assert len(stores) == 32 and all("global_store_dword " in x for x in stores), len(stores)
             assert any("vmcnt(38)" in x for x in body) and any("vmcnt(6)" in x for x in body)
     assert found == 2
+
+
+# Scratch memory of the split-plane kernels, bytes per lane: what their register use is known to exceed (the loads around it
+# are the compiler's own, so spills cost time and nothing else).  Everything that is not named here has none.
+PLANES_SCRATCH = {
+    "attn_planes_kernel<float, 64, true>": 40,
+    "attn_planes_kernel<float, 128, false>": 416,
+    "attn_planes_kernel<float, 128, true>": 564,
+    "attn_planes_kernel<__hip_bfloat16, 128, true>": 308,
+    "softmax_bwd_dkv_planes_kernel<float, 128, 2, 2>": 444,
+    "softmax_bwd_dkv_planes_kernel<float, 128, 4, 1>": 248,
+}
+
+
+@pytest.mark.parametrize("source,kernels", [("kernels_planes.hip", 32), ("kernels_planes_softmax.hip", 42)])
+def test_scratch_of_the_split_plane_kernels(tmp_path, source, kernels):
+    from paper_2502_07563_amd import build as b
+    out = tmp_path / "planes.s"
+    flags = [f for f in b.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "-S", "--cuda-device-only", "-o", str(out),
+                    os.path.join(SRC, source)], check=True, capture_output=True)
+    found = re.findall(r"\.amdhsa_kernel (\S+).*?\.amdhsa_private_segment_fixed_size (\d+)", out.read_text(), flags=re.S)
+    assert len(found) == kernels
+    names = subprocess.run(["c++filt", *(sym for sym, _ in found)], check=True, capture_output=True, text=True).stdout.splitlines()
+    for name, (_, size) in zip(names, found):
+        key = re.search(r"\w+_kernel<[^>]*>", name).group(0)
+        assert int(size) <= PLANES_SCRATCH.get(key, 0), (key, size)
