@@ -247,20 +247,22 @@ def main():
             marks.append(e)
 
     # The attention kernels may walk several of the caller's slots per workgroup (lasp2_walk_slots):
-    # the forward then reads one prefix state per walk, and the backward builds its dM states per walk.
+    # the forward then reads one prefix state per walk, and the backward for bf16 with d = 128 builds its dM
+    # states per walk (the others per slot, and they skip states only where a slot is a whole sequence).
     Leff = L or C
+    mfma = dtype == "bf16" and d == 128
     doc_lens = [N] if cu is None else [int(b - a) for a, b in zip(cu[:-1], cu[1:])]
     walks = lambda w: sum(-(-n // (w * Leff)) for n in doc_lens)
     ws_f, ws_b = bd.lasp2_walk_slots(p), bd.lasp2_walk_slots(p, backward=True)
     Tw_f, Tw_b = walks(ws_f), walks(ws_b)
-    lone_f, lone_b = Tw_f == len(doc_lens), Tw_b == len(doc_lens)
-    # What lasp2_attn_bwd spends before its attention launch: the walks' own dM_t = Q_t^T dO_t and their
-    # suffix combine, timed once here through the public calls on a descriptor whose slots are the walks
+    ws_states = ws_b if mfma else 1
+    lone_f, lone_b = (walks(w if mfma else 1) == len(doc_lens) for w in (ws_f, ws_b))
+    # What lasp2_attn_bwd spends before its attention launch: the dM_t = Q_t^T dO_t and their suffix
+    # combine, timed once here through the public calls on a descriptor whose slots are those states'
     # (the undecayed matrix-core kernels want the dM_t even when every sequence is a single walk).
     pre_ms = 0.0
-    mfma = dtype == "bf16" and d == 128
     if not lone_b or (mfma and not args.decay):
-        pw = bd.Problem(B, H, N, d, C, ws_b * Leff, dtype, cu, decay=decay) if ws_b > 1 else p
+        pw = bd.Problem(B, H, N, d, C, ws_states * Leff, dtype, cu, decay=decay) if ws_states > 1 else p
 
         def pre():
             bd.lasp2_chunk_states(pw, Q, dO, ws)
