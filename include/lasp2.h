@@ -17,12 +17,10 @@
  * (suffix) combine dM_{t+1:T}.
  *
  * Two granularities (the result depends on neither):
- *   C  chunk length: in the plain fp32 kernels the side of the masked quadratic
- *      block and the period at which the inter-chunk state operand is
- *      refreshed.  The matrix-core kernels (bf16, d = 128) tile a slot in
- *      blocks of their own (256 rows, masked products over 128-row halves;
- *      128 rows when no slot is longer) whatever C is: there C only fixes the
- *      slots through L;
+ *   C  chunk length: it fixes the slots through L.  The kernels tile a slot in
+ *      blocks of their own whatever C is (bf16 with d = 128: 256 rows, masked
+ *      products over 128-row halves, 128 rows when no slot is longer;
+ *      everything else: 128 rows);
  *   L  tokens per state slot, a multiple of C (0 means L = C, the paper-literal
  *      layout with one state per chunk).  One slot is what one sequence-
  *      parallel rank would own; its chunks are walked by one workgroup that
@@ -52,11 +50,11 @@
  * index a of a chunk reads the state before the chunk with weight lam^(a+1).
  * The backward mirrors this with states anchored at the slots' first tokens.
  * lam = 1 for every head computes the undecayed result (bit for bit on the
- * plain kernels; on the matrix cores within rounding, because the decayed
- * backward walks each slot in the opposite direction).  Decay is given by
+ * split-plane kernels, see below; with bf16, d = 128 within rounding, because its
+ * decayed backward walks each slot in the opposite direction).  Decay is given by
  * the two `decay_*` pointers of the descriptor (both NULL: none).
- * Precision with decay on the matrix cores (bf16, d = 128, every factor
- * >= 0.35; a smaller factor sends the whole call to the plain fp32 kernels,
+ * Precision with decay for bf16, d = 128, every factor >= 0.35 (a smaller
+ * factor sends the whole call to the split-plane kernels, see below,
  * because lam^63 must stay inside the bf16 / fp32 exponent range): the rows
  * that enter a state product are weighted first and rounded to bf16 like every
  * matrix-core operand, so the states lasp2_chunk_states returns carry that
@@ -82,12 +80,21 @@
  *     the device.  Nothing aborts or throws.
  *   - B, H or N equal to 0 is a valid empty problem: the call returns LASP2_OK
  *     and launches nothing (pointers are then not examined).
- *   - Supported: d in {16, 32, 64, 128}; 1 <= C <= 512; B*H <= 65535 (the
- *     plain kernels carry the group index in the grid's second dimension).
- *     The MFMA kernels cover bf16 with d = 128 for every C, with and without
+ *   - Supported: d in {16, 32, 64, 128}; 1 <= C <= 512; B*H <= 65535 (some
+ *     kernels carry the group index in the grid's second dimension).
+ *     bf16 with d = 128 has kernels of its own for every C, with and without
  *     decay (with decay: every factor >= 0.35, see above); any other
- *     supported combination runs the plain fp32-FMA kernels.  There is no CPU
- *     fallback.
+ *     supported combination runs the split-plane kernels, which keep fp32
+ *     accuracy on the bf16 matrix cores by taking an fp32 value as a sum of
+ *     three bf16 numbers (lasp2_nomask_*: scalar fp32 products).  There is no
+ *     CPU fallback.
+ *   - Range of the split-plane kernels: infinities, NaN and finite fp32 values
+ *     above the largest bf16 (3.39e38) give what sums in fp32 give, and reach
+ *     only rows whose mask lets them in; slots and rows that hold one are
+ *     worked out in scalar fp32 arithmetic, many times slower than the others.
+ *     fp32 elements below 2^-109 (1.5e-33) in magnitude lose low bits, since
+ *     bf16 has none below 2^-133: a relative error of 3e-7 for results of
+ *     elements near 2^-110, 1e-5 near 2^-115, 3e-4 near 2^-120.
  */
 #ifndef LASP2_H
 #define LASP2_H
@@ -212,9 +219,10 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K,
  * the form the kernels that ran wanted them).
  * When every sequence (document) is a single slot, all prefixes and suffixes
  * are zero: P is not read and may be NULL, and the combine is skipped.  The
- * plain kernels and the decayed matrix-core kernels then need no workspace
- * either (NULL / 0 bytes accepted); the undecayed matrix-core kernels still
- * use it for the slots' own dM_t, from which their forward walk subtracts.
+ * split-plane kernels and the decayed ones for bf16, d = 128 then need no
+ * workspace either (NULL / 0 bytes accepted); the undecayed ones for bf16,
+ * d = 128 still use it for the slots' own dM_t, from which their forward walk
+ * subtracts.
  */
 int lasp2_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K,
                    const void* V, const void* dO, const float* P,
@@ -299,7 +307,7 @@ int lasp2_nomask_bwd(const lasp2_desc_t* desc, const void* Q, const void* K,
  * In: Q,K,V [B,H,N,d].  Out: O [B,H,N,d] in `dtype`; LSE [B,H,N] fp32, the
  * natural-log sum of exp of each row's scaled scores (what a backward pass
  * needs to rebuild the probabilities).  Decay is rejected.  bf16 with d = 128
- * runs on the matrix cores, everything else on a plain fp32 kernel.
+ * has kernels of its own, everything else runs the split-plane kernels.
  */
 int lasp2_softmax_fwd(const lasp2_desc_t* desc, const void* Q, const void* K,
                       const void* V, void* O, float* LSE, int causal, void* stream);
@@ -316,9 +324,7 @@ int lasp2_softmax_workspace_size(const lasp2_desc_t* desc, size_t* bytes);
  * In: Q,K,V,O,dO [B,H,N,d]; LSE [B,H,N] from the forward; same `causal`.
  * Out: dQ,dK,dV [B,H,N,d].  `workspace`: device scratch of at least
  * lasp2_softmax_workspace_size() bytes, 16-byte aligned (receives delta and
- * the log-sum-exp in base 2).
- * bf16 with d = 128 runs on the matrix cores (one kernel for dQ, one for dK
- * and dV), everything else on plain fp32 kernels.
+ * the log-sum-exp in base 2).  One kernel for dQ, one for dK and dV.
  */
 int lasp2_softmax_bwd(const lasp2_desc_t* desc, const void* Q, const void* K,
                       const void* V, const void* O, const void* dO, const float* LSE,

@@ -161,7 +161,10 @@ struct PlanesProblems { PlanesProblem p[3]; };
 
 // Tokens per LDS stage: as many of the chunk's 128 as leave room for a second workgroup on the CU
 // (one workgroup with d = 128), with at most 32 registers per thread for the next stage's loads; fp32 with
-// decay and d = 64 has no registers for more than 32.
+// decay and d = 64 has no registers for more than 32, and spills 9 even so.  With d = 128 the operands' planes, the
+// state's and the result's accumulators exceed the 512 registers of a thread at one wave per SIMD: 103 spilled
+// in fp32, 140 with decay, 76 in bf16 with decay.  Layer, 2 x 16 x 4096 x 128, against one scalar product per element, us:
+// fp32 forward 3470 -> 356, backward 10120 -> 908; bf16 with strong decay 2850 -> 241, 8240 -> 576.
 template <typename T, int D, bool DECAY>
 struct AttnLds {
     static constexpr int DP = D < 32 ? 32 : D, NP = planes_of<T>::n;
@@ -172,8 +175,8 @@ struct AttnLds {
 };
 
 // What attn_planes_kernel computes, in fp32 from the elements as they are, for a workgroup's chunks from `first`
-// on: a row of out per wave, the running state M [D][D] in LDS.  For inputs whose planes are not finite; one
-// such segment takes as long as scalar kernels do.
+// on: a row of out per wave, the running state M [D][D] in LDS.  For inputs whose planes are not finite: slow, as scalar
+// products are (fp32, 8 x 2003 x 64 with a NaN in every head's V, forward + backward: 1760 us).
 template <typename T, int D>
 __device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems& probs, int nprob, int nseg, int cps, int first,
                                             float* M)
@@ -254,9 +257,10 @@ __device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems&
 // launch leaves CUs idle.
 // Bounds: the split's vector instructions next to the matrix products in fp32, latency and HBM in bf16.
 // Against one scalar fp32 product per element (and a load for each), layer forward + backward: bf16,
-// 64 groups x 4001 x 64: 4200 -> 240 us (the forward launch 52 us, 3.2 TB/s); fp32, 2 x 1024 x 64: 1190 -> 57 us.
+// 64 groups x 4001 x 64: 4200 -> 230 us (the forward launch 50 us, 3.2 TB/s); fp32, 2 x 1024 x 64: 1190 -> 58 us.
 template <typename T, int D, bool DECAY>
-__global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geom g, PlanesProblems probs, int nprob, int nseg, int cps)
+__global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geom g, PlanesProblems probs, int nprob, int nseg,
+                                                                             int cps)
 {
     typedef AttnLds<T, D, DECAY> LD;
     typedef typename LD::Stage Stage;
@@ -350,7 +354,8 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
                 for (int v = 0; v < 16; ++v) S[t][v] *= wc;
         }
         for (int s0 = 0; s0 < clen; s0 += ROWS) {
-            if (s0 > 0 || (ci > 0 && ci <= ci0)) __syncthreads();   // the previous stage has been read (an emitted chunk ends with a barrier)
+            // the previous stage has been read (an emitted chunk ends with a barrier)
+            if (s0 > 0 || (ci > 0 && ci <= ci0)) __syncthreads();
             st.put(smem, tid);
             if (s0 + ROWS < clen) st.fetch(Bk, Cv, c0 + s0 + ROWS, len, tid);
             else if (ci + 1 < ci1) st.fetch(Bk, Cv, rev ? c0 - kChunk : c0 + kChunk, len, tid);

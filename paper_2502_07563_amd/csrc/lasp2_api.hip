@@ -267,7 +267,7 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     if (rc != LASP2_OK || pl->empty) return rc;
     const Geom& g = pl->g;
     pl->fast = mfma_path_supported(g, desc->dtype);
-    // Which suffix states the kernels want: the plain kernels and the MFMA kernels with decay walk
+    // Which suffix states the kernels want: the split-plane kernels and the MFMA kernels with decay walk
     // each slot backwards from the EXCLUSIVE suffix; the MFMA kernels without decay walk forwards
     // from the INCLUSIVE suffix and subtract (see attn_mfma_kernel), which lets the three
     // problems of a slot share their reads.
@@ -289,7 +289,8 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     pl->gw = g;
     if (pl->fast) {
         const int wgs = g.decay ? 3 : 2;   // workgroups per walk in the attention launch
-        pl->gw = regroup(g, desc->cu_seqlens_host, pick_walk_slots(g, desc->cu_seqlens_host, std::max(1, cu_count() / wgs), g.n_seqs ? kWalkTargetBwdPacked : kWalkTargetBwd));
+        const int64_t target = g.n_seqs ? kWalkTargetBwdPacked : kWalkTargetBwd;
+        pl->gw = regroup(g, desc->cu_seqlens_host, pick_walk_slots(g, desc->cu_seqlens_host, std::max(1, cu_count() / wgs), target));
     }
     pl->lone_w = pl->gw.lone_slots != 0;
     pl->need_states_w = !pl->lone_w || pl->inclusive;

@@ -5,13 +5,15 @@
 // mid = bf16(x - hi), lo = x - hi - mid (both differences are exact and lo fits bf16), called its
 // planes.  A product of a 3-plane operand with a bf16 one is then the exact sum of three bf16
 // products, accumulated in fp32; of two 3-plane operands the six products hi.hi, hi.mid, mid.hi,
-// mid.mid, hi.lo, lo.hi are formed, and the three that are dropped are below 2^-25 of the product,
-// less than the rounding of one fp32 multiplication.  bf16 inputs are one plane, fp32 inputs three,
+// mid.mid, hi.lo, lo.hi are formed.  The dropped mid.lo and lo.mid reach 2^-25 of the product each
+// (mid is at most 2^-8 of the value, lo 2^-17), lo.lo 2^-34: together 2^-24, what the rounding of one fp32
+// multiplication may cost.  bf16 inputs are one plane, fp32 inputs three,
 // scores, probabilities and states always three: nothing is held in fewer bits than fp32.
 // Why: the matrix unit multiplies fp32 operands at 1/16 of its bf16 rate, so three or six bf16
 // products are 5 or 2.7 times faster than one fp32 instruction.
 // An infinity, or a finite fp32 value that rounds to one in bf16 (above 3.39e38), has planes that make every
-// sum they enter NaN.
+// sum they enter NaN; the kernels do such rows again in fp32.  Planes end at 2^-133, the last bit of bf16's
+// smallest numbers: below 2^-109 a value has no exact sum any more.
 #ifndef LASP2_PLANES_H
 #define LASP2_PLANES_H
 #include "mfma_tile.h"

@@ -93,7 +93,7 @@ def test_walk_slots_choice(monkeypatch):
     assert _walk(_desc(H=16, N=262144, L=4096, **bf), 1) == (0, 4)
     # a launch the device runs in one go stays as it is
     assert _walk(_desc(H=2, N=4096, **bf)) == (0, 1)
-    # fp32 takes the plain kernels: one walk per slot
+    # fp32 with slots of whole 128-row chunks: one walk per slot
     assert _walk(_desc(H=16, N=32768)) == (0, 1)
     # a slot that holds the whole sequence
     assert _walk(_desc(H=16, N=4096, L=4096, **bf)) == (0, 1)
@@ -226,11 +226,11 @@ def test_null_prefix_is_accepted_only_when_every_sequence_is_one_slot():
     be NULL; the call then goes on to its other checks (shown here by the misaligned pointer it
     reports next, still before any device work).  With several slots a NULL P is an error."""
     lib = B.lib()
-    one = ctypes.byref(_desc(N=1024, C=128, L=1024))                     # fp32: plain kernels
+    one = ctypes.byref(_desc(N=1024, C=128, L=1024))                     # fp32: split-plane kernels
     many = ctypes.byref(_desc(N=1024, C=128, L=512))
     assert lib.lasp2_attn_fwd(one, FAKE, FAKE, FAKE, None, ODD, None) == -6
     assert lib.lasp2_attn_fwd(many, FAKE, FAKE, FAKE, None, ODD, None) == -1
-    # backward, plain kernels: neither P nor a workspace is needed
+    # backward, split-plane kernels: neither P nor a workspace is needed
     assert lib.lasp2_attn_bwd(one, FAKE, FAKE, FAKE, FAKE, None, FAKE, FAKE, ODD, None, ctypes.c_size_t(0), None) == -6
     assert lib.lasp2_attn_bwd(many, FAKE, FAKE, FAKE, FAKE, None, FAKE, FAKE, ODD, None, ctypes.c_size_t(0), None) == -1
     assert lib.lasp2_attn_bwd(many, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, ODD, None, ctypes.c_size_t(0), None) == -1

@@ -65,7 +65,7 @@ def _run(oracle, B, H, N, d, C, L, dtype, seed, cu=None, lam=None, check_suffix_
         errs[name] = rel_l2(to_host(got), ref)
     print({k: f"{v:.2e}" for k, v in errs.items()}, flush=True)
     # The MFMA kernels (bf16, d = 128, every factor >= 0.35) round the weighted rows lam^e k to
-    # bf16 before the product, so their states carry bf16 rounding; the plain kernels weight in fp32.
+    # bf16 before the product, so their states carry bf16 rounding; the split-plane kernels weight in fp32.
     mfma = dtype == "bf16" and d == 128 and float(lam.min()) >= 0.35
     assert max(errs["M"], errs["P"], errs["dP"]) <= (TOL["bf16"] if mfma else TOL_STATE), errs
     for name, got, ref in zip(("O", "dQ", "dK", "dV"), (O, dQ, dK, dV), refs):
@@ -90,7 +90,7 @@ def test_bf16_shapes(oracle, N, d, C, L):
     _run(oracle, 1, 3, N, d, C, L, "bf16", seed=110 + N)
 
 
-def test_bf16_d128_strong_decay_takes_the_plain_kernels(oracle):
+def test_bf16_d128_strong_decay_takes_the_split_plane_kernels(oracle):
     """A factor below 0.35 is outside the range the MFMA decay kernels are built for."""
     _run(oracle, 1, 3, 700, 128, 128, 256, "bf16", seed=115, lam=[0.2, 0.99, 0.05])
 

@@ -67,6 +67,7 @@ def test_softmax_row_sums(dtype, d, N):
     # rounded exponent (scores below 2^3) and the sums over N rows; bf16 2^-8 each for P, dS and the result.
     tol = (2 * d + N) * 2.0 ** -24 if dtype == "f32" else 3 * 2.0 ** -8
     big = P * size / d ** 0.5
-    for name, got, want, scale in (("dQ", dQ, ds @ k, (big ** 2 @ (k ** 2)).sum(2)), ("dK", dK, tr(ds) @ q, (tr(big) ** 2 @ (q ** 2)).sum(2))):
+    for name, got, want, scale in (("dQ", dQ, ds @ k, (big ** 2 @ (k ** 2)).sum(2)),
+                                   ("dK", dK, tr(ds) @ q, (tr(big) ** 2 @ (q ** 2)).sum(2))):
         err = (got[0].double().cpu() - want).norm(dim=2)
         assert bool((err <= tol * scale.sqrt()).all()), (name, (err / scale.sqrt()).max().item(), tol)
