@@ -207,6 +207,18 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K,
                    const void* V, const float* P, void* O, void* stream);
 
 /*
+ * lasp2_chunk_states, lasp2_state_prefix (in place, P both times) and
+ * lasp2_attn_fwd in one call: O and every entry of P, the same within the
+ * rounding order.  Knowing all three, the library computes states and prefix
+ * only where its workgroups' walks start (lasp2_walk_slots; nowhere if each
+ * document is one walk) and has the walks write the other slots' states as
+ * they pass them, where slots are multiples of 64 tokens (bf16, d = 128).
+ * In: Q,K,V [B,H,N,d].  Out: P [B,H,T_s,d,d] fp32, never NULL; O [B,H,N,d].
+ */
+int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K,
+                  const void* V, float* P, void* O, void* stream);
+
+/*
  * Backward, Algorithm "LASP-2 w/ Masking (Backward Pass)":
  *   dM_t = Q_t^T dO_t, suffix combine dM_{t+1:T} (both into `workspace`), then
  *   dQ_t = [(dO_t V_t^T)(.)Psi] K_t   + dO_t M_{1:t-1}^T

@@ -56,6 +56,7 @@ def lib():
         L.lasp2_chunk_states.argtypes = [dp, vp, vp, vp, vp]
         L.lasp2_state_prefix.argtypes = [dp, vp, vp, ctypes.c_int, vp]
         L.lasp2_attn_fwd.argtypes = [dp, vp, vp, vp, vp, vp, vp]
+        L.lasp2_forward.argtypes = [dp, vp, vp, vp, vp, vp, vp]
         L.lasp2_attn_bwd.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
         L.lasp2_attn_bwd_noalloc.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.lasp2_state_total.argtypes = [dp, vp, vp, vp]
@@ -71,7 +72,7 @@ def lib():
         L.lasp2_status_string.argtypes = [ctypes.c_int]
         L.lasp2_status_string.restype = ctypes.c_char_p
         for name in ("lasp2_num_slots", "lasp2_workspace_size", "lasp2_walk_slots", "lasp2_chunk_states",
-                     "lasp2_state_prefix", "lasp2_attn_fwd", "lasp2_attn_bwd", "lasp2_attn_bwd_noalloc",
+                     "lasp2_state_prefix", "lasp2_attn_fwd", "lasp2_forward", "lasp2_attn_bwd", "lasp2_attn_bwd_noalloc",
                      "lasp2_state_total",
                      "lasp2_nomask_fwd", "lasp2_nomask_bwd", "lasp2_softmax_fwd",
                      "lasp2_softmax_workspace_size", "lasp2_softmax_bwd", "lasp2_softmax_fwd_share",
@@ -202,6 +203,14 @@ def lasp2_attn_fwd(p: Problem, Q, K, V, P, O, stream=None):
            "lasp2_attn_fwd")
 
 
+def lasp2_forward(p: Problem, Q, K, V, P, O, stream=None):
+    for n, t in (('K', K), ('V', V), ('Q', Q), ('O', O)):
+        _rows(p, t, p.N, n)
+    _states(p, P, 'P')
+    _check(lib().lasp2_forward(p.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(P), _ptr(O), _stream(stream)),
+           "lasp2_forward")
+
+
 def lasp2_attn_bwd(p: Problem, Q, K, V, dO, P, dQ, dK, dV, workspace, stream=None):
     for n, t in (('Q', Q), ('K', K), ('V', V), ('dO', dO), ('dQ', dQ), ('dK', dK), ('dV', dV)):
         _rows(p, t, p.N, n)
@@ -314,12 +323,10 @@ def workspace_states(p: Problem, ws):
 
 
 def forward(p: Problem, Q, K, V, stream=None):
-    """chunk_states -> state_prefix (in place) -> attn_fwd.  Returns (O, P)."""
+    """What chunk_states -> state_prefix (in place) -> attn_fwd give, in one call.  Returns (O, P)."""
     P = alloc_states(p, Q.device)
     O = torch.empty_like(Q)
-    lasp2_chunk_states(p, K, V, P, stream)
-    lasp2_state_prefix(p, P, P, False, stream)
-    lasp2_attn_fwd(p, Q, K, V, P, O, stream)
+    lasp2_forward(p, Q, K, V, P, O, stream)
     return O, P
 
 

@@ -19,30 +19,42 @@ __device__ __forceinline__ void st(__hip_bfloat16* p, float v) { *p = __float2bf
 // Exclusive prefix (or suffix) over the slots of each group, restarted per document.
 // One thread owns four adjacent state elements and walks the slots in order; loads are
 // batched ahead of the stores so that in-place use (P == M) stays correct and the
-// memory system sees several requests in flight.
+// memory system sees several requests in flight.  The exclusive form does not touch the last slot's own state.
+// user_slots: entry per slot of the caller's, walks of g.wslots of them (see launch_state_prefix).
 constexpr int kScanBatch = 8;
 
 __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const float* M, float* P,
-                                                                int reverse, int inclusive)
+                                                                int reverse, int inclusive, int user_slots)
 {
     const int dd = g.d * g.d;
     const int e = (blockIdx.x * kThreads + threadIdx.x) * 4;
     if (e >= dd) return;
-    const size_t base = (size_t)blockIdx.y * (size_t)g.T_s * dd + e;
+    const int stride = user_slots ? g.wslots : 1;   // array entries from one walk to the next inside a document
+    const int64_t Lp = user_slots ? g.L / g.wslots : g.L;   // tokens per array entry
+    const int entries = user_slots ? g.P_Ts : g.T_s;
+    const size_t base = (size_t)blockIdx.y * (size_t)entries * dd + e;
     const int ndocs = g.n_seqs ? g.n_seqs : 1;
     const float l2 = decay_log2(g, blockIdx.y);
-    const int step = reverse ? -1 : 1;
-    int s = reverse ? g.T_s - 1 : 0;
+    const int step = reverse ? -stride : stride;
+    int first = reverse ? entries : 0;   // entries before the document (reverse: before its end)
     for (int kk = 0; kk < ndocs; ++kk) {
         const int k = reverse ? ndocs - 1 - kk : kk;
         const int dlen = g.n_seqs ? (g.cu[k + 1] - g.cu[k]) : g.N;
         const int ns = (int)(((int64_t)dlen + g.L - 1) / g.L);
+        const int ne = (int)(((int64_t)dlen + Lp - 1) / Lp);
+        if (reverse) first -= ne;
+        int s = first + (reverse ? (ns - 1) * stride : 0);
+        if (!reverse) first += ne;
+        const int nm = inclusive ? ns : ns - 1;   // states that enter a result
         float4 run = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int r = 0; r < ns; r += kScanBatch) {
             float4 m[kScanBatch];
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u)
-                if (r + u < ns)
+                m[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int u = 0; u < kScanBatch; ++u)
+                if (r + u < nm)
                     m[u] = *reinterpret_cast<const float4*>(M + base + (size_t)(s + step * u) * dd);
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u)
@@ -58,7 +70,7 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
                     run.z = fmaf(w, run.z, m[u].z); run.w = fmaf(w, run.w, m[u].w);
                     if (inclusive) *dst = run;
                 }
-            s += step * min(kScanBatch, ns - r);
+            s += step * kScanBatch;
         }
     }
 }
@@ -260,11 +272,11 @@ hipError_t launch_rows_state_generic(const Geom& g, int dtype, const void* A, co
 }
 
 hipError_t launch_state_prefix(const Geom& g, const float* M, float* P, int reverse, int inclusive,
-                               hipStream_t st)
+                               int user_slots, hipStream_t st)
 {
     const int dd = g.d * g.d;
     dim3 grid((dd / 4 + kThreads - 1) / kThreads, g.G), block(kThreads);
-    hipLaunchKernelGGL(state_prefix_kernel, grid, block, 0, st, g, M, P, reverse, inclusive);
+    hipLaunchKernelGGL(state_prefix_kernel, grid, block, 0, st, g, M, P, reverse, inclusive, user_slots);
     return hipGetLastError();
 }
 

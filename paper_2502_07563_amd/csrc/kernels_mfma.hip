@@ -104,7 +104,8 @@ constexpr int ST_KB = 32, ST_STAGE = ST_KB * ROWB;   // tokens and bytes (per te
 template <bool DECAY>
 __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* __restrict__ X,
                                                             const char* __restrict__ Y,
-                                                            float* __restrict__ M, int anchor_start)
+                                                            float* __restrict__ M, int anchor_start,
+                                                            int per_wg, int for_prefix)
 {
     constexpr int DPS = 2;   // loads per wave per stage: one instruction (four rows) per tensor
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -118,17 +119,19 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
     // loads of the next slot's first blocks are on their way while the last blocks of this one
     // are consumed.
     const int total = g.T_s * g.G;
-    const int per_wg = (total + (int)gridDim.x - 1) / (int)gridDim.x;
     const int u_first = (int)blockIdx.x * per_wg, nunits = min(total, u_first + per_wg);
-    struct Unit { int u, len, nblk; size_t row0; };
+    struct Unit { int u, len, nblk; size_t row0, m; };   // m: index of the unit's state in M
     auto open_unit = [&](int u) {
         Unit x;
-        x.u = u; x.len = 0; x.nblk = 0; x.row0 = 0;
+        x.u = u; x.len = 0; x.nblk = 0; x.row0 = 0; x.m = 0;
         if (u < nunits) {
-            int tok0;
-            slot_range(g, u % g.T_s, tok0, x.len);
+            int tok0, ps;
+            bool last;
+            slot_range(g, u % g.T_s, tok0, x.len, ps, last);
+            if (for_prefix && last) x.len = 0;   // no blocks, no state
             x.nblk = (x.len + ST_KB - 1) / ST_KB;
             x.row0 = ((size_t)(u / g.T_s) * g.N + tok0) * ROWB;
+            x.m = for_prefix ? (size_t)(u / g.T_s) * g.P_Ts + ps : (size_t)u;
         }
         return x;
     };
@@ -156,6 +159,7 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
     constexpr int NSTORE = 16 * ST_TPW;   // store instructions per wave that write a slot's state
     int slot = 0, older_than_stores = 0;
     for (Unit cu = open_unit(u_first); cu.u < nunits; cu = open_unit(cu.u + 1)) {
+        if (for_prefix && cu.nblk == 0) continue;
         f32x16 acc[ST_TPW];
 #pragma unroll
         for (int u = 0; u < ST_TPW; ++u)
@@ -202,7 +206,7 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
             slot = slot + 1 == ST_NST ? 0 : slot + 1;
         }
 
-        float* m = M + (size_t)cu.u * (size_t)(D * D);
+        float* m = M + cu.m * (size_t)(D * D);
 #pragma unroll
         for (int u = 0; u < ST_TPW; ++u) {
             const int t = w * ST_TPW + u, a = t >> 2, b = t & 3;
@@ -317,6 +321,7 @@ struct AttnProblem {
     int anti;             // 0: causal (j <= i); 1: anti-causal (j >= i)
     const unsigned* pace; // NULL, or per (group, slot): 64-token blocks another workgroup has begun
     int lead;             // with pace: this walk may be at most `lead` blocks ahead of that count
+    float* emit;          // skew_walk with EMIT: the caller's state array, which the walk fills in
 };
 
 // The d x d state a walk starts from: entry `s` of an array with one state per walk, or, in the
@@ -695,9 +700,14 @@ __global__ __launch_bounds__(C * 2) void attn_mfma_kernel(Geom g, AttnProblem p0
 // that number right after the batch.  The difference is how many younger instructions may still
 // be outstanding when the batch is needed; memory instructions retire in order.  All batches here
 // are multiples of four instructions.
+// (48: walks that also store states, 32 instructions each; a lone state is covered by 32.)
+template <bool DEEP = false>
 __device__ __forceinline__ void wait_vmcnt_le(int n)
 {
-    if (n >= 24) wait_vmcnt<24>();
+    if (DEEP && n >= 48) wait_vmcnt<48>();
+    else if (DEEP && n >= 40) wait_vmcnt<40>();
+    else if (DEEP && n >= 32) wait_vmcnt<32>();
+    else if (n >= 24) wait_vmcnt<24>();
     else if (n >= 20) wait_vmcnt<20>();
     else if (n >= 16) wait_vmcnt<16>();
     else if (n >= 12) wait_vmcnt<12>();
@@ -706,8 +716,12 @@ __device__ __forceinline__ void wait_vmcnt_le(int n)
     else wait_vmcnt<0>();
 }
 
+template <bool DEEP = false>
 __device__ __forceinline__ uint32_t wait_vmcnt_token_le(int n)
 {
+    if (DEEP && n >= 48) return wait_vmcnt_token<48>();
+    if (DEEP && n >= 40) return wait_vmcnt_token<40>();
+    if (DEEP && n >= 32) return wait_vmcnt_token<32>();
     if (n >= 24) return wait_vmcnt_token<24>();
     if (n >= 20) return wait_vmcnt_token<20>();
     if (n >= 16) return wait_vmcnt_token<16>();
@@ -754,9 +768,13 @@ __device__ __forceinline__ uint32_t wait_vmcnt_token_le(int n)
 // contributes nothing.  All copies pass the same barriers: one per block, and for the anti-causal
 // walk one at the end.  Each half stores at a different time, so the waits are counted at run
 // time (wait_vmcnt_le).
-template <bool HC1, bool ANTI, bool DECAY>
+// EMIT (causal only): the walk also writes the state at the start of each of the caller's slots inside it
+// to pr.emit (slots of a multiple of 64 tokens).  The running state after a block is that of the slot which starts there:
+// 32 stores per wave and slot, counted like the output's.
+template <bool HC1, bool ANTI, bool DECAY, bool EMIT = false>
 __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, char* smem, int tid, int w,
-                                          int rb, int grp, int s, int tok0, int len, const float* wstate)
+                                          int rb, int grp, int s, int tok0, int len, const float* wstate,
+                                          int ps = 0)
 {
     constexpr int C = 256, NW = 8, TPW = 2, BPC = 4, DPS = 4, NOP = 4;
     // With decay the anti-causal problems walk the slot backwards from the exclusive suffix (see
@@ -963,7 +981,7 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
     auto begin = [&](int bi) __attribute__((always_inline)) {   // bi: walk position
         tK = sK + (bi % NSTAGE) * STAGE_BYTES;
         tV = sV + (bi % NSTAGE) * STAGE_BYTES;
-        wait_vmcnt_le(issued - seq_cur);
+        wait_vmcnt_le<EMIT>(issued - seq_cur);
         if (blk(bi) * KB + KB > len) {   // at the slot's end only: keep these addresses out of the walk's registers
             int ln;
             asm volatile("v_and_b32 %0, 63, %1" : "=v"(ln) : "v"(tid));
@@ -1112,6 +1130,30 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
         SCHED_FENCE();
     };
 
+    // EMIT: blocks per slot of the caller's, where the next of them starts, and its entry in the state array
+    const int eblk = EMIT ? (int)(g.L / g.wslots) / KB : 0;
+    int enext = 0;
+    float* eptr = EMIT ? pr.emit + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) : nullptr;
+    // called with the running state at the start of block bi
+    auto emit = [&](int bi) __attribute__((always_inline)) {
+        if (!EMIT || bi != enext || bi * KB >= len) return;
+        if (bi > 0 || !wstate) {   // (the first slot's own was read from there)
+            int ln;
+            asm volatile("v_and_b32 %0, 63, %1" : "=v"(ln) : "v"(tid));
+            const int lo = 4 * (ln >> 5) * D + (ln & 31);
+            float* e = eptr + (32 * (t0 >> 2)) * D + 32 * (t0 & 3);
+#pragma unroll
+            for (int u = 0; u < TPW; ++u)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    __builtin_nontemporal_store(Macc[u][v], e + 32 * u + (8 * (v >> 2) + (v & 3)) * D + lo);
+            issued += 16 * TPW;
+        }
+        enext += eblk;
+        eptr += D * D;
+    };
+    if (EMIT) emit(0);
+
     zero_out();
     using std::integral_constant;
     for (int c = 0; c < nch; ++c) {   // c: walk position of the chunk; cc: the chunk of the slot
@@ -1140,12 +1182,14 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
             issue_q(cc); issued += 8; seq_q = issued;
         }
         update(bi);
+        if (EMIT) emit(bi + 1);
 
         // ---- block 1 (the second half's waves have nothing else to do here: they store)
         begin(bi + 1);
         if (!SECOND) tiles(integral_constant<int, 1>{});
         else store_rows(REV ? cc + 1 : cc - 1);
         update(bi + 1);
+        if (EMIT) emit(bi + 2);
         // The state between the halves.  Every wave has passed block 1's barrier, so the reads of the
         // chunk-top snapshot (in block 0) are over; block 2's barrier publishes this one.  Entering
         // walks: the second half starts from the state that includes the first half's keys.
@@ -1165,13 +1209,15 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
             else if (!ENDSTATE) inter();
             tiles(integral_constant<int, 2>{});
         }
-        if (carry) update(bi + 2);
+        if (carry || (EMIT && (bi + 3) * KB < len)) update(bi + 2);
+        if (EMIT) emit(bi + 3);
 
         // ---- block 3 (the first half's waves store here)
         begin(bi + 3);
         if (SECOND) tiles(integral_constant<int, 3>{});
         else store_rows(cc);
         if (carry) update(bi + 3);
+        if (EMIT) emit(bi + 4);
     }
 
     // The first half's waves requested rows beyond the last chunk in its block 2: let them land in
@@ -1213,6 +1259,28 @@ __global__ __launch_bounds__(512) void attn_skew_mfma_kernel(Geom g, AttnProblem
         if (pr.anti) skew_walk<true, true, DECAY>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate);
         else skew_walk<true, false, DECAY>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate);
     }
+}
+
+// The causal problem alone, with the states of the caller's slots written in passing (skew_walk's EMIT).
+// Bound by memory: with one state per 256 tokens the walk writes as many bytes of state as it reads of one tensor, but
+// the states kernel then writes, and the prefix kernel reads and writes, one state per walk instead of one per slot, and
+// neither runs where a walk is a whole document.  Forward and backward of a layer, us, before -> now: 16 heads x 32 768, one
+// state per 256 tokens 513 -> 463; 8 x 32 heads x 8 192 1872 -> 1479; 32 heads, 40 documents in 131 072 4259 -> 3886.
+template <bool DECAY>
+__global__ __launch_bounds__(512) void attn_fwd_emit_mfma_kernel(Geom g, AttnProblem pr)
+{
+    extern __shared__ __attribute__((aligned(256))) char smem[];
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned unit = blockIdx.x;
+    const int s = (int)(unit % (unsigned)g.T_s), grp = (int)(unit / (unsigned)g.T_s);
+    int tok0, len, ps;
+    slot_range(g, s, tok0, len, ps);
+    if (len <= 0) return;
+    const float* wstate = pr.state ? walk_state(g, pr, grp, s, ps) : nullptr;
+    const int rb = w < 4 ? w : 11 - w;   // waves w and w+4 share a SIMD: row blocks s and 7-s
+    if (rb < 4) skew_walk<false, false, DECAY, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate, ps);
+    else skew_walk<true, false, DECAY, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate, ps);
 }
 
 // =====================================================================================
@@ -1685,7 +1753,7 @@ AttnProblem make_problem(const void* A, const void* Bk, const void* Cv, const fl
 {
     return AttnProblem{static_cast<const char*>(A), static_cast<const char*>(Bk),
                        static_cast<const char*>(Cv), state, user_state, static_cast<char*>(out),
-                       transpose_state, anti, nullptr, 0};
+                       transpose_state, anti, nullptr, 0, nullptr};
 }
 
 // =====================================================================================
@@ -2122,7 +2190,7 @@ bool mfma_path_supported(const Geom& g, int dtype)
 }
 
 hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float* M, int anchor_start,
-                              hipStream_t st)
+                              int for_prefix, hipStream_t st)
 {
     constexpr int smem = 2 * ST_NST * ST_STAGE;   // 80 KiB: two workgroups per CU
     auto kern = g.decay ? states_mfma_kernel<true> : states_mfma_kernel<false>;
@@ -2133,9 +2201,10 @@ hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float
     const int cus = cu_count();
     const long long nunits = (long long)g.T_s * g.G;
     if (nunits == 0) return hipSuccess;
-    dim3 grid((unsigned)std::min<long long>(nunits, 2LL * cus)), block(ST_NT);
+    const int per_wg = (int)((nunits + 2LL * cus - 1) / (2LL * cus));
+    dim3 grid((unsigned)((nunits + per_wg - 1) / per_wg)), block(ST_NT);
     hipLaunchKernelGGL(kern, grid, block, smem, st, g, static_cast<const char*>(K),
-                       static_cast<const char*>(V), M, anchor_start);
+                       static_cast<const char*>(V), M, anchor_start, per_wg, for_prefix);
     return hipGetLastError();
 }
 
@@ -2170,6 +2239,25 @@ hipError_t launch_attn_fwd_mfma(const Geom& g, const void* Q, const void* K, con
     if (g.decay) return launch_attn_decay(g, p, p, p, 1, st);
     if (wide_chunks(g)) return launch_attn_skew<false>(g, p, p, p, 1, st);
     return launch_attn_C<128>(g, p, p, p, 1, st);
+}
+
+bool walk_emits(const Geom& g, int dtype)
+{
+    return mfma_path_supported(g, dtype) && g.wslots > 1 && wide_chunks(g) && (g.L / g.wslots) % KB == 0;
+}
+
+hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K, const void* V,
+                                     float* P, void* O, hipStream_t st)
+{
+    constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
+    AttnProblem p = make_problem(Q, K, V, g.lone_slots ? nullptr : P, 1, O, 0, 0);
+    p.emit = P;
+    auto kern = g.decay ? attn_fwd_emit_mfma_kernel<true> : attn_fwd_emit_mfma_kernel<false>;
+    hipError_t e = g.decay ? allow_dynamic_lds<attn_fwd_emit_mfma_kernel<true>>(smem)
+                           : allow_dynamic_lds<attn_fwd_emit_mfma_kernel<false>>(smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, p);
+    return hipGetLastError();
 }
 
 hipError_t launch_attn_bwd_mfma(const Geom& g, const void* Q, const void* K, const void* V,

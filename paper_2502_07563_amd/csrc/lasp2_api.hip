@@ -239,7 +239,7 @@ size_t pace_bytes(const Geom& g) { return (((size_t)g.G * (size_t)g.T_s * sizeof
 hipError_t run_states(const Geom& g, int dtype, const void* K, const void* V, float* M,
                       int anchor_start, hipStream_t st)
 {
-    if (mfma_path_supported(g, dtype)) return launch_states_mfma(g, K, V, M, anchor_start, st);
+    if (mfma_path_supported(g, dtype)) return launch_states_mfma(g, K, V, M, anchor_start, 0, st);
     return launch_states_planes(g, dtype, K, V, M, anchor_start, st);
 }
 
@@ -309,7 +309,7 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const int32_t* cu_host, const voi
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     }
     if (!pl.lone_w) {
-        e = launch_state_prefix(g, dR, dR, 1, pl.inclusive ? 1 : 0, st);
+        e = launch_state_prefix(g, dR, dR, 1, pl.inclusive ? 1 : 0, 0, st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     }
     if (pl.fast) {
@@ -409,7 +409,7 @@ int lasp2_state_prefix(const lasp2_desc_t* desc, const float* M, float* P, int r
     if (empty) return LASP2_OK;
     rc = check_ptrs({M, P});
     if (rc != LASP2_OK) return rc;
-    return from_hip(launch_state_prefix(g, M, P, reverse ? 1 : 0, 0, (hipStream_t)stream));
+    return from_hip(launch_state_prefix(g, M, P, reverse ? 1 : 0, 0, 0, (hipStream_t)stream));
 }
 
 int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,
@@ -431,6 +431,41 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
     }
     const Geom gp = regroup(g, desc->cu_seqlens_host, pick_planes_slots(g, desc->cu_seqlens_host, 1));
     return from_hip(launch_attn_fwd_planes(gp, desc->dtype, Q, K, V, P, O, st));
+}
+
+int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,
+                  float* P, void* O, void* stream)
+{
+    Geom g;
+    bool empty = false;
+    int rc = make_geom(desc, &g, &empty);
+    if (rc != LASP2_OK) return rc;
+    if (empty) return LASP2_OK;
+    rc = check_ptrs({Q, K, V, P, O});
+    if (rc != LASP2_OK) return rc;
+    hipStream_t st = (hipStream_t)stream;
+    const int32_t* cu = desc->cu_seqlens_host;
+    const bool fast = mfma_path_supported(g, desc->dtype);
+    const Geom gw = fast ? regroup(g, cu, pick_walk_slots(g, cu, cu_count(), kWalkTargetFwd))
+                         : regroup(g, cu, pick_planes_slots(g, cu, 1));
+    hipError_t e;
+    if (walk_emits(gw, desc->dtype)) {
+        // The attention walks write the states of the slots inside them, so states and prefix are
+        // needed where a walk starts only, and not at all where every document is one walk.
+        if (!gw.lone_slots) {
+            e = launch_states_mfma(gw, K, V, P, 0, 1, st);
+            if (e != hipSuccess) return LASP2_ERR_LAUNCH;
+            e = launch_state_prefix(gw, P, P, 0, 0, 1, st);
+            if (e != hipSuccess) return LASP2_ERR_LAUNCH;
+        }
+        return from_hip(launch_attn_fwd_emit_mfma(gw, Q, K, V, P, O, st));
+    }
+    e = run_states(g, desc->dtype, K, V, P, 0, st);
+    if (e != hipSuccess) return LASP2_ERR_LAUNCH;
+    e = launch_state_prefix(g, P, P, 0, 0, 0, st);
+    if (e != hipSuccess) return LASP2_ERR_LAUNCH;
+    if (fast) return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
+    return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, P, O, st));
 }
 
 int lasp2_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,

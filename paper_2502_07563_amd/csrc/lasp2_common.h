@@ -54,11 +54,11 @@ __device__ __forceinline__ float decay_log2(const Geom& g, int grp)
     return g.decay ? log2f(g.decay[grp % g.H]) : 0.f;
 }
 
-// Token range [tok0, tok0+len) of slot (walk) s, and ps: the index, within the group, of the
-// caller's slot that starts at tok0.  Unpacked: direct.  Packed: from the last host-made mark at
+// Token range [tok0, tok0+len) of slot (walk) s, ps: the index, within the group, of the
+// caller's slot that starts at tok0, and last: whether the slot (walk) is the last of its document.  Unpacked: direct.  Packed: from the last host-made mark at
 // or before s, then document by document (at most doc_stride of them; uniform scalar loads).
 // Document lengths and L are below 2^31, so the slot counts are 32-bit divisions.
-__device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len, int& ps)
+__device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len, int& ps, bool& last)
 {
     if (g.n_seqs == 0) {
         int64_t a = (int64_t)s * g.L;
@@ -67,6 +67,7 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
         tok0 = (int)a;
         len = (int)(b - a);
         ps = s * g.wslots;
+        last = s + 1 == g.T_s;
         return;
     }
     int j = 0;
@@ -78,6 +79,7 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
     tok0 = 0;
     len = 0;
     ps = 0;
+    last = true;
     for (int k = j * g.doc_stride; k < g.n_seqs; ++k) {
         const int a = g.cu[k], b = g.cu[k + 1];
         const int ns = (int)(((uint32_t)(b - a) + (L - 1u)) / L);
@@ -87,6 +89,7 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
             tok0 = (int)t0;
             len = (int)(t1 - t0);
             ps = pbase + (s - base) * g.wslots;
+            last = s + 1 == base + ns;
             return;
         }
         base += ns;
@@ -97,6 +100,12 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
             pbase += ns;
         }
     }
+}
+
+__device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len, int& ps)
+{
+    bool last;
+    slot_range(g, s, tok0, len, ps, last);
 }
 
 __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len)
@@ -162,8 +171,10 @@ hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const
                                   const void* dO, const float* P, const float* dR, void* dQ, void* dK,
                                   void* dV, hipStream_t st);
 // inclusive = 0: P[s] excludes M[s] (the public entry point); 1: P[s] includes it.
+// user_slots: the states of g's walks lie in arrays with one entry per slot of the caller's, each walk's
+// where its first slot is; otherwise the arrays have one entry per walk.
 hipError_t launch_state_prefix(const Geom& g, const float* M, float* P, int reverse, int inclusive,
-                               hipStream_t st);
+                               int user_slots, hipStream_t st);
 
 // S[s] = sum of M over the slots of s's document; S may alias M.
 hipError_t launch_state_total(const Geom& g, const float* M, float* S, hipStream_t st);
@@ -173,11 +184,19 @@ hipError_t launch_rows_state_generic(const Geom& g, int dtype, const void* A, co
 
 // bf16 MFMA kernels (d = 128; they tile slots in their own chunks, so any C).
 bool mfma_path_supported(const Geom& g, int dtype);
+// for_prefix: the states of g's walks go where each walk's first slot is in an array with one entry per slot
+// of the caller's, and the last walk of a document, whose state no exclusive prefix contains, is left out.
 hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float* M,
-                              int anchor_start, hipStream_t st);
+                              int anchor_start, int for_prefix, hipStream_t st);
 // O = fused intra + inter pass with prefix states P.
 hipError_t launch_attn_fwd_mfma(const Geom& g, const void* Q, const void* K, const void* V,
                                 const float* P, void* O, hipStream_t st);
+// The same, and writes the prefix state of every slot of the caller's to P: a walk reads the first of its
+// slots there (nothing where every document is a single walk) and fills in the rest as it passes them.
+// g: walks of more than 128 tokens, slots of a multiple of 64 (walk_emits).
+bool walk_emits(const Geom& g, int dtype);
+hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K, const void* V,
+                                     float* P, void* O, hipStream_t st);
 // dQ, dV, dK in one launch.  P: exclusive prefix states of K^T V (from the forward);
 // dR: INCLUSIVE suffix states of Q^T dO (slot s holds the sum over slots >= s of its document);
 // with decay: the EXCLUSIVE decayed suffix of the start-anchored states.

@@ -100,7 +100,8 @@ def test_no_compiler_placed_vmcnt_wait_in_the_walk(isa):
 # (symbol fragment, number of walk copies in the function): attn_skew_mfma_kernel without / with decay
 # (two halves x two directions), and the backward's launch for long slots (four copies of the
 # anti-causal pair's walk: dV / dK rows x early / late row blocks, plus the causal walk's two halves)
-SKEW = (("attn_skew_mfma_kernelILb0E", 4), ("attn_skew_mfma_kernelILb1E", 4), ("attn_bwd_pair_mfma_kernel", 6))
+SKEW = (("attn_skew_mfma_kernelILb0E", 4), ("attn_skew_mfma_kernelILb1E", 4), ("attn_bwd_pair_mfma_kernel", 6),
+        ("attn_fwd_emit_mfma_kernelILb0E", 2), ("attn_fwd_emit_mfma_kernelILb1E", 2))
 
 
 def _skew_blocks(lines, inst):
@@ -236,6 +237,15 @@ def test_decay_attention_kernels_keep_their_loads_in_flight(isa):
             elif "vmcnt" in x and j > first_barrier:
                 assert in_asm, (cname, j, x.strip())
     assert found == 1
+
+
+@pytest.mark.parametrize("decay", [0, 1])
+def test_emitting_walk_store_count_matches_its_wait_arithmetic(isa, decay):
+    """attn_fwd_emit_mfma_kernel adds 32 to its count of memory instructions for each state a wave writes: at the walk's
+    start and after each of a chunk's four blocks, in both halves' copies.  Fewer store instructions than that
+    (merged stores) would make the waits too lenient."""
+    body, _ = _skew_blocks(isa, f"attn_fwd_emit_mfma_kernelILb{decay}E")
+    assert sum("global_store_dword " in l for l in body) == 2 * 5 * 32
 
 
 @pytest.fixture(scope="module")
