@@ -162,15 +162,16 @@ int forced_walk_slots(const Geom& g)
     return v >= 1 ? (int)std::min<int64_t>(v, max_walk_slots(g)) : 0;
 }
 
-// Slots per walk for a launch that runs `par` walks at a time and gains little from walks longer
-// than `target` tokens (measured: the forward launch is flat from about 2 048 tokens on, the
-// backward from about 4 096; starting a walk costs what streaming about a hundred tokens does).
+// Slots per walk of lasp2_attn_fwd, and of packed batches: for a launch that runs `par` walks at a time and gains
+// little from walks longer than `target` tokens (measured: the forward launch is flat from about 2 048 tokens on; starting a walk costs what streaming about a hundred tokens does).
 //   - Equal sequences, enough of them to fill the device by themselves: one walk per sequence,
 //     which needs no prefix or suffix state at all (the serial-carry order of work).
 //   - Otherwise the shortest walk of at least `target` tokens (a power of two of slots), made
 //     shorter again while the launch would have fewer than two rounds of workgroups: a launch of
 //     one round ends at the pace of its slowest CU, and less than one leaves CUs without work.
 // LASP2_WALK_SLOTS overrides the choice.
+constexpr int64_t kWalkTargetFwd = 2048;
+
 int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t target)
 {
     const int64_t longest_seq = longest_sequence(g, cu_host);
@@ -192,8 +193,65 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
     };
     int64_t ws = 1;
     while (ws * g.L < target && ws * 2 <= ws_max && ws < ws_whole) ws *= 2;
-    while (ws > 1 && units(ws) < 2 * (int64_t)par) ws /= 2;
+    const int64_t shortest = g.n_seqs ? 256 : 1;   // (packed: below, the 128-row kernel, which writes no states in passing)
+    while (ws > 1 && ws / 2 * g.L >= shortest && units(ws) < 2 * (int64_t)par) ws /= 2;
     return (int)ws;
+}
+
+// Slots per walk of lasp2_forward's emitting walks (`par` walks at a time, one per CU) and of the backward (`par` pairs of
+// workgroups) on equal sequences: the fewest rounds of `par` walks that end together.  A launch of k rounds costs k times
+// the tokens of a walk and what starting one does (`start`); k = 1 .. 16 are compared, each with the shortest walks that
+// fit into k rounds.
+//   - `start`: forward 256 tokens, backward 180 (from launches of 1 024 and 4 096 tokens: 35 and 124 us).
+//   - Walks have at least 256 tokens: shorter ones take the 128-row kernel and write no states in passing (16 heads x 3 000,
+//     64-token slots, forward: walks of 128 58 us, 192 or 256 38; backward 74 -> 54).  Not below 512 tokens, where launches
+//     are all there is (300 tokens: walks of 64 21 us, 256 25; backward 21, 29).
+//   - One round ends at the pace of the slowest CU: 8 % more in the backward (16 heads, one round | two, us: 8 192 85 | 93;
+//     16 384 149 | 151; 32 768 281 | 271; 262 144 2058 | 1949), 3 % in the forward (65 536: 346 | 361; 262 144, 4 096-token
+//     slots: 1209 | 1153).
+//   - Forward, a sequence in several walks: states and prefix, 512 bytes per token at 6 TB/s and two launches, counted in
+//     tokens of 0.03 us (160 sequences of 3 000: whole 139 us, three walks each 168).
+int pick_even_walk_slots(const Geom& g, int par, bool backward)
+{
+    const int64_t slots = ((int64_t)g.N + g.L - 1) / g.L;
+    if (slots <= 1 || g.G == 0) return 1;
+    if (const int v = forced_walk_slots(g)) return v;
+    const int64_t ws_max = std::min(slots, max_walk_slots(g));
+    const int64_t ws_min = g.N < 512 ? 1 : std::min((256 + g.L - 1) / g.L, ws_max);
+    const double start = backward ? 180.0 : 256.0;
+    const double states = backward ? 0.0 : ((double)g.G * g.N * 512.0 / 6e6 + 10.0) / 0.03;
+    int64_t best = ws_max;
+    double best_cost = -1.0;
+    for (int k = 1; k <= 16; ++k) {
+        const int64_t m = (int64_t)k * par / g.G;   // walks per sequence
+        if (m < 1) continue;
+        const int64_t ws = std::min(ws_max, std::max(ws_min, (slots + m - 1) / m));
+        const int64_t walks = (slots + ws - 1) / ws, rounds = (walks * g.G + par - 1) / par;
+        double cost = (double)rounds * ((double)std::min<int64_t>(ws * g.L, g.N) + start);
+        if (rounds == 1) cost *= backward ? 1.08 : 1.03;
+        if (walks > 1) cost += states;
+        if (best_cost < 0.0 || cost < best_cost) { best = ws; best_cost = cost; }
+        if (ws == ws_min) break;
+    }
+    return (int)best;
+}
+
+// Slots per walk of the backward.  Packed documents: as in pick_walk_slots, with walks of an eighth of what a pair of CUs
+// has to do, between 1 024 and 4 096 tokens (32 heads x 32 768 in 20 documents: 4 096 707 us, 1 024 657; 16 heads x
+// 131 072 in 40: 4 096 1216, 2 048 1205).
+int pick_bwd_walk_slots(const Geom& g, const int32_t* cu_host, int par)
+{
+    par = std::max(1, par);
+    if (g.n_seqs == 0) return pick_even_walk_slots(g, par, true);
+    const int64_t share = (int64_t)g.G * g.N / par / 8;
+    return pick_walk_slots(g, cu_host, par, std::min<int64_t>(4096, std::max<int64_t>(1024, share)));
+}
+
+// Slots per walk of lasp2_forward.
+int pick_forward_walk_slots(const Geom& g, const int32_t* cu_host)
+{
+    if (g.n_seqs == 0 && g.L % 64 == 0) return pick_even_walk_slots(g, cu_count(), false);
+    return pick_walk_slots(g, cu_host, cu_count(), kWalkTargetFwd);
 }
 
 // Slots per walk of the split-plane kernels, `nprob` workgroups per walk.  They work on chunks of 128
@@ -213,10 +271,6 @@ int pick_planes_slots(const Geom& g, const int32_t* cu_host, int nprob)
     }
     return ws;
 }
-
-// (backward, equal sequences: two rounds of 16 384-token walks beat eight of 4 096 by 2 % at config 3 -
-// the states kernel writes fewer states; ragged documents do best at 4 096)
-constexpr int64_t kWalkTargetFwd = 2048, kWalkTargetBwd = 16384, kWalkTargetBwdPacked = 4096;
 
 int check_ptrs(std::initializer_list<const void*> ptrs)
 {
@@ -289,8 +343,7 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     pl->gw = g;
     if (pl->fast) {
         const int wgs = g.decay ? 3 : 2;   // workgroups per walk in the attention launch
-        const int64_t target = g.n_seqs ? kWalkTargetBwdPacked : kWalkTargetBwd;
-        pl->gw = regroup(g, desc->cu_seqlens_host, pick_walk_slots(g, desc->cu_seqlens_host, std::max(1, cu_count() / wgs), target));
+        pl->gw = regroup(g, desc->cu_seqlens_host, pick_bwd_walk_slots(g, desc->cu_seqlens_host, cu_count() / wgs));
     }
     pl->lone_w = pl->gw.lone_slots != 0;
     pl->need_states_w = !pl->lone_w || pl->inclusive;
@@ -369,9 +422,8 @@ int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_
         *slots_per_walk = pick_planes_slots(g, desc->cu_seqlens_host, backward ? 3 : 1);
         return LASP2_OK;
     }
-    const int wgs = backward ? (g.decay ? 3 : 2) : 1;
-    *slots_per_walk = pick_walk_slots(g, desc->cu_seqlens_host, std::max(1, cu_count() / wgs),
-                                      backward ? (g.n_seqs ? kWalkTargetBwdPacked : kWalkTargetBwd) : kWalkTargetFwd);
+    *slots_per_walk = backward ? pick_bwd_walk_slots(g, desc->cu_seqlens_host, cu_count() / (g.decay ? 3 : 2))
+                               : pick_walk_slots(g, desc->cu_seqlens_host, cu_count(), kWalkTargetFwd);
     return LASP2_OK;
 }
 
@@ -446,7 +498,7 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     hipStream_t st = (hipStream_t)stream;
     const int32_t* cu = desc->cu_seqlens_host;
     const bool fast = mfma_path_supported(g, desc->dtype);
-    const Geom gw = fast ? regroup(g, cu, pick_walk_slots(g, cu, cu_count(), kWalkTargetFwd))
+    const Geom gw = fast ? regroup(g, cu, pick_forward_walk_slots(g, cu))
                          : regroup(g, cu, pick_planes_slots(g, cu, 1));
     hipError_t e;
     if (walk_emits(gw, desc->dtype)) {
