@@ -24,8 +24,13 @@ __device__ __forceinline__ void st(__hip_bfloat16* p, float v) { *p = __float2bf
 constexpr int kScanBatch = 8;
 
 __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const float* M, float* P,
-                                                                int reverse, int inclusive, int user_slots)
+                                                                int reverse, int inclusive, int user_slots,
+                                                                unsigned* clear, unsigned nclear)
 {
+    if (clear) {
+        const unsigned blk = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+        for (unsigned i = blk * kThreads + threadIdx.x; i < nclear; i += gridDim.x * gridDim.y * gridDim.z * kThreads) clear[i] = 0u;
+    }
     const int dd = g.d * g.d;
     const int e = (blockIdx.x * kThreads + threadIdx.x) * 4;
     if (e >= dd) return;
@@ -33,18 +38,17 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
     const int64_t Lp = user_slots ? g.L / g.wslots : g.L;   // tokens per array entry
     const int entries = user_slots ? g.P_Ts : g.T_s;
     const size_t base = (size_t)blockIdx.y * (size_t)entries * dd + e;
-    const int ndocs = g.n_seqs ? g.n_seqs : 1;
+    // the documents of one mark (documents are independent of each other)
+    const int k0 = (int)blockIdx.z * g.doc_stride, k1 = g.n_seqs ? min(k0 + g.doc_stride, g.n_seqs) : 1;
     const float l2 = decay_log2(g, blockIdx.y);
     const int step = reverse ? -stride : stride;
-    int first = reverse ? entries : 0;   // entries before the document (reverse: before its end)
-    for (int kk = 0; kk < ndocs; ++kk) {
-        const int k = reverse ? ndocs - 1 - kk : kk;
+    int first = user_slots ? g.doc_pmark[blockIdx.z] : g.doc_mark[blockIdx.z];   // entries before the document
+    for (int k = k0; k < k1; ++k) {
         const int dlen = g.n_seqs ? (g.cu[k + 1] - g.cu[k]) : g.N;
         const int ns = (int)(((int64_t)dlen + g.L - 1) / g.L);
         const int ne = (int)(((int64_t)dlen + Lp - 1) / Lp);
-        if (reverse) first -= ne;
         int s = first + (reverse ? (ns - 1) * stride : 0);
-        if (!reverse) first += ne;
+        first += ne;
         const int nm = inclusive ? ns : ns - 1;   // states that enter a result
         float4 run = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int r = 0; r < ns; r += kScanBatch) {
@@ -272,11 +276,12 @@ hipError_t launch_rows_state_generic(const Geom& g, int dtype, const void* A, co
 }
 
 hipError_t launch_state_prefix(const Geom& g, const float* M, float* P, int reverse, int inclusive,
-                               int user_slots, hipStream_t st)
+                               int user_slots, unsigned* clear, unsigned nclear, hipStream_t st)
 {
     const int dd = g.d * g.d;
-    dim3 grid((dd / 4 + kThreads - 1) / kThreads, g.G), block(kThreads);
-    hipLaunchKernelGGL(state_prefix_kernel, grid, block, 0, st, g, M, P, reverse, inclusive, user_slots);
+    const int marks = g.n_seqs ? (g.n_seqs + g.doc_stride - 1) / g.doc_stride : 1;
+    dim3 grid((dd / 4 + kThreads - 1) / kThreads, g.G, marks), block(kThreads);
+    hipLaunchKernelGGL(state_prefix_kernel, grid, block, 0, st, g, M, P, reverse, inclusive, user_slots, clear, nclear);
     return hipGetLastError();
 }
 

@@ -125,10 +125,9 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
         Unit x;
         x.u = u; x.len = 0; x.nblk = 0; x.row0 = 0; x.m = 0;
         if (u < nunits) {
-            int tok0, ps;
-            bool last;
-            slot_range(g, u % g.T_s, tok0, x.len, ps, last);
-            if (for_prefix && last) x.len = 0;   // no blocks, no state
+            int tok0, ps, doc0, doc1;
+            slot_range(g, u % g.T_s, tok0, x.len, ps, doc0, doc1);
+            if (for_prefix && tok0 + x.len == doc1) x.len = 0;   // the document's last: no blocks, no state
             x.nblk = (x.len + ST_KB - 1) / ST_KB;
             x.row0 = ((size_t)(u / g.T_s) * g.N + tok0) * ROWB;
             x.m = for_prefix ? (size_t)(u / g.T_s) * g.P_Ts + ps : (size_t)u;
@@ -160,11 +159,11 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
     int slot = 0, older_than_stores = 0;
     for (Unit cu = open_unit(u_first); cu.u < nunits; cu = open_unit(cu.u + 1)) {
         if (for_prefix && cu.nblk == 0) continue;
-        f32x16 acc[ST_TPW];
+        f32x16 acc[ST_TPW], tot[ST_TPW];
 #pragma unroll
         for (int u = 0; u < ST_TPW; ++u)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[u][v] = 0.f;
+            for (int v = 0; v < 16; ++v) { acc[u][v] = 0.f; tot[u][v] = 0.f; }
         float l2 = DECAY ? decay_log2(g, cu.u / g.T_s) : 0.f;
         asm volatile("" : "+v"(l2));   // waited for here, once per slot, not at its first use inside the block loop
 
@@ -203,6 +202,12 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
             __syncthreads();   // block complete in LDS; every wave has left the block before it
             issue_next();      // into the ring slot that block occupied
             update_tiles<ST_TPW, ST_KB>(acc, tx, ty, w * ST_TPW, lane);
+            if (!DECAY && for_prefix && (blk & 15) == 15) {   // (a walk of several slots: sums of 512 rows, as accurate as the slots' own)
+#pragma unroll
+                for (int u = 0; u < ST_TPW; ++u)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) { tot[u][v] += acc[u][v]; acc[u][v] = 0.f; }
+            }
             slot = slot + 1 == ST_NST ? 0 : slot + 1;
         }
 
@@ -213,7 +218,7 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = 32 * a + 8 * (v >> 2) + 4 * h + (v & 3);
-                __builtin_nontemporal_store(acc[u][v], m + row * D + 32 * b + l32);
+                __builtin_nontemporal_store(DECAY ? acc[u][v] : tot[u][v] + acc[u][v], m + row * D + 32 * b + l32);
             }
         }
         older_than_stores = inflight;
@@ -307,6 +312,23 @@ __device__ __forceinline__ void mm_update(f32x16 (&acc)[TPW], const bf16x8 (&buf
 {
 #pragma unroll
     for (int u = 0; u < TPW; ++u) acc[u] = mfma(buf[0], buf[1 + u], acc[u]);
+}
+
+// Short sequences: the state a walk starts from as gather_state leaves it in LDS, behind the walk's stages (64 KiB where
+// snapshot and output staging come to lie), each wave's two tiles as it holds them.
+constexpr int GATHERED = 2 * NSTAGE * STAGE_BYTES;
+__device__ __forceinline__ void take_gathered(f32x16 (&M)[2], const char* smem, int tid, int w)
+{
+    int ln;   // (not the caller's lane index: its registers are needed)
+    asm volatile("v_and_b32 %0, 63, %1" : "=v"(ln) : "v"(tid));
+    const f32x4* p = reinterpret_cast<const f32x4*>(smem + GATHERED + w * 8192) + ln;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const f32x4 x = p[i * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) M[i >> 2][4 * (i & 3) + e] = x[e];
+    }
+    __syncthreads();   // the first snapshot overwrites other waves' tiles
 }
 
 // One problem instance for the fused attention pass.
@@ -771,10 +793,11 @@ __device__ __forceinline__ uint32_t wait_vmcnt_token_le(int n)
 // EMIT (causal only): the walk also writes the state at the start of each of the caller's slots inside it
 // to pr.emit (slots of a multiple of 64 tokens).  The running state after a block is that of the slot which starts there:
 // 32 stores per wave and slot, counted like the output's.
+// gathered: the state is where gather_state has left it (no wstate then).
 template <bool HC1, bool ANTI, bool DECAY, bool EMIT = false>
 __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, char* smem, int tid, int w,
                                           int rb, int grp, int s, int tok0, int len, const float* wstate,
-                                          int ps = 0)
+                                          int ps = 0, bool gathered = false)
 {
     constexpr int C = 256, NW = 8, TPW = 2, BPC = 4, DPS = 4, NOP = 4;
     // With decay the anti-causal problems walk the slot backwards from the exclusive suffix (see
@@ -823,6 +846,12 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
     for (int u = 0; u < TPW; ++u)
 #pragma unroll
         for (int v = 0; v < 16; ++v) Macc[u][v] = 0.f;
+    // EMIT: Macc holds the sum since the present slot's start and Base the state there, so that the states written are sums
+    // of slot sums, as accurate as those of the states and prefix kernels (one running sum of a long walk is not: its
+    // every addition rounds the whole state).  With decay the weighted rows are bf16 and the rounding of sums does not show.
+    constexpr bool SPLIT = EMIT && !DECAY;
+    f32x16 Base[SPLIT ? TPW : 1];
+    if (gathered) take_gathered(Macc, smem, tid, w);
     if (wstate) {   // NULL: every slot opens its document and starts from a zero state
         const float* st = wstate;
         const float sg = ENDSTATE ? -1.f : 1.f;
@@ -842,6 +871,13 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
                 }
             }
         }
+    }
+
+    if (SPLIT) {
+#pragma unroll
+        for (int u = 0; u < TPW; ++u)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { Base[SPLIT ? u : 0][v] = Macc[u][v]; Macc[u][v] = 0.f; }
     }
 
     // Per-lane byte offsets into a swizzled tile.  The swizzle is an XOR on the 16-byte chunk index
@@ -902,8 +938,10 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
         for (int u = 0; u < TPW; ++u)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                u32x2 pk = {pack2(sg * Macc[u][4 * q], sg * Macc[u][4 * q + 1]),
-                            pack2(sg * Macc[u][4 * q + 2], sg * Macc[u][4 * q + 3])};
+                float x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = SPLIT ? Base[SPLIT ? u : 0][4 * q + e] + Macc[u][4 * q + e] : sg * Macc[u][4 * q + e];
+                u32x2 pk = {pack2(x[0], x[1]), pack2(x[2], x[3])};
                 *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((s0 ^ (q << 4)) + u * (32 * ROWB)) = pk;
             }
     };
@@ -1137,6 +1175,12 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
     // called with the running state at the start of block bi
     auto emit = [&](int bi) __attribute__((always_inline)) {
         if (!EMIT || bi != enext || bi * KB >= len) return;
+        if (SPLIT) {
+#pragma unroll
+            for (int u = 0; u < TPW; ++u)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { Base[SPLIT ? u : 0][v] += Macc[u][v]; Macc[u][v] = 0.f; }
+        }
         if (bi > 0 || !wstate) {   // (the first slot's own was read from there)
             int ln;
             asm volatile("v_and_b32 %0, 63, %1" : "=v"(ln) : "v"(tid));
@@ -1146,7 +1190,7 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
             for (int u = 0; u < TPW; ++u)
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    __builtin_nontemporal_store(Macc[u][v], e + 32 * u + (8 * (v >> 2) + (v & 3)) * D + lo);
+                    __builtin_nontemporal_store(SPLIT ? Base[SPLIT ? u : 0][v] : Macc[u][v], e + 32 * u + (8 * (v >> 2) + (v & 3)) * D + lo);
             issued += 16 * TPW;
         }
         enext += eblk;
@@ -1317,13 +1361,13 @@ struct PairProblem {
     const char* dO;
     const char* K;
     const char* V;
-    const float* dR;   // [G][T_s][d][d]: inclusive suffix of Q^T dO at each slot's start
+    float* dR;         // [G][T_s][d][d]: inclusive suffix of Q^T dO at each slot's start
     char* dV;
     char* dK;
     unsigned* pace;    // NULL, or per (group, slot): receives the number of blocks this walk has begun
 };
 
-template <bool DKROLE, bool LATE>
+template <bool DKROLE, bool LATE, bool GATHERS = false>
 __device__ __forceinline__ void pair_walk(const Geom& g, const PairProblem& pr, char* smem, int tid, int w,
                                           int rb, int grp, int s, int tok0, int len)
 {
@@ -1355,7 +1399,9 @@ __device__ __forceinline__ void pair_walk(const Geom& g, const PairProblem& pr, 
 
     // running state tiles (rows d_k, columns d_v), holding minus the suffix
     f32x16 Macc[TPW];
-    {
+    if (GATHERS) {   // (gather_state's, minus sign and all, instead of pr.dR)
+        take_gathered(Macc, smem, tid, w);
+    } else {
         const float* st = pr.dR + ((size_t)grp * g.T_s + s) * (size_t)(D * D);
 #pragma unroll
         for (int u = 0; u < TPW; ++u) {
@@ -1484,10 +1530,13 @@ __device__ __forceinline__ void pair_walk(const Geom& g, const PairProblem& pr, 
                                           (aC ^ ((tv << 6) | 32)) + half * (32 * ROWB) + 24 * ROWB);
             SCHED_FENCE();
             if (kt == rb) {
+                int lm = lane;
+                // (the gathering kernel has no registers left for the 16 rows across the walk)
+                if (GATHERS) asm volatile("v_and_b32 %0, 63, %1" : "=v"(lm) : "v"(tid));
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int key = 8 * (v >> 2) + 4 * h + (v & 3);
-                    const bool keep = EXIT ? key >= l32 : key < l32;
+                    const int key = 8 * (v >> 2) + 4 * (lm >> 5) + (v & 3);
+                    const bool keep = EXIT ? key >= (lm & 31) : key < (lm & 31);
                     sc[v] = keep ? sc[v] : 0.f;
                 }
             }
@@ -1706,6 +1755,151 @@ __global__ __launch_bounds__(512) void attn_bwd_pair_mfma_kernel(Geom g, AttnPro
         else if (w < 4) pair_walk<false, true>(g, pp, smem, tid, w, w, grp, s, tok0, len);
         else if (w < 6) pair_walk<true, true>(g, pp, smem, tid, w, 7 - w, grp, s, tok0, len);
         else pair_walk<true, false>(g, pp, smem, tid, w, 7 - w, grp, s, tok0, len);
+    } else {
+        const int rb = w < 4 ? w : 11 - w;
+        const float* wstate = pq.state ? walk_state(g, pq, grp, s, ps) : nullptr;
+        if (rb < 4) skew_walk<false, false, false>(g, pq, smem, tid, w, rb, grp, s, tok0, len, wstate);
+        else skew_walk<true, false, false>(g, pq, smem, tid, w, rb, grp, s, tok0, len, wstate);
+    }
+}
+
+// ---- short sequences: forward and backward in one launch each ----
+// The state a walk starts from, sign * X^T Y over `ntok` rows from byte row0 on, left in LDS for take_gathered (and, without
+// the sign, in copy [D][D] if that is not NULL).  Every workgroup streams the rows anew, so this is for sequences so short that the
+// launches it saves (states, prefix, counters: 5 to 8 us each with the gap before it) cost more.
+// Eight waves: four quadrants of 2 x 2 tiles, each by two waves that take the halves of a 64-row stage (an
+// operand is read from LDS once per two products; the walks' own update, one row of tiles per wave, reads three per
+// two); a ring of four stages, three on their way.  The halves are added through LDS at the end.
+__device__ __forceinline__ void gather_state(const char* X, const char* Y, size_t row0, int ntok, float sign,
+                                             float* copy, char* smem, int tid, int w)
+{
+    constexpr int NST = 4, DPS = 4;
+    int lane;   // (opaque: nothing derived from it is kept for the walk)
+    asm volatile("v_and_b32 %0, 63, %1" : "=v"(lane) : "v"(tid));
+    const int h = lane >> 5;
+    const int qa = w >> 2, qb = w & 1, hf = (w >> 1) & 1;
+    char* sX = smem;
+    char* sY = smem + NST * STAGE_BYTES;
+    uint32_t dvo[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) dvo[u] = dma_lane_off(2 * w + u, lane);
+    const int nst = (ntok + KB - 1) / KB;
+    auto issue = [&](int i) {
+        dma_block<8>(X, Y, row0, i * KB, ntok, sX + (i % NST) * STAGE_BYTES, sY + (i % NST) * STAGE_BYTES, w, lane, dvo);
+    };
+    // sums of at most 512 rows, and the sum of those: as accurate as the sums of a slot and of slots that they replace
+    f32x16 acc[2][2], tot[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[a][b][v] = 0.f; tot[a][b][v] = 0.f; }
+    auto flush = [&]() {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { tot[a][b][v] += acc[a][b][v]; acc[a][b][v] = 0.f; }
+    };
+    for (int i = 0; i < NST - 1 && i < nst; ++i) issue(i);
+    for (int i = 0; i < nst; ++i) {
+        char* tx = sX + (i % NST) * STAGE_BYTES;
+        char* ty = sY + (i % NST) * STAGE_BYTES;
+        // stage i has landed once only the (at most two) younger ones are outstanding
+        if (i + 2 < nst) wait_vmcnt<2 * DPS>();
+        else if (i + 1 < nst) wait_vmcnt<DPS>();
+        else wait_vmcnt<0>();
+        if (i * KB + KB > ntok) zero_tail_rows<8>(i * KB, ntok, tx, ty, w, lane);
+        __syncthreads();   // complete in LDS; every wave is past stage i - 1, whose place stage i + 3 takes
+        if (i + NST - 1 < nst) issue(i + NST - 1);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int r = 32 * hf + 16 * k + 8 * h;
+            bf16x8 x[2], y[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                x[e] = lds_read_tr8(tx, r, r + 4, 64 * qa + 32 * e, lane);
+                y[e] = lds_read_tr8(ty, r, r + 4, 64 * qb + 32 * e, lane);
+            }
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) acc[a][b] = mfma(x[a], y[b], acc[a][b]);
+        }
+        if ((i & 7) == 7) flush();
+    }
+    flush();
+    __syncthreads();
+    // this wave finishes row hf of its quadrant's tiles and hands the other to the wave with the other half
+    f32x4* out = reinterpret_cast<f32x4*>(smem + w * 8192) + lane;
+    const f32x4* in = reinterpret_cast<const f32x4*>(smem + (w ^ 2) * 8192) + lane;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            f32x4 p;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = hf ? tot[0][b][4 * q + e] : tot[1][b][4 * q + e];
+            out[(4 * b + q) * 64] = p;
+        }
+    __syncthreads();
+    f32x4* M = reinterpret_cast<f32x4*>(smem + GATHERED + w * 8192) + lane;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            f32x4 p = in[(4 * b + q) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] += hf ? tot[1][b][4 * q + e] : tot[0][b][4 * q + e];
+            if (copy) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    __builtin_nontemporal_store(p[e], copy + (32 * (w >> 1) + 8 * q + 4 * h + e) * D + 64 * qb + 32 * b + (lane & 31));
+            }
+            M[(4 * b + q) * 64] = sign * p;
+        }
+    __syncthreads();   // the walk's stages take the memory in front
+}
+
+__global__ __launch_bounds__(512) void attn_fwd_direct_mfma_kernel(Geom g, AttnProblem pr)
+{
+    extern __shared__ __attribute__((aligned(256))) char smem[];
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (the walks with the most rows before them first)
+    const unsigned unit = gridDim.x - 1 - blockIdx.x;
+    const int s = (int)(unit / (unsigned)g.G), grp = (int)(unit % (unsigned)g.G);
+    int tok0, len, ps, doc0, doc1;
+    slot_range(g, s, tok0, len, ps, doc0, doc1);
+    if (len <= 0) return;
+    gather_state(pr.Bk, pr.Cv, ((size_t)grp * g.N + doc0) * ROWB, tok0 - doc0, 1.f, nullptr, smem, tid, w);
+    const int rb = w < 4 ? w : 11 - w;   // waves w and w+4 share a SIMD: row blocks s and 7-s
+    if (rb < 4) skew_walk<false, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true);
+    else skew_walk<true, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true);
+}
+
+__global__ __launch_bounds__(512) void attn_bwd_direct_mfma_kernel(Geom g, AttnProblem pq, PairProblem pp)
+{
+    extern __shared__ __attribute__((aligned(256))) char smem[];
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // pairs first, those with the most rows after them at the start
+    const unsigned units = gridDim.x / 2;
+    const bool pair = blockIdx.x < units;
+    const unsigned unit = pair ? blockIdx.x : blockIdx.x - units;
+    const int s = (int)(unit / (unsigned)g.G), grp = (int)(unit % (unsigned)g.G);
+    int tok0, len, ps, doc0, doc1;
+    slot_range(g, s, tok0, len, ps, doc0, doc1);
+    if (len <= 0) return;
+    if (pair) {
+        gather_state(pp.Q, pp.dO, ((size_t)grp * g.N + tok0) * ROWB, doc1 - tok0, -1.f,
+                     pp.dR + ((size_t)grp * g.T_s + s) * (size_t)(D * D), smem, tid, w);
+        if (w < 2) pair_walk<false, false, true>(g, pp, smem, tid, w, w, grp, s, tok0, len);
+        else if (w < 4) pair_walk<false, true, true>(g, pp, smem, tid, w, w, grp, s, tok0, len);
+        else if (w < 6) pair_walk<true, true, true>(g, pp, smem, tid, w, 7 - w, grp, s, tok0, len);
+        else pair_walk<true, false, true>(g, pp, smem, tid, w, 7 - w, grp, s, tok0, len);
     } else {
         const int rb = w < 4 ? w : 11 - w;
         const float* wstate = pq.state ? walk_state(g, pq, grp, s, ps) : nullptr;
@@ -2201,7 +2395,9 @@ hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float
     const int cus = cu_count();
     const long long nunits = (long long)g.T_s * g.G;
     if (nunits == 0) return hipSuccess;
-    const int per_wg = (int)((nunits + 2LL * cus - 1) / (2LL * cus));
+    int per_wg = (int)((nunits + 2LL * cus - 1) / (2LL * cus));
+    // (documents of different lengths: shares of about 2 048 tokens, dealt out as workgroups end)
+    if (g.n_seqs) per_wg = (int)std::min<long long>(per_wg, std::max(1LL, 2048LL * g.T_s / g.N));
     dim3 grid((unsigned)((nunits + per_wg - 1) / per_wg)), block(ST_NT);
     hipLaunchKernelGGL(kern, grid, block, smem, st, g, static_cast<const char*>(K),
                        static_cast<const char*>(V), M, anchor_start, per_wg, for_prefix);
@@ -2243,7 +2439,7 @@ hipError_t launch_attn_fwd_mfma(const Geom& g, const void* Q, const void* K, con
 
 bool walk_emits(const Geom& g, int dtype)
 {
-    return mfma_path_supported(g, dtype) && g.wslots > 1 && wide_chunks(g) && (g.L / g.wslots) % KB == 0;
+    return mfma_path_supported(g, dtype) && ((g.wslots > 1 && wide_chunks(g)) || g.lone_slots) && (g.L / g.wslots) % KB == 0;
 }
 
 hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K, const void* V,
@@ -2260,8 +2456,33 @@ hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K
     return hipGetLastError();
 }
 
+hipError_t launch_attn_fwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V,
+                                       float* P, void* O, hipStream_t st)
+{
+    constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
+    AttnProblem p = make_problem(Q, K, V, nullptr, 1, O, 0, 0);
+    p.emit = P;
+    hipError_t e = allow_dynamic_lds<attn_fwd_direct_mfma_kernel>(smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(attn_fwd_direct_mfma_kernel, dim3((unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_attn_bwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V, const void* dO,
+                                       const float* P, float* dR, void* dQ, void* dK, void* dV, hipStream_t st)
+{
+    constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
+    const AttnProblem pq = make_problem(dO, V, K, P, 1, dQ, 1, 0);
+    const PairProblem pp = {static_cast<const char*>(Q), static_cast<const char*>(dO), static_cast<const char*>(K),
+                            static_cast<const char*>(V), dR, static_cast<char*>(dV), static_cast<char*>(dK), nullptr};
+    hipError_t e = allow_dynamic_lds<attn_bwd_direct_mfma_kernel>(smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(attn_bwd_direct_mfma_kernel, dim3(2u * (unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, pq, pp);
+    return hipGetLastError();
+}
+
 hipError_t launch_attn_bwd_mfma(const Geom& g, const void* Q, const void* K, const void* V,
-                                const void* dO, const float* P, const float* dR, unsigned* pace, void* dQ,
+                                const void* dO, const float* P, const float* dR, unsigned* pace, int pace_clear, void* dQ,
                                 void* dK, void* dV, hipStream_t st)
 {
     // dQ: the forward problem with (dO, V, K) in the roles of (Q, K, V); its state V^T K is the
@@ -2282,12 +2503,13 @@ hipError_t launch_attn_bwd_mfma(const Geom& g, const void* Q, const void* K, con
         const unsigned units = (unsigned)g.T_s * (unsigned)g.G;
         AttnProblem pq2 = pq;
         if (pace) {
-            hipLaunchKernelGGL(zero_u32_kernel, dim3((units + 255u) / 256u), dim3(256), 0, st, pace, units);
+            if (pace_clear)
+                hipLaunchKernelGGL(zero_u32_kernel, dim3((units + 255u) / 256u), dim3(256), 0, st, pace, units);
             pq2.pace = pace;
             pq2.lead = 0;   // (leads of -1 .. 2 blocks measured alike)
         }
         const PairProblem pp = {static_cast<const char*>(Q), static_cast<const char*>(dO),
-                                static_cast<const char*>(K), static_cast<const char*>(V), dR,
+                                static_cast<const char*>(K), static_cast<const char*>(V), const_cast<float*>(dR),
                                 static_cast<char*>(dV), static_cast<char*>(dK), pace};
         dim3 grid(2u * ((units + 7u) & ~7u)), block(512);
         hipLaunchKernelGGL(attn_bwd_pair_mfma_kernel, grid, block, smem, st, g, pq2, pp);

@@ -8,6 +8,7 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <cmath>
 
 namespace lasp2 {
 namespace {
@@ -193,65 +194,129 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
     };
     int64_t ws = 1;
     while (ws * g.L < target && ws * 2 <= ws_max && ws < ws_whole) ws *= 2;
-    const int64_t shortest = g.n_seqs ? 256 : 1;   // (packed: below, the 128-row kernel, which writes no states in passing)
-    while (ws > 1 && ws / 2 * g.L >= shortest && units(ws) < 2 * (int64_t)par) ws /= 2;
+    while (ws > 1 && units(ws) < 2 * (int64_t)par) ws /= 2;
     return (int)ws;
 }
 
-// Slots per walk of lasp2_forward's emitting walks (`par` walks at a time, one per CU) and of the backward (`par` pairs of
-// workgroups) on equal sequences: the fewest rounds of `par` walks that end together.  A launch of k rounds costs k times
-// the tokens of a walk and what starting one does (`start`); k = 1 .. 16 are compared, each with the shortest walks that
-// fit into k rounds.
-//   - `start`: forward 256 tokens, backward 180 (from launches of 1 024 and 4 096 tokens: 35 and 124 us).
-//   - Walks have at least 256 tokens: shorter ones take the 128-row kernel and write no states in passing (16 heads x 3 000,
-//     64-token slots, forward: walks of 128 58 us, 192 or 256 38; backward 74 -> 54).  Not below 512 tokens, where launches
-//     are all there is (300 tokens: walks of 64 21 us, 256 25; backward 21, 29).
+// How lasp2_forward (walks that write states in passing, kernels_mfma.hip) and the backward cut the sequences: slots per
+// walk, and whether the walks gather the state they start from themselves (`direct`: one launch, no states and prefix
+// before it).  Both from an estimate in us of what each choice costs, with the rates below; the candidates are the shortest
+// walks that fit into one to sixteen rounds of workgroups, or powers of two for documents of different lengths.
+//   - A row of a walk takes 0.03 us forward (dQ 0.031, the pair of the backward 0.0376), starting a walk what 256 (180)
+//     rows do, a row that is gathered 0.0068 (16 heads, walks of 256, gathered | states first, us: 300 rows 15 | 22; 1 024
+//     20 | 24; 2 048 28 | 30; 3 000 37 | 31; 4 096 45 | 36; backward 20 | 27, 25 | 32, 34 | 37, 44 | 46, 58 | 50).
+//   - Memory: 5.2 TB/s, 8 where the tensors fit the 256 MB cache.  The one-launch backward reads three tensors more, as its two
+//     workgroups per walk don't keep in step (256 sequences of 2 000: 305 | 262).
+//   - Of two choices that memory bounds alike the one with less work (0.15 of the walks' time on top).  Documents of
+//     different lengths: the last to start is a long one, and takes 0.05 us per row beside the others (32 heads, 131 072 in
+//     40 documents, forward, walks of 2 048 1434 us, 4 096 1275, 8 192 1212, whole documents 2411).
+//   - States: read at 6 TB/s, and 11 us (15 backward) for two launches; documents of different lengths spread unevenly:
+//     a third more.  (32 heads, 131 072 tokens in 40 documents, forward 1500 -> 1212 us direct in walks of 8 192; 16 heads,
+//     32 768 in 50 322 -> 187, backward 486 -> 341; 32 heads, 8 000 in 20 100 -> 72, 239 -> 155.)
+//   - Walks have at least 256 rows: shorter ones take the 128-row kernel and write no states in passing (16 heads x 3 000,
+//     64-token slots, forward: walks of 128 58 us, 192 or 256 38; backward 74 -> 54).
 //   - One round ends at the pace of the slowest CU: 8 % more in the backward (16 heads, one round | two, us: 8 192 85 | 93;
 //     16 384 149 | 151; 32 768 281 | 271; 262 144 2058 | 1949), 3 % in the forward (65 536: 346 | 361; 262 144, 4 096-token
 //     slots: 1209 | 1153).
-//   - Forward, a sequence in several walks: states and prefix, 512 bytes per token at 6 TB/s and two launches, counted in
-//     tokens of 0.03 us (160 sequences of 3 000: whole 139 us, three walks each 168).
-int pick_even_walk_slots(const Geom& g, int par, bool backward)
+struct WalkPlan { int ws; bool direct; };
+
+// What the walks of `ws` slots are, per group
+struct WalkCount {
+    double walks = 0, longest = 0;     // how many; rows of the longest
+    double before = 0, after = 0;      // rows that lie before (from the start of, to the end of the document) each, summed
+    double farthest = 0;               // ... the largest single one of `before`
+    double inner = 0;                  // rows of walks that are not their document's last
+};
+
+WalkCount count_walks(const Geom& g, const int32_t* cu_host, int64_t ws)
 {
-    const int64_t slots = ((int64_t)g.N + g.L - 1) / g.L;
-    if (slots <= 1 || g.G == 0) return 1;
-    if (const int v = forced_walk_slots(g)) return v;
-    const int64_t ws_max = std::min(slots, max_walk_slots(g));
-    const int64_t ws_min = g.N < 512 ? 1 : std::min((256 + g.L - 1) / g.L, ws_max);
-    const double start = backward ? 180.0 : 256.0;
-    const double states = backward ? 0.0 : ((double)g.G * g.N * 512.0 / 6e6 + 10.0) / 0.03;
-    int64_t best = ws_max;
-    double best_cost = -1.0;
-    for (int k = 1; k <= 16; ++k) {
-        const int64_t m = (int64_t)k * par / g.G;   // walks per sequence
-        if (m < 1) continue;
-        const int64_t ws = std::min(ws_max, std::max(ws_min, (slots + m - 1) / m));
-        const int64_t walks = (slots + ws - 1) / ws, rounds = (walks * g.G + par - 1) / par;
-        double cost = (double)rounds * ((double)std::min<int64_t>(ws * g.L, g.N) + start);
-        if (rounds == 1) cost *= backward ? 1.08 : 1.03;
-        if (walks > 1) cost += states;
-        if (best_cost < 0.0 || cost < best_cost) { best = ws; best_cost = cost; }
-        if (ws == ws_min) break;
+    WalkCount c;
+    const int64_t W = ws * g.L;
+    const int nd = g.n_seqs ? g.n_seqs : 1;
+    for (int k = 0; k < nd; ++k) {
+        const int64_t n = g.n_seqs ? cu_host[k + 1] - cu_host[k] : g.N, m = (n + W - 1) / W;
+        c.walks += (double)m;
+        c.longest = std::max(c.longest, (double)std::min(n, W));
+        c.before += 0.5 * (double)W * (double)m * (double)(m - 1);
+        c.after += (double)n * (double)m - 0.5 * (double)W * (double)m * (double)(m - 1);
+        c.farthest = std::max(c.farthest, (double)(m - 1) * (double)W);
+        c.inner += (double)(m - 1) * (double)W;
     }
-    return (int)best;
+    return c;
 }
 
-// Slots per walk of the backward.  Packed documents: as in pick_walk_slots, with walks of an eighth of what a pair of CUs
-// has to do, between 1 024 and 4 096 tokens (32 heads x 32 768 in 20 documents: 4 096 707 us, 1 024 657; 16 heads x
-// 131 072 in 40: 4 096 1216, 2 048 1205).
-int pick_bwd_walk_slots(const Geom& g, const int32_t* cu_host, int par)
+// `par`: walks that run at a time
+WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backward)
 {
-    par = std::max(1, par);
-    if (g.n_seqs == 0) return pick_even_walk_slots(g, par, true);
-    const int64_t share = (int64_t)g.G * g.N / par / 8;
-    return pick_walk_slots(g, cu_host, par, std::min<int64_t>(4096, std::max<int64_t>(1024, share)));
+    const int64_t longest = longest_sequence(g, cu_host), slots = (longest + g.L - 1) / g.L;
+    const double G = g.G, N = g.N, cus = cu_count(), start = backward ? 180.0 : 256.0;
+    const double row = backward ? 0.0376 : 0.03, gather = 0.0068;
+    const bool may_gather = !g.decay;
+    auto estimate = [&](int64_t ws, bool direct) {
+        const WalkCount c = count_walks(g, cu_host, ws);
+        const double tensor = G * N * 256.0, states = G * N / (double)g.L * 65536.0;
+        const double rate = (backward ? 7.0 : 4.0) * tensor < 2.56e8 ? 8e6 : 5.2e6;
+        const double memory = (backward ? 7.0 * tensor : 4.0 * tensor + states) / rate;
+        const double one = (c.longest + start) * row, rounds = std::ceil(c.walks * G / par);
+        const double walk = g.n_seqs ? std::max(one, G * (N + start * c.walks) * row / par)
+                                     : rounds * one * (rounds > 1.0 ? 1.0 : backward ? 1.08 : 1.03);
+        const double tail = 0.15 * walk + (g.n_seqs ? 0.6 * one : 0.0);
+        const double moved = g.n_seqs ? 4.0 * G * 65536.0 / 5.2e6 : 0.0;   // a walk's state: written, combined, read
+        if (!backward) {
+            if (direct)
+                return std::max({walk + G * c.before * gather / par, one + c.farthest * gather, memory + G * c.before * 512.0 / 2e7}) + tail;
+            if (c.inner == 0.0) return std::max(walk, memory) + tail;
+            return std::max(walk, memory) + tail + 11.0 + G * c.inner * 512.0 / 6e6 * (g.n_seqs ? 1.33 : 1.0) + moved * c.walks;
+        }
+        if (direct) {
+            const double all = G * (c.after * gather + (N + start * c.walks) * (row + 0.031)) / cus;
+            return std::max({longest * gather + one + 0.1 * all, 1.1 * all, 12.5 * tensor / rate}) + 0.15 * all;
+        }
+        return std::max(walk, memory) + tail + 15.0 + 2.0 * tensor / 6e6 * (g.n_seqs ? 1.33 : 1.0) + moved * c.walks;
+    };
+    const int forced = forced_walk_slots(g);
+    const int64_t ws_max = std::min(slots, max_walk_slots(g)), ws_min = std::min((256 + g.L - 1) / g.L, ws_max);
+    WalkPlan best = {1, false};
+    double cost = -1.0;
+    auto offer = [&](int64_t ws) {
+        for (int direct = 0; direct <= (may_gather ? 1 : 0); ++direct) {
+            const double e = estimate(ws, direct != 0);
+            if (cost < 0.0 || e < cost) { cost = e; best = {(int)ws, direct != 0}; }
+        }
+    };
+    if (slots <= 1) {
+        best.direct = may_gather && (!backward || estimate(1, true) < estimate(1, false));   // (forward: nothing to gather)
+    } else if (forced) {
+        offer(forced);
+    } else if (g.n_seqs) {
+        for (int64_t ws = ws_min; ; ws = std::min(2 * ws, ws_max)) {
+            offer(ws);
+            if (ws >= ws_max) break;
+        }
+    } else {
+        for (int k = 1; k <= 16; ++k) {
+            const int64_t m = (int64_t)k * par / g.G;   // walks per sequence
+            if (m < 1) continue;
+            const int64_t ws = std::min(ws_max, std::max(ws_min, (slots + m - 1) / m));
+            offer(ws);
+            if (ws == ws_min) break;
+        }
+        if (cost < 0.0) offer(ws_max);
+    }
+    return best;
 }
 
-// Slots per walk of lasp2_forward.
-int pick_forward_walk_slots(const Geom& g, const int32_t* cu_host)
+WalkPlan pick_bwd_walks(const Geom& g, const int32_t* cu_host, int par)
 {
-    if (g.n_seqs == 0 && g.L % 64 == 0) return pick_even_walk_slots(g, cu_count(), false);
-    return pick_walk_slots(g, cu_host, cu_count(), kWalkTargetFwd);
+    if (g.G == 0) return {1, false};
+    return pick_walks(g, cu_host, std::max(1, par), true);
+}
+
+// (slots of other lengths: no state of theirs stands between two blocks of a walk)
+WalkPlan pick_forward_walks(const Geom& g, const int32_t* cu_host)
+{
+    if (g.L % 64 == 0) return pick_walks(g, cu_host, cu_count(), false);
+    return {pick_walk_slots(g, cu_host, cu_count(), kWalkTargetFwd), false};
 }
 
 // Slots per walk of the split-plane kernels, `nprob` workgroups per walk.  They work on chunks of 128
@@ -310,6 +375,7 @@ struct BwdPlan {
     size_t need;
     bool lone_w;        // every document a single walk
     bool need_states_w;
+    bool direct;        // one launch, suffix states gathered by the walks themselves
 };
 
 // `workspace`: address of the caller's workspace pointer, or NULL for an entry point that has none.
@@ -341,9 +407,12 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     // The kernels' own walks.  The backward's dM states live in the workspace only, so they are
     // built per walk, not per slot of the caller: fewer of them, never more bytes than `need`.
     pl->gw = g;
+    pl->direct = false;
     if (pl->fast) {
         const int wgs = g.decay ? 3 : 2;   // workgroups per walk in the attention launch
-        pl->gw = regroup(g, desc->cu_seqlens_host, pick_bwd_walk_slots(g, desc->cu_seqlens_host, cu_count() / wgs));
+        const WalkPlan wp = pick_bwd_walks(g, desc->cu_seqlens_host, cu_count() / wgs);
+        pl->gw = regroup(g, desc->cu_seqlens_host, wp.ws);
+        pl->direct = wp.direct;
     }
     pl->lone_w = pl->gw.lone_slots != 0;
     pl->need_states_w = !pl->lone_w || pl->inclusive;
@@ -356,19 +425,20 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const int32_t* cu_host, const voi
     const Geom& g = pl.gw;
     if (pl.lone_w) P = nullptr;
     hipError_t e = hipSuccess;
+    if (pl.direct) return from_hip(launch_attn_bwd_direct_mfma(g, Q, K, V, dO, P, dR, dQ, dK, dV, st));
+    unsigned* pace = dR ? reinterpret_cast<unsigned*>(reinterpret_cast<char*>(dR) + states_bytes(g)) : nullptr;
+    const bool clear = pl.inclusive && !pl.lone_w && pace;   // (the prefix launch clears the counters in passing)
     if (pl.need_states_w) {
         // dM_t = Q_t^T dO_t per walk, then its suffix combine in place
         e = run_states(g, dtype, Q, dO, dR, 1, st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     }
     if (!pl.lone_w) {
-        e = launch_state_prefix(g, dR, dR, 1, pl.inclusive ? 1 : 0, 0, st);
+        e = launch_state_prefix(g, dR, dR, 1, pl.inclusive ? 1 : 0, 0, clear ? pace : nullptr, (unsigned)(g.T_s * g.G), st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     }
-    if (pl.fast) {
-        unsigned* pace = dR ? reinterpret_cast<unsigned*>(reinterpret_cast<char*>(dR) + states_bytes(g)) : nullptr;
-        return from_hip(launch_attn_bwd_mfma(g, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, pace, dQ, dK, dV, st));
-    }
+    if (pl.fast)
+        return from_hip(launch_attn_bwd_mfma(g, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, pace, clear ? 0 : 1, dQ, dK, dV, st));
     const Geom gp = regroup(g, cu_host, pick_planes_slots(g, cu_host, 3));
     return from_hip(launch_attn_bwd_planes(gp, dtype, Q, K, V, dO, P, dR, dQ, dK, dV, st));
 }
@@ -422,7 +492,7 @@ int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_
         *slots_per_walk = pick_planes_slots(g, desc->cu_seqlens_host, backward ? 3 : 1);
         return LASP2_OK;
     }
-    *slots_per_walk = backward ? pick_bwd_walk_slots(g, desc->cu_seqlens_host, cu_count() / (g.decay ? 3 : 2))
+    *slots_per_walk = backward ? pick_bwd_walks(g, desc->cu_seqlens_host, cu_count() / (g.decay ? 3 : 2)).ws
                                : pick_walk_slots(g, desc->cu_seqlens_host, cu_count(), kWalkTargetFwd);
     return LASP2_OK;
 }
@@ -461,7 +531,7 @@ int lasp2_state_prefix(const lasp2_desc_t* desc, const float* M, float* P, int r
     if (empty) return LASP2_OK;
     rc = check_ptrs({M, P});
     if (rc != LASP2_OK) return rc;
-    return from_hip(launch_state_prefix(g, M, P, reverse ? 1 : 0, 0, 0, (hipStream_t)stream));
+    return from_hip(launch_state_prefix(g, M, P, reverse ? 1 : 0, 0, 0, nullptr, 0, (hipStream_t)stream));
 }
 
 int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,
@@ -498,23 +568,24 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     hipStream_t st = (hipStream_t)stream;
     const int32_t* cu = desc->cu_seqlens_host;
     const bool fast = mfma_path_supported(g, desc->dtype);
-    const Geom gw = fast ? regroup(g, cu, pick_forward_walk_slots(g, cu))
-                         : regroup(g, cu, pick_planes_slots(g, cu, 1));
+    const WalkPlan wp = fast ? pick_forward_walks(g, cu) : WalkPlan{pick_planes_slots(g, cu, 1), false};
+    const Geom gw = regroup(g, cu, wp.ws);
     hipError_t e;
+    if (wp.direct) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, P, O, st));
     if (walk_emits(gw, desc->dtype)) {
         // The attention walks write the states of the slots inside them, so states and prefix are
         // needed where a walk starts only, and not at all where every document is one walk.
         if (!gw.lone_slots) {
             e = launch_states_mfma(gw, K, V, P, 0, 1, st);
             if (e != hipSuccess) return LASP2_ERR_LAUNCH;
-            e = launch_state_prefix(gw, P, P, 0, 0, 1, st);
+            e = launch_state_prefix(gw, P, P, 0, 0, 1, nullptr, 0, st);
             if (e != hipSuccess) return LASP2_ERR_LAUNCH;
         }
         return from_hip(launch_attn_fwd_emit_mfma(gw, Q, K, V, P, O, st));
     }
     e = run_states(g, desc->dtype, K, V, P, 0, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
-    e = launch_state_prefix(g, P, P, 0, 0, 0, st);
+    e = launch_state_prefix(g, P, P, 0, 0, 0, nullptr, 0, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     if (fast) return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
     return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, P, O, st));

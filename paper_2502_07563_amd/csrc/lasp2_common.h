@@ -55,10 +55,11 @@ __device__ __forceinline__ float decay_log2(const Geom& g, int grp)
 }
 
 // Token range [tok0, tok0+len) of slot (walk) s, ps: the index, within the group, of the
-// caller's slot that starts at tok0, and last: whether the slot (walk) is the last of its document.  Unpacked: direct.  Packed: from the last host-made mark at
+// caller's slot that starts at tok0, and the document's tokens [doc0, doc1).  Unpacked: direct.  Packed: from the last host-made mark at
 // or before s, then document by document (at most doc_stride of them; uniform scalar loads).
 // Document lengths and L are below 2^31, so the slot counts are 32-bit divisions.
-__device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len, int& ps, bool& last)
+__device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len, int& ps, int& doc0,
+                                           int& doc1)
 {
     if (g.n_seqs == 0) {
         int64_t a = (int64_t)s * g.L;
@@ -67,7 +68,8 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
         tok0 = (int)a;
         len = (int)(b - a);
         ps = s * g.wslots;
-        last = s + 1 == g.T_s;
+        doc0 = 0;
+        doc1 = g.N;
         return;
     }
     int j = 0;
@@ -79,7 +81,8 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
     tok0 = 0;
     len = 0;
     ps = 0;
-    last = true;
+    doc0 = 0;
+    doc1 = 0;
     for (int k = j * g.doc_stride; k < g.n_seqs; ++k) {
         const int a = g.cu[k], b = g.cu[k + 1];
         const int ns = (int)(((uint32_t)(b - a) + (L - 1u)) / L);
@@ -89,7 +92,8 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
             tok0 = (int)t0;
             len = (int)(t1 - t0);
             ps = pbase + (s - base) * g.wslots;
-            last = s + 1 == base + ns;
+            doc0 = a;
+            doc1 = b;
             return;
         }
         base += ns;
@@ -104,8 +108,8 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
 
 __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len, int& ps)
 {
-    bool last;
-    slot_range(g, s, tok0, len, ps, last);
+    int doc0, doc1;
+    slot_range(g, s, tok0, len, ps, doc0, doc1);
 }
 
 __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len)
@@ -173,8 +177,9 @@ hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const
 // inclusive = 0: P[s] excludes M[s] (the public entry point); 1: P[s] includes it.
 // user_slots: the states of g's walks lie in arrays with one entry per slot of the caller's, each walk's
 // where its first slot is; otherwise the arrays have one entry per walk.
+// clear: NULL, or nclear counters set to zero.
 hipError_t launch_state_prefix(const Geom& g, const float* M, float* P, int reverse, int inclusive,
-                               int user_slots, hipStream_t st);
+                               int user_slots, unsigned* clear, unsigned nclear, hipStream_t st);
 
 // S[s] = sum of M over the slots of s's document; S may alias M.
 hipError_t launch_state_total(const Geom& g, const float* M, float* S, hipStream_t st);
@@ -193,17 +198,25 @@ hipError_t launch_attn_fwd_mfma(const Geom& g, const void* Q, const void* K, con
                                 const float* P, void* O, hipStream_t st);
 // The same, and writes the prefix state of every slot of the caller's to P: a walk reads the first of its
 // slots there (nothing where every document is a single walk) and fills in the rest as it passes them.
-// g: walks of more than 128 tokens, slots of a multiple of 64 (walk_emits).
+// g: walks of several slots and more than 128 tokens, or of a whole document each; slots of a multiple of 64 (walk_emits).
 bool walk_emits(const Geom& g, int dtype);
 hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K, const void* V,
                                      float* P, void* O, hipStream_t st);
+// The whole forward in one launch: every walk adds up the state it starts from itself, from the rows of its document
+// before it.  g as above, or one slot per walk; no decay.
+hipError_t launch_attn_fwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V,
+                                       float* P, void* O, hipStream_t st);
+// The whole backward in one launch, likewise: suffix states from the rows up to the document's end, which also go to
+// dR (one per walk).  No decay.
+hipError_t launch_attn_bwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V, const void* dO,
+                                       const float* P, float* dR, void* dQ, void* dK, void* dV, hipStream_t st);
 // dQ, dV, dK in one launch.  P: exclusive prefix states of K^T V (from the forward);
 // dR: INCLUSIVE suffix states of Q^T dO (slot s holds the sum over slots >= s of its document);
 // with decay: the EXCLUSIVE decayed suffix of the start-anchored states.
 // pace: NULL, or G * T_s counters of scratch (see pace_bytes) through which the workgroups that
-// share a slot's reads keep in step; the launch clears them itself.
+// share a slot's reads keep in step; the launch clears them itself unless pace_clear = 0 (they are zero already).
 hipError_t launch_attn_bwd_mfma(const Geom& g, const void* Q, const void* K, const void* V,
-                                const void* dO, const float* P, const float* dR, unsigned* pace, void* dQ,
+                                const void* dO, const float* P, const float* dR, unsigned* pace, int pace_clear, void* dQ,
                                 void* dK, void* dV, hipStream_t st);
 
 // Row-times-state products of the unmasked path, up to three in one launch:

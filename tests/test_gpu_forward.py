@@ -1,4 +1,6 @@
-"""lasp2_forward: O and every entry of P against the definition in 64 bits and against the three calls it stands for.
+"""lasp2_forward: O and every entry of P against the definition in 64 bits and against the three calls it stands for; and
+the gradients.  Short sequences are one launch each way, whose walks gather the states they start from (the first
+cases); one head or two of a long one gets its states from the states kernel (the last cases).
 Walks of several slots write the states inside them in passing: slot lengths of one and of an odd number of 64-token
 blocks, walks whose last slot, last block or last row is the sequence's, documents of one walk and of several."""
 import numpy as np
@@ -11,7 +13,8 @@ CASES = [  # C, L, walk slots (0: the library's choice), lengths of the document
     (64, 0, 4, [1500]), (64, 0, 3, [64 * 9 + 1]), (64, 0, 5, [64 * 10]), (64, 0, 8, [449]), (192, 0, 2, [1000]),
     (128, 0, 2, [1025]), (128, 0, 16, [1931]), (256, 0, 2, [1536]), (256, 512, 2, [2047]), (64, 320, 3, [2000]),
     (64, 0, 4, [1, 64, 65, 700, 256, 257, 320]), (256, 0, 4, [3000, 5, 1024, 1025]), (100, 0, 3, [1000]),
-    (128, 0, 1, [700]), (64, 0, 0, [100, 4000]), (256, 0, 0, [1531]),
+    (128, 0, 1, [700]), (64, 0, 0, [100, 4000]), (256, 0, 0, [1531]), (256, 0, 0, [63]), (64, 0, 0, [257]),
+    (64, 0, 0, [9001]), (256, 0, 0, [16384]), (128, 384, 5, [12000]), (64, 0, 7, [9999]), (64, 0, 0, [13000, 1, 129, 64]),
 ]
 
 
@@ -22,9 +25,9 @@ def test_forward_in_one_call(monkeypatch, C, L, walk, docs, decay):
     if walk:
         monkeypatch.setenv("LASP2_WALK_SLOTS", str(walk))
     cu = np.concatenate([[0], np.cumsum(docs)]).astype(np.int32)
-    H, N, d = 3, int(cu[-1]), 128
-    B = 2 if len(docs) == 1 else 1
-    lam = np.array([1 - 2.0 ** -5, 0.9, 1.0], np.float32) if decay else None
+    N, d = int(cu[-1]), 128
+    B, H = (2 if len(docs) == 1 else 1, 3) if N < 5000 else (1, 2)
+    lam = np.array([1 - 2.0 ** -5, 0.9, 1.0], np.float32)[:H] if decay else None
     p = bd.Problem(B, H, N, d, C, L, "bf16", cu if len(docs) > 1 else None, decay=lam)
     gen = torch.Generator(device="cuda").manual_seed(N + C)
     Q, K, V = (torch.randn(B, H, N, d, generator=gen, device="cuda").mul_(d ** -0.5).to(torch.bfloat16) for _ in range(3))
@@ -46,11 +49,33 @@ def test_forward_in_one_call(monkeypatch, C, L, walk, docs, decay):
             at += 1
     assert at == P.shape[2]
     size = want.norm(dim=(3, 4)).clamp_min(1e-30)
-    # fp32 sums over at most 4000 tokens; with decay every token's weighted row is rounded to bf16 (2^-9 of it)
-    tol = 2.0 ** -8 if decay else 4000 * 2.0 ** -24
+    # fp32 sums over at most N tokens; with decay every token's weighted row is rounded to bf16 (2^-9 of it)
+    tol = 2.0 ** -8 if decay else max(N, 4000) * 2.0 ** -24
     for got in (P, P3):
         err = (got.double() - want).norm(dim=(3, 4))
         assert bool((err <= tol * size).all()), (err / size).max().item()
     diff = (O.float() - O3.float()).norm(dim=3)
     # the same products; states that differ in rounding order only: a rounding of O, the scores and the snapshot each
     assert bool((diff <= 3 * 2.0 ** -8 * O3.float().norm(dim=3) + 1e-6).all())
+
+    dO = torch.randn(B, H, N, d, generator=gen, device="cuda").mul_(d ** -0.5).to(torch.bfloat16)
+    grads = bd.backward(p, Q, K, V, dO, P)[:3]
+    tr = lambda x: x.transpose(-1, -2).contiguous()
+    for a, b in zip(cu[:-1], cu[1:]):
+        for g in range(B * H):
+            q, k, v, w = (x.reshape(B * H, N, d)[g, a:b].double() for x in (Q, K, V, dO))
+            i = torch.arange(b - a, device="cuda")
+            m = torch.tril(lamt[g % H].item() ** (i[:, None] - i[None, :]).clamp(min=0).double())
+            s, t = m * (q @ tr(k)), m * (w @ tr(v))
+            # what a result's terms add up to in quadrature if every score has the size of its own terms: a lone row whose
+            # score happens to be small keeps the rounding of the products it is the sum of
+            size = lambda x, y: (m * (x.norm(dim=1)[:, None] * y.norm(dim=1)[None, :]) / d ** 0.5) ** 2
+            ss, ts = size(q, k), size(w, v)
+            refs = (("O", O, s @ v, ss @ v ** 2), ("dQ", grads[0], t @ k, ts @ k ** 2),
+                    ("dK", grads[1], tr(t) @ q, tr(ts) @ q ** 2), ("dV", grads[2], tr(s) @ w, tr(ss) @ w ** 2))
+            for name, got, ref, terms in refs:
+                diff = (got.reshape(B * H, N, d)[g, a:b].double() - ref)
+                # operands, scores, snapshot and result each rounded to bf16: per 64 rows at most their sum, 2^-9 each
+                for r in range(0, b - a, 64):
+                    err, by = diff[r:r + 64].norm().item(), terms[r:r + 64].sum().sqrt().item()
+                    assert err <= 5 * 2.0 ** -9 * by, (name, g, a + r, err / by)

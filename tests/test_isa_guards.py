@@ -101,7 +101,9 @@ def test_no_compiler_placed_vmcnt_wait_in_the_walk(isa):
 # (two halves x two directions), and the backward's launch for long slots (four copies of the
 # anti-causal pair's walk: dV / dK rows x early / late row blocks, plus the causal walk's two halves)
 SKEW = (("attn_skew_mfma_kernelILb0E", 4), ("attn_skew_mfma_kernelILb1E", 4), ("attn_bwd_pair_mfma_kernel", 6),
-        ("attn_fwd_emit_mfma_kernelILb0E", 2), ("attn_fwd_emit_mfma_kernelILb1E", 2))
+        ("attn_fwd_emit_mfma_kernelILb0E", 2), ("attn_fwd_emit_mfma_kernelILb1E", 2),
+        # one loop more: the rows gathered before the walk
+        ("attn_fwd_direct_mfma_kernel", 3), ("attn_bwd_direct_mfma_kernel", 7))
 
 
 def _skew_blocks(lines, inst):
@@ -173,6 +175,8 @@ def test_skew_kernel_leaves_the_rows_in_flight_alone(isa, inst, ncopies):
             elif t and not t.startswith(";") and not t.startswith("."):
                 code.append((t, in_asm))
         loads = [i for i, (t, a) in enumerate(code) if a and t.startswith("global_load_dwordx4")]
+        if "direct" in inst and not loads:
+            continue                      # the gathering loop fetches no rows
         assert len(loads) == 8, (h, len(loads))
         dest = set().union(*(_regs(code[i][0].split(",")[0]) for i in loads))
         assert len(dest) == 32, (h, len(dest))
@@ -188,7 +192,7 @@ def test_skew_kernel_leaves_the_rows_in_flight_alone(isa, inst, ncopies):
             for i in r:
                 assert not (_regs(code[i][0]) & dest), (h, code[i][0])
         checked += 1
-    assert checked == ncopies
+    assert checked == ncopies - ("direct" in inst)
     # requests before the loops (the first half's walks): nothing touches their registers until the wait
     in_asm, pending = False, None
     for h, ins in blocks:
