@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
     const int e = (blockIdx.x * kThreads + threadIdx.x) * 4;
     if (e >= dd) return;
     const int stride = user_slots ? g.wslots : 1;   // array entries from one walk to the next inside a document
-    const int64_t Lp = user_slots ? g.L / g.wslots : g.L;   // tokens per array entry
+    const uint32_t L = (uint32_t)min(g.L, (int64_t)INT32_MAX), Lp = user_slots ? L / (uint32_t)g.wslots : L;   // tokens per walk, array entry
     const int entries = user_slots ? g.P_Ts : g.T_s;
     const size_t base = (size_t)blockIdx.y * (size_t)entries * dd + e;
     // the documents of one mark (documents are independent of each other)
@@ -45,8 +45,8 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
     int first = user_slots ? g.doc_pmark[blockIdx.z] : g.doc_mark[blockIdx.z];   // entries before the document
     for (int k = k0; k < k1; ++k) {
         const int dlen = g.n_seqs ? (g.cu[k + 1] - g.cu[k]) : g.N;
-        const int ns = (int)(((int64_t)dlen + g.L - 1) / g.L);
-        const int ne = (int)(((int64_t)dlen + Lp - 1) / Lp);
+        const int ns = g.n_seqs ? (int)(((uint32_t)dlen + (L - 1u)) / L) : g.T_s;
+        const int ne = g.n_seqs ? (int)(((uint32_t)dlen + (Lp - 1u)) / Lp) : 0;
         int s = first + (reverse ? (ns - 1) * stride : 0);
         first += ne;
         const int nm = inclusive ? ns : ns - 1;   // states that enter a result

@@ -101,11 +101,10 @@ __device__ __forceinline__ u32x4 scale_bf16x8(u32x4 x, float w)
 constexpr int ST_NW = 8, ST_NT = ST_NW * 64, ST_TPW = 16 / ST_NW, ST_NST = 5;
 constexpr int ST_KB = 32, ST_STAGE = ST_KB * ROWB;   // tokens and bytes (per tensor) of a stage
 
-template <bool DECAY>
-__global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* __restrict__ X,
-                                                            const char* __restrict__ Y,
-                                                            float* __restrict__ M, int anchor_start,
-                                                            int per_wg, int for_prefix)
+// for_prefix: see launch_states_mfma (a kernel of its own: its registers and tests cost the plain one 5 %).
+template <bool DECAY, bool for_prefix>
+__device__ __forceinline__ void states_body(const Geom& g, const char* __restrict__ X, const char* __restrict__ Y,
+                                            float* __restrict__ M, int anchor_start, int per_wg)
 {
     constexpr int DPS = 2;   // loads per wave per stage: one instruction (four rows) per tensor
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -125,8 +124,8 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
         Unit x;
         x.u = u; x.len = 0; x.nblk = 0; x.row0 = 0; x.m = 0;
         if (u < nunits) {
-            int tok0, ps, doc0, doc1;
-            slot_range(g, u % g.T_s, tok0, x.len, ps, doc0, doc1);
+            int tok0, ps, doc0, doc1, slot0, slot1;
+            slot_range<false>(g, u % g.T_s, tok0, x.len, ps, doc0, doc1, slot0, slot1);
             if (for_prefix && tok0 + x.len == doc1) x.len = 0;   // the document's last: no blocks, no state
             x.nblk = (x.len + ST_KB - 1) / ST_KB;
             x.row0 = ((size_t)(u / g.T_s) * g.N + tok0) * ROWB;
@@ -223,6 +222,20 @@ __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* 
         }
         older_than_stores = inflight;
     }
+}
+
+template <bool DECAY>
+__global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* __restrict__ X, const char* __restrict__ Y,
+                                                            float* __restrict__ M, int anchor_start, int per_wg)
+{
+    states_body<DECAY, false>(g, X, Y, M, anchor_start, per_wg);
+}
+
+template <bool DECAY>
+__global__ __launch_bounds__(ST_NT) void states_of_walks_kernel(Geom g, const char* __restrict__ X, const char* __restrict__ Y,
+                                                                float* __restrict__ M, int per_wg)
+{
+    states_body<DECAY, true>(g, X, Y, M, 0, per_wg);
 }
 
 // =====================================================================================
@@ -797,7 +810,7 @@ __device__ __forceinline__ uint32_t wait_vmcnt_token_le(int n)
 template <bool HC1, bool ANTI, bool DECAY, bool EMIT = false>
 __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, char* smem, int tid, int w,
                                           int rb, int grp, int s, int tok0, int len, const float* wstate,
-                                          int ps = 0, bool gathered = false)
+                                          int ps = 0, bool gathered = false, bool emit_first = true)
 {
     constexpr int C = 256, NW = 8, TPW = 2, BPC = 4, DPS = 4, NOP = 4;
     // With decay the anti-causal problems walk the slot backwards from the exclusive suffix (see
@@ -1170,7 +1183,7 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
 
     // EMIT: blocks per slot of the caller's, where the next of them starts, and its entry in the state array
     const int eblk = EMIT ? (int)(g.L / g.wslots) / KB : 0;
-    int enext = 0;
+    int enext = EMIT && pr.emit && emit_first ? 0 : INT32_MAX;
     float* eptr = EMIT ? pr.emit + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) : nullptr;
     // called with the running state at the start of block bi
     auto emit = [&](int bi) __attribute__((always_inline)) {
@@ -1765,13 +1778,14 @@ __global__ __launch_bounds__(512) void attn_bwd_pair_mfma_kernel(Geom g, AttnPro
 
 // ---- short sequences: forward and backward in one launch each ----
 // The state a walk starts from, sign * X^T Y over `ntok` rows from byte row0 on, left in LDS for take_gathered (and, without
-// the sign, in copy [D][D] if that is not NULL).  Every workgroup streams the rows anew, so this is for sequences so short that the
+// the sign, in copy [D][D] if that is not NULL).  base [D][D], if not NULL, is added to the sum.  Every workgroup streams the rows anew, so this is for sequences so short that the
 // launches it saves (states, prefix, counters: 5 to 8 us each with the gap before it) cost more.
 // Eight waves: four quadrants of 2 x 2 tiles, each by two waves that take the halves of a 64-row stage (an
 // operand is read from LDS once per two products; the walks' own update, one row of tiles per wave, reads three per
 // two); a ring of four stages, three on their way.  The halves are added through LDS at the end.
 __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_t row0, int ntok, float sign,
-                                             float* copy, char* smem, int tid, int w)
+                                             float* copy, const float* base, bool base_transposed, char* smem, int tid,
+                                             int w)
 {
     constexpr int NST = 4, DPS = 4;
     int lane;   // (opaque: nothing derived from it is kept for the walk)
@@ -1853,10 +1867,15 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
             f32x4 p = in[(4 * b + q) * 64];
 #pragma unroll
             for (int e = 0; e < 4; ++e) p[e] += hf ? tot[1][b][4 * q + e] : tot[0][b][4 * q + e];
+            if (base) {
+                const int r = 32 * (w >> 1) + 8 * q + 4 * h, c = 64 * qb + 32 * b + (lane & 31);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) p[e] += base_transposed ? base[c * D + r + e] : base[(r + e) * D + c];
+            }
             if (copy) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    __builtin_nontemporal_store(p[e], copy + (32 * (w >> 1) + 8 * q + 4 * h + e) * D + 64 * qb + 32 * b + (lane & 31));
+                    copy[(32 * (w >> 1) + 8 * q + 4 * h + e) * D + 64 * qb + 32 * b + (lane & 31)] = p[e];
             }
             M[(4 * b + q) * 64] = sign * p;
         }
@@ -1871,16 +1890,19 @@ __global__ __launch_bounds__(512) void attn_fwd_direct_mfma_kernel(Geom g, AttnP
     // (the walks with the most rows before them first)
     const unsigned unit = gridDim.x - 1 - blockIdx.x;
     const int s = (int)(unit / (unsigned)g.G), grp = (int)(unit % (unsigned)g.G);
-    int tok0, len, ps, doc0, doc1;
-    slot_range(g, s, tok0, len, ps, doc0, doc1);
+    int tok0, len, ps, doc0, doc1, slot0, slot1;
+    slot_range<true>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
     if (len <= 0) return;
-    gather_state(pr.Bk, pr.Cv, ((size_t)grp * g.N + doc0) * ROWB, tok0 - doc0, 1.f, nullptr, smem, tid, w);
+    const int from = pr.state ? slot0 : doc0;
+    const float* base = pr.state ? pr.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) : nullptr;
+    gather_state(pr.Bk, pr.Cv, ((size_t)grp * g.N + from) * ROWB, tok0 - from, 1.f, nullptr, base, false, smem, tid, w);
+    const bool first = !g.W || tok0 == slot0;
     const int rb = w < 4 ? w : 11 - w;   // waves w and w+4 share a SIMD: row blocks s and 7-s
-    if (rb < 4) skew_walk<false, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true);
-    else skew_walk<true, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true);
+    if (rb < 4) skew_walk<false, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
+    else skew_walk<true, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
 }
 
-__global__ __launch_bounds__(512) void attn_bwd_direct_mfma_kernel(Geom g, AttnProblem pq, PairProblem pp)
+__global__ __launch_bounds__(512) void attn_bwd_direct_mfma_kernel(Geom g, AttnProblem pq, PairProblem pp, int from_dR)
 {
     extern __shared__ __attribute__((aligned(256))) char smem[];
     const int tid = threadIdx.x;
@@ -1890,21 +1912,26 @@ __global__ __launch_bounds__(512) void attn_bwd_direct_mfma_kernel(Geom g, AttnP
     const bool pair = blockIdx.x < units;
     const unsigned unit = pair ? blockIdx.x : blockIdx.x - units;
     const int s = (int)(unit / (unsigned)g.G), grp = (int)(unit % (unsigned)g.G);
-    int tok0, len, ps, doc0, doc1;
-    slot_range(g, s, tok0, len, ps, doc0, doc1);
+    int tok0, len, ps, doc0, doc1, slot0, slot1;
+    slot_range<true>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
     if (len <= 0) return;
     if (pair) {
-        gather_state(pp.Q, pp.dO, ((size_t)grp * g.N + tok0) * ROWB, doc1 - tok0, -1.f,
-                     pp.dR + ((size_t)grp * g.T_s + s) * (size_t)(D * D), smem, tid, w);
+        const int to = from_dR ? slot1 : doc1;
+        const float* next = from_dR && slot1 < doc1 ? pp.dR + ((size_t)grp * g.P_Ts + ps + 1) * (size_t)(D * D) : nullptr;
+        float* copy = from_dR || g.W || !pp.dR ? nullptr : pp.dR + ((size_t)grp * g.T_s + s) * (size_t)(D * D);
+        gather_state(pp.Q, pp.dO, ((size_t)grp * g.N + tok0) * ROWB, to - tok0, -1.f, copy, next, false, smem, tid, w);
         if (w < 2) pair_walk<false, false, true>(g, pp, smem, tid, w, w, grp, s, tok0, len);
         else if (w < 4) pair_walk<false, true, true>(g, pp, smem, tid, w, w, grp, s, tok0, len);
         else if (w < 6) pair_walk<true, true, true>(g, pp, smem, tid, w, 7 - w, grp, s, tok0, len);
         else pair_walk<true, false, true>(g, pp, smem, tid, w, 7 - w, grp, s, tok0, len);
     } else {
+        // (the prefix state is V^T K: the caller's K^T V transposed)
+        const float* base = pq.state ? pq.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) : nullptr;
+        const int rows = g.W ? tok0 - slot0 : 0;
+        gather_state(pq.Bk, pq.Cv, ((size_t)grp * g.N + tok0 - rows) * ROWB, rows, 1.f, nullptr, base, true, smem, tid, w);
         const int rb = w < 4 ? w : 11 - w;
-        const float* wstate = pq.state ? walk_state(g, pq, grp, s, ps) : nullptr;
-        if (rb < 4) skew_walk<false, false, false>(g, pq, smem, tid, w, rb, grp, s, tok0, len, wstate);
-        else skew_walk<true, false, false>(g, pq, smem, tid, w, rb, grp, s, tok0, len, wstate);
+        if (rb < 4) skew_walk<false, false, false>(g, pq, smem, tid, w, rb, grp, s, tok0, len, nullptr, 0, true);
+        else skew_walk<true, false, false>(g, pq, smem, tid, w, rb, grp, s, tok0, len, nullptr, 0, true);
     }
 }
 
@@ -2387,10 +2414,6 @@ hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float
                               int for_prefix, hipStream_t st)
 {
     constexpr int smem = 2 * ST_NST * ST_STAGE;   // 80 KiB: two workgroups per CU
-    auto kern = g.decay ? states_mfma_kernel<true> : states_mfma_kernel<false>;
-    hipError_t e = g.decay ? allow_dynamic_lds<states_mfma_kernel<true>>(smem)
-                           : allow_dynamic_lds<states_mfma_kernel<false>>(smem);
-    if (e != hipSuccess) return e;
     // two workgroups per CU, each walking through its share of the slots
     const int cus = cu_count();
     const long long nunits = (long long)g.T_s * g.G;
@@ -2399,8 +2422,18 @@ hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float
     // (documents of different lengths: shares of about 2 048 tokens, dealt out as workgroups end)
     if (g.n_seqs) per_wg = (int)std::min<long long>(per_wg, std::max(1LL, 2048LL * g.T_s / g.N));
     dim3 grid((unsigned)((nunits + per_wg - 1) / per_wg)), block(ST_NT);
-    hipLaunchKernelGGL(kern, grid, block, smem, st, g, static_cast<const char*>(K),
-                       static_cast<const char*>(V), M, anchor_start, per_wg, for_prefix);
+    const char *k = static_cast<const char*>(K), *v = static_cast<const char*>(V);
+    hipError_t e;
+    if (for_prefix) {
+        e = g.decay ? allow_dynamic_lds<states_of_walks_kernel<true>>(smem) : allow_dynamic_lds<states_of_walks_kernel<false>>(smem);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((g.decay ? states_of_walks_kernel<true> : states_of_walks_kernel<false>), grid, block, smem, st, g, k, v, M, per_wg);
+    } else {
+        e = g.decay ? allow_dynamic_lds<states_mfma_kernel<true>>(smem) : allow_dynamic_lds<states_mfma_kernel<false>>(smem);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((g.decay ? states_mfma_kernel<true> : states_mfma_kernel<false>), grid, block, smem, st, g, k, v, M, anchor_start,
+                           per_wg);
+    }
     return hipGetLastError();
 }
 
@@ -2457,11 +2490,11 @@ hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K
 }
 
 hipError_t launch_attn_fwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V,
-                                       float* P, void* O, hipStream_t st)
+                                       const float* state, float* emit, void* O, hipStream_t st)
 {
     constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
-    AttnProblem p = make_problem(Q, K, V, nullptr, 1, O, 0, 0);
-    p.emit = P;
+    AttnProblem p = make_problem(Q, K, V, state, 1, O, 0, 0);
+    p.emit = emit;
     hipError_t e = allow_dynamic_lds<attn_fwd_direct_mfma_kernel>(smem);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(attn_fwd_direct_mfma_kernel, dim3((unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, p);
@@ -2469,7 +2502,7 @@ hipError_t launch_attn_fwd_direct_mfma(const Geom& g, const void* Q, const void*
 }
 
 hipError_t launch_attn_bwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V, const void* dO,
-                                       const float* P, float* dR, void* dQ, void* dK, void* dV, hipStream_t st)
+                                       const float* P, float* dR, int from_dR, void* dQ, void* dK, void* dV, hipStream_t st)
 {
     constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
     const AttnProblem pq = make_problem(dO, V, K, P, 1, dQ, 1, 0);
@@ -2477,7 +2510,8 @@ hipError_t launch_attn_bwd_direct_mfma(const Geom& g, const void* Q, const void*
                             static_cast<const char*>(V), dR, static_cast<char*>(dV), static_cast<char*>(dK), nullptr};
     hipError_t e = allow_dynamic_lds<attn_bwd_direct_mfma_kernel>(smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_bwd_direct_mfma_kernel, dim3(2u * (unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, pq, pp);
+    hipLaunchKernelGGL(attn_bwd_direct_mfma_kernel, dim3(2u * (unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, pq, pp,
+                       from_dR);
     return hipGetLastError();
 }
 

@@ -88,6 +88,8 @@ int make_geom(const lasp2_desc_t* desc, Geom* g, bool* empty)
     g->cu = desc->cu_seqlens_dev;
     // marks for slot_range: the number of slots before every doc_stride-th document
     g->wslots = 1;
+    g->W = 0;
+    g->sub = 1;
     g->P_Ts = g->T_s;
     g->doc_stride = 1;
     for (int j = 0; j < kDocMarks; ++j) g->doc_mark[j] = j == 0 ? 0 : INT32_MAX;
@@ -141,6 +143,29 @@ Geom regroup(const Geom& g, const int32_t* cu_host, int ws)
     }
     w.T_s = (int32_t)walks;
     w.lone_slots = walks == g.n_seqs ? 1 : 0;
+    return w;
+}
+
+// The geometry of walks of W tokens (a multiple of 64) inside the slots, which are longer than that.
+Geom regroup_short(const Geom& g, const int32_t* cu_host, int64_t W)
+{
+    Geom w = g;
+    w.W = (int32_t)W;
+    w.sub = (int32_t)((std::min<int64_t>(g.L, g.N) + W - 1) / W);
+    auto walks_of = [&](int64_t n) {
+        const int64_t full = (n + g.L - 1) / g.L - 1;
+        return full * w.sub + (n - full * g.L + W - 1) / W;
+    };
+    if (g.n_seqs == 0) {
+        w.T_s = (int32_t)walks_of(g.N);
+        return w;
+    }
+    int64_t walks = 0;
+    for (int k = 0; k < g.n_seqs; ++k) {
+        if (k % g.doc_stride == 0) w.doc_mark[k / g.doc_stride] = (int32_t)walks;
+        walks += walks_of(cu_host[k + 1] - cu_host[k]);
+    }
+    w.T_s = (int32_t)walks;
     return w;
 }
 
@@ -205,12 +230,12 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
 //   - A row of a walk takes 0.03 us forward (dQ 0.031, the pair of the backward 0.0376), starting a walk what 256 (180)
 //     rows do, a row that is gathered 0.0068 (16 heads, walks of 256, gathered | states first, us: 300 rows 15 | 22; 1 024
 //     20 | 24; 2 048 28 | 30; 3 000 37 | 31; 4 096 45 | 36; backward 20 | 27, 25 | 32, 34 | 37, 44 | 46, 58 | 50).
-//   - Memory: 5.2 TB/s, 8 where the tensors fit the 256 MB cache.  The one-launch backward reads three tensors more, as its two
-//     workgroups per walk don't keep in step (256 sequences of 2 000: 305 | 262).
-//   - Of two choices that memory bounds alike the one with less work (0.15 of the walks' time on top).  Documents of
+//   - Memory: 5.2 TB/s, 8 where the tensors fit the 256 MB cache.  The one-launch backward reads four tensors more, as its two
+//     workgroups per walk don't keep in step (256 sequences of 2 000: 305 | 262), large ones ten (64 of 43 174: 2420 | 2190).
+//   - Of two choices that memory bounds alike the one with less work (0.05 of the walks' time on top).  Documents of
 //     different lengths: the last to start is a long one, and takes 0.05 us per row beside the others (32 heads, 131 072 in
 //     40 documents, forward, walks of 2 048 1434 us, 4 096 1275, 8 192 1212, whole documents 2411).
-//   - States: read at 6 TB/s, and 11 us (15 backward) for two launches; documents of different lengths spread unevenly:
+//   - States: read at 6 TB/s, 0.0127 us per row of one slot, and 10 us for two launches; documents of different lengths spread unevenly:
 //     a third more.  (32 heads, 131 072 tokens in 40 documents, forward 1500 -> 1212 us direct in walks of 8 192; 16 heads,
 //     32 768 in 50 322 -> 187, backward 486 -> 341; 32 heads, 8 000 in 20 100 -> 72, 239 -> 155.)
 //   - Walks have at least 256 rows: shorter ones take the 128-row kernel and write no states in passing (16 heads x 3 000,
@@ -218,74 +243,111 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
 //   - One round ends at the pace of the slowest CU: 8 % more in the backward (16 heads, one round | two, us: 8 192 85 | 93;
 //     16 384 149 | 151; 32 768 281 | 271; 262 144 2058 | 1949), 3 % in the forward (65 536: 346 | 361; 262 144, 4 096-token
 //     slots: 1209 | 1153).
-struct WalkPlan { int ws; bool direct; };
+enum class Start {
+    states,   // states and prefix kernels first, a walk is `ws` slots
+    gather,   // the walks gather them, from or to the document's end; a walk is `ws` slots, or W > 0 tokens
+    both      // states and prefix per slot, and walks of W tokens gather from there
+};
+struct WalkPlan { int ws; int64_t W; Start start; };
 
-// What the walks of `ws` slots are, per group
+Geom regroup(const Geom& g, const int32_t* cu_host, const WalkPlan& p)
+{
+    return p.W ? regroup_short(g, cu_host, p.W) : regroup(g, cu_host, p.ws);
+}
+
+// What walks of W tokens are, per group; walks no longer than a slot don't cross its border
 struct WalkCount {
-    double walks = 0, longest = 0;     // how many; rows of the longest
-    double before = 0, after = 0;      // rows that lie before (from the start of, to the end of the document) each, summed
-    double farthest = 0;               // ... the largest single one of `before`
-    double inner = 0;                  // rows of walks that are not their document's last
+    double walks = 0, longest = 0;       // how many; rows of the longest
+    double before = 0, after = 0;        // rows that lie before (from the start of, to the end of the document) each, summed
+    double farthest = 0;                 // ... the largest single one of `before`
+    double before_in = 0, after_in = 0, farthest_in = 0;   // ... the same, as far as the slot's borders
+    double inner = 0, parts = 0;         // rows of slots (walks, if longer) that are not their document's last; how many there are
+    double longest_part = 0;
 };
 
-WalkCount count_walks(const Geom& g, const int32_t* cu_host, int64_t ws)
+WalkCount count_walks(const Geom& g, const int32_t* cu_host, int64_t W)
 {
     WalkCount c;
-    const int64_t W = ws * g.L;
-    const int nd = g.n_seqs ? g.n_seqs : 1;
-    for (int k = 0; k < nd; ++k) {
-        const int64_t n = g.n_seqs ? cu_host[k + 1] - cu_host[k] : g.N, m = (n + W - 1) / W;
-        c.walks += (double)m;
-        c.longest = std::max(c.longest, (double)std::min(n, W));
-        c.before += 0.5 * (double)W * (double)m * (double)(m - 1);
-        c.after += (double)n * (double)m - 0.5 * (double)W * (double)m * (double)(m - 1);
-        c.farthest = std::max(c.farthest, (double)(m - 1) * (double)W);
-        c.inner += (double)(m - 1) * (double)W;
+    const double w = (double)W, S = (double)std::max(W, g.L);   // slots, or walks of several
+    for (int k = 0; k < std::max(1, (int)g.n_seqs); ++k) {
+        const double n = g.n_seqs ? cu_host[k + 1] - cu_host[k] : g.N;
+        const double full = std::ceil(n / S) - 1.0, rest = n - full * S, mf = std::ceil(S / w), mr = std::ceil(rest / w);
+        const double bf = 0.5 * w * mf * (mf - 1.0), br = 0.5 * w * mr * (mr - 1.0), m = full * mf + mr;
+        const double before = 0.5 * full * (full - 1.0) * S * mf + full * bf + full * S * mr + br;
+        c.walks += m;
+        c.parts += full + 1.0;
+        c.longest_part = std::max(c.longest_part, std::min(n, S));
+        c.longest = std::max(c.longest, std::min(n, w));
+        c.before += before;
+        c.after += n * m - before;
+        c.before_in += full * bf + br;
+        c.after_in += full * (S * mf - bf) + rest * mr - br;
+        c.farthest = std::max(c.farthest, full * S + (mr - 1.0) * w);
+        c.farthest_in = std::max(c.farthest_in, (full > 0.0 ? mf - 1.0 : mr - 1.0) * w);
+        c.inner += full * S;
     }
     return c;
 }
 
-// `par`: walks that run at a time
-WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backward)
+// `par`: walks that run at a time.  may_states = false: the states are there already (lasp2_attn_fwd)
+WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backward, bool may_gather, bool may_states)
 {
     const int64_t longest = longest_sequence(g, cu_host), slots = (longest + g.L - 1) / g.L;
     const double G = g.G, N = g.N, cus = cu_count(), start = backward ? 180.0 : 256.0;
     const double row = backward ? 0.0376 : 0.03, gather = 0.0068;
-    const bool may_gather = !g.decay;
-    auto estimate = [&](int64_t ws, bool direct) {
-        const WalkCount c = count_walks(g, cu_host, ws);
+    auto estimate = [&](int64_t W, Start how) {
+        const WalkCount c = count_walks(g, cu_host, W);
         const double tensor = G * N * 256.0, states = G * N / (double)g.L * 65536.0;
         const double rate = (backward ? 7.0 : 4.0) * tensor < 2.56e8 ? 8e6 : 5.2e6;
-        const double memory = (backward ? 7.0 * tensor : 4.0 * tensor + states) / rate;
+        const double memory = (backward ? 7.0 * tensor : 4.0 * tensor + states) / rate * (!backward && c.walks * G <= par && W > 8192 ? 1.04 : 1.0);
         const double one = (c.longest + start) * row, rounds = std::ceil(c.walks * G / par);
         const double walk = g.n_seqs ? std::max(one, G * (N + start * c.walks) * row / par)
                                      : rounds * one * (rounds > 1.0 ? 1.0 : backward ? 1.08 : 1.03);
-        const double tail = 0.15 * walk + (g.n_seqs ? 0.6 * one : 0.0);
+        const double tail = 0.05 * walk + (g.n_seqs && rounds > 1.0 ? 0.6 * one : 0.0);
+        const double again = 256.0 * row * std::max(0.0, (g.n_seqs ? c.walks * G / par : rounds) - 1.0);   // gathering starts once more
+        const double cache = 2.0 * tensor < 2e8 ? 2e7 : 8e6, unsure = backward ? 1.05 : W < g.L ? 1.12 : 1.0;
         const double moved = g.n_seqs ? 4.0 * G * 65536.0 / 5.2e6 : 0.0;   // a walk's state: written, combined, read
+        const double uneven = g.n_seqs ? 1.33 : 1.0;
         if (!backward) {
-            if (direct)
-                return std::max({walk + G * c.before * gather / par, one + c.farthest * gather, memory + G * c.before * 512.0 / 2e7}) + tail;
-            if (c.inner == 0.0) return std::max(walk, memory) + tail;
-            return std::max(walk, memory) + tail + 11.0 + G * c.inner * 512.0 / 6e6 * (g.n_seqs ? 1.33 : 1.0) + moved * c.walks;
+            const double first = c.inner == 0.0 || !may_states ? 0.0 : 10.0 + G * c.inner * 512.0 / 6e6 * uneven + moved * c.parts;
+            if (how == Start::states) return std::max(walk, memory) + tail + first;
+            const bool in = how == Start::both;
+            const double rows = G * (in ? c.before_in : c.before);
+            return unsure * (std::max({walk + again + rows * gather / par, one + (in ? c.farthest_in : c.farthest) * gather,
+                                       memory + rows * 512.0 / cache}) + tail + (in ? first : 0.0));
         }
-        if (direct) {
-            const double all = G * (c.after * gather + (N + start * c.walks) * (row + 0.031)) / cus;
-            return std::max({longest * gather + one + 0.1 * all, 1.1 * all, 12.5 * tensor / rate}) + 0.15 * all;
-        }
-        return std::max(walk, memory) + tail + 15.0 + 2.0 * tensor / 6e6 * (g.n_seqs ? 1.33 : 1.0) + moved * c.walks;
+        const double first = 10.0 + std::max(2.0 * tensor / 6e6 * uneven, c.longest_part * 0.0127) + moved * c.parts;
+        if (how == Start::states) return std::max(walk, memory) + tail + first;
+        const bool in = how == Start::both;
+        const double far = in ? std::min((double)longest, (double)g.L) : (double)longest;
+        const double rows = G * ((in ? c.after_in : c.after) + (W < g.L ? c.before_in : 0.0));
+        const double all = (rows * gather + G * (N + start * c.walks) * (row + 0.031)) / cus;
+        const double passes = tensor < 2e8 ? 11.0 : 17.0;
+        return unsure * (std::max({1.5 * far * gather + 1.08 * one + 0.1 * all, 1.1 * all, passes * tensor / rate + rows * 512.0 / 1e7}) + 0.15 * all +
+                         (in ? first : 0.0));
     };
     const int forced = forced_walk_slots(g);
     const int64_t ws_max = std::min(slots, max_walk_slots(g)), ws_min = std::min((256 + g.L - 1) / g.L, ws_max);
-    WalkPlan best = {1, false};
+    WalkPlan best = {1, 0, Start::states};
     double cost = -1.0;
-    auto offer = [&](int64_t ws) {
-        for (int direct = 0; direct <= (may_gather ? 1 : 0); ++direct) {
-            const double e = estimate(ws, direct != 0);
-            if (cost < 0.0 || e < cost) { cost = e; best = {(int)ws, direct != 0}; }
-        }
+    auto take = [&](const WalkPlan& p) {
+        const double e = estimate(p.W ? p.W : p.ws * g.L, p.start);
+        if (cost < 0.0 || e < cost) { cost = e; best = p; }
     };
-    if (slots <= 1) {
-        best.direct = may_gather && (!backward || estimate(1, true) < estimate(1, false));   // (forward: nothing to gather)
+    const bool lone = slots <= 1;
+    auto offer = [&](int64_t ws) {
+        take({(int)ws, 0, Start::states});
+        if (may_gather && (may_states || backward)) take({(int)ws, 0, Start::gather});
+    };
+    // walks of about W tokens inside the slots
+    auto offer_short = [&](int64_t W) {
+        W = std::max<int64_t>(256, (W + 63) / 64 * 64);
+        if (!may_gather || forced || W >= std::min(g.L, longest)) return;
+        if (may_states || lone) take({1, W, Start::gather});
+        if (!lone) take({1, W, Start::both});
+    };
+    if (lone) {
+        offer(1);
     } else if (forced) {
         offer(forced);
     } else if (g.n_seqs) {
@@ -293,13 +355,17 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backwar
             offer(ws);
             if (ws >= ws_max) break;
         }
+    }
+    if (g.n_seqs) {
+        for (int64_t W = (std::min(g.L, longest) + 1) / 2; W >= 256; W /= 2) offer_short(W);
     } else {
         for (int k = 1; k <= 16; ++k) {
             const int64_t m = (int64_t)k * par / g.G;   // walks per sequence
             if (m < 1) continue;
-            const int64_t ws = std::min(ws_max, std::max(ws_min, (slots + m - 1) / m));
-            offer(ws);
-            if (ws == ws_min) break;
+            const int64_t ws = std::min(ws_max, std::max(ws_min, (slots + m - 1) / m)), W = (g.N + m - 1) / m;
+            if (!lone && !forced) offer(ws);
+            offer_short(W);
+            if (ws == ws_min && W <= 256) break;
         }
         if (cost < 0.0) offer(ws_max);
     }
@@ -308,15 +374,15 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backwar
 
 WalkPlan pick_bwd_walks(const Geom& g, const int32_t* cu_host, int par)
 {
-    if (g.G == 0) return {1, false};
-    return pick_walks(g, cu_host, std::max(1, par), true);
+    if (g.G == 0) return {1, 0, Start::states};
+    return pick_walks(g, cu_host, std::max(1, par), true, !g.decay, true);
 }
 
 // (slots of other lengths: no state of theirs stands between two blocks of a walk)
 WalkPlan pick_forward_walks(const Geom& g, const int32_t* cu_host)
 {
-    if (g.L % 64 == 0) return pick_walks(g, cu_host, cu_count(), false);
-    return {pick_walk_slots(g, cu_host, cu_count(), kWalkTargetFwd), false};
+    if (g.L % 64 == 0) return pick_walks(g, cu_host, cu_count(), false, !g.decay, true);
+    return {pick_walk_slots(g, cu_host, cu_count(), kWalkTargetFwd), 0, Start::states};
 }
 
 // Slots per walk of the split-plane kernels, `nprob` workgroups per walk.  They work on chunks of 128
@@ -375,7 +441,7 @@ struct BwdPlan {
     size_t need;
     bool lone_w;        // every document a single walk
     bool need_states_w;
-    bool direct;        // one launch, suffix states gathered by the walks themselves
+    Start start;        // what the walks start from (matrix-core kernels)
 };
 
 // `workspace`: address of the caller's workspace pointer, or NULL for an entry point that has none.
@@ -407,12 +473,12 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     // The kernels' own walks.  The backward's dM states live in the workspace only, so they are
     // built per walk, not per slot of the caller: fewer of them, never more bytes than `need`.
     pl->gw = g;
-    pl->direct = false;
+    pl->start = Start::states;
     if (pl->fast) {
         const int wgs = g.decay ? 3 : 2;   // workgroups per walk in the attention launch
         const WalkPlan wp = pick_bwd_walks(g, desc->cu_seqlens_host, cu_count() / wgs);
-        pl->gw = regroup(g, desc->cu_seqlens_host, wp.ws);
-        pl->direct = wp.direct;
+        pl->gw = regroup(g, desc->cu_seqlens_host, wp);
+        pl->start = wp.start;
     }
     pl->lone_w = pl->gw.lone_slots != 0;
     pl->need_states_w = !pl->lone_w || pl->inclusive;
@@ -425,7 +491,12 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const int32_t* cu_host, const voi
     const Geom& g = pl.gw;
     if (pl.lone_w) P = nullptr;
     hipError_t e = hipSuccess;
-    if (pl.direct) return from_hip(launch_attn_bwd_direct_mfma(g, Q, K, V, dO, P, dR, dQ, dK, dV, st));
+    if (pl.start == Start::gather) return from_hip(launch_attn_bwd_direct_mfma(g, Q, K, V, dO, P, dR, 0, dQ, dK, dV, st));
+    if (pl.start == Start::both) {   // suffix states per slot
+        if (run_states(pl.g, dtype, Q, dO, dR, 1, st) != hipSuccess) return LASP2_ERR_LAUNCH;
+        if (launch_state_prefix(pl.g, dR, dR, 1, 1, 0, nullptr, 0, st) != hipSuccess) return LASP2_ERR_LAUNCH;
+        return from_hip(launch_attn_bwd_direct_mfma(g, Q, K, V, dO, P, dR, 1, dQ, dK, dV, st));
+    }
     unsigned* pace = dR ? reinterpret_cast<unsigned*>(reinterpret_cast<char*>(dR) + states_bytes(g)) : nullptr;
     const bool clear = pl.inclusive && !pl.lone_w && pace;   // (the prefix launch clears the counters in passing)
     if (pl.need_states_w) {
@@ -548,6 +619,13 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
     if (rc != LASP2_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     if (mfma_path_supported(g, desc->dtype)) {
+        // long slots that leave CUs without work: walks of parts of them
+        if (g.L >= 512) {
+            const WalkPlan wp = pick_walks(g, desc->cu_seqlens_host, cu_count(), false, !g.decay, false);
+            if (wp.W)
+                return from_hip(launch_attn_fwd_direct_mfma(regroup_short(g, desc->cu_seqlens_host, wp.W), Q, K, V,
+                                                            g.lone_slots ? nullptr : P, nullptr, O, st));
+        }
         const Geom gw = regroup(g, desc->cu_seqlens_host, pick_walk_slots(g, desc->cu_seqlens_host, cu_count(), kWalkTargetFwd));
         return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
     }
@@ -568,10 +646,10 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     hipStream_t st = (hipStream_t)stream;
     const int32_t* cu = desc->cu_seqlens_host;
     const bool fast = mfma_path_supported(g, desc->dtype);
-    const WalkPlan wp = fast ? pick_forward_walks(g, cu) : WalkPlan{pick_planes_slots(g, cu, 1), false};
-    const Geom gw = regroup(g, cu, wp.ws);
+    const WalkPlan wp = fast ? pick_forward_walks(g, cu) : WalkPlan{pick_planes_slots(g, cu, 1), 0, Start::states};
+    const Geom gw = regroup(g, cu, wp);
     hipError_t e;
-    if (wp.direct) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, P, O, st));
+    if (wp.start == Start::gather) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, nullptr, P, O, st));
     if (walk_emits(gw, desc->dtype)) {
         // The attention walks write the states of the slots inside them, so states and prefix are
         // needed where a walk starts only, and not at all where every document is one walk.
@@ -587,6 +665,7 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     e = launch_state_prefix(g, P, P, 0, 0, 0, nullptr, 0, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
+    if (wp.start == Start::both) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, P, nullptr, O, st));
     if (fast) return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
     return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, P, O, st));
 }

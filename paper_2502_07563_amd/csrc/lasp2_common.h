@@ -38,6 +38,9 @@ struct Geom {
     int32_t wslots;
     int32_t P_Ts;
     int32_t doc_pmark[kDocMarks];   // the caller's slots before document j * doc_stride
+    // Walks shorter than a slot: W > 0 tokens (a multiple of 64; fewer at the slot's end), at most `sub` in a slot.  L is then
+    // the caller's slot length (wslots = 1), T_s and doc_mark count walks, P_Ts and doc_pmark slots.
+    int32_t W, sub;
     int32_t H;            // heads (group g uses decay[g % H])
     const float* decay;   // DEVICE pointer to H per-head decay factors; NULL = no decay
     int32_t decay_mfma;   // host decision: every factor is large enough for the MFMA decay kernels
@@ -55,21 +58,36 @@ __device__ __forceinline__ float decay_log2(const Geom& g, int grp)
 }
 
 // Token range [tok0, tok0+len) of slot (walk) s, ps: the index, within the group, of the
-// caller's slot that starts at tok0, and the document's tokens [doc0, doc1).  Unpacked: direct.  Packed: from the last host-made mark at
+// caller's slot that starts at tok0 (or holds it, if walks are shorter than slots), the document's tokens [doc0, doc1),
+// and the tokens [slot0, slot1) of slot ps, if walks are shorter than slots.  Unpacked: direct.  Packed: from the last host-made mark at
 // or before s, then document by document (at most doc_stride of them; uniform scalar loads).
 // Document lengths and L are below 2^31, so the slot counts are 32-bit divisions.
+// SHORT: the walks may be shorter than slots.
+template <bool SHORT>
 __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len, int& ps, int& doc0,
-                                           int& doc1)
+                                           int& doc1, int& slot0, int& slot1)
 {
+    // walk s of a document [a, b) whose slots before it number p, walks shorter than slots
+    auto inside = [&](int x, int a, int b, int p) {
+        const int slot = x / g.sub, j = x % g.sub;
+        ps = p + slot;
+        slot0 = a + (int)(slot * g.L);
+        slot1 = (int)min((int64_t)slot0 + g.L, (int64_t)b);
+        tok0 = slot0 + j * g.W;
+        len = min(g.W, slot1 - tok0);
+        doc0 = a;
+        doc1 = b;
+    };
     if (g.n_seqs == 0) {
+        if (SHORT && g.W) { inside(s, 0, g.N, 0); return; }
         int64_t a = (int64_t)s * g.L;
         int64_t b = a + g.L;
         if (b > g.N) b = g.N;
         tok0 = (int)a;
         len = (int)(b - a);
         ps = s * g.wslots;
-        doc0 = 0;
-        doc1 = g.N;
+        doc0 = slot0 = 0;
+        doc1 = slot1 = g.N;
         return;
     }
     int j = 0;
@@ -81,19 +99,27 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
     tok0 = 0;
     len = 0;
     ps = 0;
-    doc0 = 0;
-    doc1 = 0;
+    doc0 = slot0 = 0;
+    doc1 = slot1 = 0;
     for (int k = j * g.doc_stride; k < g.n_seqs; ++k) {
         const int a = g.cu[k], b = g.cu[k + 1];
-        const int ns = (int)(((uint32_t)(b - a) + (L - 1u)) / L);
+        int ns = (int)(((uint32_t)(b - a) + (L - 1u)) / L);
+        if (SHORT && g.W) {
+            const int slots = ns, rest = (b - a) - (int)((slots - 1) * (int64_t)L);
+            ns = (slots - 1) * g.sub + (rest + g.W - 1) / g.W;
+            if (s < base + ns) { inside(s - base, a, b, pbase); return; }
+            base += ns;
+            pbase += slots;
+            continue;
+        }
         if (s < base + ns) {
             const int64_t t0 = (int64_t)a + (int64_t)(s - base) * L;
             const int64_t t1 = min(t0 + (int64_t)L, (int64_t)b);
             tok0 = (int)t0;
             len = (int)(t1 - t0);
             ps = pbase + (s - base) * g.wslots;
-            doc0 = a;
-            doc1 = b;
+            doc0 = slot0 = a;
+            doc1 = slot1 = b;
             return;
         }
         base += ns;
@@ -108,8 +134,8 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
 
 __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len, int& ps)
 {
-    int doc0, doc1;
-    slot_range(g, s, tok0, len, ps, doc0, doc1);
+    int doc0, doc1, slot0, slot1;
+    slot_range<false>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
 }
 
 __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int& len)
@@ -202,14 +228,16 @@ hipError_t launch_attn_fwd_mfma(const Geom& g, const void* Q, const void* K, con
 bool walk_emits(const Geom& g, int dtype);
 hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K, const void* V,
                                      float* P, void* O, hipStream_t st);
-// The whole forward in one launch: every walk adds up the state it starts from itself, from the rows of its document
-// before it.  g as above, or one slot per walk; no decay.
+// Walks that add up the state they start from themselves (no decay; g as above, one slot per walk, or less).
+// Forward: from the rows of the document before the walk, writing the states to `emit` (NULL: not); with state, which
+// takes walks shorter than slots, from the rows of the slot before it and the slot's prefix state there.
 hipError_t launch_attn_fwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V,
-                                       float* P, void* O, hipStream_t st);
-// The whole backward in one launch, likewise: suffix states from the rows up to the document's end, which also go to
-// dR (one per walk).  No decay.
+                                       const float* state, float* emit, void* O, hipStream_t st);
+// Backward: suffix states from the rows up to the document's end (from_dR = 0; they also go to dR, one per walk, unless that
+// is NULL), or, walks shorter than slots, from the rows up to the slot's end and the next slot's inclusive suffix in dR.  P NULL:
+// every document a single slot.
 hipError_t launch_attn_bwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V, const void* dO,
-                                       const float* P, float* dR, void* dQ, void* dK, void* dV, hipStream_t st);
+                                       const float* P, float* dR, int from_dR, void* dQ, void* dK, void* dV, hipStream_t st);
 // dQ, dV, dK in one launch.  P: exclusive prefix states of K^T V (from the forward);
 // dR: INCLUSIVE suffix states of Q^T dO (slot s holds the sum over slots >= s of its document);
 // with decay: the EXCLUSIVE decayed suffix of the start-anchored states.

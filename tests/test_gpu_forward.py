@@ -15,6 +15,9 @@ CASES = [  # C, L, walk slots (0: the library's choice), lengths of the document
     (64, 0, 4, [1, 64, 65, 700, 256, 257, 320]), (256, 0, 4, [3000, 5, 1024, 1025]), (100, 0, 3, [1000]),
     (128, 0, 1, [700]), (64, 0, 0, [100, 4000]), (256, 0, 0, [1531]), (256, 0, 0, [63]), (64, 0, 0, [257]),
     (64, 0, 0, [9001]), (256, 0, 0, [16384]), (128, 384, 5, [12000]), (64, 0, 7, [9999]), (64, 0, 0, [13000, 1, 129, 64]),
+    # long slots, cut into walks: one slot, several, a last slot shorter than a walk, documents
+    (256, 7168, 0, [7000]), (256, 4096, 0, [8200]), (256, 4096, 0, [9000]), (128, 1920, 0, [7700]), (100, 1000, 0, [3500]),
+    (256, 2048, 0, [5000, 70, 2049]), (64, 4096, 0, [4096, 257, 4200, 5]),
 ]
 
 
@@ -79,3 +82,9 @@ def test_forward_in_one_call(monkeypatch, C, L, walk, docs, decay):
                 for r in range(0, b - a, 64):
                     err, by = diff[r:r + 64].norm().item(), terms[r:r + 64].sum().sqrt().item()
                     assert err <= 5 * 2.0 ** -9 * by, (name, g, a + r, err / by)
+
+    if P.shape[2] == len(docs):   # every document one slot: no states are needed
+        none = [torch.full_like(Q, float("nan")) for _ in range(4)]
+        bd.lasp2_attn_fwd(p, Q, K, V, None, none[0])
+        bd.lasp2_attn_bwd(p, Q, K, V, dO, None, *none[1:], bd.alloc_workspace(p))
+        assert torch.equal(none[0], O3) and all(torch.equal(x, y) for x, y in zip(none[1:], grads))

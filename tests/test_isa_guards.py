@@ -102,8 +102,8 @@ def test_no_compiler_placed_vmcnt_wait_in_the_walk(isa):
 # anti-causal pair's walk: dV / dK rows x early / late row blocks, plus the causal walk's two halves)
 SKEW = (("attn_skew_mfma_kernelILb0E", 4), ("attn_skew_mfma_kernelILb1E", 4), ("attn_bwd_pair_mfma_kernel", 6),
         ("attn_fwd_emit_mfma_kernelILb0E", 2), ("attn_fwd_emit_mfma_kernelILb1E", 2),
-        # one loop more: the rows gathered before the walk
-        ("attn_fwd_direct_mfma_kernel", 3), ("attn_bwd_direct_mfma_kernel", 7))
+        # one loop more for each place where rows are gathered before a walk
+        ("attn_fwd_direct_mfma_kernel", 3), ("attn_bwd_direct_mfma_kernel", 8))
 
 
 def _skew_blocks(lines, inst):
@@ -176,7 +176,8 @@ def test_skew_kernel_leaves_the_rows_in_flight_alone(isa, inst, ncopies):
                 code.append((t, in_asm))
         loads = [i for i, (t, a) in enumerate(code) if a and t.startswith("global_load_dwordx4")]
         if "direct" in inst and not loads:
-            continue                      # the gathering loop fetches no rows
+            checked += 1                  # a gathering loop fetches no rows
+            continue
         assert len(loads) == 8, (h, len(loads))
         dest = set().union(*(_regs(code[i][0].split(",")[0]) for i in loads))
         assert len(dest) == 32, (h, len(dest))
@@ -192,7 +193,7 @@ def test_skew_kernel_leaves_the_rows_in_flight_alone(isa, inst, ncopies):
             for i in r:
                 assert not (_regs(code[i][0]) & dest), (h, code[i][0])
         checked += 1
-    assert checked == ncopies - ("direct" in inst)
+    assert checked == ncopies
     # requests before the loops (the first half's walks): nothing touches their registers until the wait
     in_asm, pending = False, None
     for h, ins in blocks:
@@ -310,6 +311,14 @@ def test_states_kernel_store_count_matches_its_wait_arithmetic(isa):
             assert len(stores) == 32 and all("global_store_dword " in x for x in stores), len(stores)
             assert any("vmcnt(38)" in x for x in body) and any("vmcnt(6)" in x for x in body)
     assert found == 2
+
+
+@pytest.mark.parametrize("decay", [0, 1])
+def test_states_of_walks_store_count_matches_its_wait_arithmetic(isa, decay):
+    """The same body as states_mfma_kernel, for the states of walks of several slots."""
+    body, _ = _skew_blocks(isa, f"states_of_walks_kernelILb{decay}E")
+    stores = [l for l in body if "global_store" in l]
+    assert len(stores) == 32 and all("global_store_dword " in l for l in stores)
 
 
 # Scratch memory of the split-plane kernels, bytes per lane: what their register use is known to exceed (the loads around it
