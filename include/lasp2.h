@@ -293,6 +293,14 @@ int lasp2_nomask_fwd(const lasp2_desc_t* desc, const void* Q, const float* S, vo
                      void* stream);
 
 /*
+ * lasp2_chunk_states, lasp2_state_total (in place, S both times) and
+ * lasp2_nomask_fwd in one call: O and every entry of S, the same within the
+ * rounding order.  In: Q,K,V [B,H,N,d].  Out: S [B,H,T_s,d,d] fp32; O [B,H,N,d].
+ */
+int lasp2_nomask_forward(const lasp2_desc_t* desc, const void* Q, const void* K,
+                         const void* V, float* S, void* O, void* stream);
+
+/*
  * Backward without masking: dM_t = Q_t^T dO_t per slot and its total dM_{1:T}
  * (both into `workspace`; the range printed in the algorithm's Sum line is
  * read as the sum over all chunks), then

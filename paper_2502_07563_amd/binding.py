@@ -61,6 +61,7 @@ def lib():
         L.lasp2_attn_bwd_noalloc.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.lasp2_state_total.argtypes = [dp, vp, vp, vp]
         L.lasp2_nomask_fwd.argtypes = [dp, vp, vp, vp, vp]
+        L.lasp2_nomask_forward.argtypes = [dp, vp, vp, vp, vp, vp, vp]
         L.lasp2_nomask_bwd.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
         L.lasp2_softmax_fwd.argtypes = [dp, vp, vp, vp, vp, vp, ctypes.c_int, vp]
         L.lasp2_softmax_workspace_size.argtypes = [dp, szp]
@@ -74,7 +75,7 @@ def lib():
         for name in ("lasp2_num_slots", "lasp2_workspace_size", "lasp2_walk_slots", "lasp2_chunk_states",
                      "lasp2_state_prefix", "lasp2_attn_fwd", "lasp2_forward", "lasp2_attn_bwd", "lasp2_attn_bwd_noalloc",
                      "lasp2_state_total",
-                     "lasp2_nomask_fwd", "lasp2_nomask_bwd", "lasp2_softmax_fwd",
+                     "lasp2_nomask_fwd", "lasp2_nomask_forward", "lasp2_nomask_bwd", "lasp2_softmax_fwd",
                      "lasp2_softmax_workspace_size", "lasp2_softmax_bwd", "lasp2_softmax_fwd_share",
                      "lasp2_softmax_share_workspace_size", "lasp2_softmax_bwd_share"):
             getattr(L, name).restype = ctypes.c_int
@@ -242,6 +243,14 @@ def lasp2_nomask_fwd(p: Problem, Q, S, O, stream=None):
     _check(lib().lasp2_nomask_fwd(p.ref, _ptr(Q), _ptr(S), _ptr(O), _stream(stream)), "lasp2_nomask_fwd")
 
 
+def lasp2_nomask_forward(p: Problem, Q, K, V, S, O, stream=None):
+    for n, t in (('K', K), ('V', V), ('Q', Q), ('O', O)):
+        _rows(p, t, p.N, n)
+    _states(p, S, 'S')
+    _check(lib().lasp2_nomask_forward(p.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(S), _ptr(O), _stream(stream)),
+           "lasp2_nomask_forward")
+
+
 def lasp2_nomask_bwd(p: Problem, Q, K, V, dO, S, dQ, dK, dV, workspace, stream=None):
     for n, t in (('Q', Q), ('K', K), ('V', V), ('dO', dO), ('dQ', dQ), ('dK', dK), ('dV', dV)):
         _rows(p, t, p.N, n)
@@ -339,12 +348,10 @@ def backward(p: Problem, Q, K, V, dO, P, stream=None):
 
 
 def nomask_forward(p: Problem, Q, K, V, stream=None):
-    """chunk_states -> state_total (in place) -> nomask_fwd.  Returns (O, S)."""
+    """What chunk_states -> state_total (in place) -> nomask_fwd give, in one call.  Returns (O, S)."""
     S = alloc_states(p, Q.device)
     O = torch.empty_like(Q)
-    lasp2_chunk_states(p, K, V, S, stream)
-    lasp2_state_total(p, S, S, stream)
-    lasp2_nomask_fwd(p, Q, S, O, stream)
+    lasp2_nomask_forward(p, Q, K, V, S, O, stream)
     return O, S
 
 

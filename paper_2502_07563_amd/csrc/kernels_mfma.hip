@@ -101,10 +101,10 @@ __device__ __forceinline__ u32x4 scale_bf16x8(u32x4 x, float w)
 constexpr int ST_NW = 8, ST_NT = ST_NW * 64, ST_TPW = 16 / ST_NW, ST_NST = 5;
 constexpr int ST_KB = 32, ST_STAGE = ST_KB * ROWB;   // tokens and bytes (per tensor) of a stage
 
-// for_prefix: see launch_states_mfma (a kernel of its own: its registers and tests cost the plain one 5 %).
-template <bool DECAY, bool for_prefix>
+// of_walks: see launch_states_mfma (a kernel of its own: its registers and tests cost the plain one 5 %).
+template <bool DECAY, bool of_walks>
 __device__ __forceinline__ void states_body(const Geom& g, const char* __restrict__ X, const char* __restrict__ Y,
-                                            float* __restrict__ M, int anchor_start, int per_wg)
+                                            float* __restrict__ M, int anchor_start, int per_wg, int skip_last)
 {
     constexpr int DPS = 2;   // loads per wave per stage: one instruction (four rows) per tensor
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -126,10 +126,10 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
         if (u < nunits) {
             int tok0, ps, doc0, doc1, slot0, slot1;
             slot_range<false>(g, u % g.T_s, tok0, x.len, ps, doc0, doc1, slot0, slot1);
-            if (for_prefix && tok0 + x.len == doc1) x.len = 0;   // the document's last: no blocks, no state
+            if (of_walks && skip_last && tok0 + x.len == doc1) x.len = 0;   // no blocks, no state
             x.nblk = (x.len + ST_KB - 1) / ST_KB;
             x.row0 = ((size_t)(u / g.T_s) * g.N + tok0) * ROWB;
-            x.m = for_prefix ? (size_t)(u / g.T_s) * g.P_Ts + ps : (size_t)u;
+            x.m = of_walks ? (size_t)(u / g.T_s) * g.P_Ts + ps : (size_t)u;
         }
         return x;
     };
@@ -157,7 +157,7 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
     constexpr int NSTORE = 16 * ST_TPW;   // store instructions per wave that write a slot's state
     int slot = 0, older_than_stores = 0;
     for (Unit cu = open_unit(u_first); cu.u < nunits; cu = open_unit(cu.u + 1)) {
-        if (for_prefix && cu.nblk == 0) continue;
+        if (of_walks && cu.nblk == 0) continue;
         f32x16 acc[ST_TPW], tot[ST_TPW];
 #pragma unroll
         for (int u = 0; u < ST_TPW; ++u)
@@ -201,7 +201,7 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
             __syncthreads();   // block complete in LDS; every wave has left the block before it
             issue_next();      // into the ring slot that block occupied
             update_tiles<ST_TPW, ST_KB>(acc, tx, ty, w * ST_TPW, lane);
-            if (!DECAY && for_prefix && (blk & 15) == 15) {   // (a walk of several slots: sums of 512 rows, as accurate as the slots' own)
+            if (!DECAY && of_walks && (blk & 15) == 15) {   // (a walk of several slots: sums of 512 rows, as accurate as the slots' own)
 #pragma unroll
                 for (int u = 0; u < ST_TPW; ++u)
 #pragma unroll
@@ -228,14 +228,14 @@ template <bool DECAY>
 __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* __restrict__ X, const char* __restrict__ Y,
                                                             float* __restrict__ M, int anchor_start, int per_wg)
 {
-    states_body<DECAY, false>(g, X, Y, M, anchor_start, per_wg);
+    states_body<DECAY, false>(g, X, Y, M, anchor_start, per_wg, 0);
 }
 
 template <bool DECAY>
 __global__ __launch_bounds__(ST_NT) void states_of_walks_kernel(Geom g, const char* __restrict__ X, const char* __restrict__ Y,
-                                                                float* __restrict__ M, int per_wg)
+                                                                float* __restrict__ M, int per_wg, int skip_last)
 {
-    states_body<DECAY, true>(g, X, Y, M, 0, per_wg);
+    states_body<DECAY, true>(g, X, Y, M, 0, per_wg, skip_last);
 }
 
 // =====================================================================================
@@ -2276,6 +2276,7 @@ struct RowsStateArgs {
     const float* state;
     char* out;
     int transpose_state;
+    float* emit;
 };
 
 __global__ __launch_bounds__(RS_NW * 64) void rows_state_mfma_kernel(Geom g, RowsStateArgs p0, RowsStateArgs p1,
@@ -2293,15 +2294,18 @@ __global__ __launch_bounds__(RS_NW * 64) void rows_state_mfma_kernel(Geom g, Row
     if (unit >= (unsigned)g.T_s * (unsigned)g.G) return;
     const int s = (int)(unit % (unsigned)g.T_s), grp = (int)(unit / (unsigned)g.T_s);
     const RowsStateArgs& pr = prob == 0 ? p0 : (prob == 1 ? p1 : p2);
-    int tok0, len;
-    slot_range(g, s, tok0, len);
+    int tok0, len, ps, doc0, doc1, slot0, slot1;
+    slot_range<true>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
     if (len <= 0) return;
     const size_t row0 = ((size_t)grp * g.N + tok0) * ROWB;
     const char* __restrict__ A = pr.A + row0;
     char* __restrict__ out = pr.out + row0;
 
     {
-        const float* st = pr.state + ((size_t)grp * g.T_s + s) * (size_t)(D * D);
+        const float* st = pr.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D);
+        // the state goes to the walk's other slots as well, if that is asked for
+        const int Lp = (int)(g.L / g.wslots), more = pr.emit && !g.W ? (len + Lp - 1) / Lp - 1 : 0;
+        float* em = pr.emit + ((size_t)grp * g.P_Ts + ps + 1) * (size_t)(D * D);
         for (int i = tid; i < D * 16; i += RS_NW * 64) {
             float x[8];
             int c, q;   // column of out, 16-byte piece (contracted indices 8q .. 8q+7)
@@ -2312,11 +2316,18 @@ __global__ __launch_bounds__(RS_NW * 64) void rows_state_mfma_kernel(Geom g, Row
                 const f32x4 b = *reinterpret_cast<const f32x4*>(st + c * D + 8 * q + 4);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { x[e] = a[e]; x[4 + e] = b[e]; }
+                for (int k = 0; k < more; ++k) {
+                    __builtin_nontemporal_store(a, reinterpret_cast<f32x4*>(em + (size_t)k * (D * D) + c * D + 8 * q));
+                    __builtin_nontemporal_store(b, reinterpret_cast<f32x4*>(em + (size_t)k * (D * D) + c * D + 8 * q + 4));
+                }
             } else {
                 q = i >> 7;
                 c = i & 127;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[e] = st[(8 * q + e) * D + c];
+                for (int k = 0; k < more; ++k)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) __builtin_nontemporal_store(x[e], em + (size_t)k * (D * D) + (8 * q + e) * D + c);
             }
             const u32x4 pk = {pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(x[4], x[5]), pack2(x[6], x[7])};
             *reinterpret_cast<u32x4*>(sW + tile_off(c, q)) = pk;
@@ -2411,7 +2422,7 @@ bool mfma_path_supported(const Geom& g, int dtype)
 }
 
 hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float* M, int anchor_start,
-                              int for_prefix, hipStream_t st)
+                              WalkStates of_walks, hipStream_t st)
 {
     constexpr int smem = 2 * ST_NST * ST_STAGE;   // 80 KiB: two workgroups per CU
     // two workgroups per CU, each walking through its share of the slots
@@ -2424,10 +2435,11 @@ hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float
     dim3 grid((unsigned)((nunits + per_wg - 1) / per_wg)), block(ST_NT);
     const char *k = static_cast<const char*>(K), *v = static_cast<const char*>(V);
     hipError_t e;
-    if (for_prefix) {
+    if (of_walks != WalkStates::none) {
         e = g.decay ? allow_dynamic_lds<states_of_walks_kernel<true>>(smem) : allow_dynamic_lds<states_of_walks_kernel<false>>(smem);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((g.decay ? states_of_walks_kernel<true> : states_of_walks_kernel<false>), grid, block, smem, st, g, k, v, M, per_wg);
+        hipLaunchKernelGGL((g.decay ? states_of_walks_kernel<true> : states_of_walks_kernel<false>), grid, block, smem, st, g, k, v, M, per_wg,
+                           of_walks == WalkStates::before_last ? 1 : 0);
     } else {
         e = g.decay ? allow_dynamic_lds<states_mfma_kernel<true>>(smem) : allow_dynamic_lds<states_mfma_kernel<false>>(smem);
         if (e != hipSuccess) return e;
@@ -2558,7 +2570,7 @@ hipError_t launch_rows_state_mfma(const Geom& g, const RowsStateProblem* probs, 
     RowsStateArgs a[3];
     for (int i = 0; i < 3; ++i) {
         const RowsStateProblem& p = probs[i < n ? i : 0];
-        a[i] = RowsStateArgs{static_cast<const char*>(p.A), p.state, static_cast<char*>(p.out), p.transpose_state};
+        a[i] = RowsStateArgs{static_cast<const char*>(p.A), p.state, static_cast<char*>(p.out), p.transpose_state, p.emit};
     }
     hipError_t e = allow_dynamic_lds<rows_state_mfma_kernel>(smem);
     if (e != hipSuccess) return e;

@@ -424,8 +424,35 @@ size_t pace_bytes(const Geom& g) { return (((size_t)g.G * (size_t)g.T_s * sizeof
 hipError_t run_states(const Geom& g, int dtype, const void* K, const void* V, float* M,
                       int anchor_start, hipStream_t st)
 {
-    if (mfma_path_supported(g, dtype)) return launch_states_mfma(g, K, V, M, anchor_start, 0, st);
+    if (mfma_path_supported(g, dtype)) return launch_states_mfma(g, K, V, M, anchor_start, WalkStates::none, st);
     return launch_states_planes(g, dtype, K, V, M, anchor_start, st);
+}
+
+// Without a mask a document has one state, whatever its slots: it is summed and applied by walks of several slots, and
+// the `nprob` products' launch hands it to the slots inside a walk.  One state per 128 tokens, 8 x 16 x
+// 6233, forward 499 -> 265 us, backward 793 -> 441; 40 documents in 8 x 30 000, one per 64, 453 -> 126, 628 -> 178.
+// Walks of about 2 048 tokens, fewer while there are not two workgroups per CU; slots of 1 024 and more stay as they are, but
+// the products take parts of them where a launch would leave CUs without work.
+Geom nomask_walks(const Geom& g, const int32_t* cu_host, int nprob)
+{
+    const int64_t longest = longest_sequence(g, cu_host), cus = cu_count();
+    const int64_t wanted = std::max<int64_t>(128, std::min<int64_t>(2048, (int64_t)g.G * g.N * nprob / (2 * cus)));
+    if (g.L >= 1024) {
+        const int64_t part = std::max<int64_t>(256, (wanted + 63) / 64 * 64);
+        return (int64_t)g.G * g.T_s * nprob < cus && part <= g.L / 2 && longest > part ? regroup_short(g, cu_host, part) : g;
+    }
+    return regroup(g, cu_host, (int)std::max<int64_t>(1, std::min(wanted / g.L, (longest + g.L - 1) / g.L)));
+}
+
+// S = sum X^T Y of each document, then the products; gw: as nomask_walks gives them
+hipError_t run_nomask(const Geom& g, const Geom& gw, const void* X, const void* Y, float* S, const RowsStateProblem* p, int n, hipStream_t st)
+{
+    const Geom& gs = gw.W ? g : gw;
+    hipError_t e = launch_states_mfma(gs, X, Y, S, 0, gs.wslots > 1 ? WalkStates::all : WalkStates::none, st);
+    if (e != hipSuccess) return e;
+    e = launch_state_total(gs, S, S, st);
+    if (e != hipSuccess) return e;
+    return launch_rows_state_mfma(gw, p, n, st);
 }
 
 // What lasp2_attn_bwd and lasp2_attn_bwd_noalloc have in common: the checks that need no
@@ -654,7 +681,7 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
         // The attention walks write the states of the slots inside them, so states and prefix are
         // needed where a walk starts only, and not at all where every document is one walk.
         if (!gw.lone_slots) {
-            e = launch_states_mfma(gw, K, V, P, 0, 1, st);
+            e = launch_states_mfma(gw, K, V, P, 0, WalkStates::before_last, st);
             if (e != hipSuccess) return LASP2_ERR_LAUNCH;
             e = launch_state_prefix(gw, P, P, 0, 0, 1, nullptr, 0, st);
             if (e != hipSuccess) return LASP2_ERR_LAUNCH;
@@ -726,9 +753,33 @@ int lasp2_nomask_fwd(const lasp2_desc_t* desc, const void* Q, const float* S, vo
     if (rc != LASP2_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     if (mfma_path_supported(g, desc->dtype)) {
-        const RowsStateProblem p = {Q, S, O, 0};
-        return from_hip(launch_rows_state_mfma(g, &p, 1, st));
+        const RowsStateProblem p = {Q, S, O, 0, nullptr};
+        return from_hip(launch_rows_state_mfma(nomask_walks(g, desc->cu_seqlens_host, 1), &p, 1, st));
     }
+    return from_hip(launch_rows_state_generic(g, desc->dtype, Q, S, O, 0, st));
+}
+
+int lasp2_nomask_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,
+                         float* S, void* O, void* stream)
+{
+    Geom g;
+    bool empty = false;
+    int rc = make_geom(desc, &g, &empty);
+    if (rc != LASP2_OK) return rc;
+    if (g.decay) return LASP2_ERR_DECAY;   // decay is defined for the masked path only
+    if (empty) return LASP2_OK;
+    rc = check_ptrs({Q, K, V, S, O});
+    if (rc != LASP2_OK) return rc;
+    hipStream_t st = (hipStream_t)stream;
+    if (mfma_path_supported(g, desc->dtype)) {
+        const Geom gw = nomask_walks(g, desc->cu_seqlens_host, 1);
+        const RowsStateProblem p = {Q, S, O, 0, S};
+        return from_hip(run_nomask(g, gw, K, V, S, &p, 1, st));
+    }
+    hipError_t e = launch_states_planes(g, desc->dtype, K, V, S, 0, st);
+    if (e != hipSuccess) return LASP2_ERR_LAUNCH;
+    e = launch_state_total(g, S, S, st);
+    if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     return from_hip(launch_rows_state_generic(g, desc->dtype, Q, S, O, 0, st));
 }
 
@@ -748,15 +799,15 @@ int lasp2_nomask_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, con
 
     hipStream_t st = (hipStream_t)stream;
     float* dS = static_cast<float*>(workspace);
-    // dM_t = Q_t^T dO_t per slot, then the sum over the document's slots in place
-    hipError_t e = run_states(g, desc->dtype, Q, dO, dS, 0, st);
+    // dM_t = Q_t^T dO_t, then the sum over the document's slots in place
+    if (mfma_path_supported(g, desc->dtype)) {
+        const RowsStateProblem p[3] = {{dO, S, dQ, 1, nullptr}, {V, dS, dK, 1, dS}, {K, dS, dV, 0, nullptr}};
+        return from_hip(run_nomask(g, nomask_walks(g, desc->cu_seqlens_host, 3), Q, dO, dS, p, 3, st));
+    }
+    hipError_t e = launch_states_planes(g, desc->dtype, Q, dO, dS, 0, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     e = launch_state_total(g, dS, dS, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
-    if (mfma_path_supported(g, desc->dtype)) {
-        const RowsStateProblem p[3] = {{dO, S, dQ, 1}, {V, dS, dK, 1}, {K, dS, dV, 0}};
-        return from_hip(launch_rows_state_mfma(g, p, 3, st));
-    }
     e = launch_rows_state_generic(g, desc->dtype, dO, S, dQ, 1, st);    // dQ = dO M^T
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     e = launch_rows_state_generic(g, desc->dtype, V, dS, dK, 1, st);    // dK = V dM^T

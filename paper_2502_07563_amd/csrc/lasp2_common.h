@@ -207,7 +207,7 @@ hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const
 hipError_t launch_state_prefix(const Geom& g, const float* M, float* P, int reverse, int inclusive,
                                int user_slots, unsigned* clear, unsigned nclear, hipStream_t st);
 
-// S[s] = sum of M over the slots of s's document; S may alias M.
+// S[s] = sum of M over the slots of s's document; S may alias M.  g's walks of several slots: the entries of their first slots.
 hipError_t launch_state_total(const Geom& g, const float* M, float* S, hipStream_t st);
 // out = A * state[slot] (transpose_state: A * state[slot]^T), plain fp32-FMA kernel.
 hipError_t launch_rows_state_generic(const Geom& g, int dtype, const void* A, const float* state,
@@ -215,10 +215,12 @@ hipError_t launch_rows_state_generic(const Geom& g, int dtype, const void* A, co
 
 // bf16 MFMA kernels (d = 128; they tile slots in their own chunks, so any C).
 bool mfma_path_supported(const Geom& g, int dtype);
-// for_prefix: the states of g's walks go where each walk's first slot is in an array with one entry per slot
-// of the caller's, and the last walk of a document, whose state no exclusive prefix contains, is left out.
+// of_walks: the states of g's walks go where each walk's first slot is in an array with one entry per slot
+// of the caller's (anchored at the end); before_last: without the last walk of a document, whose state no exclusive
+// prefix contains.
+enum class WalkStates { none, all, before_last };
 hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float* M,
-                              int anchor_start, int for_prefix, hipStream_t st);
+                              int anchor_start, WalkStates of_walks, hipStream_t st);
 // O = fused intra + inter pass with prefix states P.
 hipError_t launch_attn_fwd_mfma(const Geom& g, const void* Q, const void* K, const void* V,
                                 const float* P, void* O, hipStream_t st);
@@ -248,12 +250,14 @@ hipError_t launch_attn_bwd_mfma(const Geom& g, const void* Q, const void* K, con
                                 void* dK, void* dV, hipStream_t st);
 
 // Row-times-state products of the unmasked path, up to three in one launch:
-// out_i = A_i * state_i[slot] (or its transpose), i < n.
+// out_i = A_i * state_i[slot] (or its transpose), i < n.  g's walks of several slots take the state of their first; emit:
+// NULL, or the state array whose entries of their other slots receive it.
 struct RowsStateProblem {
     const void* A;
     const float* state;
     void* out;
     int transpose_state;
+    float* emit;
 };
 hipError_t launch_rows_state_mfma(const Geom& g, const RowsStateProblem* probs, int n, hipStream_t st);
 

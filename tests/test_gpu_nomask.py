@@ -75,3 +75,43 @@ def test_bf16_other_d(oracle):
 def test_packed_documents(oracle, dtype, d, C, L):
     cu = synth.doc_offsets(5, 2048, 9, mean_len=2048 / 9, min_len=1)
     _run(oracle, 1, 2, 2048, d, C, L, dtype, seed=80, cu=cu)
+
+
+@pytest.mark.parametrize("B,H,docs,C,L", [(1, 3, [1000], 64, 0), (2, 3, [1025], 128, 0), (1, 3, [63, 700, 1, 256, 900], 64, 0),
+                                          (1, 3, [5000], 256, 4096), (1, 2, [3000, 70, 1500], 256, 1024), (1, 3, [500], 100, 0),
+                                          (8, 32, [2500], 64, 0), (1, 64, [9000, 4000], 256, 512)])
+def test_one_call_and_walks(B, H, docs, C, L):
+    """lasp2_nomask_forward and the backward, whose states are summed and applied by walks of several slots or of parts
+    of one, against the definition in 64 bits: every slot's state, and the rows."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    cu = np.concatenate([[0], np.cumsum(docs)]).astype(np.int32)
+    N, d = int(cu[-1]), 128
+    p = bd.Problem(B, H, N, d, C, L, "bf16", cu if len(docs) > 1 else None)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Q, K, V, dO = (torch.randn(B, H, N, d, generator=gen, device="cuda").mul_(d ** -0.5).to(torch.bfloat16) for _ in range(4))
+    S, O = bd.alloc_states(p).fill_(float("nan")), torch.full_like(Q, float("nan"))
+    bd.lasp2_nomask_forward(p, Q, K, V, S, O)
+    O2 = torch.full_like(Q, float("nan"))
+    bd.lasp2_nomask_fwd(p, Q, S, O2)
+    ws = bd.alloc_workspace(p).fill_(float("nan"))
+    grads = [torch.full_like(Q, float("nan")) for _ in range(3)]
+    bd.lasp2_nomask_bwd(p, Q, K, V, dO, S, *grads, ws)
+    dS = bd.workspace_states(p, ws)
+    assert torch.equal(O, O2)
+    tr, at = lambda x: x.transpose(-1, -2).contiguous(), 0
+    for a, b in zip(cu[:-1], cu[1:]):
+        q, k, v, w = (x[:, :, a:b].double() for x in (Q, K, V, dO))
+        s, r = tr(k) @ v, tr(q) @ w
+        n = -(-int(b - a) // (L or C))
+        for got, want in ((S, s), (dS, r)):
+            err = (got[:, :, at:at + n].double() - want[:, :, None]).norm(dim=(3, 4))
+            assert bool((err <= N * 2.0 ** -24 * want.norm(dim=(2, 3))[:, :, None]).all())   # fp32 sums of N products
+        at += n
+        # the state and the result are rounded to bf16: 2^-9 each, of the terms' size in quadrature for a lone row
+        for got, x, m in ((O, q, s), (grads[0], w, tr(s)), (grads[1], v, tr(r)), (grads[2], k, r)):
+            want = x @ m
+            size = (x.norm(dim=3) * m.norm(dim=(2, 3))[:, :, None] / d ** 0.5)
+            err = (got[:, :, a:b].double() - want).norm(dim=3)
+            assert bool((err <= 4 * 2.0 ** -9 * torch.maximum(size, want.norm(dim=3))).all())
+    assert at == S.shape[2]
