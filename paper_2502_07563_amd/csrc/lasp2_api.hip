@@ -432,14 +432,15 @@ hipError_t run_states(const Geom& g, int dtype, const void* K, const void* V, fl
 // the `nprob` products' launch hands it to the slots inside a walk.  One state per 128 tokens, 8 x 16 x
 // 6233, forward 499 -> 265 us, backward 793 -> 441; 40 documents in 8 x 30 000, one per 64, 453 -> 126, 628 -> 178.
 // Walks of about 2 048 tokens, fewer while there are not two workgroups per CU; slots of 1 024 and more stay as they are, but
-// the products take parts of them where a launch would leave CUs without work.
+// the products take parts of them where a launch would leave three of four CUs without work (2 x 20 x 1349, 80 of 256: 81 us whole,
+// 85 in parts).
 Geom nomask_walks(const Geom& g, const int32_t* cu_host, int nprob)
 {
     const int64_t longest = longest_sequence(g, cu_host), cus = cu_count();
     const int64_t wanted = std::max<int64_t>(128, std::min<int64_t>(2048, (int64_t)g.G * g.N * nprob / (2 * cus)));
     if (g.L >= 1024) {
         const int64_t part = std::max<int64_t>(256, (wanted + 63) / 64 * 64);
-        return (int64_t)g.G * g.T_s * nprob < cus && part <= g.L / 2 && longest > part ? regroup_short(g, cu_host, part) : g;
+        return (int64_t)g.G * g.T_s * nprob < cus / 4 && part <= g.L / 2 && longest > part ? regroup_short(g, cu_host, part) : g;
     }
     return regroup(g, cu_host, (int)std::max<int64_t>(1, std::min(wanted / g.L, (longest + g.L - 1) / g.L)));
 }
@@ -828,6 +829,12 @@ static int softmax_geom(const lasp2_desc_t* desc, int64_t q_begin, int64_t q_len
     return LASP2_OK;
 }
 
+// Launches of at most one workgroup of 64 rows per CU: 256 queries (128 keys) a workgroup would leave most CUs idle while the longest
+// row sets the time.  With more of them the small kernels' traffic (a step of 64 KB per 64 rows) costs more than the idle CUs.
+// bf16 x 128, 256-row kernels | these, us: 16 heads x 1 000 causal, forward 37 | 20, backward 82 | 53; 4 x 4 000 111 | 55, 260 | 148;
+// 16 heads, the last 1 000 of 16 000 428 | 228; and beyond the line 20 x 1 692 57 | 69, 135 | 178; 64 x 348 unmasked 19 | 24, 49 | 66.
+static bool softmax_small(const Geom& g, int rows) { return (int64_t)g.G * ((rows + 63) / 64) <= cu_count(); }
+
 static int softmax_fwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q_len, const void* Q,
                             const void* K, const void* V, void* O, float* LSE, int causal, void* stream)
 {
@@ -840,7 +847,8 @@ static int softmax_fwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q
     if (rc != LASP2_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     if (softmax_mfma_supported(g, desc->dtype))
-        return from_hip(launch_softmax_fwd_mfma(g, Q, K, V, O, LSE, causal ? 1 : 0, st));
+        return from_hip(softmax_small(g, g.qn) ? launch_softmax_fwd_small(g, Q, K, V, O, LSE, causal ? 1 : 0, st)
+                                               : launch_softmax_fwd_mfma(g, Q, K, V, O, LSE, causal ? 1 : 0, st));
     return from_hip(launch_softmax_fwd_planes(g, desc->dtype, Q, K, V, O, LSE, causal ? 1 : 0, st));
 }
 
@@ -866,9 +874,11 @@ static int softmax_bwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q
     hipError_t e = launch_softmax_delta(g, desc->dtype, O, dO, LSE, delta, fast ? lse2 : nullptr, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     if (fast) {
-        e = launch_softmax_bwd_dq_mfma(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st);
+        e = softmax_small(g, g.qn) ? launch_softmax_bwd_dq_small(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st)
+                                   : launch_softmax_bwd_dq_mfma(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
-        return from_hip(launch_softmax_bwd_dkv_mfma(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st));
+        return from_hip(softmax_small(g, g.N) ? launch_softmax_bwd_dkv_small(g, Q, K, V, dO, LSE, delta, dK, dV, causal ? 1 : 0, st)
+                                              : launch_softmax_bwd_dkv_mfma(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st));
     }
     return from_hip(launch_softmax_bwd_planes(g, desc->dtype, Q, K, V, dO, LSE, delta, dQ, dK, dV,
                                               causal ? 1 : 0, st));
