@@ -159,6 +159,25 @@ struct PlanesProblem {
 };
 struct PlanesProblems { PlanesProblem p[3]; };
 
+// Problem, segment x (= slot * nseg + segment) and group of a workgroup.  flat: a one-dimensional grid in which the nprob
+// problems of a segment are dealt to the same XCD, one after another, and find each other's rows in its L2 (backward launch, fp32,
+// 16 x 4000 x 64 64 -> 60 us; bf16, 16 x 1800 x 64 23.6 -> 21.9); otherwise (one problem, or grids past 2^32 threads) groups are
+// the second axis.
+__device__ __forceinline__ bool which_segment(const Geom& g, int nprob, int nseg, int flat, int& prob, int& x, int& grp)
+{
+    if (!flat) {
+        prob = blockIdx.x % nprob;
+        x = blockIdx.x / nprob;
+        grp = blockIdx.y;
+        return true;
+    }
+    const unsigned per = (unsigned)g.T_s * (unsigned)nseg, u = (blockIdx.x / (8u * nprob)) * 8u + (blockIdx.x & 7u);
+    prob = (int)((blockIdx.x >> 3) % (unsigned)nprob);
+    grp = (int)(u / per);
+    x = (int)(u % per);
+    return u < per * (unsigned)g.G;
+}
+
 // Tokens per LDS stage: as many of the chunk's 128 as leave room for a second workgroup on the CU
 // (one workgroup with d = 128), with at most 32 registers per thread for the next stage's loads; fp32 with
 // decay and d = 64 has no registers for more than 32, and spills 9 even so.  With d = 128 the operands' planes, the
@@ -178,14 +197,14 @@ struct AttnLds {
 // on: a row of out per wave, the running state M [D][D] in LDS.  For inputs whose planes are not finite: slow, as scalar
 // products are (fp32, 8 x 2003 x 64 with a NaN in every head's V, forward + backward: 1760 us).
 template <typename T, int D>
-__device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems& probs, int nprob, int nseg, int cps, int first,
-                                            float* M)
+__device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems& probs, int nprob, int nseg, int cps, int flat,
+                                            int first, float* M)
 {
-    int x = blockIdx.x;
-    asm volatile("" : "+s"(x));   // (all of this worked out anew, so that none of it stays in registers through the walk)
-    const PlanesProblem pb = probs.p[x % nprob];
-    x /= nprob;
-    const int tid = threadIdx.x, grp = blockIdx.y;
+    asm volatile("" : "+s"(nseg));   // (all of this worked out anew, so that none of it stays in registers through the walk)
+    int x, prob, grp;
+    which_segment(g, nprob, nseg, flat, prob, x, grp);
+    const PlanesProblem pb = probs.p[prob];
+    const int tid = threadIdx.x;
     int tok0, len, ps;
     slot_range(g, x / nseg, tok0, len, ps);
     const bool rev = pb.reverse != 0;
@@ -245,6 +264,26 @@ __device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems&
     }
 }
 
+// c += x y with the rows of the result those of x, or (TR) those of y: transposed
+template <bool TR, int LO, int HI, int NX, int NY>
+__device__ __forceinline__ f32x16 mm_either(const bf16x8 (&x)[NX], const bf16x8 (&y)[NY], f32x16 c)
+{
+    if constexpr (TR) return mm<LO, HI>(y, x, c);
+    else return mm<LO, HI>(x, y, c);
+}
+
+// four columns of a row
+__device__ __forceinline__ void store4(float* p, float a, float b, float c, float d)
+{
+    const f32x4 v = {a, b, c, d};
+    *reinterpret_cast<f32x4*>(p) = v;
+}
+__device__ __forceinline__ void store4(__hip_bfloat16* p, float a, float b, float c, float d)
+{
+    const u32x2 v = {pack2(a, b), pack2(c, d)};
+    *reinterpret_cast<u32x2*>(p) = v;
+}
+
 // out = [(A Bk^T) (.) mask] Cv + A * state for the rows of one segment of one slot, state += Bk^T Cv from
 // chunk to chunk of 128 rows (causal: first to last; reverse: mask j >= i, last to first).
 //
@@ -252,6 +291,10 @@ __device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems&
 // in stages for all four (the next stage's loads in flight in registers), scores are formed transposed (a query per lane) and are the
 // next product's operand as they stand.  The running state stays in accumulators, its planes
 // are written to LDS once per chunk, as rows of the state's second index.
+// With d = 128 the result is formed transposed too: a lane stores four columns of its row at a time, and the 64 addresses and
+// bounds of single elements no longer compete for the registers (forward | backward launch, 16 x 1800 x 128 in fp32, us: 73 -> 63 |
+// 207 -> 179; scratch 416 -> 352 bytes).  Smaller heads lose by it (bf16, 64 x 4001 x 64: 50 -> 53 | 124 -> 128): their
+// stores, rows of 32 to 256 bytes, are better made by column.
 // A slot may be cut into `nseg` segments of `cps` chunks, a workgroup each: a workgroup first adds up
 // the states of the chunks before its own (a fifth of a chunk's work), which is worth it while the
 // launch leaves CUs idle.
@@ -260,20 +303,20 @@ __device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems&
 // 64 groups x 4001 x 64: 4200 -> 230 us (the forward launch 50 us, 3.2 TB/s); fp32, 2 x 1024 x 64: 1190 -> 58 us.
 template <typename T, int D, bool DECAY>
 __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geom g, PlanesProblems probs, int nprob, int nseg,
-                                                                             int cps)
+                                                                             int cps, int flat)
 {
     typedef AttnLds<T, D, DECAY> LD;
     typedef typename LD::Stage Stage;
     constexpr int DP = LD::DP, NP = planes_of<T>::n, NT = DP / 32, KS = D / 16, NTL = Tiles<NT>::n;
     constexpr int ROWS = LD::ROWS, SUB = 32 * DP * 2;   // bytes of 32 rows of a plane
+    constexpr bool TR = D == 128;
     extern __shared__ __align__(16) char smem[];
     char* snap = smem + Stage::BYTES;
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
-    const int grp = blockIdx.y;
-    int x = blockIdx.x;
-    const PlanesProblem pb = probs.p[x % nprob];
-    x /= nprob;
+    int prob, x, grp;
+    if (!which_segment(g, nprob, nseg, flat, prob, x, grp)) return;
+    const PlanesProblem pb = probs.p[prob];
     const int s = x / nseg, seg = x % nseg;
     int tok0, len, ps;
     slot_range(g, s, tok0, len, ps);
@@ -369,19 +412,19 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
                         for (int ks = 0; ks < KS; ++ks) {
                             bf16x8 b[3];
                             row_frag<DP>(snap, LD::SPLANE, 32 * nt + l32, 2 * ks + h, b);
-                            acc[nt] = mm<1, 2>(q[ks], b, acc[nt]);
+                            acc[nt] = mm_either<TR, 1, 2>(q[ks], b, acc[nt]);
                         }
 #pragma unroll
                         for (int ks = 0; ks < KS; ++ks) {
                             bf16x8 b[1];
                             row_frag<DP>(snap, LD::SPLANE, 32 * nt + l32, 2 * ks + h, b);
-                            acc[nt] = mm<0, 0>(q[ks], b, acc[nt]);
+                            acc[nt] = mm_either<TR, 0, 0>(q[ks], b, acc[nt]);
                         }
                         if (DECAY) {
                             // the state sits one token before the chunk (causal) or one after it
 #pragma unroll
                             for (int v = 0; v < 16; ++v) {
-                                const int i = 32 * w + acc_row(v) + 4 * h;
+                                const int i = 32 * w + (TR ? l32 : acc_row(v) + 4 * h);
                                 acc[nt][v] *= decay_pow((float)(rev ? max(clen - i, 0) : i + 1), l2);
                             }
                         }
@@ -426,8 +469,8 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
                         bf16x8 v[2][NP];
                         col_frag<DP>(buf + Stage::TENSOR, Stage::PLANE, 0, 32 * nt, lane, v[0]);
                         col_frag<DP>(buf + Stage::TENSOR, Stage::PLANE, 16, 32 * nt, lane, v[1]);
-                        const f32x16 low = mm<1, 2>(p[1], v[1], mm<1, 2>(p[0], v[0], zero16()));
-                        acc[nt] = mm<0, 0>(p[1], v[1], mm<0, 0>(p[0], v[0], acc[nt] + low));
+                        const f32x16 low = mm_either<TR, 1, 2>(p[1], v[1], mm_either<TR, 1, 2>(p[0], v[0], zero16()));
+                        acc[nt] = mm_either<TR, 0, 0>(p[1], v[1], mm_either<TR, 0, 0>(p[0], v[0], acc[nt] + low));
                     }
                 }
                 if (update && owner)
@@ -445,21 +488,32 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) odd = fmaf(32 * nt + l32 < D ? acc[nt][v] : 0.f, 0.f, odd);
+            for (int v = 0; v < 16; ++v) odd = fmaf(TR || 32 * nt + l32 < D ? acc[nt][v] : 0.f, 0.f, odd);
         if (__syncthreads_or(odd != 0.f)) {
             redo = ci;
             break;
         }
+        if constexpr (TR) {
+            if (32 * w + l32 < clen) {
+                T* o = out + (size_t)(c0 + 32 * w + l32) * D + 4 * h;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+                for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int i = 32 * w + acc_row(v) + 4 * h, b = 32 * nt + l32;
-                if (i < clen && b < D) store1(out + (size_t)(c0 + i) * D + b, acc[nt][v]);
+                    for (int v = 0; v < 16; v += 4)
+                        store4(o + 32 * nt + acc_row(v), acc[nt][v], acc[nt][v + 1], acc[nt][v + 2], acc[nt][v + 3]);
             }
+        } else {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int i = 32 * w + acc_row(v) + 4 * h, b = 32 * nt + l32;
+                    if (i < clen && b < D) store1(out + (size_t)(c0 + i) * D + b, acc[nt][v]);
+                }
+        }
         have_state = true;
     }
-    if (redo < ci1) attn_scalar<T, D>(g, probs, nprob, nseg, cps, redo, reinterpret_cast<float*>(snap));
+    if (redo < ci1) attn_scalar<T, D>(g, probs, nprob, nseg, cps, flat, redo, reinterpret_cast<float*>(snap));
 }
 
 template <typename T, int D, bool DECAY>
@@ -486,13 +540,19 @@ hipError_t attn_TD(const Geom& g, const PlanesProblems& p, int n, hipStream_t st
     int64_t nseg = std::max<int64_t>(1, std::min<int64_t>({2 * (int64_t)cu_count() / wgs, chunks, 8}));
     const int64_t cps = (chunks + nseg - 1) / nseg;
     nseg = (chunks + cps - 1) / cps;
-    // (a grid holds fewer than 2^32 threads per axis: past that the problems go one by one)
+    const int64_t units = ((int64_t)g.G * g.T_s * nseg + 7) / 8 * 8;
+    if (n > 1 && units * n < ((int64_t)1 << 32) / kThr) {
+        hipLaunchKernelGGL((attn_planes_kernel<T, D, DECAY>), dim3((unsigned)(units * n)), dim3(kThr), lds, st, g, p, n, (int)nseg,
+                           (int)cps, 1);
+        return hipGetLastError();
+    }
+    // (a grid holds fewer than 2^32 threads per axis: past that groups are the other axis, and the problems may go one by one)
     const int per = (int64_t)g.T_s * nseg * n < ((int64_t)1 << 32) / kThr ? n : 1;
     for (int i = 0; i < n; i += per) {
         PlanesProblems sub = p;
         if (per == 1) sub.p[0] = p.p[i];
         hipLaunchKernelGGL((attn_planes_kernel<T, D, DECAY>), dim3((unsigned)(g.T_s * nseg * per), g.G), dim3(kThr), lds, st, g, sub,
-                           per, (int)nseg, (int)cps);
+                           per, (int)nseg, (int)cps, 0);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
