@@ -1,18 +1,36 @@
 // Softmax attention for bf16 heads of 128 in launches that kernels_softmax.hip, whose workgroups take 256 queries (128 keys),
-// would leave most of the CUs without.  A workgroup has 64 rows (queries, or keys for dK and dV): two row tiles of 32 by four
-// shares of the partner rows, a wave each, whose results are merged through LDS at the end.  A wave's row is a lane, as there:
-// scores are formed transposed, the row statistics are per lane and the probabilities are the next product's operand as they
-// stand.  Partner rows pass through LDS in steps of 128, one 32-row tile per share, by direct loads, the next step's on their way
-// while this one is worked on.  Under a causal mask the two row tiles are mirrored (tile i with the i-th from the end) and a
-// SIMD has one wave of each, so that its work is the same in every workgroup.
-// Bounds: latency; a step takes 0.7 us with two waves per SIMD.
+// would leave most of the CUs without.  A workgroup has 64 rows (queries, or keys for dK and dV), two row tiles of 32 by four
+// shares of the partner rows, or in the forward 128 rows, four tiles by two shares: a wave each, whose results are merged through LDS
+// at the end.  A wave's row is a lane, as there: scores are formed transposed, the row statistics are per lane and the
+// probabilities are the next product's operand as they stand.  Partner rows pass through LDS in steps of one 32-row tile per share,
+// by direct loads, with the ring's other steps on their way.  Under a causal mask half of the row tiles are mirrored (the i-th from
+// the start with the i-th from the end) and a SIMD has one wave of each kind, so that its work is the same in every workgroup.
+// Bounds: latency and the L2: 64 rows take 64 KB of partner rows per step of 1.7 us (0.8 without waiting), all that the LDS holds
+// in flight; 128 rows half as much per row, which pays in the forward (16 x 1 300 causal: 64 rows 34 us, 128 30) and not in
+// the backward (92, 95).
 #include "mfma_tile.h"
 
 namespace lasp2 {
 namespace {
 
-constexpr int SS_KW = 4, SS_STEP = 32 * SS_KW, SS_THR = 512;
-constexpr int SS_TENSOR = SS_STEP * ROWB, SS_RING = 2 * SS_TENSOR;   // bytes: one tensor of a step; a tensor's ring of two
+constexpr int SS_THR = 512;
+
+// QW row tiles by KW shares of the partner rows; RING steps of STEP partner rows in LDS, all but one of them on their way
+template <int QW_, int RING_>
+struct Cfg {
+    static constexpr int QW = QW_, KW = 8 / QW, RING = RING_, STEP = 32 * KW, BLOCKS = STEP / KB;
+    static constexpr int TENSOR = STEP * ROWB, RINGB = RING * TENSOR;   // bytes: one tensor of a step, of the ring
+};
+
+// One wave instruction of direct global->LDS load of 4 bytes per lane (see dma16)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void dma4(const char* sbase, uint32_t voff, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 
 __device__ __forceinline__ void document_of(const Geom& g, int i, int& lo, int& hi)
@@ -48,18 +66,29 @@ __device__ __forceinline__ void queries_of(const Geom& g, int j, int causal, int
 // Where a workgroup's rows are: tile qw of 32 rows from `wr` (at or past `rows`: none), all of them in [r0, r1).
 struct Rows { int grp, wr, r0, r1; };
 
+template <int QW>
 __device__ __forceinline__ bool find_rows(const Geom& g, int rows, bool mirrored, int qw, Rows& x)
 {
     // groups one after another, each XCD a contiguous range, so that its workgroups share the partner rows in its L2
-    const int nblk = (rows + 63) / 64;
+    constexpr int HALF = QW / 2;
+    const int tiles = (rows + 31) / 32, nblk = (tiles + QW - 1) / QW;
     const unsigned units = (unsigned)g.G * (unsigned)nblk, per_xcd = (units + 7u) / 8u;
     const unsigned unit = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if ((blockIdx.x >> 3) >= per_xcd || unit >= units) return false;
     x.grp = (int)(unit / (unsigned)nblk);
-    const int b = (int)(unit % (unsigned)nblk), tiles = (rows + 31) / 32, last = tiles - 1 - b;
-    x.wr = 32 * (!mirrored ? 2 * b + qw : qw == 0 ? last : last == b ? tiles : b);
-    x.r0 = mirrored ? 32 * b : 64 * b;
-    x.r1 = min(rows, mirrored ? 32 * (tiles - b) : 64 * (b + 1));
+    const int b = (int)(unit % (unsigned)nblk);
+    if (!mirrored) {
+        x.wr = 32 * (QW * b + qw);
+        x.r0 = 32 * QW * b;
+        x.r1 = min(rows, 32 * QW * (b + 1));
+        return true;
+    }
+    // HALF tiles from the end, HALF from the start (none where the two meet)
+    const int late = tiles - 1 - HALF * b - qw, early = HALF * b + qw - HALF;
+    if (qw < HALF) x.wr = 32 * (late >= HALF * b ? late : tiles);
+    else x.wr = 32 * (early < tiles - HALF * (b + 1) ? early : tiles);
+    x.r0 = 32 * HALF * b;
+    x.r1 = min(rows, 32 * (tiles - HALF * b));
     return true;
 }
 
@@ -147,70 +176,98 @@ __device__ __forceinline__ void store_own(char* row, const f32x16 (&acc)[4], flo
         }
 }
 
-// The loads of step i of rows [lo, hi) of X and Y ([n][128], the group's) into their rings; rows at or past n are zeroed by settle().
+// The loads of step i of rows [lo, hi) of X and Y ([n][128], the group's) into their rings, with the rows' values of two fp32
+// arrays if sx is given; rows at or past n are zeroed by settle().
+template <typename Cf>
 struct Steps {
     const char *X, *Y;
     size_t base;
     int lo, hi, n;
     char *sX, *sY;
-    __device__ __forceinline__ int count() const { return hi > lo ? (hi - lo + SS_STEP - 1) / SS_STEP : 0; }
+    const char *vx, *vy;   // fp32 arrays of the group, or NULL
+    char* sv;              // [RING][BLOCKS][2][64]
+    __device__ __forceinline__ int count() const { return hi > lo ? (hi - lo + Cf::STEP - 1) / Cf::STEP : 0; }
     __device__ __forceinline__ void issue(int i, int w, int lane) const
     {
         uint32_t dvo[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) dvo[u] = dma_lane_off(2 * w + u, lane);
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int row = lo + i * SS_STEP + b * KB, o = (i & 1) * SS_TENSOR + b * STAGE_BYTES;
-            if (row < hi) dma_block<8>(X, Y, base, row, n, sX + o, sY + o, w, lane, dvo);
+        for (int b = 0; b < Cf::BLOCKS; ++b) {
+            const int row = lo + i * Cf::STEP + b * KB, o = (i % Cf::RING) * Cf::TENSOR + b * STAGE_BYTES;
+            if (row >= hi) continue;
+            dma_block<8>(X, Y, base, row, n, sX + o, sY + o, w, lane, dvo);
+            if (vx) {   // (every wave the same bytes to the same place, so that all have as many loads in flight)
+                const uint32_t vo = 4u * (uint32_t)min(row + lane, n - 1), d = lds_addr_of(sv) + ((i % Cf::RING) * Cf::BLOCKS + b) * 512;
+                dma4(vx, vo, d);
+                dma4(vy, vo, d + 256);
+            }
         }
     }
-    // step i has landed: what lies past the end is zero
-    __device__ __forceinline__ void settle(int i, int w, int lane) const
+    // step i has landed (with steps of one block: once only the younger ones are outstanding); what lies past the end is zero
+    __device__ __forceinline__ void settle(int i, int ns, int w, int lane) const
     {
-        wait_vmcnt<0>();
+        const int younger = Cf::BLOCKS > 1 ? 0 : min(Cf::RING - 2, ns - 1 - i);
+        if (younger >= 2) { if (vx) wait_vmcnt<12>(); else wait_vmcnt<8>(); }
+        else if (younger == 1) { if (vx) wait_vmcnt<6>(); else wait_vmcnt<4>(); }
+        else wait_vmcnt<0>();
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int row = lo + i * SS_STEP + b * KB, o = (i & 1) * SS_TENSOR + b * STAGE_BYTES;
+        for (int b = 0; b < Cf::BLOCKS; ++b) {
+            const int row = lo + i * Cf::STEP + b * KB, o = (i % Cf::RING) * Cf::TENSOR + b * STAGE_BYTES;
             if (row < hi && row + KB > n) zero_tail_rows<8>(row, n, sX + o, sY + o, w, lane);
         }
     }
+    __device__ __forceinline__ void start(int ns, int w, int lane) const
+    {
+        for (int i = 0; i < Cf::RING - 1 && i < ns; ++i) issue(i, w, lane);
+    }
+    // block until step i is in LDS for all; the step whose place is free then starts
+    __device__ __forceinline__ void enter(int i, int ns, int w, int lane) const
+    {
+        settle(i, ns, w, lane);
+        __syncthreads();   // complete in LDS; every wave is past step i - 1
+        if (i + Cf::RING - 1 < ns) issue(i + Cf::RING - 1, w, lane);
+    }
 };
 
-// The shares' accumulators of one kind, added up in the wave of share 0 (part: the tile's 3 x 64 places of 64 lanes).
+// The shares' accumulators of one kind, added up in the wave of share 0.
+template <int QW>
 __device__ __forceinline__ float* share_part(char* smem, int k, int qw, int regs, int lane)
 {
-    return reinterpret_cast<float*>(smem) + (((k - 1) * 2 + qw) * regs) * 64 + lane;
+    return reinterpret_cast<float*>(smem) + (((k - 1) * QW + qw) * regs) * 64 + lane;
 }
 
+template <int QW>
 __device__ __forceinline__ void add_shares(f32x16 (&acc)[4], char* smem, int kw, int qw, int lane)
 {
     __syncthreads();
     if (kw > 0) {
-        float* o = share_part(smem, kw, qw, 64, lane);
+        float* o = share_part<QW>(smem, kw, qw, 64, lane);
 #pragma unroll
         for (int i = 0; i < 64; ++i) o[64 * i] = acc[i >> 4][i & 15];
     }
     __syncthreads();
     if (kw == 0) {
 #pragma unroll 1
-        for (int k = 1; k < SS_KW; ++k) {
-            const float* o = share_part(smem, k, qw, 64, lane);
+        for (int k = 1; k < 8 / QW; ++k) {
+            const float* o = share_part<QW>(smem, k, qw, 64, lane);
 #pragma unroll
             for (int i = 0; i < 64; ++i) acc[i >> 4][i & 15] += o[64 * i];
         }
     }
 }
 
+template <int QW, int RING>
 __global__ __launch_bounds__(SS_THR) void softmax_fwd_small_kernel(Geom g, const char* __restrict__ Q, const char* __restrict__ K,
                                                                    const char* __restrict__ V, char* __restrict__ O,
                                                                    float* __restrict__ LSE, int causal, float c)
 {
+    typedef Cfg<QW, RING> Cf;
     extern __shared__ __attribute__((aligned(256))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), qw = w >> 2, kw = w & 3;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), qw = w / Cf::KW, kw = w % Cf::KW;
     Rows x;
-    if (!find_rows(g, g.qn, causal && g.n_seqs == 0, qw, x)) return;
+    if (!find_rows<QW>(g, g.qn, causal && g.n_seqs == 0, qw, x)) return;
     const int row = x.wr + l32;
     const bool valid = row < g.qn;
     int lo = 0, hi = 0, wlo = 0, whi = 0, klo, khi, t;
@@ -222,9 +279,9 @@ __global__ __launch_bounds__(SS_THR) void softmax_fwd_small_kernel(Geom g, const
     keys_of(g, g.q0 + x.r0, causal, klo, t);
     keys_of(g, g.q0 + x.r1 - 1, causal, t, khi);
     const unsigned span = (unsigned)max(hi - lo, 0);   // key j counts if (unsigned)(j - lo) < span
-    const Steps st = {K, V, (size_t)x.grp * g.N * ROWB, klo, khi, g.N, smem, smem + SS_RING};
+    const Steps<Cf> st = {K, V, (size_t)x.grp * g.N * ROWB, klo, khi, g.N, smem, smem + Cf::RINGB, nullptr, nullptr, nullptr};
     const int ns = st.count();
-    if (ns > 0) st.issue(0, w, lane);
+    st.start(ns, w, lane);
 
     const size_t qbase = (size_t)x.grp * g.qn * ROWB;
     bf16x8 q[8];
@@ -234,12 +291,10 @@ __global__ __launch_bounds__(SS_THR) void softmax_fwd_small_kernel(Geom g, const
     zero_acc(acc);
     float m = -INFINITY, l = 0.f;   // m: of the row's keys of this share, l: of this lane's half of them
     for (int i = 0; i < ns; ++i) {
-        st.settle(i, w, lane);
-        __syncthreads();   // the step is complete in LDS; every wave is past the one whose place the next takes
-        if (i + 1 < ns) st.issue(i + 1, w, lane);
-        const int t0 = klo + i * SS_STEP + 32 * kw;
+        st.enter(i, ns, w, lane);
+        const int t0 = klo + i * Cf::STEP + 32 * kw;
         if (t0 >= whi || t0 + 32 <= wlo) continue;
-        const uint32_t tk = lds_addr_of(smem) + (i & 1) * SS_TENSOR + kw * (32 * ROWB), tv = tk + SS_RING;
+        const uint32_t tk = lds_addr_of(smem) + (i % RING) * Cf::TENSOR + kw * (32 * ROWB), tv = tk + Cf::RINGB;
         f32x16 s = tile_scores(tk, a, q);
         float mx = -INFINITY;
 #pragma unroll
@@ -268,7 +323,7 @@ __global__ __launch_bounds__(SS_THR) void softmax_fwd_small_kernel(Geom g, const
     l += __shfl_xor(l, 32, 64);
     __syncthreads();
     if (kw > 0) {
-        float* o = share_part(smem, kw, qw, 66, lane);
+        float* o = share_part<QW>(smem, kw, qw, 66, lane);
 #pragma unroll
         for (int i = 0; i < 64; ++i) o[64 * i] = acc[i >> 4][i & 15];
         o[64 * 64] = m;
@@ -277,8 +332,8 @@ __global__ __launch_bounds__(SS_THR) void softmax_fwd_small_kernel(Geom g, const
     __syncthreads();
     if (kw > 0) return;
 #pragma unroll 1
-    for (int k = 1; k < SS_KW; ++k) {
-        const float* o = share_part(smem, k, qw, 66, lane);
+    for (int k = 1; k < 8 / QW; ++k) {
+        const float* o = share_part<QW>(smem, k, qw, 66, lane);
         const float om = o[64 * 64], mn = fmaxf(m, om), mu = mn == -INFINITY ? 0.f : mn;
         const float fa = __builtin_amdgcn_exp2f(m - mu), fb = __builtin_amdgcn_exp2f(om - mu);
         l = l * fa + o[65 * 64] * fb;
@@ -292,16 +347,18 @@ __global__ __launch_bounds__(SS_THR) void softmax_fwd_small_kernel(Geom g, const
 }
 
 // dQ = scale * sum_j dS_j k_j, dS = P (dO . v - delta), P rebuilt from the log-sum-exp
+template <int QW, int RING>
 __global__ __launch_bounds__(SS_THR) void softmax_bwd_dq_small_kernel(Geom g, const char* __restrict__ Q, const char* __restrict__ K,
                                                                       const char* __restrict__ V, const char* __restrict__ dO,
                                                                       const float* __restrict__ LSE, const float* __restrict__ delta,
                                                                       char* __restrict__ dQ, int causal, float c, float scale)
 {
+    typedef Cfg<QW, RING> Cf;
     extern __shared__ __attribute__((aligned(256))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), qw = w >> 2, kw = w & 3;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), qw = w / Cf::KW, kw = w % Cf::KW;
     Rows x;
-    if (!find_rows(g, g.qn, causal && g.n_seqs == 0, qw, x)) return;
+    if (!find_rows<QW>(g, g.qn, causal && g.n_seqs == 0, qw, x)) return;
     const int row = x.wr + l32;
     const bool valid = row < g.qn;
     int lo = 0, hi = 0, wlo = 0, whi = 0, klo, khi, t;
@@ -313,9 +370,9 @@ __global__ __launch_bounds__(SS_THR) void softmax_bwd_dq_small_kernel(Geom g, co
     keys_of(g, g.q0 + x.r0, causal, klo, t);
     keys_of(g, g.q0 + x.r1 - 1, causal, t, khi);
     const unsigned span = (unsigned)max(hi - lo, 0);
-    const Steps st = {K, V, (size_t)x.grp * g.N * ROWB, klo, khi, g.N, smem, smem + SS_RING};
+    const Steps<Cf> st = {K, V, (size_t)x.grp * g.N * ROWB, klo, khi, g.N, smem, smem + Cf::RINGB, nullptr, nullptr, nullptr};
     const int ns = st.count();
-    if (ns > 0) st.issue(0, w, lane);
+    st.start(ns, w, lane);
 
     const size_t qbase = (size_t)x.grp * g.qn * ROWB, at = (size_t)min(row, g.qn - 1);
     bf16x8 q[8], d[8];
@@ -326,12 +383,10 @@ __global__ __launch_bounds__(SS_THR) void softmax_bwd_dq_small_kernel(Geom g, co
     f32x16 acc[4];
     zero_acc(acc);
     for (int i = 0; i < ns; ++i) {
-        st.settle(i, w, lane);
-        __syncthreads();
-        if (i + 1 < ns) st.issue(i + 1, w, lane);
-        const int t0 = klo + i * SS_STEP + 32 * kw;
+        st.enter(i, ns, w, lane);
+        const int t0 = klo + i * Cf::STEP + 32 * kw;
         if (t0 >= whi || t0 + 32 <= wlo) continue;
-        const uint32_t tk = lds_addr_of(smem) + (i & 1) * SS_TENSOR + kw * (32 * ROWB), tv = tk + SS_RING;
+        const uint32_t tk = lds_addr_of(smem) + (i % RING) * Cf::TENSOR + kw * (32 * ROWB), tv = tk + Cf::RINGB;
         f32x16 s = tile_scores(tk, a, q);
         const f32x16 dp = tile_scores(tv, a, d);
 #pragma unroll
@@ -341,25 +396,27 @@ __global__ __launch_bounds__(SS_THR) void softmax_bwd_dq_small_kernel(Geom g, co
         }
         tile_add(acc, tk, a, s);
     }
-    add_shares(acc, smem, kw, qw, lane);
+    add_shares<QW>(acc, smem, kw, qw, lane);
     if (kw == 0 && valid) store_own(dQ + qbase + (size_t)row * ROWB, acc, scale, h);
 }
 
 // dV = sum_i P_i dO_i, dK = scale * sum_i dS_i q_i: a key per lane, its row of K in registers and of V in LDS (with two
 // accumulators both don't fit the 256 registers of two waves per SIMD); queries in steps with their statistics.
+template <int QW, int RING>
 __global__ __launch_bounds__(SS_THR) void softmax_bwd_dkv_small_kernel(Geom g, const char* __restrict__ Q, const char* __restrict__ K,
                                                                        const char* __restrict__ V, const char* __restrict__ dO,
-                                                                       const float* __restrict__ LSE, const float* __restrict__ delta,
+                                                                       const float* __restrict__ LSE2, const float* __restrict__ delta,
                                                                        char* __restrict__ dK, char* __restrict__ dV, int causal,
                                                                        float c, float scale)
 {
+    typedef Cfg<QW, RING> Cf;
     extern __shared__ __attribute__((aligned(256))) char smem[];
-    char* own = smem + 2 * SS_RING;                                            // [2 row tiles][32][128]
-    float* stat = reinterpret_cast<float*>(own + 2 * 32 * ROWB);               // [2 steps][2][SS_STEP]
+    char* own = smem + 2 * Cf::RINGB;          // [QW row tiles][32][128]
+    char* stat = own + QW * 32 * ROWB;         // [RING][BLOCKS][2][64]
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), qw = w >> 2, kw = w & 3;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), qw = w / Cf::KW, kw = w % Cf::KW;
     Rows x;
-    if (!find_rows(g, g.N, causal && g.n_seqs == 0, qw, x)) return;
+    if (!find_rows<QW>(g, g.N, causal && g.n_seqs == 0, qw, x)) return;
     const int row = x.wr + l32;
     const bool valid = row < g.N;
     int lo = 0, hi = 0, wlo = 0, whi = 0, ilo, ihi, t;
@@ -372,25 +429,20 @@ __global__ __launch_bounds__(SS_THR) void softmax_bwd_dkv_small_kernel(Geom g, c
     queries_of(g, x.r1 - 1, causal, t, ihi);
     const unsigned span = (unsigned)max(hi - lo, 0);
     // query rows are counted from the call's first
-    const Steps st = {Q, dO, (size_t)x.grp * g.qn * ROWB, ilo - g.q0, ihi - g.q0, g.qn, smem, smem + SS_RING};
+    const size_t first = (size_t)x.grp * g.qn;
+    const Steps<Cf> st = {Q, dO, first * ROWB, ilo - g.q0, ihi - g.q0, g.qn, smem, smem + Cf::RINGB,
+                          reinterpret_cast<const char*>(LSE2 + first), reinterpret_cast<const char*>(delta + first), stat};
     const int ns = st.count();
-    float sv = 0.f;
-    auto fetch_stat = [&](int i) {   // one value per thread of the first four waves
-        const int r = st.lo + i * SS_STEP + (tid & (SS_STEP - 1));
-        sv = 0.f;
-        if (tid < 2 * SS_STEP && r < st.hi)
-            sv = tid < SS_STEP ? LSE[(size_t)x.grp * g.qn + r] * kLog2e : delta[(size_t)x.grp * g.qn + r];
-    };
-    if (ns > 0) { st.issue(0, w, lane); fetch_stat(0); }
+    st.start(ns, w, lane);
 
     const size_t kbase = (size_t)x.grp * g.N * ROWB;
     bf16x8 k[8];
     load_own(k, K + kbase + (size_t)min(row, g.N - 1) * ROWB, valid, h);
-    {   // the tile's four waves take eight rows of V each (published by the first step's barrier)
+    {   // the tile's KW waves take 32 / KW rows of V each (published by the first step's barrier)
         char* o = own + qw * 32 * ROWB;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int r = 8 * kw + 4 * u + (lane >> 4), ch = lane & 15;
+        for (int u = 0; u < 8 / Cf::KW; ++u) {
+            const int r = (32 / Cf::KW) * kw + 4 * u + (lane >> 4), ch = lane & 15;
             const u32x4 z = {0u, 0u, 0u, 0u};
             *reinterpret_cast<u32x4*>(o + tile_off(r, ch)) =
                 x.wr + r < g.N ? *reinterpret_cast<const u32x4*>(V + kbase + (size_t)(x.wr + r) * ROWB + 16 * ch) : z;
@@ -401,20 +453,16 @@ __global__ __launch_bounds__(SS_THR) void softmax_bwd_dkv_small_kernel(Geom g, c
     zero_acc(ak);
     zero_acc(av);
     for (int i = 0; i < ns; ++i) {
-        st.settle(i, w, lane);
-        float* sl = stat + (i & 1) * (2 * SS_STEP);
-        if (tid < 2 * SS_STEP) sl[tid] = sv;
-        __syncthreads();
-        if (i + 1 < ns) { st.issue(i + 1, w, lane); fetch_stat(i + 1); }
-        const int t0 = ilo + i * SS_STEP + 32 * kw;   // token of the tile's first query
+        st.enter(i, ns, w, lane);
+        const int t0 = ilo + i * Cf::STEP + 32 * kw;   // token of the tile's first query
         if (t0 >= whi || t0 + 32 <= wlo) continue;
-        const uint32_t tq = lds_addr_of(smem) + (i & 1) * SS_TENSOR + kw * (32 * ROWB), td = tq + SS_RING;
+        const uint32_t tq = lds_addr_of(smem) + (i % RING) * Cf::TENSOR + kw * (32 * ROWB), td = tq + Cf::RINGB;
         f32x16 s = tile_scores(tq, a, k);
         f32x16 dp = tile_scores(td, a, lds_addr_of(own) + qw * 32 * ROWB);
-        const float* ls = sl + 32 * kw + 4 * h;
+        const float* ls = reinterpret_cast<const float*>(stat + ((i % RING) * Cf::BLOCKS + kw / 2) * 512) + 32 * (kw & 1) + 4 * h;
 #pragma unroll
         for (int v = 0; v < 16; v += 4) {
-            const f32x4 le = *reinterpret_cast<const f32x4*>(ls + 2 * v), de = *reinterpret_cast<const f32x4*>(ls + SS_STEP + 2 * v);
+            const f32x4 le = *reinterpret_cast<const f32x4*>(ls + 2 * v), de = *reinterpret_cast<const f32x4*>(ls + 64 + 2 * v);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const bool keep = (unsigned)(t0 + 2 * v + e + 4 * h - lo) < span;
@@ -426,56 +474,86 @@ __global__ __launch_bounds__(SS_THR) void softmax_bwd_dkv_small_kernel(Geom g, c
         tile_add(av, td, a, s);
         tile_add(ak, tq, a, dp);
     }
-    add_shares(ak, smem, kw, qw, lane);
-    add_shares(av, smem, kw, qw, lane);
+    add_shares<QW>(ak, smem, kw, qw, lane);
+    add_shares<QW>(av, smem, kw, qw, lane);
     if (kw > 0 || !valid) return;
     store_own(dK + kbase + (size_t)row * ROWB, ak, scale, h);
     store_own(dV + kbase + (size_t)row * ROWB, av, 1.f, h);
 }
 
+const float kScale = 0.08838834764831845f;   // 1 / sqrt(128)
+
+template <int QW>
 unsigned small_grid(const Geom& g, int rows)
 {
-    const unsigned units = (unsigned)g.G * (unsigned)((rows + 63) / 64);
+    const unsigned units = (unsigned)g.G * (unsigned)((rows + 32 * QW - 1) / (32 * QW));
     return 8u * ((units + 7u) / 8u);
 }
 
-constexpr int kSmallLds = 2 * SS_RING, kSmallLdsKv = kSmallLds + 2 * 32 * ROWB + 2 * 2 * SS_STEP * 4;
-const float kScale = 0.08838834764831845f;   // 1 / sqrt(128)
+// RING: what the LDS holds (64 KB a step of 128 rows, 32 KB of 64)
+template <int QW, int RING>
+hipError_t fwd_small(const Geom& g, const char* Q, const char* K, const char* V, char* O, float* LSE, int causal, hipStream_t st)
+{
+    constexpr int lds = 2 * Cfg<QW, RING>::RINGB;
+    hipError_t e = allow_dynamic_lds<softmax_fwd_small_kernel<QW, RING>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((softmax_fwd_small_kernel<QW, RING>), dim3(small_grid<QW>(g, g.qn)), dim3(SS_THR), lds, st, g, Q, K, V, O, LSE,
+                       causal, kScale * kLog2e);
+    return hipGetLastError();
+}
+
+template <int QW, int RING>
+hipError_t dq_small(const Geom& g, const char* Q, const char* K, const char* V, const char* dO, const float* LSE, const float* delta,
+                    char* dQ, int causal, hipStream_t st)
+{
+    constexpr int lds = 2 * Cfg<QW, RING>::RINGB;
+    hipError_t e = allow_dynamic_lds<softmax_bwd_dq_small_kernel<QW, RING>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((softmax_bwd_dq_small_kernel<QW, RING>), dim3(small_grid<QW>(g, g.qn)), dim3(SS_THR), lds, st, g, Q, K, V, dO,
+                       LSE, delta, dQ, causal, kScale * kLog2e, kScale);
+    return hipGetLastError();
+}
+
+template <int QW, int RING>
+hipError_t dkv_small(const Geom& g, const char* Q, const char* K, const char* V, const char* dO, const float* LSE2, const float* delta,
+                     char* dK, char* dV, int causal, hipStream_t st)
+{
+    typedef Cfg<QW, RING> Cf;
+    constexpr int lds = 2 * Cf::RINGB + QW * 32 * ROWB + RING * Cf::BLOCKS * 512;
+    hipError_t e = allow_dynamic_lds<softmax_bwd_dkv_small_kernel<QW, RING>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((softmax_bwd_dkv_small_kernel<QW, RING>), dim3(small_grid<QW>(g, g.N)), dim3(SS_THR), lds, st, g, Q, K, V, dO,
+                       LSE2, delta, dK, dV, causal, kScale * kLog2e, kScale);
+    return hipGetLastError();
+}
 
 }  // namespace
 
-hipError_t launch_softmax_fwd_small(const Geom& g, const void* Q, const void* K, const void* V, void* O, float* LSE, int causal,
-                                    hipStream_t st)
+hipError_t launch_softmax_fwd_small(const Geom& g, int tiles, const void* Q_, const void* K_, const void* V_, void* O_, float* LSE,
+                                    int causal, hipStream_t st)
 {
-    hipError_t e = allow_dynamic_lds<softmax_fwd_small_kernel>(kSmallLds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(softmax_fwd_small_kernel, dim3(small_grid(g, g.qn)), dim3(SS_THR), kSmallLds, st, g, static_cast<const char*>(Q),
-                       static_cast<const char*>(K), static_cast<const char*>(V), static_cast<char*>(O), LSE, causal, kScale * kLog2e);
-    return hipGetLastError();
+    const char *Q = static_cast<const char*>(Q_), *K = static_cast<const char*>(K_), *V = static_cast<const char*>(V_);
+    char* O = static_cast<char*>(O_);
+    return tiles == 2 ? fwd_small<2, 2>(g, Q, K, V, O, LSE, causal, st) : fwd_small<4, 4>(g, Q, K, V, O, LSE, causal, st);
 }
 
-hipError_t launch_softmax_bwd_dq_small(const Geom& g, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
-                                       const float* delta, void* dQ, int causal, hipStream_t st)
+hipError_t launch_softmax_bwd_dq_small(const Geom& g, const void* Q_, const void* K_, const void* V_, const void* dO_,
+                                       const float* LSE, const float* delta, void* dQ_, int causal, hipStream_t st)
 {
     if (g.qn == 0) return hipSuccess;
-    hipError_t e = allow_dynamic_lds<softmax_bwd_dq_small_kernel>(kSmallLds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(softmax_bwd_dq_small_kernel, dim3(small_grid(g, g.qn)), dim3(SS_THR), kSmallLds, st, g,
-                       static_cast<const char*>(Q), static_cast<const char*>(K), static_cast<const char*>(V),
-                       static_cast<const char*>(dO), LSE, delta, static_cast<char*>(dQ), causal, kScale * kLog2e, kScale);
-    return hipGetLastError();
+    const char *Q = static_cast<const char*>(Q_), *K = static_cast<const char*>(K_), *V = static_cast<const char*>(V_);
+    const char* dO = static_cast<const char*>(dO_);
+    char* dQ = static_cast<char*>(dQ_);
+    return dq_small<2, 2>(g, Q, K, V, dO, LSE, delta, dQ, causal, st);
 }
 
-hipError_t launch_softmax_bwd_dkv_small(const Geom& g, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
-                                        const float* delta, void* dK, void* dV, int causal, hipStream_t st)
+hipError_t launch_softmax_bwd_dkv_small(const Geom& g, const void* Q_, const void* K_, const void* V_, const void* dO_,
+                                        const float* LSE2, const float* delta, void* dK_, void* dV_, int causal, hipStream_t st)
 {
-    hipError_t e = allow_dynamic_lds<softmax_bwd_dkv_small_kernel>(kSmallLdsKv);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(softmax_bwd_dkv_small_kernel, dim3(small_grid(g, g.N)), dim3(SS_THR), kSmallLdsKv, st, g,
-                       static_cast<const char*>(Q), static_cast<const char*>(K), static_cast<const char*>(V),
-                       static_cast<const char*>(dO), LSE, delta, static_cast<char*>(dK), static_cast<char*>(dV), causal, kScale * kLog2e,
-                       kScale);
-    return hipGetLastError();
+    const char *Q = static_cast<const char*>(Q_), *K = static_cast<const char*>(K_), *V = static_cast<const char*>(V_);
+    const char* dO = static_cast<const char*>(dO_);
+    char *dK = static_cast<char*>(dK_), *dV = static_cast<char*>(dV_);
+    return dkv_small<2, 2>(g, Q, K, V, dO, LSE2, delta, dK, dV, causal, st);
 }
 
 }  // namespace lasp2

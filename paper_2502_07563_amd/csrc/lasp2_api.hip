@@ -829,11 +829,12 @@ static int softmax_geom(const lasp2_desc_t* desc, int64_t q_begin, int64_t q_len
     return LASP2_OK;
 }
 
-// Launches of at most one workgroup of 64 rows per CU: 256 queries (128 keys) a workgroup would leave most CUs idle while the longest
-// row sets the time.  With more of them the small kernels' traffic (a step of 64 KB per 64 rows) costs more than the idle CUs.
-// bf16 x 128, 256-row kernels | these, us: 16 heads x 1 000 causal, forward 37 | 20, backward 82 | 53; 4 x 4 000 111 | 55, 260 | 148;
-// 16 heads, the last 1 000 of 16 000 428 | 228; and beyond the line 20 x 1 692 57 | 69, 135 | 178; 64 x 348 unmasked 19 | 24, 49 | 66.
-static bool softmax_small(const Geom& g, int rows) { return (int64_t)g.G * ((rows + 63) / 64) <= cu_count(); }
+// Launches of at most one workgroup of 64 rows (forward: or 128) per CU: 256 queries (128 keys) a workgroup would leave most CUs idle
+// while the longest row sets the time.  With more of them the small kernels' traffic costs more than the idle CUs.  bf16 x
+// 128, 256-row kernels | 64 rows, 128 rows, us: 16 heads x 1 000 causal, forward 37 | 20, 25, backward 82 | 53; 4 x 4 000 112 | 54, 74,
+// 260 | 139; 16 heads, the last 1 000 of 16 000 438 | 231, 357; 32 x 1 000 (512 and 256 of them) 36 | 33, 26, 84 | 92; and beyond
+// the lines 20 x 1 692 (540, 280) 57 | 67, 61, 132 | 170; 16 x 4 000 124 | 163, 134, 315 | 410.
+static bool softmax_rows_fit(const Geom& g, int rows, int per) { return (int64_t)g.G * ((rows + per - 1) / per) <= cu_count(); }
 
 static int softmax_fwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q_len, const void* Q,
                             const void* K, const void* V, void* O, float* LSE, int causal, void* stream)
@@ -846,8 +847,9 @@ static int softmax_fwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q
     rc = check_ptrs({Q, K, V, O, LSE});
     if (rc != LASP2_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
+    const int small = softmax_rows_fit(g, g.qn, 64) ? 2 : softmax_rows_fit(g, g.qn, 128) ? 4 : 0;   // row tiles per workgroup
     if (softmax_mfma_supported(g, desc->dtype))
-        return from_hip(softmax_small(g, g.qn) ? launch_softmax_fwd_small(g, Q, K, V, O, LSE, causal ? 1 : 0, st)
+        return from_hip(small ? launch_softmax_fwd_small(g, small, Q, K, V, O, LSE, causal ? 1 : 0, st)
                                                : launch_softmax_fwd_mfma(g, Q, K, V, O, LSE, causal ? 1 : 0, st));
     return from_hip(launch_softmax_fwd_planes(g, desc->dtype, Q, K, V, O, LSE, causal ? 1 : 0, st));
 }
@@ -874,10 +876,10 @@ static int softmax_bwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q
     hipError_t e = launch_softmax_delta(g, desc->dtype, O, dO, LSE, delta, fast ? lse2 : nullptr, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     if (fast) {
-        e = softmax_small(g, g.qn) ? launch_softmax_bwd_dq_small(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st)
+        e = softmax_rows_fit(g, g.qn, 64) ? launch_softmax_bwd_dq_small(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st)
                                    : launch_softmax_bwd_dq_mfma(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
-        return from_hip(softmax_small(g, g.N) ? launch_softmax_bwd_dkv_small(g, Q, K, V, dO, LSE, delta, dK, dV, causal ? 1 : 0, st)
+        return from_hip(softmax_rows_fit(g, g.N, 64) ? launch_softmax_bwd_dkv_small(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st)
                                               : launch_softmax_bwd_dkv_mfma(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st));
     }
     return from_hip(launch_softmax_bwd_planes(g, desc->dtype, Q, K, V, dO, LSE, delta, dQ, dK, dV,

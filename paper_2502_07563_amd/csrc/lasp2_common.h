@@ -272,12 +272,13 @@ hipError_t launch_softmax_bwd_planes(const Geom& g, int dtype, const void* Q, co
                                      const void* V, const void* dO, const float* LSE, const float* delta,
                                      void* dQ, void* dK, void* dV, int causal, hipStream_t st);
 bool softmax_mfma_supported(const Geom& g, int dtype);
-// bf16, d = 128, launches too small for the kernels below (LSE: natural)
-hipError_t launch_softmax_fwd_small(const Geom& g, const void* Q, const void* K, const void* V, void* O, float* LSE, int causal,
+// bf16, d = 128, launches too small for the kernels below; tiles: 2 or 4 row tiles of 32 per workgroup,
+// backward 2 (LSE2: base 2)
+hipError_t launch_softmax_fwd_small(const Geom& g, int tiles, const void* Q, const void* K, const void* V, void* O, float* LSE, int causal,
                                     hipStream_t st);
 hipError_t launch_softmax_bwd_dq_small(const Geom& g, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
                                        const float* delta, void* dQ, int causal, hipStream_t st);
-hipError_t launch_softmax_bwd_dkv_small(const Geom& g, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
+hipError_t launch_softmax_bwd_dkv_small(const Geom& g, const void* Q, const void* K, const void* V, const void* dO, const float* LSE2,
                                         const float* delta, void* dK, void* dV, int causal, hipStream_t st);
 hipError_t launch_softmax_bwd_dq_mfma(const Geom& g, const void* Q, const void* K, const void* V,
                                       const void* dO, const float* LSE, const float* delta, void* dQ,

@@ -1,7 +1,7 @@
 """bf16 heads of 128, softmax: the kernels for launches of at most a workgroup of 64 rows per CU and those for more (the
 same lengths with many heads), against the definition in 64 bits: one row more or less than row tiles, steps of 128 partner
 rows and blocks of 256 queries; mirrored row tiles with an odd number of them; documents; one rank's share, with fewer
-queries than a tile and with forward and dK, dV on different sides of the line."""
+queries than a tile and with forward and dK, dV on different sides of a line."""
 import numpy as np
 import pytest
 import torch
@@ -15,12 +15,12 @@ SIZES = [(1, None, None), (31, None, None), (65, None, None), (95, None, None), 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("heads", [2, 0])   # 0: so many that no kernel's launch is small
+@pytest.mark.parametrize("per_cu", [0, 64, 128])   # two heads, or just too many for that many rows per workgroup and CU
 @pytest.mark.parametrize("N,share,docs", SIZES)
-def test_bf16_d128(N, share, docs, heads, causal):
+def test_bf16_d128(N, share, docs, per_cu, causal):
     q0, n = share or (0, N)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    H = heads or cus // -(-max(min(n, N), 1) // 64) + 1
+    H = cus // -(-max(n, 1) // per_cu) + 1 if per_cu else 2
     d, cu = 128, np.concatenate([[0], np.cumsum(docs or [N])]).astype(np.int32)
     p = bd.Problem(1, H, N, d, 64, 0, "bf16", cu if docs else None)
     gen = torch.Generator(device="cuda").manual_seed(N + n)
