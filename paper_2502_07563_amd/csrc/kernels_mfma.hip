@@ -1783,9 +1783,11 @@ __global__ __launch_bounds__(512) void attn_bwd_pair_mfma_kernel(Geom g, AttnPro
 // Eight waves: four quadrants of 2 x 2 tiles, each by two waves that take the halves of a 64-row stage (an
 // operand is read from LDS once per two products; the walks' own update, one row of tiles per wave, reads three per
 // two); a ring of four stages, three on their way.  The halves are added through LDS at the end.
+// With decay (l2: log2 of the factor) row r counts lam^(ntok - 1 - r), or lam^r if anchor_start, and base lam^ntok.
+template <bool DECAY = false>
 __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_t row0, int ntok, float sign,
                                              float* copy, const float* base, bool base_transposed, char* smem, int tid,
-                                             int w)
+                                             int w, float l2 = 0.f, bool anchor_start = false)
 {
     constexpr int NST = 4, DPS = 4;
     int lane;   // (opaque: nothing derived from it is kept for the walk)
@@ -1826,6 +1828,14 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
         else if (i + 1 < nst) wait_vmcnt<DPS>();
         else wait_vmcnt<0>();
         if (i * KB + KB > ntok) zero_tail_rows<8>(i * KB, ntok, tx, ty, w, lane);
+        if (DECAY) {   // each wave the rows it fetched (a row takes one weight: the swizzle does not matter)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int b = 4 * (2 * w + u) + (lane >> 4), r = i * KB + b;
+                u32x4* p = reinterpret_cast<u32x4*>(tx + b * ROWB + (lane & 15) * 16);
+                *p = scale_bf16x8(*p, __builtin_amdgcn_exp2f((float)(anchor_start ? r : max(ntok - 1 - r, 0)) * l2));
+            }
+        }
         __syncthreads();   // complete in LDS; every wave is past stage i - 1, whose place stage i + 3 takes
         if (i + NST - 1 < nst) issue(i + NST - 1);
 #pragma unroll
@@ -1860,6 +1870,7 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
         }
     __syncthreads();
     f32x4* M = reinterpret_cast<f32x4*>(smem + GATHERED + w * 8192) + lane;
+    const float wbase = DECAY ? __builtin_amdgcn_exp2f((float)ntok * l2) : 1.f;
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -1870,7 +1881,7 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
             if (base) {
                 const int r = 32 * (w >> 1) + 8 * q + 4 * h, c = 64 * qb + 32 * b + (lane & 31);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) p[e] += base_transposed ? base[c * D + r + e] : base[(r + e) * D + c];
+                for (int e = 0; e < 4; ++e) p[e] = fmaf(wbase, base_transposed ? base[c * D + r + e] : base[(r + e) * D + c], p[e]);
             }
             if (copy) {
 #pragma unroll
@@ -1900,6 +1911,62 @@ __global__ __launch_bounds__(512) void attn_fwd_direct_mfma_kernel(Geom g, AttnP
     const int rb = w < 4 ? w : 11 - w;   // waves w and w+4 share a SIMD: row blocks s and 7-s
     if (rb < 4) skew_walk<false, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
     else skew_walk<true, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
+}
+
+// The same two with scalar decay: the three backward problems have a workgroup each, and the anti-causal ones (first in the
+// grid) gather the exclusive suffix beyond their walk.
+__global__ __launch_bounds__(512) void attn_decay_fwd_direct_kernel(Geom g, AttnProblem pr)
+{
+    extern __shared__ __attribute__((aligned(256))) char smem[];
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned unit = gridDim.x - 1 - blockIdx.x;
+    const int s = (int)(unit / (unsigned)g.G), grp = (int)(unit % (unsigned)g.G);
+    int tok0, len, ps, doc0, doc1, slot0, slot1;
+    slot_range<true>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
+    if (len <= 0) return;
+    const int from = pr.state ? slot0 : doc0;
+    const float* base = pr.state ? pr.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) : nullptr;
+    gather_state<true>(pr.Bk, pr.Cv, ((size_t)grp * g.N + from) * ROWB, tok0 - from, 1.f, nullptr, base, false, smem, tid, w,
+                       decay_log2(g, grp));
+    const bool first = !g.W || tok0 == slot0;
+    const int rb = w < 4 ? w : 11 - w;
+    if (rb < 4) skew_walk<false, false, true, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
+    else skew_walk<true, false, true, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
+}
+
+__global__ __launch_bounds__(512) void attn_decay_bwd_direct_kernel(Geom g, AttnProblem pq, AttnProblem pv, AttnProblem pk, float* dR,
+                                                                    int from_dR)
+{
+    extern __shared__ __attribute__((aligned(256))) char smem[];
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned units = gridDim.x / 3, prob = blockIdx.x / units, unit = blockIdx.x % units;
+    const int s = (int)(unit / (unsigned)g.G), grp = (int)(unit % (unsigned)g.G);
+    int tok0, len, ps, doc0, doc1, slot0, slot1;
+    slot_range<true>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
+    if (len <= 0) return;
+    const float l2 = decay_log2(g, grp);
+    const int rb = w < 4 ? w : 11 - w;
+    const size_t slot = ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D);
+    if (prob < 2) {
+        const AttnProblem& pr = prob == 0 ? pv : pk;
+        const int end = tok0 + len, to = from_dR ? slot1 : doc1;
+        const float* beyond = from_dR && slot1 < doc1 ? dR + slot : nullptr;
+        // (the suffix states stay behind in dR, one per walk, or per slot if walks are shorter)
+        float* copy = prob != 0 || from_dR || !dR ? nullptr : !g.W ? dR + ((size_t)grp * g.T_s + s) * (size_t)(D * D)
+                                                           : end == slot1 ? dR + slot : nullptr;
+        gather_state<true>(pr.Bk, pr.Cv, ((size_t)grp * g.N + (to > end ? end : tok0)) * ROWB, to - end, 1.f, copy, beyond, prob == 1, smem,
+                           tid, w, l2, true);
+        if (rb < 4) skew_walk<false, true, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, 0, true);
+        else skew_walk<true, true, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, 0, true);
+    } else {
+        const int rows = g.W ? tok0 - slot0 : 0;
+        gather_state<true>(pq.Bk, pq.Cv, ((size_t)grp * g.N + tok0 - rows) * ROWB, rows, 1.f, nullptr, pq.state ? pq.state + slot : nullptr,
+                           true, smem, tid, w, l2);
+        if (rb < 4) skew_walk<false, false, true>(g, pq, smem, tid, w, rb, grp, s, tok0, len, nullptr, 0, true);
+        else skew_walk<true, false, true>(g, pq, smem, tid, w, rb, grp, s, tok0, len, nullptr, 0, true);
+    }
 }
 
 __global__ __launch_bounds__(512) void attn_bwd_direct_mfma_kernel(Geom g, AttnProblem pq, PairProblem pp, int from_dR)
@@ -2507,9 +2574,9 @@ hipError_t launch_attn_fwd_direct_mfma(const Geom& g, const void* Q, const void*
     constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
     AttnProblem p = make_problem(Q, K, V, state, 1, O, 0, 0);
     p.emit = emit;
-    hipError_t e = allow_dynamic_lds<attn_fwd_direct_mfma_kernel>(smem);
+    hipError_t e = g.decay ? allow_dynamic_lds<attn_decay_fwd_direct_kernel>(smem) : allow_dynamic_lds<attn_fwd_direct_mfma_kernel>(smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_fwd_direct_mfma_kernel, dim3((unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, p);
+    hipLaunchKernelGGL((g.decay ? attn_decay_fwd_direct_kernel : attn_fwd_direct_mfma_kernel), dim3((unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, p);
     return hipGetLastError();
 }
 
@@ -2518,6 +2585,14 @@ hipError_t launch_attn_bwd_direct_mfma(const Geom& g, const void* Q, const void*
 {
     constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
     const AttnProblem pq = make_problem(dO, V, K, P, 1, dQ, 1, 0);
+    if (g.decay) {
+        const AttnProblem pv = make_problem(K, Q, dO, nullptr, 0, dV, 0, 1), pk = make_problem(V, dO, Q, nullptr, 0, dK, 1, 1);
+        hipError_t e = allow_dynamic_lds<attn_decay_bwd_direct_kernel>(smem);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(attn_decay_bwd_direct_kernel, dim3(3u * (unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, pq, pv, pk,
+                           dR, from_dR);
+        return hipGetLastError();
+    }
     const PairProblem pp = {static_cast<const char*>(Q), static_cast<const char*>(dO), static_cast<const char*>(K),
                             static_cast<const char*>(V), dR, static_cast<char*>(dV), static_cast<char*>(dK), nullptr};
     hipError_t e = allow_dynamic_lds<attn_bwd_direct_mfma_kernel>(smem);

@@ -227,7 +227,7 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
 // walk, and whether the walks gather the state they start from themselves (`direct`: one launch, no states and prefix
 // before it).  Both from an estimate in us of what each choice costs, with the rates below; the candidates are the shortest
 // walks that fit into one to sixteen rounds of workgroups, or powers of two for documents of different lengths.
-//   - A row of a walk takes 0.03 us forward (dQ 0.031, the pair of the backward 0.0376), starting a walk what 256 (180)
+//   - A row of a walk takes 0.03 us forward (dQ 0.031, the pair of the backward 0.0376; with decay 0.033 each, and 0.009 gathered), starting a walk what 256 (180)
 //     rows do, a row that is gathered 0.0068 (16 heads, walks of 256, gathered | states first, us: 300 rows 15 | 22; 1 024
 //     20 | 24; 2 048 28 | 30; 3 000 37 | 31; 4 096 45 | 36; backward 20 | 27, 25 | 32, 34 | 37, 44 | 46, 58 | 50).
 //   - Memory: 5.2 TB/s, 8 where the tensors fit the 256 MB cache.  The one-launch backward reads four tensors more, as its two
@@ -289,18 +289,20 @@ WalkCount count_walks(const Geom& g, const int32_t* cu_host, int64_t W)
     return c;
 }
 
-// `par`: walks that run at a time.  may_states = false: the states are there already (lasp2_attn_fwd)
-WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backward, bool may_gather, bool may_states)
+// may_states = false: the states are there already (lasp2_attn_fwd)
+WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, bool backward, bool may_states)
 {
     const int64_t longest = longest_sequence(g, cu_host), slots = (longest + g.L - 1) / g.L;
-    const double G = g.G, N = g.N, cus = cu_count(), start = backward ? 180.0 : 256.0;
-    const double row = backward ? 0.0376 : 0.03, gather = 0.0068;
+    const int wgs = !backward ? 1 : g.decay ? 3 : 2;   // workgroups per walk
+    const double G = g.G, N = g.N, cus = cu_count(), par = cus / wgs, start = backward ? 180.0 : 256.0;
+    const double row = g.decay ? 0.033 : backward ? 0.0376 : 0.03, gather = g.decay ? 0.009 : 0.0068;
+    const double per_row = g.decay ? 3.0 * row : row + 0.031, ends = g.decay ? 2.0 : 1.0;   // backward: of all workgroups of a walk; that gather `after`
     auto estimate = [&](int64_t W, Start how) {
         const WalkCount c = count_walks(g, cu_host, W);
         const double tensor = G * N * 256.0, states = G * N / (double)g.L * 65536.0;
         const double rate = (backward ? 7.0 : 4.0) * tensor < 2.56e8 ? 8e6 : 5.2e6;
-        const double memory = (backward ? 7.0 * tensor : 4.0 * tensor + states) / rate * (!backward && c.walks * G <= par && W > 8192 ? 1.04 : 1.0);
-        const double one = (c.longest + start) * row, rounds = std::ceil(c.walks * G / par);
+        const double memory = (backward ? 7.0 * tensor : 4.0 * tensor + states) / rate * (!backward && c.walks * G <= par && W > (g.decay ? 4096 : 8192) ? 1.04 : 1.0);
+        const double one = (c.longest + start) * row, rounds = std::ceil(c.walks * G * wgs / cus);
         const double walk = g.n_seqs ? std::max(one, G * (N + start * c.walks) * row / par)
                                      : rounds * one * (rounds > 1.0 ? 1.0 : backward ? 1.08 : 1.03);
         const double tail = 0.05 * walk + (g.n_seqs && rounds > 1.0 ? 0.6 * one : 0.0);
@@ -316,12 +318,13 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backwar
             return unsure * (std::max({walk + again + rows * gather / par, one + (in ? c.farthest_in : c.farthest) * gather,
                                        memory + rows * 512.0 / cache}) + tail + (in ? first : 0.0));
         }
-        const double first = 10.0 + std::max(2.0 * tensor / 6e6 * uneven, c.longest_part * 0.0127) + moved * c.parts;
+        const double first = g.decay && c.inner == 0.0 ? 0.0   // (exclusive suffixes, all zero)
+                             : 10.0 + std::max(2.0 * tensor / 6e6 * uneven, c.longest_part * 0.0127) + moved * c.parts;
         if (how == Start::states) return std::max(walk, memory) + tail + first;
         const bool in = how == Start::both;
         const double far = in ? std::min((double)longest, (double)g.L) : (double)longest;
-        const double rows = G * ((in ? c.after_in : c.after) + (W < g.L ? c.before_in : 0.0));
-        const double all = (rows * gather + G * (N + start * c.walks) * (row + 0.031)) / cus;
+        const double rows = G * (ends * (in ? c.after_in : c.after) + (W < g.L ? c.before_in : 0.0));
+        const double all = (rows * gather + G * (N + start * c.walks) * per_row) / cus;
         const double passes = tensor < 2e8 ? 11.0 : 17.0;
         return unsure * (std::max({1.5 * far * gather + 1.08 * one + 0.1 * all, 1.1 * all, passes * tensor / rate + rows * 512.0 / 1e7}) + 0.15 * all +
                          (in ? first : 0.0));
@@ -337,12 +340,12 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backwar
     const bool lone = slots <= 1;
     auto offer = [&](int64_t ws) {
         take({(int)ws, 0, Start::states});
-        if (may_gather && (may_states || backward)) take({(int)ws, 0, Start::gather});
+        if (may_states || backward) take({(int)ws, 0, Start::gather});
     };
     // walks of about W tokens inside the slots
     auto offer_short = [&](int64_t W) {
         W = std::max<int64_t>(256, (W + 63) / 64 * 64);
-        if (!may_gather || forced || W >= std::min(g.L, longest)) return;
+        if (forced || W >= std::min(g.L, longest)) return;
         if (may_states || lone) take({1, W, Start::gather});
         if (!lone) take({1, W, Start::both});
     };
@@ -360,7 +363,7 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backwar
         for (int64_t W = (std::min(g.L, longest) + 1) / 2; W >= 256; W /= 2) offer_short(W);
     } else {
         for (int k = 1; k <= 16; ++k) {
-            const int64_t m = (int64_t)k * par / g.G;   // walks per sequence
+            const int64_t m = (int64_t)k * cu_count() / ((int64_t)wgs * g.G);   // walks per sequence
             if (m < 1) continue;
             const int64_t ws = std::min(ws_max, std::max(ws_min, (slots + m - 1) / m)), W = (g.N + m - 1) / m;
             if (!lone && !forced) offer(ws);
@@ -372,16 +375,16 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, int par, bool backwar
     return best;
 }
 
-WalkPlan pick_bwd_walks(const Geom& g, const int32_t* cu_host, int par)
+WalkPlan pick_bwd_walks(const Geom& g, const int32_t* cu_host)
 {
     if (g.G == 0) return {1, 0, Start::states};
-    return pick_walks(g, cu_host, std::max(1, par), true, !g.decay, true);
+    return pick_walks(g, cu_host, true, true);
 }
 
 // (slots of other lengths: no state of theirs stands between two blocks of a walk)
 WalkPlan pick_forward_walks(const Geom& g, const int32_t* cu_host)
 {
-    if (g.L % 64 == 0) return pick_walks(g, cu_host, cu_count(), false, !g.decay, true);
+    if (g.L % 64 == 0) return pick_walks(g, cu_host, false, true);
     return {pick_walk_slots(g, cu_host, cu_count(), kWalkTargetFwd), 0, Start::states};
 }
 
@@ -503,8 +506,7 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     pl->gw = g;
     pl->start = Start::states;
     if (pl->fast) {
-        const int wgs = g.decay ? 3 : 2;   // workgroups per walk in the attention launch
-        const WalkPlan wp = pick_bwd_walks(g, desc->cu_seqlens_host, cu_count() / wgs);
+        const WalkPlan wp = pick_bwd_walks(g, desc->cu_seqlens_host);
         pl->gw = regroup(g, desc->cu_seqlens_host, wp);
         pl->start = wp.start;
     }
@@ -522,7 +524,7 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const int32_t* cu_host, const voi
     if (pl.start == Start::gather) return from_hip(launch_attn_bwd_direct_mfma(g, Q, K, V, dO, P, dR, 0, dQ, dK, dV, st));
     if (pl.start == Start::both) {   // suffix states per slot
         if (run_states(pl.g, dtype, Q, dO, dR, 1, st) != hipSuccess) return LASP2_ERR_LAUNCH;
-        if (launch_state_prefix(pl.g, dR, dR, 1, 1, 0, nullptr, 0, st) != hipSuccess) return LASP2_ERR_LAUNCH;
+        if (launch_state_prefix(pl.g, dR, dR, 1, pl.inclusive ? 1 : 0, 0, nullptr, 0, st) != hipSuccess) return LASP2_ERR_LAUNCH;
         return from_hip(launch_attn_bwd_direct_mfma(g, Q, K, V, dO, P, dR, 1, dQ, dK, dV, st));
     }
     unsigned* pace = dR ? reinterpret_cast<unsigned*>(reinterpret_cast<char*>(dR) + states_bytes(g)) : nullptr;
@@ -591,7 +593,7 @@ int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_
         *slots_per_walk = pick_planes_slots(g, desc->cu_seqlens_host, backward ? 3 : 1);
         return LASP2_OK;
     }
-    *slots_per_walk = backward ? pick_bwd_walks(g, desc->cu_seqlens_host, cu_count() / (g.decay ? 3 : 2)).ws
+    *slots_per_walk = backward ? pick_bwd_walks(g, desc->cu_seqlens_host).ws
                                : pick_walk_slots(g, desc->cu_seqlens_host, cu_count(), kWalkTargetFwd);
     return LASP2_OK;
 }
@@ -649,7 +651,7 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
     if (mfma_path_supported(g, desc->dtype)) {
         // long slots that leave CUs without work: walks of parts of them
         if (g.L >= 512) {
-            const WalkPlan wp = pick_walks(g, desc->cu_seqlens_host, cu_count(), false, !g.decay, false);
+            const WalkPlan wp = pick_walks(g, desc->cu_seqlens_host, false, false);
             if (wp.W)
                 return from_hip(launch_attn_fwd_direct_mfma(regroup_short(g, desc->cu_seqlens_host, wp.W), Q, K, V,
                                                             g.lone_slots ? nullptr : P, nullptr, O, st));

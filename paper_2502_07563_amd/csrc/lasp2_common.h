@@ -230,14 +230,14 @@ hipError_t launch_attn_fwd_mfma(const Geom& g, const void* Q, const void* K, con
 bool walk_emits(const Geom& g, int dtype);
 hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K, const void* V,
                                      float* P, void* O, hipStream_t st);
-// Walks that add up the state they start from themselves (no decay; g as above, one slot per walk, or less).
+// Walks that add up the state they start from themselves (g as above, one slot per walk, or less).
 // Forward: from the rows of the document before the walk, writing the states to `emit` (NULL: not); with state, which
 // takes walks shorter than slots, from the rows of the slot before it and the slot's prefix state there.
 hipError_t launch_attn_fwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V,
                                        const float* state, float* emit, void* O, hipStream_t st);
 // Backward: suffix states from the rows up to the document's end (from_dR = 0; they also go to dR, one per walk, unless that
-// is NULL), or, walks shorter than slots, from the rows up to the slot's end and the next slot's inclusive suffix in dR.  P NULL:
-// every document a single slot.
+// is NULL), or, walks shorter than slots, from the rows up to the slot's end and the next slot's inclusive suffix in dR.  With decay the
+// suffixes in dR are the exclusive ones.  P NULL: every document a single slot.
 hipError_t launch_attn_bwd_direct_mfma(const Geom& g, const void* Q, const void* K, const void* V, const void* dO,
                                        const float* P, float* dR, int from_dR, void* dQ, void* dK, void* dV, hipStream_t st);
 // dQ, dV, dK in one launch.  P: exclusive prefix states of K^T V (from the forward);

@@ -103,7 +103,8 @@ def test_no_compiler_placed_vmcnt_wait_in_the_walk(isa):
 SKEW = (("attn_skew_mfma_kernelILb0E", 4), ("attn_skew_mfma_kernelILb1E", 4), ("attn_bwd_pair_mfma_kernel", 6),
         ("attn_fwd_emit_mfma_kernelILb0E", 2), ("attn_fwd_emit_mfma_kernelILb1E", 2),
         # one loop more for each place where rows are gathered before a walk
-        ("attn_fwd_direct_mfma_kernel", 3), ("attn_bwd_direct_mfma_kernel", 8))
+        ("attn_fwd_direct_mfma_kernel", 3), ("attn_bwd_direct_mfma_kernel", 8),
+        ("attn_decay_fwd_direct_kernel", 3), ("attn_decay_bwd_direct_kernel", 6))
 
 
 def _skew_blocks(lines, inst):
