@@ -149,7 +149,9 @@ int lasp2_num_slots(const lasp2_desc_t* desc, int64_t* T_s);
  * length that keeps the device's CUs busy with the fewest starts (never across
  * a document edge).  Results are the same within the rounding order.
  *   bf16, d = 128 (without decay, or every factor >= 0.35): any L;
- *     lasp2_attn_bwd builds its dM states per walk.
+ *     lasp2_attn_bwd builds its dM states per walk.  1 also where a walk is a
+ *     part of a slot (long slots that would leave CUs idle): it starts from the
+ *     slot's P and the rows of the slot before it.
  *   Everything else: only where L is not a multiple of the kernels' 128-row
  *     chunk, so that single slots would leave chunks partly empty; 1 otherwise.
  *     dM states are built per slot.
