@@ -195,11 +195,24 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
                 *reinterpret_cast<u32x4*>(ty + myrow * ROWB + (lane & 15) * 16) = z;
             } else if (DECAY) {
                 // weight this wave's own rows of the X tile (a row takes one weight: the swizzle does not matter)
-                const float wt = exp2f((float)(anchor_start ? tok : cu.len - 1 - tok) * l2);
+                const float wt = exp2f((float)(anchor_start ? tok : (of_walks ? min(tok | 63, cu.len - 1) : cu.len - 1) - tok) * l2);
                 *px = scale_bf16x8(*px, wt);
             }
             __syncthreads();   // block complete in LDS; every wave has left the block before it
             issue_next();      // into the ring slot that block occupied
+            // Weighted rows are rounded to bf16, and a weight within 2^-9 of one is then lost, for many rows in a row if the factor is
+            // close to one.  So a walk's rows count from the end of their 64 rows on, as in the shortest slots whose states this
+            // stands in for, and the sum takes the rest in fp32 (16 x 9358 in slots of 64, factors 1 - 2^-5 .. 1 - 2^-20, error of
+            // the head with the factor 1 - 2^-16, weights over a walk 1.6e-3, over 64 rows 5.6e-4, with states per slot 5.6e-4;
+            // layer forward 207 | 204 us).  Not for slots, weighted over their length: backward (blocks in descending order)
+            // at 16 x 131072 the launch takes 238 us instead of 199, the layer 2 064 instead of 2 040.
+            if (DECAY && of_walks && blk > 0 && !(blk & 1)) {
+                const float wb = exp2f((float)min(64, cu.len - blk * ST_KB) * l2);
+#pragma unroll
+                for (int u = 0; u < ST_TPW; ++u)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[u][v] *= wb;
+            }
             update_tiles<ST_TPW, ST_KB>(acc, tx, ty, w * ST_TPW, lane);
             if (!DECAY && of_walks && (blk & 15) == 15) {   // (a walk of several slots: sums of 512 rows, as accurate as the slots' own)
 #pragma unroll
@@ -1783,7 +1796,8 @@ __global__ __launch_bounds__(512) void attn_bwd_pair_mfma_kernel(Geom g, AttnPro
 // Eight waves: four quadrants of 2 x 2 tiles, each by two waves that take the halves of a 64-row stage (an
 // operand is read from LDS once per two products; the walks' own update, one row of tiles per wave, reads three per
 // two); a ring of four stages, three on their way.  The halves are added through LDS at the end.
-// With decay (l2: log2 of the factor) row r counts lam^(ntok - 1 - r), or lam^r if anchor_start, and base lam^ntok.
+// With decay (l2: log2 of the factor) row r counts lam^(ntok - 1 - r), or lam^r if anchor_start, and base lam^ntok: the rows of a stage
+// are weighted among themselves (and rounded), the stage's sum in fp32, as in states_body.
 template <bool DECAY = false>
 __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_t row0, int ntok, float sign,
                                              float* copy, const float* base, bool base_transposed, char* smem, int tid,
@@ -1811,13 +1825,16 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) { acc[a][b][v] = 0.f; tot[a][b][v] = 0.f; }
-    auto flush = [&]() {
+    auto flush = [&](float wb) {
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) { tot[a][b][v] += acc[a][b][v]; acc[a][b][v] = 0.f; }
+                for (int v = 0; v < 16; ++v) {
+                    tot[a][b][v] = DECAY ? fmaf(wb, acc[a][b][v], tot[a][b][v]) : tot[a][b][v] + acc[a][b][v];
+                    acc[a][b][v] = 0.f;
+                }
     };
     for (int i = 0; i < NST - 1 && i < nst; ++i) issue(i);
     for (int i = 0; i < nst; ++i) {
@@ -1833,7 +1850,7 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
             for (int u = 0; u < 2; ++u) {
                 const int b = 4 * (2 * w + u) + (lane >> 4), r = i * KB + b;
                 u32x4* p = reinterpret_cast<u32x4*>(tx + b * ROWB + (lane & 15) * 16);
-                *p = scale_bf16x8(*p, __builtin_amdgcn_exp2f((float)(anchor_start ? r : max(ntok - 1 - r, 0)) * l2));
+                *p = scale_bf16x8(*p, __builtin_amdgcn_exp2f((float)(anchor_start ? b : max(min(i * KB + KB, ntok) - 1 - r, 0)) * l2));
             }
         }
         __syncthreads();   // complete in LDS; every wave is past stage i - 1, whose place stage i + 3 takes
@@ -1852,9 +1869,10 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
 #pragma unroll
                 for (int b = 0; b < 2; ++b) acc[a][b] = mfma(x[a], y[b], acc[a][b]);
         }
-        if ((i & 7) == 7) flush();
+        if (DECAY) flush(__builtin_amdgcn_exp2f((float)(anchor_start ? i * KB : max(ntok - KB - i * KB, 0)) * l2));
+        else if ((i & 7) == 7) flush(1.f);
     }
-    flush();
+    if (!DECAY) flush(1.f);
     __syncthreads();
     // this wave finishes row hf of its quadrant's tiles and hands the other to the wave with the other half
     f32x4* out = reinterpret_cast<f32x4*>(smem + w * 8192) + lane;

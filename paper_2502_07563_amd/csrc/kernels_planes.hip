@@ -181,7 +181,7 @@ __device__ __forceinline__ bool which_segment(const Geom& g, int nprob, int nseg
 // Tokens per LDS stage: as many of the chunk's 128 as leave room for a second workgroup on the CU
 // (one workgroup with d = 128), with at most 32 registers per thread for the next stage's loads; fp32 with
 // decay and d = 64 has no registers for more than 32, and spills 9 even so.  With d = 128 the operands' planes, the
-// state's and the result's accumulators exceed the 512 registers of a thread at one wave per SIMD: 103 spilled
+// state's and the result's accumulators exceed the 512 registers of a thread at one wave per SIMD: 88 spilled
 // in fp32, 140 with decay, 76 in bf16 with decay.  Layer, 2 x 16 x 4096 x 128, against one scalar product per element, us:
 // fp32 forward 3470 -> 356, backward 10120 -> 908; bf16 with strong decay 2850 -> 241, 8240 -> 576.
 template <typename T, int D, bool DECAY>

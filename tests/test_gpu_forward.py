@@ -88,3 +88,25 @@ def test_forward_in_one_call(monkeypatch, C, L, walk, docs, decay):
         bd.lasp2_attn_fwd(p, Q, K, V, None, none[0])
         bd.lasp2_attn_bwd(p, Q, K, V, dO, None, *none[1:], bd.alloc_workspace(p))
         assert torch.equal(none[0], O3) and all(torch.equal(x, y) for x, y in zip(none[1:], grads))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("C,walk,N", [(64, 0, 707), (64, 8, 3050), (256, 2, 3050), (64, 3, 1000)])
+def test_decayed_states_of_walks_weigh_rows_within_64(monkeypatch, C, walk, N):
+    """States at a walk's start with a factor so close to one that weights round to it in bf16: a row's weight
+    counts within its 64 rows only, so it is off by 63 * (1 - factor) at most however long the walk is."""
+    if walk:
+        monkeypatch.setenv("LASP2_WALK_SLOTS", str(walk))
+    H, d, near = 3, 128, 2.0 ** -16
+    lam = np.full(H, 1.0 - near, dtype=np.float32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    Q, K, V = (torch.randn(1, H, N, d, generator=gen, device="cuda").mul_(d ** -0.5).to(torch.bfloat16) for _ in range(3))
+    P = bd.forward(bd.Problem(1, H, N, d, C, 0, "bf16", decay=lam), Q, K, V)[1]
+    i = torch.arange(N, device="cuda", dtype=torch.float64)
+    for t in range(1, P.shape[2]):
+        a = t * C
+        w = float(lam[0]) ** (a - 1 - i[:a])
+        ref = torch.bmm((K[0, :, :a].double() * w[None, :, None]).transpose(1, 2).contiguous(), V[0, :, :a].double())
+        # 2^-14: 64 roundings in fp32 of sums and factors.  (A slot of C rows that no walk starts in counts within 64 rows too.)
+        assert (P[0, :, t].double() - ref).norm() <= (63 * near + 2.0 ** -14) * ref.norm(), t
