@@ -104,7 +104,7 @@ constexpr int ST_KB = 32, ST_STAGE = ST_KB * ROWB;   // tokens and bytes (per te
 // of_walks: see launch_states_mfma (a kernel of its own: its registers and tests cost the plain one 5 %).
 template <bool DECAY, bool of_walks>
 __device__ __forceinline__ void states_body(const Geom& g, const char* __restrict__ X, const char* __restrict__ Y,
-                                            float* __restrict__ M, int anchor_start, int per_wg, int skip_last)
+                                            float* __restrict__ M, int anchor_start, int skip_last)
 {
     constexpr int DPS = 2;   // loads per wave per stage: one instruction (four rows) per tensor
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -118,6 +118,7 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
     // loads of the next slot's first blocks are on their way while the last blocks of this one
     // are consumed.
     const int total = g.T_s * g.G;
+    const int per_wg = (total + (int)gridDim.x - 1) / (int)gridDim.x;
     const int u_first = (int)blockIdx.x * per_wg, nunits = min(total, u_first + per_wg);
     struct Unit { int u, len, nblk; size_t row0, m; };   // m: index of the unit's state in M
     auto open_unit = [&](int u) {
@@ -125,11 +126,12 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
         x.u = u; x.len = 0; x.nblk = 0; x.row0 = 0; x.m = 0;
         if (u < nunits) {
             int tok0, ps, doc0, doc1, slot0, slot1;
-            slot_range<false>(g, u % g.T_s, tok0, x.len, ps, doc0, doc1, slot0, slot1);
+            if constexpr (of_walks) slot_range<false>(g, u % g.T_s, tok0, x.len, ps, doc0, doc1, slot0, slot1);
+            else slot_range(g, u % g.T_s, tok0, x.len);
             if (of_walks && skip_last && tok0 + x.len == doc1) x.len = 0;   // no blocks, no state
             x.nblk = (x.len + ST_KB - 1) / ST_KB;
             x.row0 = ((size_t)(u / g.T_s) * g.N + tok0) * ROWB;
-            x.m = of_walks ? (size_t)(u / g.T_s) * g.P_Ts + ps : (size_t)u;
+            if constexpr (of_walks) x.m = (size_t)(u / g.T_s) * g.P_Ts + ps;
         }
         return x;
     };
@@ -158,14 +160,22 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
     int slot = 0, older_than_stores = 0;
     for (Unit cu = open_unit(u_first); cu.u < nunits; cu = open_unit(cu.u + 1)) {
         if (of_walks && cu.nblk == 0) continue;
-        f32x16 acc[ST_TPW], tot[ST_TPW];
+        constexpr bool SPLIT = of_walks && !DECAY;
+        f32x16 acc[ST_TPW], tot[SPLIT ? ST_TPW : 1];
 #pragma unroll
         for (int u = 0; u < ST_TPW; ++u)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { acc[u][v] = 0.f; tot[u][v] = 0.f; }
+            for (int v = 0; v < 16; ++v) {
+                acc[u][v] = 0.f;
+                if constexpr (SPLIT) tot[u][v] = 0.f;
+            }
         float l2 = DECAY ? decay_log2(g, cu.u / g.T_s) : 0.f;
         asm volatile("" : "+v"(l2));   // waited for here, once per slot, not at its first use inside the block loop
 
+        // Code placement: the loop's time depends on where its instructions lie within 32 bytes.  With the first matrix product at
+        // 8 (mod 32) a workgroup alone on its CU takes 236 us for 20 000 tokens, at 16 250, at 20 or 24 245 (128 workgroups);
+        // with two per CU it does not show.
+        asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0");
         for (int blk = 0; blk < cu.nblk; ++blk) {
             char* tx = sX + slot * ST_STAGE;
             char* ty = sY + slot * ST_STAGE;
@@ -214,23 +224,25 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
                     for (int v = 0; v < 16; ++v) acc[u][v] *= wb;
             }
             update_tiles<ST_TPW, ST_KB>(acc, tx, ty, w * ST_TPW, lane);
-            if (!DECAY && of_walks && (blk & 15) == 15) {   // (a walk of several slots: sums of 512 rows, as accurate as the slots' own)
+            if constexpr (SPLIT) {
+                if ((blk & 15) == 15) {   // (a walk of several slots: sums of 512 rows, as accurate as the slots' own)
 #pragma unroll
-                for (int u = 0; u < ST_TPW; ++u)
+                    for (int u = 0; u < ST_TPW; ++u)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) { tot[u][v] += acc[u][v]; acc[u][v] = 0.f; }
+                        for (int v = 0; v < 16; ++v) { tot[u][v] += acc[u][v]; acc[u][v] = 0.f; }
+                }
             }
             slot = slot + 1 == ST_NST ? 0 : slot + 1;
         }
 
-        float* m = M + cu.m * (size_t)(D * D);
+        float* m = M + (of_walks ? cu.m : (size_t)cu.u) * (size_t)(D * D);
 #pragma unroll
         for (int u = 0; u < ST_TPW; ++u) {
             const int t = w * ST_TPW + u, a = t >> 2, b = t & 3;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = 32 * a + 8 * (v >> 2) + 4 * h + (v & 3);
-                __builtin_nontemporal_store(DECAY ? acc[u][v] : tot[u][v] + acc[u][v], m + row * D + 32 * b + l32);
+                __builtin_nontemporal_store(SPLIT ? tot[SPLIT ? u : 0][v] + acc[u][v] : acc[u][v], m + row * D + 32 * b + l32);
             }
         }
         older_than_stores = inflight;
@@ -239,16 +251,16 @@ __device__ __forceinline__ void states_body(const Geom& g, const char* __restric
 
 template <bool DECAY>
 __global__ __launch_bounds__(ST_NT) void states_mfma_kernel(Geom g, const char* __restrict__ X, const char* __restrict__ Y,
-                                                            float* __restrict__ M, int anchor_start, int per_wg)
+                                                            float* __restrict__ M, int anchor_start)
 {
-    states_body<DECAY, false>(g, X, Y, M, anchor_start, per_wg, 0);
+    states_body<DECAY, false>(g, X, Y, M, anchor_start, 0);
 }
 
 template <bool DECAY>
 __global__ __launch_bounds__(ST_NT) void states_of_walks_kernel(Geom g, const char* __restrict__ X, const char* __restrict__ Y,
-                                                                float* __restrict__ M, int per_wg, int skip_last)
+                                                                float* __restrict__ M, int skip_last)
 {
-    states_body<DECAY, true>(g, X, Y, M, 0, per_wg, skip_last);
+    states_body<DECAY, true>(g, X, Y, M, 0, skip_last);
 }
 
 // =====================================================================================
@@ -2523,13 +2535,12 @@ hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float
     if (of_walks != WalkStates::none) {
         e = g.decay ? allow_dynamic_lds<states_of_walks_kernel<true>>(smem) : allow_dynamic_lds<states_of_walks_kernel<false>>(smem);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((g.decay ? states_of_walks_kernel<true> : states_of_walks_kernel<false>), grid, block, smem, st, g, k, v, M, per_wg,
+        hipLaunchKernelGGL((g.decay ? states_of_walks_kernel<true> : states_of_walks_kernel<false>), grid, block, smem, st, g, k, v, M,
                            of_walks == WalkStates::before_last ? 1 : 0);
     } else {
         e = g.decay ? allow_dynamic_lds<states_mfma_kernel<true>>(smem) : allow_dynamic_lds<states_mfma_kernel<false>>(smem);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((g.decay ? states_mfma_kernel<true> : states_mfma_kernel<false>), grid, block, smem, st, g, k, v, M, anchor_start,
-                           per_wg);
+        hipLaunchKernelGGL((g.decay ? states_mfma_kernel<true> : states_mfma_kernel<false>), grid, block, smem, st, g, k, v, M, anchor_start);
     }
     return hipGetLastError();
 }

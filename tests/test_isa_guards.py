@@ -314,6 +314,22 @@ def test_states_kernel_store_count_matches_its_wait_arithmetic(isa):
     assert found == 2
 
 
+def test_states_loop_lies_where_it_was_measured(tmp_path):
+    """states_mfma_kernel's block loop with the first matrix product at 8 (mod 32): the same instructions elsewhere
+    take 3 to 6 % longer where a CU has one workgroup."""
+    from paper_2502_07563_amd import build as b
+    out = tmp_path / "mfma.o"
+    flags = [f for f in b.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, *flags, "-c", "--cuda-device-only", "--no-gpu-bundle-output", "-o", str(out),
+                    os.path.join(SRC, "kernels_mfma.hip")], check=True, capture_output=True)
+    dump = os.path.join(os.path.dirname(os.path.realpath(hipcc)), "..", "llvm", "bin", "llvm-objdump")
+    text = subprocess.run([dump, "-d", "--mcpu=gfx950", str(out)], check=True, capture_output=True, text=True).stdout
+    body = text[text.index("states_mfma_kernelILb0"):]
+    first = next(l for l in body.split("\n") if "v_mfma" in l)
+    assert int(re.search(r"// ([0-9A-F]+):", first).group(1), 16) % 32 == 8, first
+
+
 @pytest.mark.parametrize("decay", [0, 1])
 def test_states_of_walks_store_count_matches_its_wait_arithmetic(isa, decay):
     """The same body as states_mfma_kernel, for the states of walks of several slots."""
