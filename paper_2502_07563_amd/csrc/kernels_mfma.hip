@@ -2526,10 +2526,16 @@ hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float
     const int cus = cu_count();
     const long long nunits = (long long)g.T_s * g.G;
     if (nunits == 0) return hipSuccess;
-    int per_wg = (int)((nunits + 2LL * cus - 1) / (2LL * cus));
-    // (documents of different lengths: shares of about 2 048 tokens, dealt out as workgroups end)
-    if (g.n_seqs) per_wg = (int)std::min<long long>(per_wg, std::max(1LL, 2048LL * g.T_s / g.N));
-    dim3 grid((unsigned)((nunits + per_wg - 1) / per_wg)), block(ST_NT);
+    long long wgs = std::min<long long>(nunits, 2LL * cus);
+    // Documents of different lengths: shares of about 2 048 tokens, dealt out as workgroups end, where that makes at least
+    // four rounds of them (one share each | dealt, us, 131 072 tokens in 40 documents: 32 heads 625 | 613, 64 heads 1 231 | 1 176;
+    // a second or third round that is nearly empty costs more than it evens out: 8 heads 157 | 178, 16 heads 311 | 323, 16 heads x
+    // 65 536 in 1 000 510 | 646) and a document is found in few steps from its mark (32 heads x 262 144 in 4 000 8 735 | 8 970).
+    if (g.n_seqs && g.doc_stride <= 8) {
+        const long long share = std::max(1LL, 2048LL * g.T_s / g.N), dealt = (nunits + share - 1) / share;
+        if (dealt >= 8LL * cus) wgs = dealt;
+    }
+    dim3 grid((unsigned)wgs), block(ST_NT);
     const char *k = static_cast<const char*>(K), *v = static_cast<const char*>(V);
     hipError_t e;
     if (of_walks != WalkStates::none) {
