@@ -21,8 +21,11 @@ __device__ __forceinline__ void st(__hip_bfloat16* p, float v) { *p = __float2bf
 // batched ahead of the stores so that in-place use (P == M) stays correct and the
 // memory system sees several requests in flight.  The exclusive form does not touch the last slot's own state.
 // user_slots: entry per slot of the caller's, walks of g.wslots of them (see launch_state_prefix).
+// PACKED, a kernel of its own: what the marks and divisions of packed batches take before the first load shows where
+// a sequence has few slots (1 280 sequences of one slot: 25.1 us with them, 17.4 without).
 constexpr int kScanBatch = 8;
 
+template <bool PACKED>
 __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const float* M, float* P,
                                                                 int reverse, int inclusive, int user_slots,
                                                                 unsigned* clear, unsigned nclear)
@@ -35,18 +38,20 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
     const int e = (blockIdx.x * kThreads + threadIdx.x) * 4;
     if (e >= dd) return;
     const int stride = user_slots ? g.wslots : 1;   // array entries from one walk to the next inside a document
-    const uint32_t L = (uint32_t)min(g.L, (int64_t)INT32_MAX), Lp = user_slots ? L / (uint32_t)g.wslots : L;   // tokens per walk, array entry
     const int entries = user_slots ? g.P_Ts : g.T_s;
     const size_t base = (size_t)blockIdx.y * (size_t)entries * dd + e;
-    // the documents of one mark (documents are independent of each other)
-    const int k0 = (int)blockIdx.z * g.doc_stride, k1 = g.n_seqs ? min(k0 + g.doc_stride, g.n_seqs) : 1;
     const float l2 = decay_log2(g, blockIdx.y);
     const int step = reverse ? -stride : stride;
-    int first = user_slots ? g.doc_pmark[blockIdx.z] : g.doc_mark[blockIdx.z];   // entries before the document
+    // a packed batch's documents of one mark, or all of them (documents are independent of each other)
+    const uint32_t L = (uint32_t)min(g.L, (int64_t)INT32_MAX);
+    const uint32_t Lp = PACKED && user_slots ? L / (uint32_t)g.wslots : L;   // tokens per walk, array entry
+    const int k0 = PACKED ? (int)blockIdx.z * g.doc_stride : 0;
+    const int k1 = !PACKED ? 1 : gridDim.z == 1 ? g.n_seqs : min(k0 + g.doc_stride, g.n_seqs);
+    int first = !PACKED ? 0 : user_slots ? g.doc_pmark[blockIdx.z] : g.doc_mark[blockIdx.z];   // entries before the document
     for (int k = k0; k < k1; ++k) {
-        const int dlen = g.n_seqs ? (g.cu[k + 1] - g.cu[k]) : g.N;
-        const int ns = g.n_seqs ? (int)(((uint32_t)dlen + (L - 1u)) / L) : g.T_s;
-        const int ne = g.n_seqs ? (int)(((uint32_t)dlen + (Lp - 1u)) / Lp) : 0;
+        const int dlen = PACKED ? (g.cu[k + 1] - g.cu[k]) : g.N;
+        const int ns = PACKED ? (int)(((uint32_t)dlen + (L - 1u)) / L) : g.T_s;
+        const int ne = PACKED ? (int)(((uint32_t)dlen + (Lp - 1u)) / Lp) : 0;
         int s = first + (reverse ? (ns - 1) * stride : 0);
         first += ne;
         const int nm = inclusive ? ns : ns - 1;   // states that enter a result
@@ -83,32 +88,37 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
 // after the gather and the sum when there is no mask); walks of several slots: over the entries of their first slots, which
 // receive it.  Each thread owns four elements of the d x d state and sums a document's entries in ascending order
 // before it writes any of them, so S may alias M.  The documents of a mark in turn, eight loads ahead (latency bounds it: 25
-// entries of 16 heads one by one 19 us, 10 so).
+// entries of 16 heads one by one 19 us, 10 so).  PACKED: as above (1 280 sequences of one slot: 28.6 -> 25.0 us).
+template <bool PACKED>
 __global__ __launch_bounds__(kThreads) void state_total_kernel(Geom g, const float* M, float* S)
 {
     const int dd = g.d * g.d;
     const int e = (blockIdx.x * kThreads + threadIdx.x) * 4;
     if (e >= dd) return;
     const size_t base = (size_t)blockIdx.y * (size_t)g.P_Ts * dd + e, step = (size_t)g.wslots * dd;
-    const int k0 = (int)blockIdx.z * g.doc_stride, k1 = g.n_seqs ? min(k0 + g.doc_stride, g.n_seqs) : 1;
-    const uint32_t L = (uint32_t)min(g.L, (int64_t)INT32_MAX), Lp = L / (uint32_t)g.wslots;
-    int first = g.doc_pmark[blockIdx.z];
+    const uint32_t L = (uint32_t)min(g.L, (int64_t)INT32_MAX), Lp = PACKED ? L / (uint32_t)g.wslots : L;
+    const int k0 = PACKED ? (int)blockIdx.z * g.doc_stride : 0;
+    const int k1 = !PACKED ? 1 : gridDim.z == 1 ? g.n_seqs : min(k0 + g.doc_stride, g.n_seqs);
+    int first = PACKED ? g.doc_pmark[blockIdx.z] : 0;
     for (int k = k0; k < k1; ++k) {
-        const uint32_t dlen = g.n_seqs ? (uint32_t)(g.cu[k + 1] - g.cu[k]) : (uint32_t)g.N;
-        const int ns = (int)((dlen + (L - 1u)) / L);
+        const uint32_t dlen = PACKED ? (uint32_t)(g.cu[k + 1] - g.cu[k]) : (uint32_t)g.N;
+        const int ns = PACKED ? (int)((dlen + (L - 1u)) / L) : g.T_s;
         const float* m = M + base + (size_t)first * dd;
         float* out = S + base + (size_t)first * dd;
         float4 run = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int r = 0; r < ns; r += kScanBatch) {
             float4 x[kScanBatch];
 #pragma unroll
-            for (int u = 0; u < kScanBatch; ++u) x[u] = *reinterpret_cast<const float4*>(m + (size_t)min(r + u, ns - 1) * step);
+            for (int u = 0; u < kScanBatch; ++u) x[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int u = 0; u < kScanBatch; ++u)
+                if (r + u < ns) x[u] = *reinterpret_cast<const float4*>(m + (size_t)(r + u) * step);
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u)
                 if (r + u < ns) { run.x += x[u].x; run.y += x[u].y; run.z += x[u].z; run.w += x[u].w; }
         }
         for (int r = 0; r < ns; ++r) *reinterpret_cast<float4*>(out + (size_t)r * step) = run;
-        first += (int)((dlen + (Lp - 1u)) / Lp);
+        if (PACKED) first += (int)((dlen + (Lp - 1u)) / Lp);
     }
 }
 
@@ -265,12 +275,22 @@ hipError_t launch_softmax_delta(const Geom& g, int dtype, const void* O, const v
     return softmax_delta_T<__hip_bfloat16>(g, rows, O, dO, LSE, delta, lse2, st);
 }
 
+// The grid's third axis: a packed batch's documents are dealt out by marks, where one thread that takes them in turn would wait
+// for each (documents in turn | by marks, us: 16 x 65 536 in 1 000 990 | 231; 8 x 131 072 in 40 158 | 113), or go in turn, where they have
+// many slots and the groups alone give every CU a workgroup (states of 12 documents apart from each other at a time, 32 x 131 072 in slots of
+// 64: suffix 1 602 | 1 770; 16 x 131 072 in 40 203 | 214, in slots of 256).
+static int scan_marks(const Geom& g)
+{
+    if (!g.n_seqs || (g.G >= 16 && g.T_s >= 8LL * g.n_seqs)) return 1;
+    return (g.n_seqs + g.doc_stride - 1) / g.doc_stride;
+}
+
 hipError_t launch_state_total(const Geom& g, const float* M, float* S, hipStream_t st)
 {
     const int dd = g.d * g.d;
-    const int marks = g.n_seqs ? (g.n_seqs + g.doc_stride - 1) / g.doc_stride : 1;
+    const int marks = scan_marks(g);
     dim3 grid((dd / 4 + kThreads - 1) / kThreads, g.G, marks), block(kThreads);
-    hipLaunchKernelGGL(state_total_kernel, grid, block, 0, st, g, M, S);
+    hipLaunchKernelGGL((g.n_seqs ? state_total_kernel<true> : state_total_kernel<false>), grid, block, 0, st, g, M, S);
     return hipGetLastError();
 }
 
@@ -288,9 +308,10 @@ hipError_t launch_state_prefix(const Geom& g, const float* M, float* P, int reve
                                int user_slots, unsigned* clear, unsigned nclear, hipStream_t st)
 {
     const int dd = g.d * g.d;
-    const int marks = g.n_seqs ? (g.n_seqs + g.doc_stride - 1) / g.doc_stride : 1;
+    const int marks = scan_marks(g);
     dim3 grid((dd / 4 + kThreads - 1) / kThreads, g.G, marks), block(kThreads);
-    hipLaunchKernelGGL(state_prefix_kernel, grid, block, 0, st, g, M, P, reverse, inclusive, user_slots, clear, nclear);
+    hipLaunchKernelGGL((g.n_seqs ? state_prefix_kernel<true> : state_prefix_kernel<false>), grid, block, 0, st, g, M, P, reverse, inclusive,
+                       user_slots, clear, nclear);
     return hipGetLastError();
 }
 

@@ -42,6 +42,31 @@ def test_state_prefix(d, slots, decay, reverse, in_place):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("H", [15, 16])
+@pytest.mark.parametrize("slots", [[8] * 5, [7] * 5, [1, 2, 9, 20, 8, 8] * 7, [3] * 70 + [40], [33]])
+def test_documents_of_packed_batches_in_turn_and_by_marks(slots, H):
+    """Prefix, suffix and total of packed states on both sides of the line between the two orders (16 groups and eight slots
+    per document on average), with one, two and three documents per mark; the arrays' NaN must not reach a result."""
+    lens = [n * C - 5 * (i % 2) for i, n in enumerate(slots)]
+    cu, d, T = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), 32, sum(slots)
+    p = bd.Problem(1, H, int(cu[-1]), d, C, C, "f32", cu)
+    M = torch.randn(1, H, T, d, d, generator=torch.Generator(device="cuda").manual_seed(T + H), device="cuda")
+    at = np.concatenate([[0], np.cumsum(slots)])
+    part = [M[:, :, a:b].double() for a, b in zip(at[:-1], at[1:])]
+    # at most 40 roundings of a document's running sum, 2^-24 each
+    tol = lambda want: 40 * 2.0 ** -24 * max(1.0, want.abs().max().item())
+    for reverse in (False, True):
+        got = torch.full_like(M, float("nan"))
+        bd.lasp2_state_prefix(p, M, got, reverse)
+        want = torch.cat([(x.flip(2).cumsum(2).flip(2) if reverse else x.cumsum(2)) - x for x in part], 2)
+        assert (got.double() - want).abs().max().item() <= tol(want)
+    got = torch.full_like(M, float("nan"))
+    bd.lasp2_state_total(p, M, got)
+    want = torch.cat([x.sum(2, keepdim=True).expand_as(x) for x in part], 2)
+    assert (got.double() - want).abs().max().item() <= tol(want)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d", [16, 32, 64, 128])
 @pytest.mark.parametrize("N", [1, 31, 257])
