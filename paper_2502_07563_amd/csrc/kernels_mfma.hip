@@ -2401,7 +2401,7 @@ __global__ __launch_bounds__(RS_NW * 64) void rows_state_mfma_kernel(Geom g, Row
     {
         const float* st = pr.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D);
         // the state goes to the walk's other slots as well, if that is asked for
-        const int Lp = (int)(g.L / g.wslots), more = pr.emit && !g.W ? (len + Lp - 1) / Lp - 1 : 0;
+        const int more = pr.emit && !g.W ? (int)((uint32_t)(len - 1) / (uint32_t)(g.L / g.wslots)) : 0;
         float* em = pr.emit + ((size_t)grp * g.P_Ts + ps + 1) * (size_t)(D * D);
         for (int i = tid; i < D * 16; i += RS_NW * 64) {
             float x[8];

@@ -115,3 +115,25 @@ def test_one_call_and_walks(B, H, docs, C, L):
             err = (got[:, :, a:b].double() - want).norm(dim=3)
             assert bool((err <= 4 * 2.0 ** -9 * torch.maximum(size, want.norm(dim=3))).all())
     assert at == S.shape[2]
+
+
+@pytest.mark.parametrize("docs", [[700], [300, 1, 399]])
+def test_slots_as_long_as_they_can_be(docs):
+    """L close to 2^31, with and without masking: sums of a length and a row count must not leave 32 bits.  The results are those of
+    slots that just hold the longest document."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    cu = np.concatenate([[0], np.cumsum(docs)]).astype(np.int32)
+    B, H, N, d, C = 1, 3, int(cu[-1]), 128, 256
+    gen = torch.Generator(device="cuda").manual_seed(N + len(docs))
+    Q, K, V, dO = (torch.randn(B, H, N, d, generator=gen, device="cuda").mul_(d ** -0.5).to(torch.bfloat16) for _ in range(4))
+    got = []
+    for L in (768, 2 ** 31 - 256):
+        p = bd.Problem(B, H, N, d, C, L, "bf16", cu if len(docs) > 1 else None)
+        assert bd.lasp2_num_slots(p) == len(docs)
+        O, P = bd.forward(p, Q, K, V)
+        O2, S = bd.nomask_forward(p, Q, K, V)
+        got.append((O, P, O2, S) + bd.backward(p, Q, K, V, dO, P)[:3] + bd.nomask_backward(p, Q, K, V, dO, S)[:3])
+    # the same inputs by the same products: a bf16 rounding of the scores, the state and the result each
+    for a, b in zip(*got):
+        assert (a.double() - b.double()).norm() <= 3 * 2.0 ** -9 * a.double().norm()
