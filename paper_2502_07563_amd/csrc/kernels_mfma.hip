@@ -2376,6 +2376,9 @@ struct RowsStateArgs {
     float* emit;
 };
 
+// WALKS: walks of several slots or of parts of one (a kernel of its own: finding them takes longer, 32 x 8 sequences of 73 rows
+// 7.1 us so, 6.6 without).
+template <bool WALKS>
 __global__ __launch_bounds__(RS_NW * 64) void rows_state_mfma_kernel(Geom g, RowsStateArgs p0, RowsStateArgs p1,
                                                                      RowsStateArgs p2, int nprob)
 {
@@ -2391,17 +2394,23 @@ __global__ __launch_bounds__(RS_NW * 64) void rows_state_mfma_kernel(Geom g, Row
     if (unit >= (unsigned)g.T_s * (unsigned)g.G) return;
     const int s = (int)(unit % (unsigned)g.T_s), grp = (int)(unit / (unsigned)g.T_s);
     const RowsStateArgs& pr = prob == 0 ? p0 : (prob == 1 ? p1 : p2);
-    int tok0, len, ps, doc0, doc1, slot0, slot1;
-    slot_range<true>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
+    int tok0, len, ps = s;
+    if constexpr (WALKS) {
+        int doc0, doc1, slot0, slot1;
+        slot_range<true>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
+    } else {
+        slot_range(g, s, tok0, len);
+    }
     if (len <= 0) return;
     const size_t row0 = ((size_t)grp * g.N + tok0) * ROWB;
     const char* __restrict__ A = pr.A + row0;
     char* __restrict__ out = pr.out + row0;
 
     {
-        const float* st = pr.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D);
+        const float* st = pr.state + ((size_t)grp * (WALKS ? g.P_Ts : g.T_s) + ps) * (size_t)(D * D);
         // the state goes to the walk's other slots as well, if that is asked for
-        const int more = pr.emit && !g.W ? (int)((uint32_t)(len - 1) / (uint32_t)(g.L / g.wslots)) : 0;
+        int more = 0;
+        if (WALKS && pr.emit) more = (int)((uint32_t)(len - 1) / ((uint32_t)g.L / (uint32_t)g.wslots));
         float* em = pr.emit + ((size_t)grp * g.P_Ts + ps + 1) * (size_t)(D * D);
         for (int i = tid; i < D * 16; i += RS_NW * 64) {
             float x[8];
@@ -2680,14 +2689,16 @@ hipError_t launch_rows_state_mfma(const Geom& g, const RowsStateProblem* probs, 
     RowsStateArgs a[3];
     for (int i = 0; i < 3; ++i) {
         const RowsStateProblem& p = probs[i < n ? i : 0];
-        a[i] = RowsStateArgs{static_cast<const char*>(p.A), p.state, static_cast<char*>(p.out), p.transpose_state, p.emit};
+        a[i] = RowsStateArgs{static_cast<const char*>(p.A), p.state, static_cast<char*>(p.out), p.transpose_state,
+                             g.wslots > 1 ? p.emit : nullptr};   // (one slot, or a part of one: no others)
     }
-    hipError_t e = allow_dynamic_lds<rows_state_mfma_kernel>(smem);
+    const bool walks = g.wslots > 1 || g.W > 0;
+    hipError_t e = walks ? allow_dynamic_lds<rows_state_mfma_kernel<true>>(smem) : allow_dynamic_lds<rows_state_mfma_kernel<false>>(smem);
     if (e != hipSuccess) return e;
     const unsigned units = (unsigned)g.T_s * (unsigned)g.G;
     const unsigned gx = (unsigned)n * ((units + 7u) & ~7u);
     dim3 grid(gx), block(RS_NW * 64);
-    hipLaunchKernelGGL(rows_state_mfma_kernel, grid, block, smem, st, g, a[0], a[1], a[2], n);
+    hipLaunchKernelGGL((walks ? rows_state_mfma_kernel<true> : rows_state_mfma_kernel<false>), grid, block, smem, st, g, a[0], a[1], a[2], n);
     return hipGetLastError();
 }
 

@@ -101,17 +101,19 @@ __device__ __forceinline__ void slot_range(const Geom& g, int s, int& tok0, int&
     ps = 0;
     doc0 = slot0 = 0;
     doc1 = slot1 = 0;
-    for (int k = j * g.doc_stride; k < g.n_seqs; ++k) {
-        const int a = g.cu[k], b = g.cu[k + 1];
-        int ns = (int)(((uint32_t)(b - a) + (L - 1u)) / L);
-        if (SHORT && g.W) {
-            const int slots = ns, rest = (b - a) - (int)((slots - 1) * (int64_t)L);
-            ns = (slots - 1) * g.sub + (rest + g.W - 1) / g.W;
+    if (SHORT && g.W) {
+        for (int k = j * g.doc_stride; k < g.n_seqs; ++k) {
+            const int a = g.cu[k], b = g.cu[k + 1], slots = (int)(((uint32_t)(b - a) + (L - 1u)) / L);
+            const int rest = (b - a) - (int)((slots - 1) * (int64_t)L), ns = (slots - 1) * g.sub + (rest + g.W - 1) / g.W;
             if (s < base + ns) { inside(s - base, a, b, pbase); return; }
             base += ns;
             pbase += slots;
-            continue;
         }
+        return;
+    }
+    for (int k = j * g.doc_stride; k < g.n_seqs; ++k) {
+        const int a = g.cu[k], b = g.cu[k + 1];
+        const int ns = (int)(((uint32_t)(b - a) + (L - 1u)) / L);
         if (s < base + ns) {
             const int64_t t0 = (int64_t)a + (int64_t)(s - base) * L;
             const int64_t t1 = min(t0 + (int64_t)L, (int64_t)b);
