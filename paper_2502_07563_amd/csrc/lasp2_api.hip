@@ -836,7 +836,15 @@ static int softmax_geom(const lasp2_desc_t* desc, int64_t q_begin, int64_t q_len
 // 128, 256-row kernels | 64 rows, 128 rows, us: 16 heads x 1 000 causal, forward 37 | 20, 25, backward 82 | 53; 4 x 4 000 112 | 54, 74,
 // 260 | 139; 16 heads, the last 1 000 of 16 000 438 | 231, 357; 32 x 1 000 (512 and 256 of them) 36 | 33, 26, 84 | 92; and beyond
 // the lines 20 x 1 692 (540, 280) 57 | 67, 61, 132 | 170; 16 x 4 000 124 | 163, 134, 315 | 410.
-static bool softmax_rows_fit(const Geom& g, int rows, int per) { return (int64_t)g.G * ((rows + per - 1) / per) <= cu_count(); }
+// `partners`: the rows that the call's rows can see (keys of its queries, queries of its keys).  A few of them are one or two steps of either
+// kernel, and merging the shares costs more than splitting them gains: 16 heads causal, forward | backward, 64 rows 6.0 -> 8.3 | 17.3 -> 23.7,
+// 128 8.1 -> 8.5 | 22.5 -> 24.4, 160 9.4 -> 9.6 | 26.6 -> 27.2, 192 10.4 -> 9.6 | 27.2 -> 27.6, 200 11.4 -> 9.6 | 31.4 -> 27.7.
+constexpr int64_t kFewKeysFwd = 160, kFewPartnersBwd = 192;
+static bool softmax_rows_fit(const Geom& g, int rows, int per, int64_t partners, int64_t few)
+{
+    return partners > few && (int64_t)g.G * ((rows + per - 1) / per) <= cu_count();
+}
+static int64_t softmax_keys(const Geom& g, int causal) { return causal ? (int64_t)g.q0 + g.qn : g.N; }
 
 static int softmax_fwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q_len, const void* Q,
                             const void* K, const void* V, void* O, float* LSE, int causal, void* stream)
@@ -849,7 +857,8 @@ static int softmax_fwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q
     rc = check_ptrs({Q, K, V, O, LSE});
     if (rc != LASP2_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    const int small = softmax_rows_fit(g, g.qn, 64) ? 2 : softmax_rows_fit(g, g.qn, 128) ? 4 : 0;   // row tiles per workgroup
+    const int64_t keys = softmax_keys(g, causal);
+    const int small = softmax_rows_fit(g, g.qn, 64, keys, kFewKeysFwd) ? 2 : softmax_rows_fit(g, g.qn, 128, keys, kFewKeysFwd) ? 4 : 0;   // row tiles per workgroup
     if (softmax_mfma_supported(g, desc->dtype))
         return from_hip(small ? launch_softmax_fwd_small(g, small, Q, K, V, O, LSE, causal ? 1 : 0, st)
                                                : launch_softmax_fwd_mfma(g, Q, K, V, O, LSE, causal ? 1 : 0, st));
@@ -878,11 +887,13 @@ static int softmax_bwd_impl(const lasp2_desc_t* desc, int64_t q_begin, int64_t q
     hipError_t e = launch_softmax_delta(g, desc->dtype, O, dO, LSE, delta, fast ? lse2 : nullptr, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     if (fast) {
-        e = softmax_rows_fit(g, g.qn, 64) ? launch_softmax_bwd_dq_small(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st)
-                                   : launch_softmax_bwd_dq_mfma(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st);
+        e = softmax_rows_fit(g, g.qn, 64, softmax_keys(g, causal), kFewPartnersBwd)
+                ? launch_softmax_bwd_dq_small(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st)
+                : launch_softmax_bwd_dq_mfma(g, Q, K, V, dO, LSE, delta, dQ, causal ? 1 : 0, st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
-        return from_hip(softmax_rows_fit(g, g.N, 64) ? launch_softmax_bwd_dkv_small(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st)
-                                              : launch_softmax_bwd_dkv_mfma(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st));
+        return from_hip(softmax_rows_fit(g, g.N, 64, g.qn, kFewPartnersBwd)
+                            ? launch_softmax_bwd_dkv_small(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st)
+                            : launch_softmax_bwd_dkv_mfma(g, Q, K, V, dO, lse2, delta, dK, dV, causal ? 1 : 0, st));
     }
     return from_hip(launch_softmax_bwd_planes(g, desc->dtype, Q, K, V, dO, LSE, delta, dQ, dK, dV,
                                               causal ? 1 : 0, st));

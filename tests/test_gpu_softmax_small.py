@@ -1,7 +1,7 @@
 """bf16 heads of 128, softmax: the kernels for launches of at most a workgroup of 64 rows per CU and those for more (the
 same lengths with many heads), against the definition in 64 bits: one row more or less than row tiles, steps of 128 partner
 rows and blocks of 256 queries; mirrored row tiles with an odd number of them; documents; one rank's share, with fewer
-queries than a tile and with forward and dK, dV on different sides of a line."""
+queries than a tile and with forward and dK, dV on different sides of a line; few partner rows, which the kernels for more take."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +10,9 @@ from paper_2502_07563_amd import binding as bd
 
 SIZES = [(1, None, None), (31, None, None), (65, None, None), (95, None, None), (128, None, None), (129, None, None), (257, None, None),
          (321, None, None), (700, None, None), (420, None, (32, 63, 33, 65, 64, 163)), (600, (500, 100), None), (600, (37, 5), None),
-         (500, (499, 1), None), (512, (128, 300), (100, 412)), (300, (300, 0), None)]
+         (500, (499, 1), None), (512, (128, 300), (100, 412)), (300, (300, 0), None),
+         # beside the numbers of partner rows from which the kernels for small launches are taken
+         (160, None, None), (161, None, None), (192, None, None), (193, None, None), (193, None, (60, 70, 63)), (400, (150, 43), None)]
 
 
 @pytest.mark.gpu
