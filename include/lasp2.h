@@ -151,7 +151,8 @@ int lasp2_num_slots(const lasp2_desc_t* desc, int64_t* T_s);
  *   bf16, d = 128 (without decay, or every factor >= 0.35): any L;
  *     lasp2_attn_bwd builds its dM states per walk.  1 also where a walk is a
  *     part of a slot (long slots that would leave CUs idle): it starts from the
- *     slot's P and the rows of the slot before it.
+ *     slot's P and the rows of the slot before it.  lasp2_walk_plan tells the
+ *     two apart.
  *   Everything else: only where L is not a multiple of the kernels' 128-row
  *     chunk, so that single slots would leave chunks partly empty; 1 otherwise.
  *     dM states are built per slot.
@@ -159,6 +160,24 @@ int lasp2_num_slots(const lasp2_desc_t* desc, int64_t* T_s);
  * call) overrides the choice where there is one; 1 gives one walk per slot.
  */
 int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_walk);
+
+/*
+ * The same for each call, lasp2_forward among them, which plans its walks by
+ * itself: *walk_tokens, the longest a walk can be (a multiple of L, or less than
+ * L where walks are parts of slots), and *start, what a walk starts from:
+ *   LASP2_START_STATES  a state per walk: the caller's P at its first slot
+ *       (lasp2_attn_fwd), or what lasp2_forward and lasp2_attn_bwd compute in
+ *       launches before the attention launch (none where no walk needs one);
+ *   LASP2_START_GATHER  the rows of its document before it (backward: from it to
+ *       the end), which the walk adds up itself: one launch;
+ *   LASP2_START_SLOTS   a state per slot, given or computed as above, and the
+ *       rows of the slot on that side of the walk.
+ * (Of lasp2_attn_bwd's dQ, whose states are the given P, this is said of the
+ * suffix states dM.)  An unknown `call` is LASP2_ERR_SHAPE.
+ */
+typedef enum { LASP2_CALL_ATTN_FWD = 0, LASP2_CALL_ATTN_BWD = 1, LASP2_CALL_FORWARD = 2 } lasp2_call_t;
+typedef enum { LASP2_START_STATES = 0, LASP2_START_GATHER = 1, LASP2_START_SLOTS = 2 } lasp2_start_t;
+int lasp2_walk_plan(const lasp2_desc_t* desc, int call, int64_t* walk_tokens, int* start);
 
 /* Bytes of device scratch lasp2_attn_bwd and lasp2_nomask_bwd need: room for one fp32 state
  * array [B,H,T_s,d,d] that holds dM_t and then, in place, its suffix combine (lasp2_attn_bwd
@@ -212,9 +231,10 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K,
  * lasp2_chunk_states, lasp2_state_prefix (in place, P both times) and
  * lasp2_attn_fwd in one call: O and every entry of P, the same within the
  * rounding order.  Knowing all three, the library computes states and prefix
- * only where its workgroups' walks start (lasp2_walk_slots; nowhere if each
- * document is one walk) and has the walks write the other slots' states as
- * they pass them, where slots are multiples of 64 tokens (bf16, d = 128).
+ * only where its workgroups' walks start (lasp2_walk_plan; nowhere if each
+ * document is one walk or walks gather their own) and has the walks write the
+ * other slots' states as they pass them, where slots are multiples of 64 tokens
+ * (bf16, d = 128).
  * In: Q,K,V [B,H,N,d].  Out: P [B,H,T_s,d,d] fp32, never NULL; O [B,H,N,d].
  */
 int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K,

@@ -53,6 +53,7 @@ def lib():
         L.lasp2_num_slots.argtypes = [dp, i64p]
         L.lasp2_workspace_size.argtypes = [dp, szp]
         L.lasp2_walk_slots.argtypes = [dp, ctypes.c_int, i64p]
+        L.lasp2_walk_plan.argtypes = [dp, ctypes.c_int, i64p, ctypes.POINTER(ctypes.c_int)]
         L.lasp2_chunk_states.argtypes = [dp, vp, vp, vp, vp]
         L.lasp2_state_prefix.argtypes = [dp, vp, vp, ctypes.c_int, vp]
         L.lasp2_attn_fwd.argtypes = [dp, vp, vp, vp, vp, vp, vp]
@@ -72,7 +73,7 @@ def lib():
         L.lasp2_softmax_bwd_share.argtypes = [dp, i64, i64] + [vp] * 10 + [ctypes.c_size_t, ctypes.c_int, vp]
         L.lasp2_status_string.argtypes = [ctypes.c_int]
         L.lasp2_status_string.restype = ctypes.c_char_p
-        for name in ("lasp2_num_slots", "lasp2_workspace_size", "lasp2_walk_slots", "lasp2_chunk_states",
+        for name in ("lasp2_num_slots", "lasp2_workspace_size", "lasp2_walk_slots", "lasp2_walk_plan", "lasp2_chunk_states",
                      "lasp2_state_prefix", "lasp2_attn_fwd", "lasp2_forward", "lasp2_attn_bwd", "lasp2_attn_bwd_noalloc",
                      "lasp2_state_total",
                      "lasp2_nomask_fwd", "lasp2_nomask_forward", "lasp2_nomask_bwd", "lasp2_softmax_fwd",
@@ -176,6 +177,17 @@ def lasp2_walk_slots(p: Problem, backward=False) -> int:
     out = ctypes.c_int64(0)
     _check(lib().lasp2_walk_slots(p.ref, 1 if backward else 0, ctypes.byref(out)), "lasp2_walk_slots")
     return out.value
+
+
+CALLS = {"attn_fwd": 0, "attn_bwd": 1, "forward": 2}      # lasp2_call_t
+STARTS = ("states", "gather", "slots")                    # lasp2_start_t
+
+
+def lasp2_walk_plan(p: Problem, call):
+    """Tokens per walk of `call` (a key of CALLS), and what a walk starts from (one of STARTS)."""
+    tokens, start = ctypes.c_int64(0), ctypes.c_int(0)
+    _check(lib().lasp2_walk_plan(p.ref, CALLS[call], ctypes.byref(tokens), ctypes.byref(start)), "lasp2_walk_plan")
+    return tokens.value, STARTS[start.value]
 
 
 def lasp2_workspace_size(p: Problem) -> int:

@@ -406,6 +406,20 @@ int pick_planes_slots(const Geom& g, const int32_t* cu_host, int nprob)
     return ws;
 }
 
+// What each call does with its descriptor (lasp2_walk_plan).
+WalkPlan plan_of(const Geom& g, const int32_t* cu_host, int dtype, int call)
+{
+    if (!mfma_path_supported(g, dtype)) return {pick_planes_slots(g, cu_host, call == LASP2_CALL_ATTN_BWD ? 3 : 1), 0, Start::states};
+    if (call == LASP2_CALL_ATTN_BWD) return pick_bwd_walks(g, cu_host);
+    if (call == LASP2_CALL_FORWARD) return pick_forward_walks(g, cu_host);
+    // long slots that leave CUs without work: walks of parts of them
+    if (g.L >= 512) {
+        const WalkPlan wp = pick_walks(g, cu_host, false, false);
+        if (wp.W) return {1, wp.W, g.lone_slots ? Start::gather : Start::both};
+    }
+    return {pick_walk_slots(g, cu_host, cu_count(), kWalkTargetFwd), 0, Start::states};
+}
+
 int check_ptrs(std::initializer_list<const void*> ptrs)
 {
     for (const void* p : ptrs)
@@ -506,7 +520,7 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     pl->gw = g;
     pl->start = Start::states;
     if (pl->fast) {
-        const WalkPlan wp = pick_bwd_walks(g, desc->cu_seqlens_host);
+        const WalkPlan wp = plan_of(g, desc->cu_seqlens_host, desc->dtype, LASP2_CALL_ATTN_BWD);
         pl->gw = regroup(g, desc->cu_seqlens_host, wp);
         pl->start = wp.start;
     }
@@ -587,14 +601,21 @@ int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_
     bool empty = false;
     int rc = make_geom(desc, &g, &empty);
     if (rc != LASP2_OK) return rc;
-    *slots_per_walk = 1;
-    if (empty) return LASP2_OK;
-    if (!mfma_path_supported(g, desc->dtype)) {
-        *slots_per_walk = pick_planes_slots(g, desc->cu_seqlens_host, backward ? 3 : 1);
-        return LASP2_OK;
-    }
-    *slots_per_walk = backward ? pick_bwd_walks(g, desc->cu_seqlens_host).ws
-                               : pick_walk_slots(g, desc->cu_seqlens_host, cu_count(), kWalkTargetFwd);
+    *slots_per_walk = empty ? 1 : plan_of(g, desc->cu_seqlens_host, desc->dtype, backward ? LASP2_CALL_ATTN_BWD : LASP2_CALL_ATTN_FWD).ws;
+    return LASP2_OK;
+}
+
+int lasp2_walk_plan(const lasp2_desc_t* desc, int call, int64_t* walk_tokens, int* start)
+{
+    if (!walk_tokens || !start) return LASP2_ERR_NULL;
+    Geom g;
+    bool empty = false;
+    int rc = make_geom(desc, &g, &empty);
+    if (rc != LASP2_OK) return rc;
+    if (call < LASP2_CALL_ATTN_FWD || call > LASP2_CALL_FORWARD) return LASP2_ERR_SHAPE;
+    const WalkPlan wp = empty ? WalkPlan{1, 0, Start::states} : plan_of(g, desc->cu_seqlens_host, desc->dtype, call);
+    *walk_tokens = wp.W ? wp.W : wp.ws * g.L;
+    *start = wp.start == Start::gather ? LASP2_START_GATHER : wp.start == Start::both ? LASP2_START_SLOTS : LASP2_START_STATES;
     return LASP2_OK;
 }
 
@@ -648,19 +669,12 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
     rc = (P == nullptr && g.lone_slots) ? check_ptrs({Q, K, V, O}) : check_ptrs({Q, K, V, P, O});
     if (rc != LASP2_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    if (mfma_path_supported(g, desc->dtype)) {
-        // long slots that leave CUs without work: walks of parts of them
-        if (g.L >= 512) {
-            const WalkPlan wp = pick_walks(g, desc->cu_seqlens_host, false, false);
-            if (wp.W)
-                return from_hip(launch_attn_fwd_direct_mfma(regroup_short(g, desc->cu_seqlens_host, wp.W), Q, K, V,
-                                                            g.lone_slots ? nullptr : P, nullptr, O, st));
-        }
-        const Geom gw = regroup(g, desc->cu_seqlens_host, pick_walk_slots(g, desc->cu_seqlens_host, cu_count(), kWalkTargetFwd));
+    const WalkPlan wp = plan_of(g, desc->cu_seqlens_host, desc->dtype, LASP2_CALL_ATTN_FWD);
+    const Geom gw = regroup(g, desc->cu_seqlens_host, wp);
+    if (wp.W) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, g.lone_slots ? nullptr : P, nullptr, O, st));
+    if (mfma_path_supported(g, desc->dtype))
         return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
-    }
-    const Geom gp = regroup(g, desc->cu_seqlens_host, pick_planes_slots(g, desc->cu_seqlens_host, 1));
-    return from_hip(launch_attn_fwd_planes(gp, desc->dtype, Q, K, V, P, O, st));
+    return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, P, O, st));
 }
 
 int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,
@@ -676,7 +690,7 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     hipStream_t st = (hipStream_t)stream;
     const int32_t* cu = desc->cu_seqlens_host;
     const bool fast = mfma_path_supported(g, desc->dtype);
-    const WalkPlan wp = fast ? pick_forward_walks(g, cu) : WalkPlan{pick_planes_slots(g, cu, 1), 0, Start::states};
+    const WalkPlan wp = plan_of(g, cu, desc->dtype, LASP2_CALL_FORWARD);
     const Geom gw = regroup(g, cu, wp);
     hipError_t e;
     if (wp.start == Start::gather) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, nullptr, P, O, st));

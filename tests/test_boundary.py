@@ -33,7 +33,7 @@ def test_header_symbols_are_exported():
     names = set(re.findall(r"\b(lasp2_[a-z0-9_]+)\s*\(", text))
     assert {"lasp2_chunk_states", "lasp2_state_prefix", "lasp2_attn_fwd", "lasp2_attn_bwd",
             "lasp2_num_slots", "lasp2_workspace_size", "lasp2_status_string", "lasp2_state_total",
-            "lasp2_attn_bwd_noalloc",
+            "lasp2_attn_bwd_noalloc", "lasp2_forward", "lasp2_nomask_forward", "lasp2_walk_slots", "lasp2_walk_plan",
             "lasp2_nomask_fwd", "lasp2_nomask_bwd", "lasp2_softmax_fwd", "lasp2_softmax_bwd",
             "lasp2_softmax_workspace_size", "lasp2_softmax_fwd_share", "lasp2_softmax_bwd_share",
             "lasp2_softmax_share_workspace_size"} <= names
@@ -76,9 +76,8 @@ def test_walk_slots_choice(monkeypatch):
     as the device can keep busy; fp32, and slots that already hold a whole sequence, stay as they are."""
     monkeypatch.delenv("LASP2_WALK_SLOTS", raising=False)
     bf = dict(d=128, C=256, dtype=B.LASP2_BF16)
-    # 16 heads x 32 768 tokens, one state per chunk: walks of about 2 048 (forward) / 16 384 (backward;
-    # 4 096 in packed batches) tokens, halved until the launch has two rounds of workgroups (256 forward walks at a time, 128
-    # backward ones, which take two workgroups each)
+    # 16 heads x 32 768 tokens, one state per chunk.  lasp2_attn_fwd: walks of about 2 048 tokens, halved until the launch has
+    # two rounds of workgroups (256 walks at a time).  Backward: the estimate's choice, one round of 128 walks of two workgroups each
     assert _walk(_desc(H=16, N=32768, **bf)) == (0, 4)
     assert _walk(_desc(H=16, N=32768, **bf), 1) == (0, 8)
     # 256 sequences of 8 192 tokens: one walk per sequence (the serial-carry order of work)
@@ -88,7 +87,7 @@ def test_walk_slots_choice(monkeypatch):
     assert _walk(_desc(B=10, H=30, N=8192, **bf)) == (0, 8)
     # 16 heads x 262 144 tokens in 4 096-token slots: long enough as they are
     assert _walk(_desc(H=16, N=262144, L=4096, **bf)) == (0, 1)
-    # ... for the forward; the backward, which builds its states per walk, takes four of them
+    # ... for lasp2_attn_fwd; the backward, which builds its states per walk, takes four of them
     # (16 384 tokens, two rounds of 128 walks)
     assert _walk(_desc(H=16, N=262144, L=4096, **bf), 1) == (0, 4)
     # a launch the device runs in one go stays as it is
@@ -112,6 +111,41 @@ def test_walk_slots_choice(monkeypatch):
     out = ctypes.c_int64(0)
     assert B.lib().lasp2_walk_slots(None, 0, ctypes.byref(out)) == -1
     assert B.lib().lasp2_walk_slots(ctypes.byref(_desc()), 0, None) == -1
+
+
+def _plan(desc, call):
+    w, start = ctypes.c_int64(-1), ctypes.c_int(-1)
+    rc = B.lib().lasp2_walk_plan(ctypes.byref(desc), B.CALLS[call], ctypes.byref(w), ctypes.byref(start))
+    return rc, w.value, B.STARTS[start.value] if rc == 0 else None
+
+
+def test_walk_plan_tells_the_calls_apart(monkeypatch):
+    """lasp2_forward and the backward plan their walks by themselves; the query says what each call does."""
+    monkeypatch.delenv("LASP2_WALK_SLOTS", raising=False)
+    bf = dict(H=16, d=128, C=256, dtype=B.LASP2_BF16)
+    for kw, fwd, forward, bwd in (
+            (dict(N=32768), (1024, "states"), (2048, "states"), (2048, "states")),
+            (dict(N=262144, L=4096), (4096, "states"), (8192, "states"), (16384, "states")),
+            (dict(N=1531), (256, "states"), (256, "gather"), (256, "states")),
+            # one head in slots of 4 096: 25 of them, parts of a slot a walk
+            (dict(H=1, N=100003, L=4096), (448, "slots"), (448, "slots"), (832, "slots"))):
+        got = [_plan(_desc(**dict(bf, **kw)), c)[1:] for c in ("attn_fwd", "forward", "attn_bwd")]
+        assert got == [fwd, forward, bwd], (kw, got)
+    # where a walk is part of a slot the count of slots is 1; elsewhere the two queries agree
+    for kw in (dict(N=32768), dict(N=262144, L=4096), dict(H=1, N=100003, L=4096), dict(H=2, N=20000, L=512), dict(N=700, C=64)):
+        for back, call in ((0, "attn_fwd"), (1, "attn_bwd")):
+            desc = _desc(**dict(bf, **kw))
+            w = _plan(desc, call)[1]
+            assert _walk(desc, back) == (0, max(1, w // (desc.L or desc.C))), (kw, call)
+    # off the bf16, d = 128 path: one walk per slot, states first
+    assert [_plan(_desc(), c)[1:] for c in B.CALLS] == [(128, "states")] * 3
+    monkeypatch.setenv("LASP2_WALK_SLOTS", "3")
+    assert all(_plan(_desc(**dict(bf, N=32768)), c)[1] == 768 for c in B.CALLS)
+    lib, r, w, st = B.lib(), ctypes.byref(_desc()), ctypes.c_int64(), ctypes.c_int()
+    assert lib.lasp2_walk_plan(r, 0, None, ctypes.byref(st)) == -1 and lib.lasp2_walk_plan(r, 0, ctypes.byref(w), None) == -1
+    assert lib.lasp2_walk_plan(None, 0, ctypes.byref(w), ctypes.byref(st)) == -1
+    assert lib.lasp2_walk_plan(r, 3, ctypes.byref(w), ctypes.byref(st)) == -2 == lib.lasp2_walk_plan(r, -1, ctypes.byref(w), ctypes.byref(st))
+    assert _plan(_desc(N=0), "forward") == (0, 128, "states")
 
 
 def test_walk_slots_off_the_bf16_d128_path(monkeypatch):
