@@ -246,23 +246,30 @@ def main():
         if record:
             marks.append(e)
 
-    # The attention kernels may walk several of the caller's slots per workgroup (lasp2_walk_slots):
-    # the forward then reads one prefix state per walk, and the backward for bf16 with d = 128 builds its dM
-    # states per walk (the others per slot, and they skip states only where a slot is a whole sequence).
+    # The attention kernels walk several of the caller's slots per workgroup, or parts of one (lasp2_walk_plan), and start from
+    # a state per walk, from a state per slot, or from none (the walk then adds the rows up itself).
     Leff = L or C
     mfma = dtype == "bf16" and d == 128
     doc_lens = [N] if cu is None else [int(b - a) for a, b in zip(cu[:-1], cu[1:])]
-    walks = lambda w: sum(-(-n // (w * Leff)) for n in doc_lens)
+
+    def walks(w):
+        if w >= Leff:
+            return sum(-(-n // w) for n in doc_lens)
+        full = [-(-n // Leff) - 1 for n in doc_lens]
+        return sum(f * -(-Leff // w) + -(-(n - f * Leff) // w) for f, n in zip(full, doc_lens))
+    (w_f, start_f), (w_b, start_b) = bd.lasp2_walk_plan(p, "attn_fwd"), bd.lasp2_walk_plan(p, "attn_bwd")
     ws_f, ws_b = bd.lasp2_walk_slots(p), bd.lasp2_walk_slots(p, backward=True)
-    Tw_f, Tw_b = walks(ws_f), walks(ws_b)
-    ws_states = ws_b if mfma else 1
-    lone_f, lone_b = (walks(w if mfma else 1) == len(doc_lens) for w in (ws_f, ws_b))
+    # tokens per state that the backward builds before its attention launch (off the matrix-core kernels per slot, whatever the walk)
+    w_states = w_b if mfma and start_b == "states" else Leff
+    lone_f, lone_b = walks(w_f if mfma else Leff) == len(doc_lens), walks(w_states) == len(doc_lens)
+    n_states = lambda start, w, one: 0 if start == "gather" or one else walks(w) if start == "states" else T_s
     # What lasp2_attn_bwd spends before its attention launch: the dM_t = Q_t^T dO_t and their suffix
     # combine, timed once here through the public calls on a descriptor whose slots are those states'
-    # (the undecayed matrix-core kernels want the dM_t even when every sequence is a single walk).
+    # (the undecayed matrix-core kernels want the dM_t even when every sequence is a single walk; walks that gather
+    # want none).
     pre_ms = 0.0
-    if not lone_b or (mfma and not args.decay):
-        pw = bd.Problem(B, H, N, d, C, ws_states * Leff, dtype, cu, decay=decay) if ws_states > 1 else p
+    if start_b != "gather" and (not lone_b or (mfma and not args.decay)):
+        pw = bd.Problem(B, H, N, d, C, w_states, dtype, cu, decay=decay) if w_states != Leff else p
 
         def pre():
             bd.lasp2_chunk_states(pw, Q, dO, ws)
@@ -330,30 +337,29 @@ def main():
 
     esz = 2 if dtype == "bf16" else 4
     mfma_path = dtype == "bf16" and d == 128
-    pair_kernel = mfma_path and ws_b * Leff > 128 and not args.decay   # dV and dK of a walk in one workgroup
+    pair_kernel = mfma_path and w_b > 128 and not args.decay   # dV and dK of a walk in one workgroup
     # Dominant kernels: the attention launches, one per direction.  Algorithmic bytes:
     #   forward launch : Q, K, V read, O written, one state array read            (4 passes)
     #   backward launch: Q, K, V, dO read once, dQ, dK, dV written, P read once and the suffix states
     #                    once (dV and dK in one workgroup) or twice (one workgroup each)   (7 passes)
-    # With one slot per sequence no prefix state is read.
+    # With one slot per sequence no prefix state is read, and no state at all by walks that gather.
     tensor = B * H * N * d * esz
     state = B * H * d * d * 4
-    bytes_fwd = 4 * tensor + (0 if lone_f else Tw_f * state)
-    bytes_bwd = 7 * tensor + ((0 if lone_b else 1) + (1 if pair_kernel else 2)) * Tw_b * state
+    states_f, states_b = n_states(start_f, w_f, lone_f), n_states(start_b, w_states, False)
+    reads_P = 0 if lone or (start_b == "states" and lone_b) else T_s if w_b < Leff else walks(w_b)
+    bytes_fwd = 4 * tensor + states_f * state
+    bytes_bwd = 7 * tensor + (reads_P + (1 if pair_kernel else 2) * states_b) * state
     # HIP events bracket the forward launch exactly.  The backward launch sits inside
     # lasp2_attn_bwd behind a states kernel and a combine kernel, timed before the loop (pre_ms),
     # so its time is attn_bwd minus those.
     fwd_v = per_step[seg_names.index("attn_fwd")]
     bwd_v = [t - pre_ms for t in per_step[seg_names.index("attn_bwd")]]
-    wide_f, wide_b = ws_f * Leff > 128, ws_b * Leff > 128
-    if not mfma_path:
-        kern_fwd = kern_bwd = "attn_planes_kernel"
-    elif args.decay:
-        kern_fwd = "attn_skew_mfma_kernel<decay>" if wide_f else "attn_decay_mfma_kernel<128>"
-        kern_bwd = "attn_skew_mfma_kernel<decay>" if wide_b else "attn_decay_mfma_kernel<128>"
-    else:
-        kern_fwd = "attn_skew_mfma_kernel" if wide_f else "attn_mfma_kernel<128>"
-        kern_bwd = "attn_bwd_pair_mfma_kernel" if wide_b else "attn_mfma_kernel<128>"
+    names = {"fwd": ("attn_skew_mfma_kernel", "attn_mfma_kernel<128>", "attn_fwd_direct_mfma_kernel"),
+             "bwd": ("attn_bwd_pair_mfma_kernel", "attn_mfma_kernel<128>", "attn_bwd_direct_mfma_kernel")}
+    if args.decay:
+        names = {k: ("attn_skew_mfma_kernel<decay>", "attn_decay_mfma_kernel<128>", f"attn_decay_{k}_direct_kernel") for k in names}
+    pick = lambda k, w, start: "attn_planes_kernel" if not mfma_path else names[k][2 if start != "states" else 0 if w > 128 else 1]
+    kern_fwd, kern_bwd = pick("fwd", w_f, start_f), pick("bwd", w_b, start_b)
     consts = {} if (args.decay or args.slot_len is not None or args.heads is not None) else PROFILE_CONSTANTS.get(args.workload, {})
 
     def launch(v, nbytes, traffic):
@@ -376,7 +382,8 @@ def main():
                                + (f" packed {cfg['n_docs']} docs" if cu is not None else "")
                                + (" decay 1-2^(-5-h)" if args.decay else "")
                                + (" serial carry: one slot per sequence, no state arrays in the forward" if lone else ""),
-                   "state_slots": int(T_s), "slots_per_walk": {"fwd": ws_f, "bwd": ws_b}},
+                   "state_slots": int(T_s), "slots_per_walk": {"fwd": ws_f, "bwd": ws_b},
+                   "walk_tokens": {"fwd": w_f, "bwd": w_b}, "walk_start": {"fwd": start_f, "bwd": start_b}},
         "ms": {n: seg[n]["mean"] for n in seg_names},
         "ms_median": {n: seg[n]["median"] for n in seg_names},
         "ms_min": {n: seg[n]["min"] for n in seg_names},
