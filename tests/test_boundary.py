@@ -148,6 +148,31 @@ def test_walk_plan_tells_the_calls_apart(monkeypatch):
     assert _plan(_desc(N=0), "forward") == (0, 128, "states")
 
 
+@pytest.mark.parametrize("C,L", [(64, 0), (256, 4096)])
+def test_planning_packed_batches_costs_a_few_passes_over_the_documents(monkeypatch, C, L):
+    """A plan weighs some thirty choices.  It must not pass through the documents for each: measured in counts of the slots, two
+    passes each (1.3 to 1.6 of them; 28 and 20 when it did)."""
+    import time
+    monkeypatch.delenv("LASP2_WALK_SLOTS", raising=False)
+    rng = np.random.default_rng(0)
+    lens = np.maximum(1, rng.lognormal(3.8, 0.8, 4000).astype(np.int64))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    desc = _desc(H=16, N=int(cu[-1]), d=128, C=C, L=L, dtype=B.LASP2_BF16, n_seqs=4000, cu_seqlens_host=cu.ctypes.data,
+                 cu_seqlens_dev=0x2000)
+
+    def fastest(f):
+        best = 1e9
+        for _ in range(40):
+            t0 = time.perf_counter()
+            for _ in range(5):
+                f()
+            best = min(best, time.perf_counter() - t0)
+        return best
+    slots = fastest(lambda: _slots(desc))
+    for call in B.CALLS:
+        assert fastest(lambda: _plan(desc, call)) <= 6 * slots, call
+
+
 def test_walk_slots_off_the_bf16_d128_path(monkeypatch):
     """The kernels for fp32, d < 128 and strong decay take slots that leave their 128-row chunks partly empty two,
     four or eight at a time while every CU gets a workgroup; the query says so, and the override reaches them."""
