@@ -2540,9 +2540,10 @@ hipError_t launch_states_mfma(const Geom& g, const void* K, const void* V, float
     // four rounds of them (one share each | dealt, us, 131 072 tokens in 40 documents: 32 heads 625 | 613, 64 heads 1 231 | 1 176;
     // a second or third round that is nearly empty costs more than it evens out: 8 heads 157 | 178, 16 heads 311 | 323, 16 heads x
     // 65 536 in 1 000 510 | 646) and a document is found in few steps from its mark (32 heads x 262 144 in 4 000 8 735 | 8 970).
-    if (g.n_seqs && g.doc_stride <= 8) {
+    // Slots longer than a share one by one, as a few of them together are of any length (16 heads x 262 144 in 40, 4 096 a slot 440 | 410).
+    if (g.n_seqs) {
         const long long share = std::max(1LL, 2048LL * g.T_s / g.N), dealt = (nunits + share - 1) / share;
-        if (dealt >= 8LL * cus) wgs = dealt;
+        if (share == 1 || (g.doc_stride <= 8 && dealt >= 8LL * cus)) wgs = dealt;
     }
     dim3 grid((unsigned)wgs), block(ST_NT);
     const char *k = static_cast<const char*>(K), *v = static_cast<const char*>(V);
