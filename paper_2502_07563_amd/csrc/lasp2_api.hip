@@ -192,7 +192,7 @@ int forced_walk_slots(const Geom& g)
     return v >= 1 ? (int)std::min<int64_t>(v, max_walk_slots(g)) : 0;
 }
 
-// Slots per walk of lasp2_attn_fwd, and of packed batches: for a launch that runs `par` walks at a time and gains
+// Slots per walk of lasp2_attn_fwd, and of lasp2_forward where slots are not a multiple of 64 tokens: for a launch that runs `par` walks at a time and gains
 // little from walks longer than `target` tokens (measured: the forward launch is flat from about 2 048 tokens on; starting a walk costs what streaming about a hundred tokens does).
 //   - Equal sequences, enough of them to fill the device by themselves: one walk per sequence,
 //     which needs no prefix or suffix state at all (the serial-carry order of work).
@@ -229,24 +229,37 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
 
 // How lasp2_forward (walks that write states in passing, kernels_mfma.hip) and the backward cut the sequences: slots per
 // walk, and whether the walks gather the state they start from themselves (`direct`: one launch, no states and prefix
-// before it).  Both from an estimate in us of what each choice costs, with the rates below; the candidates are the shortest
-// walks that fit into one to sixteen rounds of workgroups, or powers of two for documents of different lengths.
+// before it); also which long slots lasp2_attn_fwd takes in parts.  From an estimate in us of what each choice costs; the candidates are the
+// shortest walks that fit into one to sixteen rounds of workgroups, the shortest at all, and powers of two for documents of different lengths.
+// The rates are measured, the rest is fitted to 284 shapes (1 to 300 sequences of 3 to 200 000 tokens, packed batches among them) with every choice
+// timed: the chosen one takes 2.2 % more than the best in the forward and 2.5 % in the backward (geometric means).
 //   - A row of a walk takes 0.03 us forward (dQ 0.031, the pair of the backward 0.0376; with decay 0.033 each, and 0.009 gathered), starting a walk what 256 (180)
 //     rows do, a row that is gathered 0.0068 (16 heads, walks of 256, gathered | states first, us: 300 rows 15 | 22; 1 024
-//     20 | 24; 2 048 28 | 30; 3 000 37 | 31; 4 096 45 | 36; backward 20 | 27, 25 | 32, 34 | 37, 44 | 46, 58 | 50).
+//     20 | 24; 2 048 28 | 30; 3 000 37 | 31; 4 096 45 | 36; backward 20 | 27, 25 | 32, 34 | 37, 44 | 46, 58 | 50).  Rows come 128 at
+//     a time, with decay 256 (4 x 8 000 decayed, backward, walks of 256 51, 384 66, 512 47; 2 x 16 x 271, whole 25.7, 256 21.6).
+//   - `crowded`: parts of slots gather the same rows at once, past the L2s (32 MB) at less than half that rate (2 x 4 x 38 206, slots of 2 560,
+//     lasp2_attn_fwd 84 whole, 100 in parts of 640; backward 2 x 50 000, slots of 2 048, 121 whole, 128 to 145 in parts of 384 to 576).
 //   - Memory: 5.2 TB/s, 8 where the tensors fit the 256 MB cache.  The one-launch backward reads four tensors more, as its two
 //     workgroups per walk don't keep in step (256 sequences of 2 000: 305 | 262), large ones ten (64 of 43 174: 2420 | 2190).
 //   - Of two choices that memory bounds alike the one with less work (0.05 of the walks' time on top).  Documents of
-//     different lengths: the last to start is a long one, and takes 0.05 us per row beside the others (32 heads, 131 072 in
+//     different lengths: the last to start is a long one, and takes 0.05 us per row beside the others, 0.6 of a walk on average (32 heads, 131 072 in
 //     40 documents, forward, walks of 2 048 1434 us, 4 096 1275, 8 192 1212, whole documents 2411).
-//   - States: read at 6 TB/s, 0.0127 us per row of one slot, and 10 us for two launches; documents of different lengths spread unevenly:
+//   - States: read at 6 TB/s, 0.0118 us per row of one slot (128 slots of 20 000 rows: 236; backward with its suffix 0.0127), and 10 us for two launches; beyond 16 of
+//     a sequence's states 0.1 each, as they are combined one after another (1 x 39 086, forward, walks of 192 66, 384 56); documents of different lengths spread unevenly:
 //     a third more.  (32 heads, 131 072 tokens in 40 documents, forward 1500 -> 1212 us direct in walks of 8 192; 16 heads,
 //     32 768 in 50 322 -> 187, backward 486 -> 341; 32 heads, 8 000 in 20 100 -> 72, 239 -> 155.)
-//   - Walks have at least 256 rows: shorter ones take the 128-row kernel and write no states in passing (16 heads x 3 000,
-//     64-token slots, forward: walks of 128 58 us, 192 or 256 38; backward 74 -> 54).
+//   - Forward walks have more than 128 rows: shorter ones take the 128-row kernel and write no states in passing (16 heads x 3 000,
+//     64-token slots: walks of 128 58 us, 192 or 256 38; 2 x 2 581, slots of 192, 23 one by one, 33 by two).  Backward walks have 96 or more; the kernels for up to 128 rows, with three
+//     workgroups a walk, pay while all of them fit (4 x 1 000 21 us, 26 with 256; 32 x 1 000 49, 33), and gathering walks of 128 while there are few (4 x 300 16, 21).
 //   - One round ends at the pace of the slowest CU: 8 % more in the backward (16 heads, one round | two, us: 8 192 85 | 93;
 //     16 384 149 | 151; 32 768 281 | 271; 262 144 2058 | 1949), 3 % in the forward (65 536: 346 | 361; 262 144, 4 096-token
-//     slots: 1209 | 1153).
+//     slots: 1209 | 1153), 4 % more where it is long and memory bounds it.  Backward (`busy`): a device with few workgroups runs them a fifth faster, and every round
+//     past the first, to the third, costs 6 % more than it alone (states first, 64 x 1 000 0.89 of the estimate, 64 x 4 000 in two rounds 1.07, 64 x 8 000 in four 1.12).
+//   - A gathering backward of a few rounds lasts as long as they do, however short the walks (8 x 20 sequences of 59 rows, two rounds, 24; states first 22; parts of
+//     slots gather in each, 1 x 100 003 in slots of 4 096, parts of 448, two rounds, 196, of 832, one, 156).  With decay
+//     and one walk per document there is nothing to gather: a kernel of its own for that is slower (32 x 4 of 13 rows 27; 13).
+//   - Margins: gathering where the estimate errs more (backward 1.05, packed with decay 1.12 (8 heads, 20 000 in 50, slots of 1 024, 176; 163), forward parts of slots
+//     1.12), and up to 6 us for parts of short slots that are given states (lasp2_attn_fwd, slots of 512, in halves | whole: 4 x 13 887, 217 workgroups, 23.6 | 21.2; 8 x 3 297, 104, 18.0 | 19.9).
 enum class Start {
     states,   // states and prefix kernels first, a walk is `ws` slots
     gather,   // the walks gather them, from or to the document's end; a walk is `ws` slots, or W > 0 tokens
@@ -340,7 +353,7 @@ WalkCount count_inside(const Geom& g, const int32_t* cu_host, int64_t longest, i
     return c;
 }
 
-// may_states = false: the states are there already (lasp2_attn_fwd)
+// may_states = false: the states are there already (lasp2_attn_fwd, slots only)
 WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, bool backward, bool may_states)
 {
     const int64_t longest = longest_sequence(g, cu_host), slots = slots_of(longest, g.L);
@@ -348,40 +361,56 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, bool backward, bool m
     const int ncu = cu_count();
     const double G = g.G, N = g.N, cus = ncu, par = cus / wgs, start = backward ? 180.0 : 256.0;
     const double row = g.decay ? 0.033 : backward ? 0.0376 : 0.03, gather = g.decay ? 0.009 : 0.0068;
+    const int part = g.decay ? 256 : 128;   // rows that a walk takes at a time
     const double per_row = g.decay ? 3.0 * row : row + 0.031, ends = g.decay ? 2.0 : 1.0;   // backward: of all workgroups of a walk; that gather `after`
     auto estimate = [&](const WalkCount& c, int64_t W, Start how) {
         const double tensor = G * N * 256.0, states = G * N / (double)g.L * 65536.0;
         const double rate = (backward ? 7.0 : 4.0) * tensor < 2.56e8 ? 8e6 : 5.2e6;
         const double memory = (backward ? 7.0 * tensor : 4.0 * tensor + states) / rate * (!backward && c.walks * G <= par && W > (g.decay ? 4096 : 8192) ? 1.04 : 1.0);
-        const double one = (c.longest + start) * row, rounds = std::ceil(c.walks * G * wgs / cus);
+        const double rows_of_one = c.longest < 2048.0 ? std::ceil(c.longest / part) * part : c.longest;
+        const double crowded = how != Start::both || 2.0 * tensor < 2.4e7 ? gather : backward ? (g.decay ? 0.012 : 0.0113) : g.decay ? 0.02 : 0.015;
+        const double one = (rows_of_one + start) * row, units = c.walks * G * wgs, rounds = std::ceil(units / cus);
+        const double busy = g.n_seqs || !backward ? 1.0 : units <= cus ? 0.8 + 0.2 * units / cus
+                                                        : 1.0 + (g.decay ? 0.0 : 0.06) * std::min(3.0, rounds - 1.0);
         const double walk = g.n_seqs ? std::max(one, G * (N + start * c.walks) * row / par)
-                                     : rounds * one * (rounds > 1.0 ? 1.0 : backward ? 1.08 : 1.03);
+                                     : rounds * one * busy * (rounds > 1.0 ? 1.0 : backward ? 1.08 : 1.03);
         const double tail = 0.05 * walk + (g.n_seqs && rounds > 1.0 ? 0.6 * one : 0.0);
         const double again = 256.0 * row * std::max(0.0, (g.n_seqs ? c.walks * G / par : rounds) - 1.0);   // gathering starts once more
-        const double cache = 2.0 * tensor < 2e8 ? 2e7 : 8e6, unsure = backward ? 1.05 : W < g.L ? 1.12 : 1.0;
+        const double cache = 2.0 * tensor < 2e8 ? 2e7 : 8e6, unsure = !backward ? (W >= g.L ? 1.0 : 1.12) : g.decay && g.n_seqs ? 1.12 : 1.05;
         const double moved = g.n_seqs ? 4.0 * G * 65536.0 / 5.2e6 : 0.0;   // a walk's state: written, combined, read
         const double uneven = g.n_seqs ? 1.33 : 1.0;
+        const double chain = g.n_seqs ? 0.0 : 0.1 * std::max(0.0, (double)longest / (double)(how == Start::states ? W : g.L) - 16.0);   // states combined one after another
         if (!backward) {
-            const double first = c.inner == 0.0 || !may_states ? 0.0 : 10.0 + G * c.inner * 512.0 / 6e6 * uneven + moved * c.parts;
+            const double first = c.inner == 0.0 || !may_states ? 0.0
+                                 : 10.0 + std::max(G * c.inner * 512.0 / 6e6 * uneven, c.longest_part * 0.0118) + moved * c.parts + chain;
             if (how == Start::states) return std::max(walk, memory) + tail + first;
             const bool in = how == Start::both;
             const double rows = G * (in ? c.before_in : c.before);
-            return unsure * (std::max({walk + again + rows * gather / par, one + (in ? c.farthest_in : c.farthest) * gather,
-                                       memory + rows * 512.0 / cache}) + tail + (in ? first : 0.0));
+            return unsure * (std::max({walk + again + rows * crowded / par, one + (in ? c.farthest_in : c.farthest) * gather,
+                                       memory + rows * 512.0 / cache}) + tail + (!in ? 0.0 : may_states ? first : g.L <= 1024 ? 6.0 * std::min(1.0, units / cus) : 0.0));
         }
         const double first = g.decay && c.inner == 0.0 ? 0.0   // (exclusive suffixes, all zero)
-                             : 10.0 + std::max(2.0 * tensor / 6e6 * uneven, c.longest_part * 0.0127) + moved * c.parts;
+                             : 10.0 + std::max(2.0 * tensor / 6e6 * uneven, std::ceil(c.longest_part / part) * part * 0.0127) + moved * c.parts + chain;
+        if (how == Start::states && W <= 128) {   // the kernels for 128 rows, three workgroups per walk
+            const double wide = 3.0 * c.walks * G / cus;
+            if (c.inner == 0.0) return (g.decay ? 12.0 : 15.0) + std::max(0.0, wide - 1.0) * (7.0 + 0.05 * c.longest) + 2.0 * tensor / 6e6 + moved * c.parts;
+            return std::max(18.0, 10.0 + 13.5 * wide * (c.longest + 64.0) / 192.0) + 2.0 * tensor / 6e6 + 0.19 * (double)longest / (double)W +
+                   moved * c.parts;
+        }
         if (how == Start::states) return std::max(walk, memory) + tail + first;
         const bool in = how == Start::both;
         const double far = in ? std::min((double)longest, (double)g.L) : (double)longest;
         const double rows = G * (ends * (in ? c.after_in : c.after) + (W < g.L ? c.before_in : 0.0));
-        const double all = (rows * gather + G * (N + start * c.walks) * per_row) / cus;
+        const double all = (rows * crowded + G * (N + start * c.walks) * per_row) / cus;
         const double passes = tensor < 2e8 ? 11.0 : 17.0;
-        return unsure * (std::max({1.5 * far * gather + 1.08 * one + 0.1 * all, 1.1 * all, passes * tensor / rate + rows * 512.0 / 1e7}) + 0.15 * all +
-                         (in ? first : 0.0));
+        double slowest = 1.5 * far * gather + 1.08 * one * std::min(1.0, busy) + 0.1 * all;
+        if (!g.n_seqs && rounds > 1.0 && rounds <= 4.0)
+            slowest = std::max(slowest, g.decay ? rounds * one : W >= g.L ? rounds * ((rows_of_one + start) * 0.031 + 3.3)
+                                        : far * gather + one + (rounds - 1.0) * ((rows_of_one + start) * 0.031 + 3.3 + 0.5 * far * crowded));
+        return unsure * (std::max({slowest, 1.1 * all, passes * tensor / rate + rows * 512.0 / 1e7}) + 0.15 * all + (in ? first : 0.0));
     };
     const int forced = forced_walk_slots(g);
-    const int64_t ws_max = std::min(slots, max_walk_slots(g)), ws_min = std::min((256 + g.L - 1) / g.L, ws_max);
+    const int64_t ws_max = std::min(slots, max_walk_slots(g)), ws_min = std::min(backward ? slots_of(96, g.L) : 128 / g.L + 1, ws_max);
     WalkPlan best = {1, 0, Start::states};
     double cost = -1.0;
     auto take = [&](const WalkPlan& p, const WalkCount& c) {
@@ -390,8 +419,8 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, bool backward, bool m
     };
     const bool lone = slots <= 1;
     auto offer_counted = [&](int64_t ws, const WalkCount& c) {
-        take({(int)ws, 0, Start::states}, c);
-        if (may_states || backward) take({(int)ws, 0, Start::gather}, c);
+        if (!backward || lone || forced || ws * g.L >= 256 || 3.0 * c.walks * G <= cus) take({(int)ws, 0, Start::states}, c);
+        if (backward ? !(lone && g.decay) : may_states) take({(int)ws, 0, Start::gather}, c);
     };
     auto offer = [&](int64_t ws) {
         WalkCount c;
@@ -425,10 +454,16 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, bool backward, bool m
             const int64_t m = (int64_t)k * ncu / ((int64_t)wgs * g.G);   // walks per sequence
             if (m < 1) continue;
             const int64_t ws = std::min(ws_max, std::max(ws_min, (slots + m - 1) / m)), W = (g.N + m - 1) / m;
-            if (!lone && !forced) offer(ws);
+            if (!lone && !forced) {
+                offer(ws);
+                const int64_t whole = std::min(ws_max, (ws * g.L + part - 1) / part * part / g.L);   // whole rounds of a walk's rows
+                if (whole > ws) offer(whole);
+            }
             offer_short(W);
+            if (m >= 2 * slots) offer_short((std::min<int64_t>(g.L, g.N) + m / slots - 1) / (m / slots));   // as many walks in every slot
             if (ws == ws_min && W <= 256) break;
         }
+        if (!lone && !forced && ws_min < ws_max) offer(std::min(2 * ws_min, ws_max));
         if (cost < 0.0) offer(ws_max);
     }
     return best;

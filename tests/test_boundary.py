@@ -128,9 +128,16 @@ def test_walk_plan_tells_the_calls_apart(monkeypatch):
             (dict(N=262144, L=4096), (4096, "states"), (8192, "states"), (16384, "states")),
             (dict(N=1531), (256, "states"), (256, "gather"), (256, "states")),
             # one head in slots of 4 096: 25 of them, parts of a slot a walk
-            (dict(H=1, N=100003, L=4096), (448, "slots"), (448, "slots"), (832, "slots"))):
+            (dict(H=1, N=100003, L=4096), (448, "slots"), (448, "slots"), (832, "slots")),
+            # few heads: walks of 128 rows in the backward; more of them, and 256 are the shorter launch
+            (dict(H=4, N=1000, C=128), (128, "states"), (256, "gather"), (128, "states")),
+            (dict(H=32, N=1000, C=128), (128, "states"), (256, "gather"), (256, "states"))):
         got = [_plan(_desc(**dict(bf, **kw)), c)[1:] for c in ("attn_fwd", "forward", "attn_bwd")]
         assert got == [fwd, forward, bwd], (kw, got)
+    # with decay and one walk per document there is nothing to gather, and no launch that it would save
+    lam = (ctypes.c_float * 4)(*([0.9] * 4))
+    one = dict(bf, B=32, H=4, N=13, C=64, decay_host=ctypes.addressof(lam), decay_dev=0x3000)
+    assert _plan(_desc(**one), "attn_bwd")[1:] == (64, "states")
     # where a walk is part of a slot the count of slots is 1; elsewhere the two queries agree
     for kw in (dict(N=32768), dict(N=262144, L=4096), dict(H=1, N=100003, L=4096), dict(H=2, N=20000, L=512), dict(N=700, C=64)):
         for back, call in ((0, "attn_fwd"), (1, "attn_bwd")):
