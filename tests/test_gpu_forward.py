@@ -18,20 +18,51 @@ CASES = [  # C, L, walk slots (0: the library's choice), lengths of the document
     # long slots, cut into walks: one slot, several, a last slot shorter than a walk, documents
     (256, 7168, 0, [7000]), (256, 4096, 0, [8200]), (256, 4096, 0, [9000]), (128, 1920, 0, [7700]), (100, 1000, 0, [3500]),
     (256, 2048, 0, [5000, 70, 2049]), (64, 4096, 0, [4096, 257, 4200, 5]),
+    # walks of single slots: of 128 rows and fewer, of between 128 and 256, and forced
+    (128, 0, 0, [300]), (100, 0, 0, [245]), (192, 0, 0, [380]), (256, 0, 1, [500]),
 ]
+
+
+def _case(monkeypatch, C, L, walk, docs, decay, device="cuda"):
+    if walk:
+        monkeypatch.setenv("LASP2_WALK_SLOTS", str(walk))
+    else:
+        monkeypatch.delenv("LASP2_WALK_SLOTS", raising=False)
+    cu = np.concatenate([[0], np.cumsum(docs)]).astype(np.int32)
+    N, d = int(cu[-1]), 128
+    B, H = (2 if len(docs) == 1 else 1, 3) if N < 5000 else (1, 2)
+    lam = np.array([1 - 2.0 ** -5, 0.9, 1.0], np.float32)[:H] if decay else None
+    return bd.Problem(B, H, N, d, C, L, "bf16", cu if len(docs) > 1 else None, decay=lam, device=device), cu, lam
+
+
+@pytest.mark.parametrize("decay", [False, True])
+def test_the_cases_take_every_route(monkeypatch, decay):
+    """What the library chooses for the cases below (256 CUs assumed where no device answers): each call's walks of several slots,
+    of one and of parts of one, for each kind of start that it has."""
+    routes = set()
+    for C, L, walk, docs in CASES:
+        p, cu, _ = _case(monkeypatch, C, L, walk, docs, decay, "cpu")
+        for call in bd.CALLS:
+            w, start = bd.lasp2_walk_plan(p, call)
+            lone = max(docs) <= (w if start == "states" else L or C)
+            routes.add((call, start, "part" if w < (L or C) else "one" if w == (L or C) else "several", lone))
+    states = {("states", kind, lone) for kind in ("one", "several") for lone in (False, True)}
+    alone = {("states", kind, True) for kind in ("one", "several")}
+    gather = {("gather", "one", False), ("gather", "several", False), ("gather", "part", False)}
+    want = {(call,) + r for call in bd.CALLS for r in states | {("gather", "part", True), ("slots", "part", False)}}
+    want |= {(call,) + r for call in ("forward", "attn_bwd") for r in gather}
+    if not decay:   # (whole documents without decay: few of them gather, many are for the full sizes)
+        want -= {("attn_bwd",) + r for r in alone}
+        want.add(("attn_bwd", "gather", "one", True))
+    assert want <= routes, sorted(want - routes)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("decay", [False, True])
 @pytest.mark.parametrize("C,L,walk,docs", CASES)
 def test_forward_in_one_call(monkeypatch, C, L, walk, docs, decay):
-    if walk:
-        monkeypatch.setenv("LASP2_WALK_SLOTS", str(walk))
-    cu = np.concatenate([[0], np.cumsum(docs)]).astype(np.int32)
-    N, d = int(cu[-1]), 128
-    B, H = (2 if len(docs) == 1 else 1, 3) if N < 5000 else (1, 2)
-    lam = np.array([1 - 2.0 ** -5, 0.9, 1.0], np.float32)[:H] if decay else None
-    p = bd.Problem(B, H, N, d, C, L, "bf16", cu if len(docs) > 1 else None, decay=lam)
+    p, cu, lam = _case(monkeypatch, C, L, walk, docs, decay)
+    B, H, N, d = p.B, p.H, p.N, p.d
     gen = torch.Generator(device="cuda").manual_seed(N + C)
     Q, K, V = (torch.randn(B, H, N, d, generator=gen, device="cuda").mul_(d ** -0.5).to(torch.bfloat16) for _ in range(3))
     P, O = bd.alloc_states(p).fill_(float("nan")), torch.full_like(Q, float("nan"))

@@ -16,6 +16,22 @@ pytestmark = pytest.mark.gpu
 _CACHE = {}   # one config's device results and host inputs at a time
 
 
+def _check_one_call(p, Q, K, V, P, O):
+    """lasp2_forward against the three calls it stands for (whose P and O the oracle checks): every entry of P, every row
+    of O, group by group; both arrays NaN beforehand."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    P1, O1 = torch.full_like(P, float("nan")), torch.full_like(O, float("nan"))
+    bd.lasp2_forward(p, Q, K, V, P1, O1)
+    flat = lambda t: t.reshape((-1,) + tuple(t.shape[2:]))
+    for a, b, oa, ob in zip(flat(P1), flat(P), flat(O1), flat(O)):
+        # the same fp32 sums in another order
+        assert bool(((a - b).norm(dim=(1, 2)) <= TOL_STATE * b.norm(dim=(1, 2))).all())
+        # states that differ in rounding order: a bf16 rounding of O, the scores and the snapshot each, per row
+        oa, ob = oa.float(), ob.float()
+        assert bool(((oa - ob).norm(dim=1) <= 3 * 2.0 ** -8 * ob.norm(dim=1) + 1e-6).all())
+
+
 def _run_config(name):
     import torch
     from paper_2502_07563_amd import binding as bd
@@ -44,6 +60,7 @@ def _run_config(name):
     bd.lasp2_chunk_states(p, dev["Q"], dev["dO"], dP)
     bd.lasp2_state_prefix(p, dP, dP, True)
     torch.cuda.synchronize()
+    _check_one_call(p, dev["Q"], dev["K"], dev["V"], P, O)
     out = dict(O=O, dQ=dQ, dK=dK, dV=dV, M=M, P=P, dP=dP)
     _CACHE[name] = (cfg, cu, out, host)
     return _CACHE[name]
@@ -119,8 +136,8 @@ def test_cfg3_long_sequence_bench_configuration(oracle, first_head):
 
 def test_walk_choices_of_the_named_workloads():
     """What the library does with the named workloads on this device (one state per chunk in configs 2, 4
-    and 5 still gives long walks; config 3's 4 096-token slots are walked one by one forwards, four at a
-    time backwards) - the paths the
+    and 5 still gives long walks; config 3's 4 096-token slots are walked one by one by lasp2_attn_fwd, two at a time
+    by lasp2_forward, four at a time backwards) - the paths the
     tests in this file then compare with the oracle."""
     from paper_2502_07563_amd import binding as bd
     want = {"cfg2": (4, 8), "cfg3": (1, 4), "cfg4": (32, 32)}
@@ -131,6 +148,11 @@ def test_walk_choices_of_the_named_workloads():
     cfg = synth.CONFIGS["cfg5"]
     p = bd.Problem(*(cfg[k] for k in ("B", "H", "N", "d", "C", "L", "dtype")), synth.config_offsets(cfg))
     assert bd.lasp2_walk_slots(p) > 1 and bd.lasp2_walk_slots(p, backward=True) > 1
+    forward = {"cfg2": (2048, "states"), "cfg3": (8192, "states"), "cfg4": (8192, "states"), "cfg5": (8192, "gather")}
+    for name, plan in forward.items():
+        cfg = synth.CONFIGS[name]
+        p = bd.Problem(*(cfg[k] for k in ("B", "H", "N", "d", "C", "L", "dtype")), synth.config_offsets(cfg))
+        assert bd.lasp2_walk_plan(p, "forward") == plan, name
 
 
 def test_cfg4_llama8b_layer(oracle):
@@ -184,6 +206,7 @@ def test_tensors_beyond_4_gib_and_2_31_elements(oracle):
     bd.lasp2_attn_fwd(p, Q, K, V, P, O)
     bd.lasp2_attn_bwd(p, Q, K, V, dO, P, dQ, dK, dV, nan(bd.alloc_workspace(p)))
     torch.cuda.synchronize()
+    _check_one_call(p, Q, K, V, P, O)
     groups = [0, H - 1]
     host = lambda t: t[0, groups].float().cpu().numpy().astype(np.float64)
     x = {n: host(t) for n, t in (("Q", Q), ("K", K), ("V", V), ("dO", dO))}
