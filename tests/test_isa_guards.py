@@ -105,6 +105,8 @@ SKEW = (("attn_skew_mfma_kernelILb0E", 4), ("attn_skew_mfma_kernelILb1E", 4), ("
         # one loop more for each place where rows are gathered before a walk
         ("attn_fwd_direct_mfma_kernel", 3), ("attn_bwd_direct_mfma_kernel", 8),
         ("attn_decay_fwd_direct_kernel", 3), ("attn_decay_bwd_direct_kernel", 6))
+GATHERS = {"attn_fwd_direct_mfma_kernel": 1, "attn_bwd_direct_mfma_kernel": 2,
+           "attn_decay_fwd_direct_kernel": 1, "attn_decay_bwd_direct_kernel": 2}   # ... of them
 
 
 def _skew_blocks(lines, inst):
@@ -162,7 +164,7 @@ def test_skew_kernel_leaves_the_rows_in_flight_alone(isa, inst, ncopies):
     for h, ins in blocks:
         if h:
             by_loop.setdefault(h, []).extend(ins)
-    checked = 0
+    checked = gathering = 0
     for h, ins in by_loop.items():
         if not any("v_mfma" in l for l in ins):
             continue                      # the walk over the documents of a packed batch
@@ -176,8 +178,8 @@ def test_skew_kernel_leaves_the_rows_in_flight_alone(isa, inst, ncopies):
             elif t and not t.startswith(";") and not t.startswith("."):
                 code.append((t, in_asm))
         loads = [i for i, (t, a) in enumerate(code) if a and t.startswith("global_load_dwordx4")]
-        if "direct" in inst and not loads:
-            checked += 1                  # a gathering loop fetches no rows
+        if not loads:
+            gathering += 1                # a gathering loop fetches no rows
             continue
         assert len(loads) == 8, (h, len(loads))
         dest = set().union(*(_regs(code[i][0].split(",")[0]) for i in loads))
@@ -194,7 +196,7 @@ def test_skew_kernel_leaves_the_rows_in_flight_alone(isa, inst, ncopies):
             for i in r:
                 assert not (_regs(code[i][0]) & dest), (h, code[i][0])
         checked += 1
-    assert checked == ncopies
+    assert gathering == GATHERS.get(inst, 0) and checked == ncopies - gathering, (gathering, checked)
     # requests before the loops (the first half's walks): nothing touches their registers until the wait
     in_asm, pending = False, None
     for h, ins in blocks:
@@ -245,12 +247,13 @@ def test_decay_attention_kernels_keep_their_loads_in_flight(isa):
     assert found == 1
 
 
-@pytest.mark.parametrize("decay", [0, 1])
-def test_emitting_walk_store_count_matches_its_wait_arithmetic(isa, decay):
-    """attn_fwd_emit_mfma_kernel adds 32 to its count of memory instructions for each state a wave writes: at the walk's
+@pytest.mark.parametrize("inst", ["attn_fwd_emit_mfma_kernelILb0E", "attn_fwd_emit_mfma_kernelILb1E", "attn_fwd_direct_mfma_kernel",
+                                  "attn_decay_fwd_direct_kernel"])
+def test_emitting_walk_store_count_matches_its_wait_arithmetic(isa, inst):
+    """The walks that write states in passing add 32 to their count of memory instructions for each state a wave writes: at the walk's
     start and after each of a chunk's four blocks, in both halves' copies.  Fewer store instructions than that
     (merged stores) would make the waits too lenient."""
-    body, _ = _skew_blocks(isa, f"attn_fwd_emit_mfma_kernelILb{decay}E")
+    body, _ = _skew_blocks(isa, inst)
     assert sum("global_store_dword " in l for l in body) == 2 * 5 * 32
 
 
@@ -350,7 +353,8 @@ PLANES_SCRATCH = {
 }
 
 
-@pytest.mark.parametrize("source,kernels", [("kernels_planes.hip", 32), ("kernels_planes_softmax.hip", 42)])
+@pytest.mark.parametrize("source,kernels", [("kernels_planes.hip", 32), ("kernels_planes_softmax.hip", 42),
+                                            ("kernels_softmax_small.hip", 4)])   # (the last counts its loads by hand: none at all)
 def test_scratch_of_the_split_plane_kernels(tmp_path, source, kernels):
     from paper_2502_07563_amd import build as b
     out = tmp_path / "planes.s"
