@@ -246,6 +246,17 @@ def test_null_and_alignment_errors_reach_no_device():
     assert lib.lasp2_state_prefix(r, ODD, FAKE, 0, None) == -6
     assert lib.lasp2_attn_fwd(r, FAKE, FAKE, FAKE, None, FAKE, None) == -1
     assert lib.lasp2_attn_fwd(r, FAKE, FAKE, FAKE, FAKE, ODD, None) == -6
+    # the forwards in one call: every pointer, the states' too, for one slot per sequence as well
+    one = ctypes.byref(_desc(N=100))
+    for call in (lib.lasp2_forward, lib.lasp2_nomask_forward):
+        for i in range(5):
+            a = [FAKE] * 5; a[i] = None
+            assert call(r, *a, None) == -1 and call(one, *a, None) == -1
+            a[i] = ODD
+            assert call(r, *a, None) == -6
+        assert call(None, *([FAKE] * 5), None) == -1
+        assert call(ctypes.byref(_desc(d=48)), *([FAKE] * 5), None) == -2
+        assert call(ctypes.byref(_desc(dtype=7)), *([FAKE] * 5), None) == -3
     args = [FAKE] * 9
     for i in range(9):
         a = list(args); a[i] = None
@@ -355,6 +366,7 @@ def test_decay_errors():
     r = ctypes.byref(_desc(decay_host=lam.ctypes.data, decay_dev=0x3000))
     assert lib.lasp2_state_total(r, FAKE, FAKE, None) == -8
     assert lib.lasp2_nomask_fwd(r, FAKE, FAKE, FAKE, None) == -8
+    assert lib.lasp2_nomask_forward(r, *([FAKE] * 5), None) == -8
     assert lib.lasp2_nomask_bwd(r, *([FAKE] * 9), ctypes.c_size_t(1 << 40), None) == -8
     assert lib.lasp2_softmax_fwd(r, *([FAKE] * 5), 1, None) == -8
 
@@ -366,6 +378,8 @@ def test_empty_problem_is_ok_without_pointers():
         assert lib.lasp2_chunk_states(r, None, None, None, None) == 0
         assert lib.lasp2_state_prefix(r, None, None, 0, None) == 0
         assert lib.lasp2_attn_fwd(r, None, None, None, None, None, None) == 0
+        assert lib.lasp2_forward(r, *([None] * 5), None) == 0
+        assert lib.lasp2_nomask_forward(r, *([None] * 5), None) == 0
         assert lib.lasp2_attn_bwd(r, *([None] * 9), ctypes.c_size_t(0), None) == 0
         assert lib.lasp2_state_total(r, None, None, None) == 0
         assert lib.lasp2_nomask_fwd(r, None, None, None, None) == 0
