@@ -165,6 +165,12 @@ struct PlanesProblems { PlanesProblem p[3]; };
 // the second axis.
 __device__ __forceinline__ bool which_segment(const Geom& g, int nprob, int nseg, int flat, int& prob, int& x, int& grp)
 {
+    if (nprob == 1) {   // (the forward: without the divisions 64 x 4001 x 64 in bf16 takes 46.6 us instead of 47.9)
+        prob = 0;
+        x = blockIdx.x;
+        grp = blockIdx.y;
+        return true;
+    }
     if (!flat) {
         prob = blockIdx.x % nprob;
         x = blockIdx.x / nprob;
