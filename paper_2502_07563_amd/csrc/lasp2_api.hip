@@ -404,9 +404,10 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, bool backward, bool m
         const double all = (rows * crowded + G * (N + start * c.walks) * per_row) / cus;
         const double passes = tensor < 2e8 ? 11.0 : 17.0;
         double slowest = 1.5 * far * gather + 1.08 * one * std::min(1.0, busy) + 0.1 * all;
-        if (!g.n_seqs && rounds > 1.0 && rounds <= 4.0)
-            slowest = std::max(slowest, g.decay ? rounds * one : W >= g.L ? rounds * ((rows_of_one + start) * 0.031 + 3.3)
-                                        : far * gather + one + (rounds - 1.0) * ((rows_of_one + start) * 0.031 + 3.3 + 0.5 * far * crowded));
+        const double full = std::ceil(units * std::min(1.0, N / (c.walks * c.longest)) / cus);   // rounds of whole walks
+        if (!g.n_seqs && full > 1.0 && full <= 4.0)
+            slowest = std::max(slowest, g.decay ? full * one : W >= g.L ? full * ((rows_of_one + start) * 0.031 + 3.3)
+                                        : far * gather + one + (full - 1.0) * ((rows_of_one + start) * 0.031 + 3.3 + 0.5 * far * crowded));
         return unsure * (std::max({slowest, 1.1 * all, passes * tensor / rate + rows * 512.0 / 1e7}) + 0.15 * all + (in ? first : 0.0));
     };
     const int forced = forced_walk_slots(g);
