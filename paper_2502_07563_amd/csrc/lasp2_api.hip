@@ -258,7 +258,7 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
 //   - A gathering backward of a few rounds lasts as long as they do, however short the walks (8 x 20 sequences of 59 rows, two rounds, 24; states first 22; parts of
 //     slots gather in each, 1 x 100 003 in slots of 4 096, parts of 448, two rounds, 196, of 832, one, 156).  With decay
 //     and one walk per document there is nothing to gather: a kernel of its own for that is slower (32 x 4 of 13 rows 27; 13).
-//   - Margins: gathering where the estimate errs more (backward 1.05, packed with decay 1.12 (8 heads, 20 000 in 50, slots of 1 024, 176; 163), forward parts of slots
+//   - Margins: gathering where the estimate errs more (backward 1.05, packed with decay 1.07 (8 heads, 20 000 in 50, slots of 1 024, 176; 163), forward parts of slots
 //     1.12), and up to 6 us for parts of short slots that are given states (lasp2_attn_fwd, slots of 512, in halves | whole: 4 x 13 887, 217 workgroups, 23.6 | 21.2; 8 x 3 297, 104, 18.0 | 19.9).
 enum class Start {
     states,   // states and prefix kernels first, a walk is `ws` slots
@@ -376,7 +376,7 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, bool backward, bool m
                                      : rounds * one * busy * (rounds > 1.0 ? 1.0 : backward ? 1.08 : 1.03);
         const double tail = 0.05 * walk + (g.n_seqs && rounds > 1.0 ? 0.6 * one : 0.0);
         const double again = 256.0 * row * std::max(0.0, (g.n_seqs ? c.walks * G / par : rounds) - 1.0);   // gathering starts once more
-        const double cache = 2.0 * tensor < 2e8 ? 2e7 : 8e6, unsure = !backward ? (W >= g.L ? 1.0 : 1.12) : g.decay && g.n_seqs ? 1.12 : 1.05;
+        const double cache = 2.0 * tensor < 2e8 ? 2e7 : 8e6, unsure = !backward ? (W >= g.L ? 1.0 : 1.12) : g.decay && g.n_seqs ? 1.07 : 1.05;
         const double moved = g.n_seqs ? 4.0 * G * 65536.0 / 5.2e6 : 0.0;   // a walk's state: written, combined, read
         const double uneven = g.n_seqs ? 1.33 : 1.0;
         const double chain = g.n_seqs ? 0.0 : 0.1 * std::max(0.0, (double)longest / (double)(how == Start::states ? W : g.L) - 16.0);   // states combined one after another
@@ -442,10 +442,12 @@ WalkPlan pick_walks(const Geom& g, const int32_t* cu_host, bool backward, bool m
         offer(forced);
     } else if (g.n_seqs) {
         WalkCount c[kMostDoubled];
-        int n = 0;   // ws_min, 2 ws_min, .. below ws_max
-        while (ws_min << n < ws_max) ++n;
-        count_whole(g, cu_host, longest, ws_min * g.L, n, c);
-        for (int i = 0; i < n; ++i) offer_counted(ws_min << i, c[i]);
+        const int64_t base = std::min((256 + g.L - 1) / g.L, ws_max);
+        int n = 0;   // base, 2 base, .. below ws_max, and the shortest
+        while (base << n < ws_max) ++n;
+        count_whole(g, cu_host, longest, base * g.L, n, c);
+        for (int i = 0; i < n; ++i) offer_counted(base << i, c[i]);
+        if (ws_min < base) offer(ws_min);
         offer(ws_max);
     }
     if (g.n_seqs) {
