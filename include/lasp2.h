@@ -310,6 +310,9 @@ int lasp2_state_total(const lasp2_desc_t* desc, const float* M, float* S, void* 
 /*
  * Line "O_t = Q_t M_{1:T}".  In: Q [B,H,N,d]; S [B,H,T_s,d,d] fp32 from
  * lasp2_state_total.  Out: O [B,H,N,d] in `dtype`, written once.
+ * Every entry of S must hold its document's total, but not every entry is
+ * necessarily read (a workgroup that takes several slots of a document reads
+ * the first one's); the same goes for S of lasp2_nomask_bwd.
  */
 int lasp2_nomask_fwd(const lasp2_desc_t* desc, const void* Q, const float* S, void* O,
                      void* stream);

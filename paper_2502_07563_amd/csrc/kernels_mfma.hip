@@ -1347,7 +1347,7 @@ __global__ __launch_bounds__(512) void attn_skew_mfma_kernel(Geom g, AttnProblem
 // Bound by memory: with one state per 256 tokens the walk writes as many bytes of state as it reads of one tensor, but
 // the states kernel then writes, and the prefix kernel reads and writes, one state per walk instead of one per slot, and
 // neither runs where a walk is a whole document.  Forward and backward of a layer, us, before -> now: 16 heads x 32 768, one
-// state per 256 tokens 513 -> 463; 8 x 32 heads x 8 192 1872 -> 1479; 32 heads, 40 documents in 131 072 4259 -> 3886.
+// state per 256 tokens 513 -> 463; 8 x 32 heads x 8 192 1872 -> 1479.  (Packed batches of long documents gather: attn_fwd_direct_mfma_kernel.)
 template <bool DECAY>
 __global__ __launch_bounds__(512) void attn_fwd_emit_mfma_kernel(Geom g, AttnProblem pr)
 {

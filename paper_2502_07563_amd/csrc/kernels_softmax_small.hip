@@ -3,11 +3,13 @@
 // shares of the partner rows, or in the forward 128 rows, four tiles by two shares: a wave each, whose results are merged through LDS
 // at the end.  A wave's row is a lane, as there: scores are formed transposed, the row statistics are per lane and the
 // probabilities are the next product's operand as they stand.  Partner rows pass through LDS in steps of one 32-row tile per share,
-// by direct loads, with the ring's other steps on their way.  Under a causal mask half of the row tiles are mirrored (the i-th from
-// the start with the i-th from the end) and a SIMD has one wave of each kind, so that its work is the same in every workgroup.
-// Bounds: latency and the L2: 64 rows take 64 KB of partner rows per step of 1.7 us (0.8 without waiting), all that the LDS holds
-// in flight; 128 rows half as much per row, which pays in the forward (16 x 1 300 causal: 64 rows 34 us, 128 30) and not in
-// the backward (92, 95).
+// by direct loads, the ring's other steps requested ahead.  (Forward and dQ: the own rows are ordinary loads whose first use lies inside
+// the loop, and the wait that the compiler puts there takes in the step just requested, so a step's loads are not on their
+// way while the one before it is computed, whatever settle() would leave outstanding.  In dK, dV they are.)  Under a causal mask half
+// of the row tiles are mirrored (the i-th from the start with the i-th from the end) and a SIMD has one wave of each kind, so that its
+// work is the same in every workgroup.
+// Bounds: latency and the L2: 64 rows take 64 KB of partner rows per step of 1.7 us; 128 rows half as much per row, which pays in the
+// forward (16 x 1 300 causal: 64 rows 34 us, 128 30) and not in the backward (92, 95).
 #include "mfma_tile.h"
 
 namespace lasp2 {
@@ -15,7 +17,7 @@ namespace {
 
 constexpr int SS_THR = 512;
 
-// QW row tiles by KW shares of the partner rows; RING steps of STEP partner rows in LDS, all but one of them on their way
+// QW row tiles by KW shares of the partner rows; RING steps of STEP partner rows in LDS, all but one of them requested ahead
 template <int QW_, int RING_>
 struct Cfg {
     static constexpr int QW = QW_, KW = 8 / QW, RING = RING_, STEP = 32 * KW, BLOCKS = STEP / KB;
