@@ -232,7 +232,8 @@ int pick_walk_slots(const Geom& g, const int32_t* cu_host, int par, int64_t targ
 // before it); also which long slots lasp2_attn_fwd takes in parts.  From an estimate in us of what each choice costs; the candidates are the
 // shortest walks that fit into one to sixteen rounds of workgroups, the shortest at all, and powers of two for documents of different lengths.
 // The rates are measured, the rest is fitted to 284 shapes (1 to 300 sequences of 3 to 200 000 tokens, packed batches among them) with every choice
-// timed: the chosen one takes 2.2 % more than the best in the forward and 2.5 % in the backward (geometric means).
+// timed: the chosen one takes 2.2 % more than the best in the forward and 2.5 % in the backward (geometric means; 71 packed batches alone, half of
+// them long documents in long slots, 6 % and 5 %: which workgroups start last, and beside which, is not followed).
 //   - A row of a walk takes 0.03 us forward (dQ 0.031, the pair of the backward 0.0376; with decay 0.033 each, and 0.009 gathered), starting a walk what 256 (180)
 //     rows do, a row that is gathered 0.0068 (16 heads, walks of 256, gathered | states first, us: 300 rows 15 | 22; 1 024
 //     20 | 24; 2 048 28 | 30; 3 000 37 | 31; 4 096 45 | 36; backward 20 | 27, 25 | 32, 34 | 37, 44 | 46, 58 | 50).  Rows come 128 at
