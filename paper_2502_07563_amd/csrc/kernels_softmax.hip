@@ -523,9 +523,13 @@ __global__ __launch_bounds__(SM_NW * 64) void softmax_bwd_dq_mfma_kernel(
 //   S = Q_tile K_w^T, dP = dO_tile V_w^T, P = exp(S/sqrt(d) - lse), dS = P (dP - delta)/sqrt(d),
 //   dV^T += dO_tile^T P,  dK^T += Q_tile^T dS.
 // Four waves, one per SIMD, so that a wave may hold both accumulators and both operand sets
-// (about 330 registers, the upper part in the accumulation file).
+// (460 registers, 208 of them in the accumulation file).  Bounds: with one wave per SIMD every instruction but the 32
+// matrix ones of a tile has to be issued while one of those runs (eight issue slots each), and the chip lowers its clock as the matrix
+// unit fills: so exponentials, conversions and LDS reads are spread evenly over the matrix instructions, with results
+// pinned where they are formed (left to itself the compiler moves a tile's vector work behind its last product).  16 x 32768
+// causal: 8490 -> 7900 us, matrix unit 45 -> 52 % busy at 2.22 -> 1.98 GHz; 16 x 4000 unmasked, backward 498 -> 455.
 // =====================================================================================
-constexpr int SK_NW = 4, SK_KB = SK_NW * 32;
+constexpr int SK_NW = 4, SK_KB = SK_NW * 32, SK_RING = 4;
 
 // four bytes per lane, otherwise as dma16 (M0 is written and named as clobbered)
 #pragma clang diagnostic push
@@ -544,8 +548,8 @@ __global__ __launch_bounds__(SK_NW * 64) void softmax_bwd_dkv_mfma_kernel(
     constexpr int NW = SK_NW, DPS = 2 * (16 / NW) + 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* sQ = smem;
-    char* sG = smem + NSTAGE * STAGE_BYTES;
-    char* sL = smem + 2 * NSTAGE * STAGE_BYTES;   // per stage: 64 lse, then 64 delta (512 bytes)
+    char* sG = smem + SK_RING * STAGE_BYTES;
+    char* sL = smem + 2 * SK_RING * STAGE_BYTES;  // per stage: 64 lse, then 64 delta (512 bytes)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -592,7 +596,7 @@ __global__ __launch_bounds__(SK_NW * 64) void softmax_bwd_dkv_mfma_kernel(
     const char* lse_g = reinterpret_cast<const char*>(LSE2 + (size_t)grp * g.qn);
     const char* dlt_g = reinterpret_cast<const char*>(delta + (size_t)grp * g.qn);
     auto issue = [&](int i) {
-        const int st = i % NSTAGE, q0 = (qb0 + i) * KB;     // first row of the block
+        const int st = i % SK_RING, q0 = (qb0 + i) * KB;     // first row of the block
         dma_block<NW>(Q, dO, qbase, q0, g.qn, sQ + st * STAGE_BYTES, sG + st * STAGE_BYTES, w, lane, dvo);
         // every wave fetches the stage's 64 log2-domain lse and 64 delta values (the same bytes to the same
         // place), which keeps the number of loads in flight equal across waves
@@ -602,6 +606,7 @@ __global__ __launch_bounds__(SK_NW * 64) void softmax_bwd_dkv_mfma_kernel(
     };
     if (NBK > 0) issue(0);
     if (NBK > 1) issue(1);
+    if (NBK > 2) issue(2);
 
     // per-lane LDS addresses inside ring slot 0, first half: natural reads of Q and dO tiles
     // (row = query), transposed reads of both (row = d), and the lane's quarter of the staged
@@ -651,146 +656,133 @@ __global__ __launch_bounds__(SK_NW * 64) void softmax_bwd_dkv_mfma_kernel(
         for (int v = 0; v < 16; ++v) { Kacc[tv][v] = 0.f; Vacc[tv][v] = 0.f; }
 
     typedef const __attribute__((address_space(3))) f32x4* lds_f32x4_ptr;
+    const uint32_t span = (uint32_t)max(hi_j - lo_j, 0);   // query x counts if (uint32_t)(x - lo_j) < span
 
-    // One stage of 64 queries.  The ring slot is a compile-time constant (the loop below is
-    // unrolled by the ring length), so every LDS read is a pinned register plus an immediate.
-    auto block = [&](auto stage_c, int bi) {
-        constexpr int ST = decltype(stage_c)::value;
-        constexpr uint32_t SO = ST * STAGE_BYTES;
-        const int row0 = (qb0 + bi) * KB;      // first row of the block in Q, dO
-        const int q0b = g.q0 + row0;           // ... as a token of the sequence
-        if (bi + 1 < NBK) wait_vmcnt<DPS>(); else wait_vmcnt<0>();
-        if (row0 + KB > g.qn) zero_tail_rows<NW>(row0, g.qn, sQ + SO, sG + SO, w, lane);
-        __syncthreads();
-        if (bi + 2 < NBK) issue(bi + 2);
-
-        // The mask enters through the accumulators the score products start from: 0 where the
-        // (query, key) pair is kept, -inf where it is not, so that P = exp2(-inf) = 0 and
-        // dS = 0 * (dP - delta) = 0 there with no compare in the per-element code.  Halves inside
-        // every lane's range (all but the few at mask edges) start from zeros.  One code path for
-        // every block also keeps the two accumulators in place from block to block.
-        // The two halves are software-pipelined so that one half's exponentials run under the
-        // other's MFMAs (a workgroup has one wave per SIMD; nothing else would fill those slots).
-        const bool whole0 = (q0b >= lo_max) && (q0b + 32 <= hi_min);
-        const bool whole1 = (q0b + 32 >= lo_max) && (q0b + 64 <= hi_min);
-        bf16x8 A0[8], B0[8], A1[8], B1[8];
+    // The walk goes by tiles of 32 queries.  Three tiles are at work in a step: the products of the next one's scores
+    // and dP (16) and those of the last one's dV and dK (16) are issued between the exponentials of the one at hand.  Ring slot and
+    // half are compile-time constants (the loop is unrolled by the ring length): every LDS read is a pinned register
+    // plus an immediate.  The mask makes scores -inf, so that P = 0 and dS = 0 * (dP - delta) = 0 there.
+    f32x16 sc[2], dp[2];         // scores and dP of tiles, by the half of the stage
+    uint32_t pp[2][8], pd[2][8]; // P and dS, two queries each
+    f32x4 ls[2][4], dl[2][4];    // log-sum-exp and delta of the tile's queries
+    bf16x8 tQ[2], tG[2];         // transposed operands that are read ahead
+    auto stats = [&](int q, auto half_c, auto off) {
+        constexpr int H = decltype(half_c)::value, O = decltype(off)::value / STAGE_BYTES * 512 + H * 128;
+        ls[H][q] = *reinterpret_cast<lds_f32x4_ptr>(aL + (O + 32 * q));
+        dl[H][q] = *reinterpret_cast<lds_f32x4_ptr>(aL + (O + 256 + 32 * q));
+    };
+    auto transposed = [&](int j, int off) {   // k-step j / 4, columns 32 (j % 4) .., of the tile at off
+        tQ[j & 1] = lds_read_tr8_u(trQ[j & 3][0] + (off + (j >> 2) * (16 * ROWB)), trQ[j & 3][1] + (off + (j >> 2) * (16 * ROWB)));
+        tG[j & 1] = lds_read_tr8_u(trG[j & 3][0] + (off + (j >> 2) * (16 * ROWB)), trG[j & 3][1] + (off + (j >> 2) * (16 * ROWB)));
+    };
+    auto accumulate = [&](int j, auto half_c) {
+        constexpr int H = decltype(half_c)::value;
+        const int k = 4 * (j >> 2);
+        const u32x4 pk = {pp[H][k], pp[H][k + 1], pp[H][k + 2], pp[H][k + 3]};
+        const u32x4 dk = {pd[H][k], pd[H][k + 1], pd[H][k + 2], pd[H][k + 3]};
+        Vacc[j & 3] = mfma(tG[j & 1], __builtin_bit_cast(bf16x8, pk), Vacc[j & 3]);
+        Kacc[j & 3] = mfma(tQ[j & 1], __builtin_bit_cast(bf16x8, dk), Kacc[j & 3]);
+    };
+    // Tile with first query q0 (a token), its half `half` of a stage at `off`; the next one at `noff`, the last one at `loff`.
+    auto step = [&](auto half_c, auto off_c, auto noff_c, auto loff_c, auto last_c, int q0) {
+        constexpr int H = decltype(half_c)::value, OFF = decltype(off_c)::value, NOFF = decltype(noff_c)::value, LOFF = decltype(loff_c)::value;
+        constexpr bool LAST = decltype(last_c)::value;
+        constexpr std::integral_constant<int, H ^ 1> other{};
+        if (!((q0 >= lo_max) && (q0 + 32 <= hi_min))) {
+            uint32_t at = (uint32_t)(q0 - lo_j + 4 * h);
+            pin_vgpr(at);
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) A0[ks] = lds_read16_u(natQ[ks] + SO);
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) B0[ks] = lds_read16_u(natG[ks] + SO);
-        f32x4 ls[4], dl[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            ls[q] = *reinterpret_cast<lds_f32x4_ptr>(aL + (ST * 512 + 32 * q));
-            dl[q] = *reinterpret_cast<lds_f32x4_ptr>(aL + (ST * 512 + 256 + 32 * q));
+            for (int v = 0; v < 16; ++v) sc[H][v] = at + (8 * (v >> 2) + (v & 3)) < span ? sc[H][v] : -INFINITY;
         }
+        bf16x8 nQ[8], nG[8];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            nQ[ks] = lds_read16_u(natQ[ks] + NOFF);
+            nG[ks] = lds_read16_u(natG[ks] + NOFF);
+        }
+        f32x16 s, d;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { s[v] = 0.f; d[v] = 0.f; }
         SCHED_FENCE();
-        // phase A: S0 = Q0 K^T, dP0 = dO0 V^T
-        f32x16 sc0, dp0;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { sc0[v] = 0.f; dp0[v] = 0.f; }
-        if (!whole0) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int qi = q0b + 8 * (v >> 2) + 4 * h + (v & 3);
-                sc0[v] = (qi >= lo_j && qi < hi_j) ? 0.f : -INFINITY;
+        for (int j = 0; j < 8; ++j) {
+            if constexpr (LAST) accumulate(j, other);
+            const int v = 2 * j;
+            const float pa = fast_exp2(fmaf(sc[H][v], scale_log2e, -ls[H][v >> 2][v & 3]));
+            const float pb = fast_exp2(fmaf(sc[H][v + 1], scale_log2e, -ls[H][v >> 2][(v & 3) + 1]));
+            pp[H][j] = pack2(pa, pb);
+            pd[H][j] = pack2(pa * (dp[H][v] - dl[H][v >> 2][v & 3]), pb * (dp[H][v + 1] - dl[H][v >> 2][(v & 3) + 1]));
+            pin_vgpr(pp[H][j]);
+            pin_vgpr(pd[H][j]);
+            if constexpr (LAST) {
+                if (j < 6) transposed(j + 2, LOFF); else transposed(j - 6, OFF);
+            } else {
+                if (j >= 6) transposed(j - 6, OFF);
             }
+            SCHED_FENCE();
+            s = mfma(nQ[j], kf[j], s);
+            d = mfma(nG[j], vf[j], d);
+            if (j < 6) {
+                nQ[j + 2] = lds_read16_u(natQ[j + 2] + NOFF);
+                nG[j + 2] = lds_read16_u(natG[j + 2] + NOFF);
+            }
+            if (j & 1) stats(j >> 1, other, std::integral_constant<int, NOFF>{});
+            SCHED_FENCE();
         }
+        sc[H ^ 1] = s;
+        dp[H ^ 1] = d;
+    };
+    // block bi has arrived for all waves, and all are past the first half of block bi - 1
+    auto arrive = [&](int bi) {
+        if (bi + 1 < NBK) wait_vmcnt<DPS>(); else wait_vmcnt<0>();
+        const int row0 = (qb0 + bi) * KB, st = bi % SK_RING;
+        if (row0 + KB > g.qn) zero_tail_rows<NW>(row0, g.qn, sQ + st * STAGE_BYTES, sG + st * STAGE_BYTES, w, lane);
+        __syncthreads();
+        if (bi >= 1 && bi + 2 < NBK) issue(bi + 2);
+    };
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 1> I1;
+    constexpr int HALF = 32 * ROWB;
+    if (NBK > 0) {
+        if (NBK > 2) wait_vmcnt<2 * DPS>(); else if (NBK > 1) wait_vmcnt<DPS>(); else wait_vmcnt<0>();
+        if ((qb0 + 1) * KB > g.qn) zero_tail_rows<NW>(qb0 * KB, g.qn, sQ, sG, w, lane);
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { sc[0][v] = 0.f; dp[0][v] = 0.f; }
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-            // the first of half 1's natural operands arrive under these products, into the
-            // registers that half 0's first ones have left
-            if (ks >= 4) {
-                A1[ks - 4] = lds_read16_u(natQ[ks - 4] + (SO + 32 * ROWB));
-                B1[ks - 4] = lds_read16_u(natG[ks - 4] + (SO + 32 * ROWB));
-            }
-            sc0 = mfma(A0[ks], kf[ks], sc0);
-            dp0 = mfma(B0[ks], vf[ks], dp0);
-            SCHED_FENCE();
+            sc[0] = mfma(lds_read16_u(natQ[ks]), kf[ks], sc[0]);
+            dp[0] = mfma(lds_read16_u(natG[ks]), vf[ks], dp[0]);
         }
-        // transposed operands of half 0 (into the registers its natural operands used)
 #pragma unroll
-        for (int tv = 0; tv < 4; ++tv) {
-            A0[tv] = lds_read_tr8_u(trQ[tv][0] + SO, trQ[tv][1] + SO);
-            A0[4 + tv] = lds_read_tr8_u(trQ[tv][0] + (SO + 16 * ROWB), trQ[tv][1] + (SO + 16 * ROWB));
-            B0[tv] = lds_read_tr8_u(trG[tv][0] + SO, trG[tv][1] + SO);
-            B0[4 + tv] = lds_read_tr8_u(trG[tv][0] + (SO + 16 * ROWB), trG[tv][1] + (SO + 16 * ROWB));
-        }
-        f32x16 sc1, dp1;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { sc1[v] = 0.f; dp1[v] = 0.f; }
-        if (!whole1) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int qi = q0b + 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-                sc1[v] = (qi >= lo_j && qi < hi_j) ? 0.f : -INFINITY;
-            }
-        }
-        SCHED_FENCE();
-        // phase B: S1, dP1 on the matrix unit; P0 and P0 (dP0 - delta) on the vector unit; half 1's
-        // log-sum-exp and delta replace half 0's as those are used up
-        uint32_t pp0[8], pd0[8];
-        f32x4 ls1[4], dl1[4];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (j < 4) {
-                A1[j + 4] = lds_read16_u(natQ[j + 4] + (SO + 32 * ROWB));
-                B1[j + 4] = lds_read16_u(natG[j + 4] + (SO + 32 * ROWB));
-            }
-            sc1 = mfma(A1[j], kf[j], sc1);
-            dp1 = mfma(B1[j], vf[j], dp1);
-            const int v = 2 * j;
-            const float pa = fast_exp2(fmaf(sc0[v], scale_log2e, -ls[v >> 2][v & 3]));
-            const float pb = fast_exp2(fmaf(sc0[v + 1], scale_log2e, -ls[v >> 2][(v & 3) + 1]));
-            pp0[j] = pack2(pa, pb);
-            pd0[j] = pack2(pa * (dp0[v] - dl[v >> 2][v & 3]), pb * (dp0[v + 1] - dl[v >> 2][(v & 3) + 1]));
-            if (j & 1) {
-                ls1[j >> 1] = *reinterpret_cast<lds_f32x4_ptr>(aL + (ST * 512 + 128 + 32 * (j >> 1)));
-                dl1[j >> 1] = *reinterpret_cast<lds_f32x4_ptr>(aL + (ST * 512 + 256 + 128 + 32 * (j >> 1)));
-            }
-            SCHED_FENCE();
-        }
-        // half 1's transposed operands
-#pragma unroll
-        for (int tv = 0; tv < 4; ++tv) {
-            A1[tv] = lds_read_tr8_u(trQ[tv][0] + (SO + 32 * ROWB), trQ[tv][1] + (SO + 32 * ROWB));
-            A1[4 + tv] = lds_read_tr8_u(trQ[tv][0] + (SO + 48 * ROWB), trQ[tv][1] + (SO + 48 * ROWB));
-            B1[tv] = lds_read_tr8_u(trG[tv][0] + (SO + 32 * ROWB), trG[tv][1] + (SO + 32 * ROWB));
-            B1[4 + tv] = lds_read_tr8_u(trG[tv][0] + (SO + 48 * ROWB), trG[tv][1] + (SO + 48 * ROWB));
-        }
-        SCHED_FENCE();
-        // phase C: half 0 into dV^T, dK^T on the matrix unit; P1 and dS1 on the vector unit
-        uint32_t pp1[8], pd1[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int kst = j >> 2, tv = j & 3;
-            const u32x4 pk = {pp0[4 * kst], pp0[4 * kst + 1], pp0[4 * kst + 2], pp0[4 * kst + 3]};
-            const u32x4 dk = {pd0[4 * kst], pd0[4 * kst + 1], pd0[4 * kst + 2], pd0[4 * kst + 3]};
-            Vacc[tv] = mfma(B0[4 * kst + tv], __builtin_bit_cast(bf16x8, pk), Vacc[tv]);
-            Kacc[tv] = mfma(A0[4 * kst + tv], __builtin_bit_cast(bf16x8, dk), Kacc[tv]);
-            const int v = 2 * j;
-            const float pa = fast_exp2(fmaf(sc1[v], scale_log2e, -ls1[v >> 2][v & 3]));
-            const float pb = fast_exp2(fmaf(sc1[v + 1], scale_log2e, -ls1[v >> 2][(v & 3) + 1]));
-            pp1[j] = pack2(pa, pb);
-            pd1[j] = pack2(pa * (dp1[v] - dl1[v >> 2][v & 3]), pb * (dp1[v + 1] - dl1[v >> 2][(v & 3) + 1]));
-            SCHED_FENCE();
-        }
-        // phase D: half 1 into dV^T, dK^T
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int kst = j >> 2, tv = j & 3;
-            const u32x4 pk = {pp1[4 * kst], pp1[4 * kst + 1], pp1[4 * kst + 2], pp1[4 * kst + 3]};
-            const u32x4 dk = {pd1[4 * kst], pd1[4 * kst + 1], pd1[4 * kst + 2], pd1[4 * kst + 3]};
-            Vacc[tv] = mfma(B1[4 * kst + tv], __builtin_bit_cast(bf16x8, pk), Vacc[tv]);
-            Kacc[tv] = mfma(A1[4 * kst + tv], __builtin_bit_cast(bf16x8, dk), Kacc[tv]);
-        }
-        SCHED_FENCE();
+        for (int q = 0; q < 4; ++q) stats(q, I0{}, I0{});
+        step(I0{}, I0{}, std::integral_constant<int, HALF>{}, I0{}, std::integral_constant<bool, false>{}, g.q0 + qb0 * KB);
+    }
+    // second half of block bi, first half of the next one
+    auto block = [&](auto stage_c, int bi) {
+        constexpr int S0 = decltype(stage_c)::value * STAGE_BYTES, S1 = ((decltype(stage_c)::value + 1) % SK_RING) * STAGE_BYTES;
+        constexpr std::integral_constant<bool, true> yes{};
+        const int q0b = g.q0 + (qb0 + bi) * KB;
+        if (bi + 1 < NBK) arrive(bi + 1);
+        step(I1{}, std::integral_constant<int, S0 + HALF>{}, std::integral_constant<int, S1>{}, std::integral_constant<int, S0>{}, yes, q0b + 32);
+        if (bi + 1 < NBK)
+            step(I0{}, std::integral_constant<int, S1>{}, std::integral_constant<int, S1 + HALF>{}, std::integral_constant<int, S0 + HALF>{}, yes,
+                 q0b + KB);
     };
-    static_assert(NSTAGE == 3, "the block loop is unrolled by the ring length");
-    for (int bi = 0; bi < NBK; bi += 3) {
+    static_assert(SK_RING == 4, "the block loop is unrolled by the ring length");
+    for (int bi = 0; bi < NBK; bi += 4) {
         block(std::integral_constant<int, 0>{}, bi);
         if (bi + 1 < NBK) block(std::integral_constant<int, 1>{}, bi + 1);
         if (bi + 2 < NBK) block(std::integral_constant<int, 2>{}, bi + 2);
+        if (bi + 3 < NBK) block(std::integral_constant<int, 3>{}, bi + 3);
+    }
+    if (NBK > 0) {   // the last tile's dV and dK (its first two operands are there)
+        const int off = ((NBK - 1) % SK_RING) * STAGE_BYTES + HALF;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            accumulate(j, I1{});
+            if (j < 6) transposed(j + 2, off);
+        }
     }
 
     // dK^T and dV^T (d x keys) -> rows of dK, dV through a 4 KiB per-wave staging area that
@@ -833,7 +825,7 @@ hipError_t launch_softmax_bwd_dkv_mfma(const Geom& g, const void* Q, const void*
                                        const void* dO, const float* LSE2, const float* delta, void* dK,
                                        void* dV, int causal, hipStream_t st)
 {
-    constexpr int smem = 2 * NSTAGE * STAGE_BYTES + NSTAGE * 512;   // 97.5 KiB
+    constexpr int smem = 2 * SK_RING * STAGE_BYTES + SK_RING * 512;   // 130 KiB
     hipError_t e = allow_dynamic_lds<softmax_bwd_dkv_mfma_kernel>(smem);
     if (e != hipSuccess) return e;
     const unsigned nkb = ((unsigned)g.N + SK_KB - 1) / SK_KB;
