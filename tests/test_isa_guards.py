@@ -367,3 +367,18 @@ def test_scratch_of_the_split_plane_kernels(tmp_path, source, kernels):
     for name, (_, size) in zip(names, found):
         key = re.search(r"\w+_kernel<[^>]*>", name).group(0)
         assert int(size) <= PLANES_SCRATCH.get(key, 0), (key, size)
+
+
+@pytest.mark.parametrize("source", ["kernels_planes.hip", "kernels_planes_softmax.hip"])
+def test_factors_of_the_split_are_registers(tmp_path, source):
+    """The pairs (-1, 0) and (0, -1) of the dot products that split fp32 values: as constants the compiler writes the
+    second as -1.0, which the instruction reads as another pair."""
+    from paper_2502_07563_amd import build as b
+    out = tmp_path / "planes.s"
+    flags = [f for f in b.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "-S", "--cuda-device-only", "-o", str(out),
+                    os.path.join(SRC, source)], check=True, capture_output=True)
+    dots = [l.split(";")[0] for l in out.read_text().splitlines() if "v_dot2" in l]
+    assert len(dots) > 1000
+    for l in dots:
+        assert len(re.findall(r"\bs\d+\b", l)) == 1 and not re.search(r"-?\d+\.\d|0x", l), l
