@@ -155,7 +155,10 @@ int lasp2_num_slots(const lasp2_desc_t* desc, int64_t* T_s);
  *     two apart.
  *   Everything else: only where L is not a multiple of the kernels' 128-row
  *     chunk, so that single slots would leave chunks partly empty; 1 otherwise.
- *     dM states are built per slot.
+ *     lasp2_attn_bwd builds its dM states per walk.  With d = 64 this (and
+ *     lasp2_walk_plan) is what lasp2_attn_fwd does, and the least that
+ *     lasp2_forward and lasp2_attn_bwd take: theirs are up to 1024 tokens
+ *     long, or whole sequences.
  * The environment variable LASP2_WALK_SLOTS (a positive integer, read at every
  * call) overrides the choice where there is one; 1 gives one walk per slot.
  */
@@ -234,7 +237,7 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K,
  * only where its workgroups' walks start (lasp2_walk_plan; nowhere if each
  * document is one walk or walks gather their own) and has the walks write the
  * other slots' states as they pass them, where slots are multiples of 64 tokens
- * (bf16, d = 128).
+ * (bf16, d = 128; d = 64).
  * In: Q,K,V [B,H,N,d].  Out: P [B,H,T_s,d,d] fp32, never NULL; O [B,H,N,d].
  */
 int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K,

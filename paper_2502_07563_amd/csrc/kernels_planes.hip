@@ -86,7 +86,7 @@ __device__ __forceinline__ float state_element(const T* x, const T* y, int D, in
 // M[slot] = sum over the slot's tokens of (weighted) k^T v; one workgroup per slot.
 template <typename T, int D, bool DECAY>
 __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __restrict__ K, const T* __restrict__ V,
-                                                             float* __restrict__ M, int anchor_start)
+                                                             float* __restrict__ M, int anchor_start, int of_slots)
 {
     constexpr int DP = D < 32 ? 32 : D, NT = DP / 32;
     constexpr int ROWS = (planes_of<T>::n == 3 && D == 128) ? 32 : 64;   // two stages fit the LDS
@@ -94,8 +94,9 @@ __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int s = blockIdx.x, grp = blockIdx.y;
-    int tok0, len;
-    slot_range(g, s, tok0, len);
+    int tok0, len, ps, doc0, doc1, slot0, slot1;
+    slot_range<false>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
+    if (of_slots && tok0 + len == doc1) return;   // (no exclusive prefix contains a document's last walk)
     const size_t base = ((size_t)grp * (size_t)g.N + tok0) * D;
     const float l2 = decay_log2(g, grp);
     const int e0 = anchor_start ? 0 : len - 1, de = anchor_start ? 1 : -1;
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __
             state_step<T, D, DP, Stage::PLANE, DECAY, 1>(S, buf, Stage::TENSOR, 16 * w, w, lane, e0 + de * i * ROWS, de, l2);
         }
     }
-    float* m = M + ((size_t)grp * g.T_s + s) * (size_t)(D * D);
+    float* m = M + (of_slots ? (size_t)grp * g.P_Ts + ps : (size_t)grp * g.T_s + s) * (size_t)(D * D);
     // Planes make NaN of an infinity and of what rounds to one (planes.h): such a slot is summed again in fp32.
     float odd = 0.f;
 #pragma unroll
@@ -156,81 +157,113 @@ struct PlanesProblem {
     const float* state;
     void* out;
     int transpose, reverse;
+    int of_walks;   // the states are one per walk, not one per slot of the caller's
 };
 struct PlanesProblems { PlanesProblem p[3]; };
 
-// Problem, segment x (= slot * nseg + segment) and group of a workgroup.  flat: a one-dimensional grid in which the nprob
-// problems of a segment are dealt to the same XCD, one after another, and find each other's rows in its L2 (backward launch, fp32,
-// 16 x 4000 x 64 64 -> 60 us; bf16, 16 x 1800 x 64 23.6 -> 21.9); otherwise (one problem, or grids past 2^32 threads) groups are
-// the second axis.
-__device__ __forceinline__ bool which_segment(const Geom& g, int nprob, int nseg, int flat, int& prob, int& x, int& grp)
+// How a launch is cut: `nseg` segments of `cps` chunks per walk and `nprob` problems (1 or 3).  flat: a one-dimensional grid in which
+// the problems of a segment are dealt to the same XCD, one after another, and find each other's rows in its L2 (backward launch,
+// fp32, 16 x 4000 x 64 64 -> 60 us; bf16, 16 x 1800 x 64 23.6 -> 21.9); otherwise (one problem, or grids past 2^32 threads)
+// groups are the second axis.
+struct PlanesGrid {
+    int nprob, nseg, cps, flat;
+    uint32_t per, per_inv, nseg_inv;   // segments of a group; 2^32 / per and 2^32 / nseg, rounded down
+};
+
+// u / d, inv = 2^32 / d rounded down (d > 1): the product is the quotient or one less.  (A division is forty instructions, and a
+// workgroup of one chunk starts with five of them: 1900 clocks of its 20000.)
+__device__ __forceinline__ uint32_t div_by(uint32_t u, uint32_t d, uint32_t inv)
 {
-    if (nprob == 1) {   // (the forward: without the divisions 64 x 4001 x 64 in bf16 takes 46.6 us instead of 47.9)
-        prob = 0;
-        x = blockIdx.x;
-        grp = blockIdx.y;
-        return true;
+    const uint32_t q = __umulhi(u, inv);
+    return q + (u - q * d >= d);
+}
+
+// Problem, walk, segment and group of a workgroup
+__device__ __forceinline__ bool which_segment(const Geom& g, const PlanesGrid& pg, int& prob, int& s, int& seg, int& grp)
+{
+    uint32_t x = blockIdx.x;
+    bool there = true;
+    prob = 0;
+    grp = blockIdx.y;
+    if (pg.flat) {
+        const uint32_t i = x >> 3, t = i / 3u, u = t * 8u + (x & 7u);
+        prob = (int)(i - 3u * t);
+        const uint32_t q = pg.per > 1 ? div_by(u, pg.per, pg.per_inv) : u;
+        grp = (int)q;
+        x = u - q * pg.per;
+        there = q < (uint32_t)g.G;
+    } else if (pg.nprob > 1) {
+        prob = (int)(x % 3u);
+        x /= 3u;
     }
-    if (!flat) {
-        prob = blockIdx.x % nprob;
-        x = blockIdx.x / nprob;
-        grp = blockIdx.y;
-        return true;
-    }
-    const unsigned per = (unsigned)g.T_s * (unsigned)nseg, u = (blockIdx.x / (8u * nprob)) * 8u + (blockIdx.x & 7u);
-    prob = (int)((blockIdx.x >> 3) % (unsigned)nprob);
-    grp = (int)(u / per);
-    x = (int)(u % per);
-    return u < per * (unsigned)g.G;
+    const uint32_t walk = pg.nseg > 1 ? div_by(x, (uint32_t)pg.nseg, pg.nseg_inv) : x;
+    s = (int)walk;
+    seg = (int)(x - walk * (uint32_t)pg.nseg);
+    return there;
 }
 
 // Tokens per LDS stage: as many of the chunk's 128 as leave room for a second workgroup on the CU
-// (one workgroup with d = 128), with at most 32 registers per thread for the next stage's loads; fp32 with
-// decay and d = 64 has no registers for more than 32, and spills 9 even so.  With d = 128 the operands' planes, the
+// (one workgroup with d = 128), with at most 32 registers per thread for the next stage's loads.  With d = 128 the operands' planes, the
 // state's and the result's accumulators exceed the 512 registers of a thread at one wave per SIMD: 88 spilled
 // in fp32, 140 with decay, 76 in bf16 with decay.  Layer, 2 x 16 x 4096 x 128, against one scalar product per element, us:
 // fp32 forward 3470 -> 356, backward 10120 -> 908; bf16 with strong decay 2850 -> 241, 8240 -> 576.
 template <typename T, int D, bool DECAY>
 struct AttnLds {
     static constexpr int DP = D < 32 ? 32 : D, NP = planes_of<T>::n;
-    static constexpr int ROWS = D == 128 ? (NP == 3 ? 32 : 64) : (NP == 3 && D == 64) ? (DECAY ? 32 : 64) : 128;
+    static constexpr int ROWS = D == 128 ? (NP == 3 ? 32 : 64) : 128;
     typedef PairStage<T, D, DP, ROWS, kThr> Stage;
     static constexpr int SPLANE = DP * DP * 2;
-    static constexpr int BYTES = Stage::BYTES + 3 * SPLANE;
+    static constexpr int FLAG = Stage::BYTES + 3 * SPLANE, BYTES = FLAG + 16;
 };
+
+// Where a problem's state lies, in states: ps is the caller's slot (the walk's first), s the walk.
+__device__ __forceinline__ size_t state_index(const Geom& g, const PlanesProblem& pb, int grp, int s, int ps)
+{
+    return pb.of_walks ? (size_t)grp * g.T_s + s : (size_t)grp * g.P_Ts + ps;
+}
+
+// Tokens of the caller's slots
+__device__ __forceinline__ int slot_tokens(const Geom& g)
+{
+    return g.wslots > 1 ? (int)((uint32_t)g.L / (uint32_t)g.wslots) : (int)min(g.L, (int64_t)INT32_MAX);
+}
 
 // What attn_planes_kernel computes, in fp32 from the elements as they are, for a workgroup's chunks from `first`
 // on: a row of out per wave, the running state M [D][D] in LDS.  For inputs whose planes are not finite: slow, as scalar
 // products are (fp32, 8 x 2003 x 64 with a NaN in every head's V, forward + backward: 1760 us).
-template <typename T, int D>
-__device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems& probs, int nprob, int nseg, int cps, int flat,
-                                            int first, float* M)
+template <typename T, int D, int CHUNK>
+__device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems& probs, PlanesGrid pg, int first, float* M,
+                                            float* emit)
 {
-    asm volatile("" : "+s"(nseg));   // (all of this worked out anew, so that none of it stays in registers through the walk)
-    int x, prob, grp;
-    which_segment(g, nprob, nseg, flat, prob, x, grp);
+    asm volatile("" : "+s"(pg.nseg));   // (all of this worked out anew, so that none of it stays in registers through the walk)
+    int s, seg, prob, grp;
+    which_segment(g, pg, prob, s, seg, grp);
     const PlanesProblem pb = probs.p[prob];
     const int tid = threadIdx.x;
     int tok0, len, ps;
-    slot_range(g, x / nseg, tok0, len, ps);
+    slot_range(g, s, tok0, len, ps);
     const bool rev = pb.reverse != 0;
-    if (rev && g.wslots > 1) ps += (len - 1) / ((int)g.L / g.wslots);
     const size_t base = ((size_t)grp * (size_t)g.N + tok0) * D;
     const T* A = static_cast<const T*>(pb.A) + base;
     const T* Bk = static_cast<const T*>(pb.Bk) + base;
     const T* Cv = static_cast<const T*>(pb.Cv) + base;
     T* out = static_cast<T*>(pb.out) + base;
-    const float* state = pb.state ? pb.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) : nullptr;
+    const float* state = pb.state ? pb.state + state_index(g, pb, grp, s, ps) * (size_t)(D * D) : nullptr;
     const float l2 = decay_log2(g, grp);
-    const int transpose = pb.transpose, last = min((len + kChunk - 1) / kChunk, (x % nseg + 1) * cps);
+    const int transpose = pb.transpose, last = min((len + CHUNK - 1) / CHUNK, (seg + 1) * pg.cps);
     constexpr int NB = D > 64 ? 2 : 1;
-    const int lane = tid & 63, nch = (len + kChunk - 1) / kChunk;
+    const int lane = tid & 63, nch = (len + CHUNK - 1) / CHUNK;
 #pragma unroll 1
     for (int e = tid; e < D * D; e += kThr) M[e] = state ? state[transpose ? (e % D) * D + e / D : e] : 0.f;
 #pragma unroll 1
     for (int ci = 0; ci < last; ++ci) {
-        const int c0 = (rev ? nch - 1 - ci : ci) * kChunk, clen = min(kChunk, len - c0);
+        const int c0 = (rev ? nch - 1 - ci : ci) * CHUNK, clen = min(CHUNK, len - c0);
         __syncthreads();   // M is written
+        if (emit && ci >= first && (c0 > 0 || !pb.state) && c0 % slot_tokens(g) == 0) {
+            float* at = emit + ((size_t)grp * g.P_Ts + ps + c0 / slot_tokens(g)) * (size_t)(D * D);
+#pragma unroll 1
+            for (int e = tid; e < D * D; e += kThr) at[e] = M[e];
+        }
 #pragma unroll 1
         for (int i = ci < first ? clen : tid >> 6; i < clen; i += kThr / 64) {
             float o[NB], t[NB];
@@ -278,6 +311,31 @@ __device__ __forceinline__ f32x16 mm_either(const bf16x8 (&x)[NX], const bf16x8 
     else return mm<LO, HI>(x, y, c);
 }
 
+// Scores of a tile: times lam^(distance), zero outside the mask where the tile lies on the diagonal.  dist: query minus key, for
+// the accumulator's first row.  (Bounds that hold for either direction, and one compare each: a choice of the
+// direction per element had become a branch each, 1800 clocks a tile.)
+template <bool DECAY>
+__device__ __forceinline__ void mask_tile(f32x16& sc, int dist, bool diagonal, bool rev, float l2)
+{
+    const int lo = diagonal && rev ? dist : -64;                            // accumulator rows lo .. lo + span are kept
+    const uint32_t span = (uint32_t)((diagonal && !rev ? dist : 64) - lo);
+    const float e2 = rev ? -l2 : l2;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        if (DECAY) sc[v] *= decay_pow((float)(dist - acc_row(v)), e2);
+        sc[v] = (uint32_t)(acc_row(v) - lo) <= span ? sc[v] : 0.f;
+    }
+}
+
+// Whether any thread of the workgroup says `odd`, by a flag in LDS that starts at zero (and is asked no more once it is set); a
+// barrier.  The wave's answer is a compare: the reduction inside __syncthreads_or takes 1000 clocks, a tenth of a chunk.
+__device__ __forceinline__ bool any_odd(bool odd, int* flag)
+{
+    if (__any(odd)) *flag = 1;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(*static_cast<volatile int*>(flag)) != 0;
+}
+
 // four columns of a row
 __device__ __forceinline__ void store4(float* p, float a, float b, float c, float d)
 {
@@ -308,8 +366,7 @@ __device__ __forceinline__ void store4(__hip_bfloat16* p, float a, float b, floa
 // Against one scalar fp32 product per element (and a load for each), layer forward + backward: bf16,
 // 64 groups x 4001 x 64: 4200 -> 230 us (the forward launch 50 us, 3.2 TB/s); fp32, 2 x 1024 x 64: 1190 -> 58 us.
 template <typename T, int D, bool DECAY>
-__global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geom g, PlanesProblems probs, int nprob, int nseg,
-                                                                             int cps, int flat)
+__global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geom g, PlanesProblems probs, PlanesGrid pg)
 {
     typedef AttnLds<T, D, DECAY> LD;
     typedef typename LD::Stage Stage;
@@ -318,16 +375,17 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
     constexpr bool TR = D == 128;
     extern __shared__ __align__(16) char smem[];
     char* snap = smem + Stage::BYTES;
+    int* flag = reinterpret_cast<int*>(smem + LD::FLAG);
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
-    int prob, x, grp;
-    if (!which_segment(g, nprob, nseg, flat, prob, x, grp)) return;
+    if (tid == 0) *flag = 0;
+    int prob, s, seg, grp;
+    if (!which_segment(g, pg, prob, s, seg, grp)) return;
     const PlanesProblem pb = probs.p[prob];
-    const int s = x / nseg, seg = x % nseg;
     int tok0, len, ps;
     slot_range(g, s, tok0, len, ps);
     const int nch = (len + kChunk - 1) / kChunk;
-    const int ci0 = seg * cps, ci1 = min(nch, ci0 + cps);
+    const int ci0 = seg * pg.cps, ci1 = min(nch, ci0 + pg.cps);
     if (ci0 >= nch) return;
     const bool rev = pb.reverse != 0;
     const size_t base = ((size_t)grp * (size_t)g.N + tok0) * D;
@@ -346,9 +404,7 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
 #pragma unroll
     for (int t = 0; t < NTL; ++t) S[t] = zero16();
     if (have_state && owner) {
-        // (several slots in one walk: the prefix of its first, the suffix of its last)
-        if (rev && g.wslots > 1) ps += (len - 1) / ((int)g.L / g.wslots);
-        const float* st0 = pb.state + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D);
+        const float* st0 = pb.state + state_index(g, pb, grp, s, ps) * (size_t)(D * D);
 #pragma unroll
         for (int t = 0; t < NTL; ++t)
 #pragma unroll
@@ -459,13 +515,7 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
                         sc = mm<0, 0>(k, q[ks], sc);
                     }
                     if (DECAY || sb == w) {
-                        const int dist = 32 * (w - sb) + l32 - 4 * h;   // query minus key, for the first row
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const int d = dist - acc_row(v);
-                            if (DECAY) sc[v] *= decay_pow((float)d, rev ? -l2 : l2);
-                            if (sb == w && (rev ? d > 0 : d < 0)) sc[v] = 0.f;
-                        }
+                        mask_tile<DECAY>(sc, 32 * (w - sb) + l32 - 4 * h, sb == w, rev, l2);
                     }
                     bf16x8 p[2][3];
                     acc_frag(sc, 0, p[0]);
@@ -495,7 +545,7 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) odd = fmaf(TR || 32 * nt + l32 < D ? acc[nt][v] : 0.f, 0.f, odd);
-        if (__syncthreads_or(odd != 0.f)) {
+        if (any_odd(odd != 0.f, flag)) {
             redo = ci;
             break;
         }
@@ -519,63 +569,317 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
         }
         have_state = true;
     }
-    if (redo < ci1) attn_scalar<T, D>(g, probs, nprob, nseg, cps, flat, redo, reinterpret_cast<float*>(snap));
+    if (redo < ci1) attn_scalar<T, D, kChunk>(g, probs, pg, redo, reinterpret_cast<float*>(snap), nullptr);
+}
+
+// 8 consecutive elements of a row in all its planes
+template <int NP>
+__device__ __forceinline__ void frag_at(const char* tile, int plane_bytes, uint32_t off, bf16x8 (&f)[NP])
+{
+#pragma unroll
+    for (int p = 0; p < NP; ++p) f[p] = *reinterpret_cast<const bf16x8*>(tile + p * plane_bytes + off);
+}
+
+// ---- The same for heads of 64 ----
+// Chunks of 64 rows; a wave has 32 of them and 32 of the 64 columns: the scores of its rows are formed by two waves, but a
+// chunk is three score tiles instead of ten per 128 rows, the longest of a wave two instead of four, and accumulators and
+// state take a third of the registers: three workgroups per CU in bf16 (48 KB of LDS and 168 registers each) where there were
+// two; fp32 and decay have two.  Walks of several slots write the states of the slots inside them (emit).  bf16 rows go out through
+// LDS, 128 bytes at a time.  Bounds: the chain of a chunk (snapshot, stage, barrier, state product, two tiles, barrier: about
+// 8000 clocks, 3000 of them the tiles), of which a CU runs two or three side by side.  With walks as pick_planes_slots has
+// them, us, against 128-row chunks in four waves of 32 rows and all columns: bf16, 64 x 4001, layer forward 81 -> 57, backward
+// 149 -> 97 (the launches 47 -> 35 and 119 -> 80, 4.7 and 3.8 TB/s); 16 x 4000 29 -> 27, 48 -> 36; fp32, 64 x 4001 146 -> 122, 276
+// -> 257; 2 x 1024 25 -> 21, 29 -> 27.
+template <typename T>
+struct Attn64Lds {
+    typedef PairStage<T, 64, 64, 64, kThr> Stage;
+    static constexpr int SPLANE = 64 * 64 * 2, PATCH = planes_of<T>::n == 1 ? 64 * 128 : 0;   // (rows of out in bf16 on their way to whole lines)
+    static constexpr int FLAG = Stage::BYTES + 3 * SPLANE + PATCH, BYTES = FLAG + 16;
+};
+constexpr int kRows64 = 64;
+
+template <typename T, bool DECAY>
+__global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void attn64_planes_kernel(Geom g, PlanesProblems probs, PlanesGrid pg,
+                                                                                                      float* emit)
+{
+    typedef Attn64Lds<T> LD;
+    typedef typename LD::Stage Stage;
+    constexpr int D = 64, NP = planes_of<T>::n, KS = D / 16, SUB = 32 * D * 2;
+    constexpr bool TR = NP == 1;
+    extern __shared__ __align__(16) char smem[];
+    char* snap = smem + Stage::BYTES;
+    char* patch = snap + 3 * LD::SPLANE;
+    int* flag = reinterpret_cast<int*>(smem + LD::FLAG);
+
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
+    if (tid == 0) *flag = 0;
+    int prob, s, seg, grp;
+    if (!which_segment(g, pg, prob, s, seg, grp)) return;
+    const PlanesProblem pb = probs.p[prob];
+    int tok0, len, ps;
+    slot_range(g, s, tok0, len, ps);
+    const int nch = (len + kRows64 - 1) / kRows64;
+    const int ci0 = seg * pg.cps, ci1 = min(nch, ci0 + pg.cps);
+    if (ci0 >= nch) return;
+    const bool rev = pb.reverse != 0;
+    const size_t base = ((size_t)grp * (size_t)g.N + tok0) * D;
+    const T* A = static_cast<const T*>(pb.A) + base;
+    const T* Bk = static_cast<const T*>(pb.Bk) + base;
+    const T* Cv = static_cast<const T*>(pb.Cv) + base;
+    T* out = static_cast<T*>(pb.out) + base;
+    const float l2 = DECAY ? decay_log2(g, grp) : 0.f;
+    const int rt = w >> 1, ct = w & 1;   // row and column tile; the state's tile has the same numbers
+
+    Stage st;
+    st.fetch(Bk, Cv, (rev ? nch - 1 : 0) * kRows64, len, tid);
+    f32x16 S[1] = {zero16()};
+    bool have_state = pb.state != nullptr;
+    if (have_state) {
+        const float* st0 = pb.state + state_index(g, pb, grp, s, ps) * (size_t)(D * D);
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) {
+            const int a = 32 * rt + acc_row(v) + 4 * h, b = 32 * ct + l32;
+            if (pb.transpose) {
+                const f32x4 q4 = *reinterpret_cast<const f32x4*>(st0 + b * D + a);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) S[0][v + e] = q4[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) S[0][v + e] = st0[(a + e) * D + b];
+            }
+        }
+    }
+
+    // the next slot of the caller's whose state goes to `emit`: its first row, and ps, its number
+    int slot = 0, to_emit = -1;
+    if (emit) {
+        slot = slot_tokens(g);
+        const int k = (int)(((uint32_t)(ci0 * kRows64) + (uint32_t)slot - 1u) / (uint32_t)slot);
+        to_emit = k * slot;
+        ps += k;
+    }
+    // offset of a lane's first piece of its row in a tile; the next ones differ in bits 5 and 6 alone
+    uint32_t row_at = (uint32_t)plane_off<D>(l32, h);
+    int redo = ci1;
+    for (int ci = 0; ci < ci1; ++ci) {
+        const int c0 = (rev ? nch - 1 - ci : ci) * kRows64, clen = min(kRows64, len - c0);
+        const bool rows = ci >= ci0, update = ci + 1 < ci1;
+        f32x16 acc, low;   // (products of the higher orders have a sum of their own for the whole chunk)
+        bf16x8 q[KS][NP];
+        if (rows) {
+            // (rows past the end: the last one once more, whose results nobody reads; a zero instead of it would be a select
+            // that waits for the load here)
+            const T* row = A + (size_t)min(c0 + 32 * rt + l32, len - 1) * D + 8 * h;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) to_planes(load8(row + 16 * ks, true), q[ks]);
+            if (c0 == to_emit) {   // a slot of the caller's starts here (a walk's first has its state, unless there is none)
+                if (c0 > 0 || !pb.state) {
+                    float* at = emit + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) + (32 * rt + 4 * h) * D + 32 * ct + l32;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) at[acc_row(v) * D] = S[0][v];
+                }
+                ++ps;
+                to_emit += slot;
+            }
+            // snapshot of the running state, rows = its second index
+            if (have_state) {
+#pragma unroll
+                for (int v = 0; v < 16; v += 8) {
+                    bf16x8 p[3];
+                    acc_frag(S[0], v, p);
+                    const int b = 32 * ct + l32, a = 32 * rt + acc_row(v) + 4 * h;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        const bf16x4 lo = {p[i][0], p[i][1], p[i][2], p[i][3]}, hi = {p[i][4], p[i][5], p[i][6], p[i][7]};
+                        *reinterpret_cast<bf16x4*>(snap + i * LD::SPLANE + plane_off<D>(b, a >> 3) + (a & 7) * 2) = lo;
+                        *reinterpret_cast<bf16x4*>(snap + i * LD::SPLANE + plane_off<D>(b, (a >> 3) + 1) + (a & 7) * 2) = hi;
+                    }
+                }
+            }
+        }
+        if (DECAY && update) {
+            const float wc = decay_pow((float)clen, l2);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) S[0][v] *= wc;
+        }
+        if (ci > 0 && ci <= ci0) __syncthreads();   // the previous stage has been read (a chunk with rows ends with a barrier)
+        st.put(smem, tid);
+        if (update) st.fetch(Bk, Cv, rev ? c0 - kRows64 : c0 + kRows64, len, tid);
+        __syncthreads();
+        if (rows) {
+            acc = zero16();
+            low = zero16();
+            if (have_state) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    bf16x8 b[3];
+                    frag_at<3>(snap + 32 * ct * 2 * D, LD::SPLANE, row_at ^ (32 * ks), b);
+                    low = mm_either<TR, 1, 2>(q[ks], b, low);
+                }
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    bf16x8 b[1];
+                    frag_at<1>(snap + 32 * ct * 2 * D, LD::SPLANE, row_at ^ (32 * ks), b);
+                    acc = mm_either<TR, 0, 0>(q[ks], b, acc);
+                }
+                if (DECAY) {
+                    // the state sits one token before the chunk (causal) or one after it
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int i = 32 * rt + (TR ? l32 : acc_row(v) + 4 * h);
+                        const float f = decay_pow((float)(rev ? max(clen - i, 0) : i + 1), l2);
+                        acc[v] *= f;
+                        low[v] *= f;
+                    }
+                }
+            }
+#pragma unroll 1
+            for (int u = rev ? rt : 0; u <= (rev ? 1 : rt); ++u) {
+                if (32 * u >= clen) break;
+                pin_vgpr(row_at);   // (four offsets worked out at each use, not kept)
+                const char* buf = smem + u * SUB;
+                f32x16 sc = zero16();
+                if constexpr (NP > 1) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        bf16x8 k[NP];
+                        frag_at<NP>(buf, Stage::PLANE, row_at ^ (32 * ks), k);
+                        sc = mm<1, 2>(k, q[ks], sc);
+                    }
+                }
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    bf16x8 k[1];
+                    frag_at<1>(buf, Stage::PLANE, row_at ^ (32 * ks), k);
+                    sc = mm<0, 0>(k, q[ks], sc);
+                }
+                if (DECAY || u == rt) {
+                    mask_tile<DECAY>(sc, 32 * (rt - u) + l32 - 4 * h, u == rt, rev, l2);
+                }
+                bf16x8 p[2][3];
+                acc_frag(sc, 0, p[0]);
+                acc_frag(sc, 8, p[1]);
+                bf16x8 v[2][NP];
+                col_frag<D>(buf + Stage::TENSOR, Stage::PLANE, 0, 32 * ct, lane, v[0]);
+                col_frag<D>(buf + Stage::TENSOR, Stage::PLANE, 16, 32 * ct, lane, v[1]);
+                low = mm_either<TR, 1, 2>(p[1], v[1], mm_either<TR, 1, 2>(p[0], v[0], low));
+                acc = mm_either<TR, 0, 0>(p[1], v[1], mm_either<TR, 0, 0>(p[0], v[0], acc));
+            }
+        }
+        if (update) {
+#pragma unroll 1
+            for (int r0 = 0; r0 < clen; r0 += 32)
+                state_step<T, D, D, Stage::PLANE, DECAY, 2>(S, smem + (r0 / 32) * SUB, Stage::TENSOR, 0, w, lane,
+                                                            rev ? r0 : clen - 1 - r0, rev ? 1 : -1, l2);
+        }
+        have_state = true;
+        if (!rows) continue;
+
+        // (not finite: from this chunk on in fp32, as above)
+        acc += low;
+        float odd = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) odd = fmaf(acc[v], 0.f, odd);
+        if constexpr (TR) {   // a lane has 16 columns of its row
+            const int row = 32 * rt + l32;
+#pragma unroll
+            for (int v = 0; v < 16; v += 4) {
+                const u32x2 two = {pack2(acc[v], acc[v + 1]), pack2(acc[v + 2], acc[v + 3])};
+                *reinterpret_cast<u32x2*>(patch + row * 128 + (((4 * ct + v / 4) ^ (row >> 1 & 7)) << 4) + 8 * h) = two;
+            }
+        }
+        if (any_odd(odd != 0.f, flag)) {
+            redo = ci;
+            break;
+        }
+        if constexpr (TR) {
+            int t = threadIdx.x;
+            asm volatile("" : "+v"(t));   // (worked out anew: 168 registers are what three workgroups on a CU leave)
+            const int ch = t & 7;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int row = (t >> 3) + 32 * i;
+                const u32x4 piece = *reinterpret_cast<const u32x4*>(patch + row * 128 + ((ch ^ (row >> 1 & 7)) << 4));
+                if (row < clen) *reinterpret_cast<u32x4*>(out + (size_t)(c0 + row) * D + 8 * ch) = piece;
+            }
+        } else {
+            T* o = out + (size_t)(c0 + 32 * rt + 4 * h) * D + 32 * ct + l32;
+            int left = clen - 32 * rt - 4 * h;
+            if (clen >= 32 * rt + 32) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) store1(o + acc_row(v) * D, acc[v]);
+            } else {
+                asm volatile("" : "+v"(left));   // (else the answers for the rows are kept through the walk)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (acc_row(v) < left) store1(o + acc_row(v) * D, acc[v]);
+            }
+        }
+    }
+    if (redo < ci1) attn_scalar<T, D, kRows64>(g, probs, pg, redo, reinterpret_cast<float*>(snap), emit);
 }
 
 template <typename T, int D, bool DECAY>
-hipError_t states_TD(const Geom& g, const T* K, const T* V, float* M, int anchor, hipStream_t st)
+hipError_t states_TD(const Geom& g, const T* K, const T* V, float* M, int anchor, int of_slots, hipStream_t st)
 {
     constexpr int DP = D < 32 ? 32 : D, ROWS = (planes_of<T>::n == 3 && D == 128) ? 32 : 64;
     constexpr int stages = 2 * PairStage<T, D, DP, ROWS, kThr>::BYTES, lds = stages < 16384 ? 16384 : stages;
     hipError_t e = allow_dynamic_lds<states_planes_kernel<T, D, DECAY>>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((states_planes_kernel<T, D, DECAY>), dim3(g.T_s, g.G), dim3(kThr), lds, st, g, K, V, M, anchor);
+    hipLaunchKernelGGL((states_planes_kernel<T, D, DECAY>), dim3(g.T_s, g.G), dim3(kThr), lds, st, g, K, V, M, anchor, of_slots);
     return hipGetLastError();
 }
 
 template <typename T, int D, bool DECAY>
-hipError_t attn_TD(const Geom& g, const PlanesProblems& p, int n, hipStream_t st)
+hipError_t attn_TD(const Geom& g, const PlanesProblems& p, int n, float* emit, hipStream_t st)
 {
-    constexpr int lds = AttnLds<T, D, DECAY>::BYTES;
-    hipError_t e = allow_dynamic_lds<attn_planes_kernel<T, D, DECAY>>(lds);
+    constexpr int lds = D == 64 ? Attn64Lds<T>::BYTES : AttnLds<T, D, DECAY>::BYTES, rows = D == 64 ? kRows64 : kChunk;
+    hipError_t e;
+    if constexpr (D == 64) e = allow_dynamic_lds<attn64_planes_kernel<T, DECAY>>(lds);
+    else e = allow_dynamic_lds<attn_planes_kernel<T, D, DECAY>>(lds);
     if (e != hipSuccess) return e;
     // Segments: as many as bring the launch to two workgroups per CU, at most eight per slot (the last
-    // one then re-adds seven eighths of the slot's states).
-    const int64_t chunks = std::min<int64_t>((std::min<int64_t>(g.L, g.N) + kChunk - 1) / kChunk, INT32_MAX / 2);
-    const int64_t wgs = (int64_t)g.G * g.T_s * n;
-    int64_t nseg = std::max<int64_t>(1, std::min<int64_t>({2 * (int64_t)cu_count() / wgs, chunks, 8}));
+    // one then re-adds seven eighths of the slot's states).  Heads of 64, us, one | two per CU: forward of what has more work to
+    // a row, one (fp32, 16 x 2000 in slots of 512 45 | 50, 32 x 2000 52 | 59; with decay 39 | 45, 44 | 47); bf16 without decay
+    // two (16 x 8000 37 | 35, 256 x 1000 53 | 45), but segments of a chunk only while there is a CU for each (16 x 2000 24 | 27).
+    const int64_t chunks = std::min<int64_t>((std::min<int64_t>(g.L, g.N) + rows - 1) / rows, INT32_MAX / 2), cus = cu_count();
+    const int64_t wgs = (int64_t)g.G * g.T_s * n, per_cu = D == 64 && n == 1 && (planes_of<T>::n > 1 || DECAY) ? 1 : 2;
+    const int64_t most = D == 64 && wgs * chunks > cus ? (chunks + 1) / 2 : chunks;
+    int64_t nseg = std::max<int64_t>(1, std::min<int64_t>({per_cu * cus / wgs, most, 8}));
     const int64_t cps = (chunks + nseg - 1) / nseg;
     nseg = (chunks + cps - 1) / cps;
-    const int64_t units = ((int64_t)g.G * g.T_s * nseg + 7) / 8 * 8;
-    if (n > 1 && units * n < ((int64_t)1 << 32) / kThr) {
-        hipLaunchKernelGGL((attn_planes_kernel<T, D, DECAY>), dim3((unsigned)(units * n)), dim3(kThr), lds, st, g, p, n, (int)nseg,
-                           (int)cps, 1);
+    auto launch = [&](dim3 grid, const PlanesProblems& q, int per, int flat) {
+        const uint32_t in_group = (uint32_t)(g.T_s * nseg);
+        const PlanesGrid pg = {per, (int)nseg, (int)cps, flat, in_group, (uint32_t)(((uint64_t)1 << 32) / std::max(2u, in_group)),
+                               (uint32_t)(((uint64_t)1 << 32) / std::max<int64_t>(2, nseg))};
+        if constexpr (D == 64) hipLaunchKernelGGL((attn64_planes_kernel<T, DECAY>), grid, dim3(kThr), lds, st, g, q, pg, emit);
+        else hipLaunchKernelGGL((attn_planes_kernel<T, D, DECAY>), grid, dim3(kThr), lds, st, g, q, pg);
         return hipGetLastError();
-    }
+    };
+    const int64_t units = ((int64_t)g.G * g.T_s * nseg + 7) / 8 * 8;
+    if (n == 3 && units * n < ((int64_t)1 << 32) / kThr) return launch(dim3((unsigned)(units * n)), p, n, 1);
     // (a grid holds fewer than 2^32 threads per axis: past that groups are the other axis, and the problems may go one by one)
     const int per = (int64_t)g.T_s * nseg * n < ((int64_t)1 << 32) / kThr ? n : 1;
     for (int i = 0; i < n; i += per) {
         PlanesProblems sub = p;
         if (per == 1) sub.p[0] = p.p[i];
-        hipLaunchKernelGGL((attn_planes_kernel<T, D, DECAY>), dim3((unsigned)(g.T_s * nseg * per), g.G), dim3(kThr), lds, st, g, sub,
-                           per, (int)nseg, (int)cps, 0);
-        e = hipGetLastError();
+        e = launch(dim3((unsigned)(g.T_s * nseg * per), g.G), sub, per, 0);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 template <typename T, int D>
-hipError_t states_T(const Geom& g, const void* K, const void* V, float* M, int anchor, hipStream_t st)
+hipError_t states_T(const Geom& g, const void* K, const void* V, float* M, int anchor, int of_slots, hipStream_t st)
 {
     const T *k = static_cast<const T*>(K), *v = static_cast<const T*>(V);
-    return g.decay ? states_TD<T, D, true>(g, k, v, M, anchor, st) : states_TD<T, D, false>(g, k, v, M, anchor, st);
+    return g.decay ? states_TD<T, D, true>(g, k, v, M, anchor, of_slots, st) : states_TD<T, D, false>(g, k, v, M, anchor, of_slots, st);
 }
 
 template <typename T, int D>
-hipError_t attn_T(const Geom& g, const PlanesProblems& p, int n, hipStream_t st)
+hipError_t attn_T(const Geom& g, const PlanesProblems& p, int n, float* emit, hipStream_t st)
 {
-    return g.decay ? attn_TD<T, D, true>(g, p, n, st) : attn_TD<T, D, false>(g, p, n, st);
+    return g.decay ? attn_TD<T, D, true>(g, p, n, emit, st) : attn_TD<T, D, false>(g, p, n, emit, st);
 }
 
 // one instance per (type, head size)
@@ -593,25 +897,27 @@ hipError_t attn_T(const Geom& g, const PlanesProblems& p, int n, hipStream_t st)
         default: return CALL<__hip_bfloat16, 128>(__VA_ARGS__);                    \
     }
 
-hipError_t attn_any(const Geom& g, int dtype, const PlanesProblems& p, int n, hipStream_t st)
+hipError_t attn_any(const Geom& g, int dtype, const PlanesProblems& p, int n, float* emit, hipStream_t st)
 {
-    LASP2_FOR_TYPE_AND_SIZE(attn_T, g, p, n, st)
+    LASP2_FOR_TYPE_AND_SIZE(attn_T, g, p, n, emit, st)
 }
 
 }  // namespace
 
 hipError_t launch_states_planes(const Geom& g, int dtype, const void* K, const void* V, float* M, int anchor_start,
-                                hipStream_t st)
+                                int of_slots, hipStream_t st)
 {
-    LASP2_FOR_TYPE_AND_SIZE(states_T, g, K, V, M, anchor_start, st)
+    LASP2_FOR_TYPE_AND_SIZE(states_T, g, K, V, M, anchor_start, of_slots, st)
 }
 
+bool planes_emit(const Geom& g) { return g.d == 64 && (g.L / g.wslots) % kRows64 == 0 && (g.wslots > 1 || g.lone_slots); }
+
 hipError_t launch_attn_fwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V, const float* P,
-                                  void* O, hipStream_t st)
+                                  float* emit, void* O, hipStream_t st)
 {
     PlanesProblems p = {};
-    p.p[0] = {Q, K, V, P, O, 0, 0};
-    return attn_any(g, dtype, p, 1, st);
+    p.p[0] = {Q, K, V, P, O, 0, 0, 0};
+    return attn_any(g, dtype, p, 1, emit, st);
 }
 
 hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V, const void* dO,
@@ -620,12 +926,12 @@ hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const
     PlanesProblems p = {};
     // dQ: the forward problem with (dO, V, K) in the roles of (Q, K, V); its state is
     // V^T K = (K^T V)^T, i.e. the cached prefix read transposed.
-    p.p[0] = {dO, V, K, P, dQ, 1, 0};
+    p.p[0] = {dO, V, K, P, dQ, 1, 0, 0};
     // dV: anti-causal problem with (K, Q, dO); state dM_{t+1:T} = sum Q^T dO.
-    p.p[1] = {K, Q, dO, dR, dV, 0, 1};
+    p.p[1] = {K, Q, dO, dR, dV, 0, 1, 1};
     // dK: anti-causal problem with (V, dO, Q); state dO^T Q = dM^T.
-    p.p[2] = {V, dO, Q, dR, dK, 1, 1};
-    return attn_any(g, dtype, p, 3, st);
+    p.p[2] = {V, dO, Q, dR, dK, 1, 1, 1};
+    return attn_any(g, dtype, p, 3, nullptr, st);
 }
 
 }  // namespace lasp2

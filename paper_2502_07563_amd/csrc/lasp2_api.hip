@@ -504,6 +504,40 @@ int pick_planes_slots(const Geom& g, const int32_t* cu_host, int nprob)
     return ws;
 }
 
+// The same for heads of 64 in lasp2_forward and the backward, which build the states: one per walk (the forward writes the others in
+// passing, planes_emit).  A walk starts with the rows of its predecessors read once more and one state each written, combined
+// and read, and holds a third of a CU (half in fp32); so about two walks per CU, and not below the length under which states cost
+// more than CUs without work.
+//   - Layer forward | backward, us, tokens per walk: bf16, 64 x 4001 64 tokens 84 | 139, 128 75 | 119, 256 62 | 106, 512 57 | 97,
+//     1024 60 | 94, 2048 78 | 124; 16 x 4000 128 28 | 40, 256 27 | 35, 512 29 | 42; fp32, 64 x 4001 128 135 | 269, 256 130 | 259, 512
+//     125 | 255, 1024 140 | 262; 16 x 4000 64 54 | 81, 128 45 | 75, 256 46 | 77, 512 57 | 87.
+//   - Short sequences whole, in one launch without states (in segments that add up the rows before them, where CUs are free),
+//     three launches | one, forward and backward: bf16, 16 x 1000 20 + 26 | 19 + 22, 32 x 500 20 + 27 | 15 + 21, 64 x 1000 25 + 33 | 29 + 35,
+//     128 x 500 25 + 33 | 19 + 30, 256 x 1000 52 + 96 | 42 + 78; with decay 16 x 1000 23 + 28 | 34 + 49; fp32 4 x 1000 21 + 27 | 36 + 37,
+//     128 x 500 40 + 71 | 38 + 66, 256 x 1000 124 + 253 | 104 + 228.
+int pick_planes64_slots(const Geom& g, const int32_t* cu_host, int dtype, bool backward)
+{
+    const int64_t longest = longest_sequence(g, cu_host);
+    if (g.G == 0 || g.L >= longest) return 1;
+    if (const int v = forced_walk_slots(g)) return v;
+    const bool light = dtype == LASP2_BF16 && !g.decay;
+    const int64_t slots = slots_of(longest, g.L), cus = cu_count(), ws_max = std::min(slots, max_walk_slots(g));
+    if (g.n_seqs == 0 && longest <= 1024 && slots == ws_max &&
+        (g.G >= cus / 2 || (light && g.G <= cus / 8) || (dtype == LASP2_BF16 && longest <= 512)))
+        return (int)slots;
+    const int64_t tokens = (int64_t)g.G * g.N, target = std::max<int64_t>(light ? 256 : 128, std::min<int64_t>(1024, tokens / (backward && light ? cus : 2 * cus)));
+    int64_t ws = 1;
+    while (ws * g.L < target && 2 * ws <= ws_max && !(backward && tokens * 3 < 2 * ws * g.L * cus)) ws *= 2;
+    return (int)ws;
+}
+
+// Slots per walk of what lasp2_forward and the backward launch on these kernels.  (lasp2_walk_slots and lasp2_walk_plan report
+// pick_planes_slots: the fewest a walk takes.)
+int planes_slots(const Geom& g, const int32_t* cu_host, int dtype, bool backward)
+{
+    return g.d == 64 ? pick_planes64_slots(g, cu_host, dtype, backward) : pick_planes_slots(g, cu_host, backward ? 3 : 1);
+}
+
 // What each call does with its descriptor (lasp2_walk_plan).
 WalkPlan plan_of(const Geom& g, const int32_t* cu_host, int dtype, int call)
 {
@@ -540,7 +574,7 @@ hipError_t run_states(const Geom& g, int dtype, const void* K, const void* V, fl
                       int anchor_start, hipStream_t st)
 {
     if (mfma_path_supported(g, dtype)) return launch_states_mfma(g, K, V, M, anchor_start, WalkStates::none, st);
-    return launch_states_planes(g, dtype, K, V, M, anchor_start, st);
+    return launch_states_planes(g, dtype, K, V, M, anchor_start, 0, st);
 }
 
 // Without a mask a document has one state, whatever its slots: it is summed and applied by walks of several slots, and
@@ -617,17 +651,16 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     // built per walk, not per slot of the caller: fewer of them, never more bytes than `need`.
     pl->gw = g;
     pl->start = Start::states;
-    if (pl->fast) {
-        const WalkPlan wp = plan_of(g, desc->cu_seqlens_host, desc->dtype, LASP2_CALL_ATTN_BWD);
-        pl->gw = regroup(g, desc->cu_seqlens_host, wp);
-        pl->start = wp.start;
-    }
+    const int32_t* cu = desc->cu_seqlens_host;
+    const WalkPlan wp = pl->fast ? plan_of(g, cu, desc->dtype, LASP2_CALL_ATTN_BWD) : WalkPlan{planes_slots(g, cu, desc->dtype, true), 0, Start::states};
+    pl->gw = regroup(g, cu, wp);
+    pl->start = wp.start;
     pl->lone_w = pl->gw.lone_slots != 0;
     pl->need_states_w = !pl->lone_w || pl->inclusive;
     return LASP2_OK;
 }
 
-int run_attn_bwd(const BwdPlan& pl, int dtype, const int32_t* cu_host, const void* Q, const void* K, const void* V, const void* dO,
+int run_attn_bwd(const BwdPlan& pl, int dtype, const void* Q, const void* K, const void* V, const void* dO,
                  const float* P, void* dQ, void* dK, void* dV, float* dR, hipStream_t st)
 {
     const Geom& g = pl.gw;
@@ -652,8 +685,7 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const int32_t* cu_host, const voi
     }
     if (pl.fast)
         return from_hip(launch_attn_bwd_mfma(g, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, pace, clear ? 0 : 1, dQ, dK, dV, st));
-    const Geom gp = regroup(g, cu_host, pick_planes_slots(g, cu_host, 3));
-    return from_hip(launch_attn_bwd_planes(gp, dtype, Q, K, V, dO, P, dR, dQ, dK, dV, st));
+    return from_hip(launch_attn_bwd_planes(g, dtype, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, dQ, dK, dV, st));
 }
 
 // Scratch of lasp2_attn_bwd_noalloc: device memory that belongs to the loaded library itself, one
@@ -772,7 +804,7 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
     if (wp.W) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, g.lone_slots ? nullptr : P, nullptr, O, st));
     if (mfma_path_supported(g, desc->dtype))
         return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
-    return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, P, O, st));
+    return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, gw.lone_slots ? nullptr : P, nullptr, O, st));
 }
 
 int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,
@@ -788,7 +820,7 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     hipStream_t st = (hipStream_t)stream;
     const int32_t* cu = desc->cu_seqlens_host;
     const bool fast = mfma_path_supported(g, desc->dtype);
-    const WalkPlan wp = plan_of(g, cu, desc->dtype, LASP2_CALL_FORWARD);
+    const WalkPlan wp = fast ? plan_of(g, cu, desc->dtype, LASP2_CALL_FORWARD) : WalkPlan{planes_slots(g, cu, desc->dtype, false), 0, Start::states};
     const Geom gw = regroup(g, cu, wp);
     hipError_t e;
     if (wp.start == Start::gather) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, nullptr, P, O, st));
@@ -803,13 +835,22 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
         }
         return from_hip(launch_attn_fwd_emit_mfma(gw, Q, K, V, P, O, st));
     }
+    if (!fast && planes_emit(gw)) {   // likewise
+        if (!gw.lone_slots) {
+            e = launch_states_planes(gw, desc->dtype, K, V, P, 0, 1, st);
+            if (e != hipSuccess) return LASP2_ERR_LAUNCH;
+            e = launch_state_prefix(gw, P, P, 0, 0, 1, nullptr, 0, st);
+            if (e != hipSuccess) return LASP2_ERR_LAUNCH;
+        }
+        return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, gw.lone_slots ? nullptr : P, P, O, st));
+    }
     e = run_states(g, desc->dtype, K, V, P, 0, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     e = launch_state_prefix(g, P, P, 0, 0, 0, nullptr, 0, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     if (wp.start == Start::both) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, P, nullptr, O, st));
     if (fast) return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
-    return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, P, O, st));
+    return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, gw.lone_slots ? nullptr : P, nullptr, O, st));
 }
 
 int lasp2_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,
@@ -821,7 +862,7 @@ int lasp2_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
     if (rc != LASP2_OK) return rc;
     if (pl.empty) return LASP2_OK;
     if (pl.need_states && workspace_bytes < pl.need) return LASP2_ERR_WORKSPACE;
-    return run_attn_bwd(pl, desc->dtype, desc->cu_seqlens_host, Q, K, V, dO, P, dQ, dK, dV,
+    return run_attn_bwd(pl, desc->dtype, Q, K, V, dO, P, dQ, dK, dV,
                         pl.need_states ? static_cast<float*>(workspace) : nullptr, (hipStream_t)stream);
 }
 
@@ -840,7 +881,7 @@ int lasp2_attn_bwd_noalloc(const lasp2_desc_t* desc, const void* Q, const void* 
     }
     // Nothing in the array has to start at zero: the states kernel writes every slot's state
     // before the combine and the attention kernels read any of it.
-    return run_attn_bwd(pl, desc->dtype, desc->cu_seqlens_host, Q, K, V, dO, P, dQ, dK, dV, dR, (hipStream_t)stream);
+    return run_attn_bwd(pl, desc->dtype, Q, K, V, dO, P, dQ, dK, dV, dR, (hipStream_t)stream);
 }
 
 int lasp2_state_total(const lasp2_desc_t* desc, const float* M, float* S, void* stream)
@@ -891,7 +932,7 @@ int lasp2_nomask_forward(const lasp2_desc_t* desc, const void* Q, const void* K,
         const RowsStateProblem p = {Q, S, O, 0, S};
         return from_hip(run_nomask(g, gw, K, V, S, &p, 1, st));
     }
-    hipError_t e = launch_states_planes(g, desc->dtype, K, V, S, 0, st);
+    hipError_t e = launch_states_planes(g, desc->dtype, K, V, S, 0, 0, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     e = launch_state_total(g, S, S, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
@@ -919,7 +960,7 @@ int lasp2_nomask_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, con
         const RowsStateProblem p[3] = {{dO, S, dQ, 1, nullptr}, {V, dS, dK, 1, dS}, {K, dS, dV, 0, nullptr}};
         return from_hip(run_nomask(g, nomask_walks(g, desc->cu_seqlens_host, 3), Q, dO, dS, p, 3, st));
     }
-    hipError_t e = launch_states_planes(g, desc->dtype, Q, dO, dS, 0, st);
+    hipError_t e = launch_states_planes(g, desc->dtype, Q, dO, dS, 0, 0, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     e = launch_state_total(g, dS, dS, st);
     if (e != hipSuccess) return LASP2_ERR_LAUNCH;

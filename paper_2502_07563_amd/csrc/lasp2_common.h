@@ -194,11 +194,16 @@ inline int cu_count()
 
 // Split-plane matrix-core kernels (kernels_planes.hip), any supported (dtype, d, C).
 // anchor_start (decay only): weights lam^(token - slot start) instead of lam^(slot end - token).
+// of_slots: M has one entry per slot of the caller's, and the state of each of g's walks goes where its first slot is (not that
+// of a document's last walk, which no exclusive prefix contains); otherwise one entry per walk.
 hipError_t launch_states_planes(const Geom& g, int dtype, const void* K, const void* V,
-                                float* M, int anchor_start, hipStream_t st);
+                                float* M, int anchor_start, int of_slots, hipStream_t st);
+// emit (where planes_emit(g)): NULL, or the prefix states, which the walks write for every slot but a walk's first (and
+// for that too where P is NULL: every document a single walk).
+bool planes_emit(const Geom& g);
 hipError_t launch_attn_fwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V,
-                                  const float* P, void* O, hipStream_t st);
-// dR: EXCLUSIVE suffix states of Q^T dO; P, dR NULL: zero (every document a single slot)
+                                  const float* P, float* emit, void* O, hipStream_t st);
+// dR: EXCLUSIVE suffix states of Q^T dO, one per walk of g; P, dR NULL: zero (every document a single walk)
 hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V,
                                   const void* dO, const float* P, const float* dR, void* dQ, void* dK,
                                   void* dV, hipStream_t st);

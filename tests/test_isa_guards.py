@@ -344,7 +344,7 @@ def test_states_of_walks_store_count_matches_its_wait_arithmetic(isa, decay):
 # Scratch memory of the split-plane kernels, bytes per lane: what their register use is known to exceed (the loads around it
 # are the compiler's own, so spills cost time and nothing else).  Everything that is not named here has none.
 PLANES_SCRATCH = {
-    "attn_planes_kernel<float, 64, true>": 40,
+    "attn64_planes_kernel<float, true>": 24,
     "attn_planes_kernel<float, 128, false>": 416,
     "attn_planes_kernel<float, 128, true>": 564,
     "attn_planes_kernel<__hip_bfloat16, 128, true>": 308,
