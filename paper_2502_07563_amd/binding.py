@@ -132,14 +132,14 @@ def _ptr(t):
         raise ValueError("lasp2: tensors must live in device memory (got a host tensor)")
     if not t.is_contiguous():
         raise ValueError("lasp2: tensors must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _rows(p, t, n_tokens, name):
     """A [B,H,n_tokens,d] tensor of the problem's dtype (None passes: the library reports it)."""
     if t is None:
         return
-    if t.dtype != p.torch_dtype:
+    if t.dtype is not p.torch_dtype:
         raise ValueError(f"lasp2: {name} has dtype {t.dtype}, the problem is {p.torch_dtype}")
     if t.numel() != p.B * p.H * n_tokens * p.d:
         raise ValueError(f"lasp2: {name} has {t.numel()} elements, expected B*H*{n_tokens}*d = "
@@ -162,9 +162,11 @@ def _states(p, t, name):
 
 
 def _stream(stream):
+    """Handle of the stream, of the current device's current one if None: that without a torch.cuda.Stream made for it
+    (3 us of the 17 that a small forward takes the host)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def lasp2_num_slots(p: Problem) -> int:
@@ -337,39 +339,54 @@ def alloc_workspace(p: Problem, device="cuda"):
     return torch.empty(lasp2_workspace_size(p) // 4, dtype=torch.float32, device=device)
 
 
-def workspace_states(p: Problem, ws):
-    """The fp32 [B,H,T_s,d,d] state array at the head of a workspace."""
-    T_s = lasp2_num_slots(p)
+def _head(p, ws, T_s):
     return ws[:p.B * p.H * T_s * p.d * p.d].view(p.B, p.H, T_s, p.d, p.d)
 
 
+def workspace_states(p: Problem, ws):
+    """The fp32 [B,H,T_s,d,d] state array at the head of a workspace."""
+    return _head(p, ws, lasp2_num_slots(p))
+
+
+# The four calls below allocate what they return.  They ask for the number of slots once and check what the caller gave, not
+# the arrays of their own: with the stream's handle 8 us less host time in a small layer's forward and backward of 49.
+
 def forward(p: Problem, Q, K, V, stream=None):
     """What chunk_states -> state_prefix (in place) -> attn_fwd give, in one call.  Returns (O, P)."""
-    P = alloc_states(p, Q.device)
-    O = torch.empty_like(Q)
-    lasp2_forward(p, Q, K, V, P, O, stream)
+    P, O = alloc_states(p, Q.device), torch.empty_like(Q)
+    _rows(p, K, p.N, 'K'); _rows(p, V, p.N, 'V'); _rows(p, Q, p.N, 'Q')
+    _check(lib().lasp2_forward(p.ref, _ptr(Q), _ptr(K), _ptr(V), P.data_ptr(), _ptr(O), _stream(stream)), "lasp2_forward")
     return O, P
 
 
 def backward(p: Problem, Q, K, V, dO, P, stream=None):
     """attn_bwd with a freshly allocated workspace.  Returns (dQ, dK, dV, the workspace's state array)."""
-    ws = alloc_workspace(p, Q.device)
+    ws, T_s = alloc_workspace(p, Q.device), lasp2_num_slots(p)
     dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
-    lasp2_attn_bwd(p, Q, K, V, dO, P, dQ, dK, dV, ws, stream)
-    return dQ, dK, dV, workspace_states(p, ws)
+    for n, t in (('Q', Q), ('K', K), ('V', V), ('dO', dO)):
+        _rows(p, t, p.N, n)
+    _f32(P, p.B * p.H * T_s * p.d * p.d, 'P')
+    _check(lib().lasp2_attn_bwd(p.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(dO), _ptr(P), _ptr(dQ), _ptr(dK), _ptr(dV),
+                                ws.data_ptr(), ws.numel() * 4, _stream(stream)), "lasp2_attn_bwd")
+    return dQ, dK, dV, _head(p, ws, T_s)
 
 
 def nomask_forward(p: Problem, Q, K, V, stream=None):
     """What chunk_states -> state_total (in place) -> nomask_fwd give, in one call.  Returns (O, S)."""
-    S = alloc_states(p, Q.device)
-    O = torch.empty_like(Q)
-    lasp2_nomask_forward(p, Q, K, V, S, O, stream)
+    S, O = alloc_states(p, Q.device), torch.empty_like(Q)
+    _rows(p, K, p.N, 'K'); _rows(p, V, p.N, 'V'); _rows(p, Q, p.N, 'Q')
+    _check(lib().lasp2_nomask_forward(p.ref, _ptr(Q), _ptr(K), _ptr(V), S.data_ptr(), _ptr(O), _stream(stream)),
+           "lasp2_nomask_forward")
     return O, S
 
 
 def nomask_backward(p: Problem, Q, K, V, dO, S, stream=None):
     """nomask_bwd with a freshly allocated workspace.  Returns (dQ, dK, dV, the workspace's state array)."""
-    ws = alloc_workspace(p, Q.device)
+    ws, T_s = alloc_workspace(p, Q.device), lasp2_num_slots(p)
     dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
-    lasp2_nomask_bwd(p, Q, K, V, dO, S, dQ, dK, dV, ws, stream)
-    return dQ, dK, dV, workspace_states(p, ws)
+    for n, t in (('Q', Q), ('K', K), ('V', V), ('dO', dO)):
+        _rows(p, t, p.N, n)
+    _f32(S, p.B * p.H * T_s * p.d * p.d, 'S')
+    _check(lib().lasp2_nomask_bwd(p.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(dO), _ptr(S), _ptr(dQ), _ptr(dK), _ptr(dV),
+                                  ws.data_ptr(), ws.numel() * 4, _stream(stream)), "lasp2_nomask_bwd")
+    return dQ, dK, dV, _head(p, ws, T_s)
