@@ -1807,7 +1807,11 @@ __global__ __launch_bounds__(512) void attn_bwd_pair_mfma_kernel(Geom g, AttnPro
 // launches it saves (states, prefix, counters: 5 to 8 us each with the gap before it) cost more.
 // Eight waves: four quadrants of 2 x 2 tiles, each by two waves that take the halves of a 64-row stage (an
 // operand is read from LDS once per two products; the walks' own update, one row of tiles per wave, reads three per
-// two); a ring of four stages, three on their way.  The halves are added through LDS at the end.
+// two); a ring of four stages.  A stage cannot take less than 512 clk of matrix instructions, about as many of LDS (its fill
+// and the reads) and as many of the requests' addresses, and the eight waves come to each at the same time: 1 420 clk with the
+// reads before the products and all requests behind the barrier, 1 160 as it stands (160 of them the sum of sums, every eighth
+// stage).  32 heads x 1 531, forward, us: 26.1 -> 24.2; 4 x 4 000, slots of 2 048, 47.7 -> 42.3, backward 55.0 -> 49.4.
+// The halves are added through LDS at the end.
 // With decay (l2: log2 of the factor) row r counts lam^(ntok - 1 - r), or lam^r if anchor_start, and base lam^ntok: the rows of a stage
 // are weighted among themselves (and rounded), the stage's sum in fp32, as in states_body.
 template <bool DECAY = false>
@@ -1826,8 +1830,26 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
 #pragma unroll
     for (int u = 0; u < 2; ++u) dvo[u] = dma_lane_off(2 * w + u, lane);
     const int nst = (ntok + KB - 1) / KB;
-    auto issue = [&](int i) {
-        dma_block<8>(X, Y, row0, i * KB, ntok, sX + (i % NST) * STAGE_BYTES, sY + (i % NST) * STAGE_BYTES, w, lane, dvo);
+    // request half u (one instruction per tensor) of this wave's part of stage i; rows past the end are its last one, zeroed later
+    auto issue = [&](int i, int u) __attribute__((always_inline)) {
+        const size_t blk = row0 + (size_t)(i * KB) * ROWB;
+        const int k = 2 * w + u;
+        uint32_t voff = dvo[u];
+        if (i * KB + KB > ntok)
+            voff = (uint32_t)(min(4 * k + (lane >> 4), ntok - 1 - i * KB) * ROWB + (int)(voff & (ROWB - 1)));
+        dma16(X + blk, voff, lds_addr_of(sX + (i % NST) * STAGE_BYTES + 4 * k * ROWB));
+        dma16(Y + blk, voff, lds_addr_of(sY + (i % NST) * STAGE_BYTES + 4 * k * ROWB));
+    };
+    // this wave's operands of 16 rows: columns 64 q + lane's of the first tile, 32 more (an XOR) of the second
+    const int li = lane & 15, cl = 16 * ((lane >> 4) & 1) + 4 * (li & 3), rl = 32 * hf + 8 * h + (li >> 2);
+    uint32_t ox = lds_addr_of(sX) + (uint32_t)tr_off(rl, 64 * qa + cl), oy = lds_addr_of(sY) + (uint32_t)tr_off(rl, 64 * qb + cl);
+    auto fetch = [&](int i, int k, bf16x8 (&x)[2], bf16x8 (&y)[2]) __attribute__((always_inline)) {
+        const uint32_t px = ox + (i % NST) * STAGE_BYTES, py = oy + (i % NST) * STAGE_BYTES;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            x[e] = lds_read_tr8_u((px ^ (e << 6)) + k * (16 * ROWB), (px ^ (e << 6) ^ 16) + (4 + 16 * k) * ROWB);
+            y[e] = lds_read_tr8_u((py ^ (e << 6)) + k * (16 * ROWB), (py ^ (e << 6) ^ 16) + (4 + 16 * k) * ROWB);
+        }
     };
     // sums of at most 512 rows, and the sum of those: as accurate as the sums of a slot and of slots that they replace
     f32x16 acc[2][2], tot[2][2];
@@ -1848,15 +1870,17 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
                     acc[a][b][v] = 0.f;
                 }
     };
-    for (int i = 0; i < NST - 1 && i < nst; ++i) issue(i);
-    for (int i = 0; i < nst; ++i) {
-        char* tx = sX + (i % NST) * STAGE_BYTES;
-        char* ty = sY + (i % NST) * STAGE_BYTES;
-        // stage i has landed once only the (at most two) younger ones are outstanding
-        if (i + 2 < nst) wait_vmcnt<2 * DPS>();
-        else if (i + 1 < nst) wait_vmcnt<DPS>();
+    auto product = [&](const bf16x8 (&x)[2], const bf16x8 (&y)[2], int a, int b) __attribute__((always_inline)) {
+        acc[a][b] = mfma(x[a], y[b], acc[a][b]);
+    };
+    // stage i in LDS, for every wave once the next barrier is past; stages up to `last` have been requested
+    auto landed = [&](int i, int last) {
+        if (i + 3 <= last) wait_vmcnt<3 * DPS>();
+        else if (i + 2 <= last) wait_vmcnt<2 * DPS>();
+        else if (i + 1 <= last) wait_vmcnt<DPS>();
         else wait_vmcnt<0>();
-        if (i * KB + KB > ntok) zero_tail_rows<8>(i * KB, ntok, tx, ty, w, lane);
+        char* tx = sX + (i % NST) * STAGE_BYTES;
+        if (i * KB + KB > ntok) zero_tail_rows<8>(i * KB, ntok, tx, sY + (i % NST) * STAGE_BYTES, w, lane);
         if (DECAY) {   // each wave the rows it fetched (a row takes one weight: the swizzle does not matter)
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -1865,22 +1889,43 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
                 *p = scale_bf16x8(*p, __builtin_amdgcn_exp2f((float)(anchor_start ? b : max(min(i * KB + KB, ntok) - 1 - r, 0)) * l2));
             }
         }
-        __syncthreads();   // complete in LDS; every wave is past stage i - 1, whose place stage i + 3 takes
-        if (i + NST - 1 < nst) issue(i + NST - 1);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int r = 32 * hf + 16 * k + 8 * h;
-            bf16x8 x[2], y[2];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                x[e] = lds_read_tr8(tx, r, r + 4, 64 * qa + 32 * e, lane);
-                y[e] = lds_read_tr8(ty, r, r + 4, 64 * qb + 32 * e, lane);
-            }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) acc[a][b] = mfma(x[a], y[b], acc[a][b]);
+    };
+    // The operands of the second 16 rows are read under the products of the first, those of the next stage's first rows under
+    // the products of the second; the barrier lies between them, where every wave has read all of stage i.  The requests of a
+    // stage are spread over both: all at once behind the barrier they fill the address unit for 500 clk, and a wave that
+    // waits there does not come to its products.
+    bf16x8 xA[2], yA[2], xB[2], yB[2];
+    for (int i = 0; i < NST && i < nst; ++i) { issue(i, 0); issue(i, 1); }
+    if (nst) {
+        landed(0, min(NST, nst) - 1);
+        __syncthreads();
+        fetch(0, 0, xA, yA);
+    }
+    for (int i = 0; i < nst; ++i) {
+        product(xA, yA, 0, 0);
+        SCHED_FENCE();
+        fetch(i, 1, xB, yB);
+        SCHED_FENCE();
+        product(xA, yA, 0, 1);
+        SCHED_FENCE();
+        if (i && i + NST - 1 < nst) issue(i + NST - 1, 1);
+        SCHED_FENCE();
+        product(xA, yA, 1, 0);
+        product(xA, yA, 1, 1);
+        SCHED_FENCE();
+        if (i + 1 < nst) {
+            landed(i + 1, min(i + NST, nst) - 1);
+            __syncthreads();   // stage i + 1 complete in LDS; every wave has read stage i, whose place stage i + 4 takes
+            fetch(i + 1, 0, xA, yA);
         }
+        SCHED_FENCE();
+        product(xB, yB, 0, 0);
+        product(xB, yB, 0, 1);
+        SCHED_FENCE();
+        if (i + NST < nst) issue(i + NST, 0);
+        SCHED_FENCE();
+        product(xB, yB, 1, 0);
+        product(xB, yB, 1, 1);
         if (DECAY) flush(__builtin_amdgcn_exp2f((float)(anchor_start ? i * KB : max(ntok - KB - i * KB, 0)) * l2));
         else if ((i & 7) == 7) flush(1.f);
     }
