@@ -382,6 +382,7 @@ struct AttnProblem {
     const unsigned* pace; // NULL, or per (group, slot): 64-token blocks another workgroup has begun
     int lead;             // with pace: this walk may be at most `lead` blocks ahead of that count
     float* emit;          // skew_walk with EMIT: the caller's state array, which the walk fills in
+    int once;             // skew_walk with STREAM: Bk and Cv don't stay in the caches until they are read again (streams_past_caches)
 };
 
 // The d x d state a walk starts from: entry `s` of an array with one state per walk, or, in the
@@ -832,7 +833,7 @@ __device__ __forceinline__ uint32_t wait_vmcnt_token_le(int n)
 // to pr.emit (slots of a multiple of 64 tokens).  The running state after a block is that of the slot which starts there:
 // 32 stores per wave and slot, counted like the output's.
 // gathered: the state is where gather_state has left it (no wstate then).
-template <bool HC1, bool ANTI, bool DECAY, bool EMIT = false>
+template <bool HC1, bool ANTI, bool DECAY, bool EMIT = false, bool STREAM = EMIT>
 __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, char* smem, int tid, int w,
                                           int rb, int grp, int s, int tok0, int len, const float* wstate,
                                           int ps = 0, bool gathered = false, bool emit_first = true)
@@ -853,6 +854,7 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
     const char* __restrict__ Bk = pr.Bk;
     const char* __restrict__ Cv = pr.Cv;
     char* __restrict__ out = pr.out;
+    const int once = pr.once;
     const size_t row0 = ((size_t)grp * g.N + tok0) * ROWB;
     const int t0 = w * TPW;
     const int nch = (len + C - 1) / C;
@@ -871,8 +873,8 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
         uint32_t dvo[16 / NW];
 #pragma unroll
         for (int u = 0; u < 16 / NW; ++u) dvo[u] = dma_lane_off(w * (16 / NW) + u, ln);
-        dma_block<NW>(Bk, Cv, row0, blk(i) * KB, len, sK + (i % NSTAGE) * STAGE_BYTES,
-                      sV + (i % NSTAGE) * STAGE_BYTES, w, ln, dvo);
+        dma_block<NW, STREAM>(Bk, Cv, row0, blk(i) * KB, len, sK + (i % NSTAGE) * STAGE_BYTES,
+                              sV + (i % NSTAGE) * STAGE_BYTES, w, ln, dvo, once, once);
     };
     if (blk(0) * KB < len) issue(0);
     if (blk(1) * KB < len) issue(1);
@@ -1336,10 +1338,10 @@ __global__ __launch_bounds__(512) void attn_skew_mfma_kernel(Geom g, AttnProblem
     const int rb = w < 4 ? w : 11 - w;   // waves w and w+4 share a SIMD: row blocks s and 7-s
     if (rb < 4) {
         if (pr.anti) skew_walk<false, true, DECAY>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate);
-        else skew_walk<false, false, DECAY>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate);
+        else skew_walk<false, false, DECAY, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate);
     } else {
         if (pr.anti) skew_walk<true, true, DECAY>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate);
-        else skew_walk<true, false, DECAY>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate);
+        else skew_walk<true, false, DECAY, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, wstate);
     }
 }
 
@@ -1403,6 +1405,7 @@ struct PairProblem {
     char* dV;
     char* dK;
     unsigned* pace;    // NULL, or per (group, slot): receives the number of blocks this walk has begun
+    int once;          // Q does not stay in the caches until it is read again (streams_past_caches)
 };
 
 template <bool DKROLE, bool LATE, bool GATHERS = false>
@@ -1429,8 +1432,8 @@ __device__ __forceinline__ void pair_walk(const Geom& g, const PairProblem& pr, 
         uint32_t dvo[IPW];
 #pragma unroll
         for (int u = 0; u < IPW; ++u) dvo[u] = dma_lane_off(w * IPW + u, ln);
-        dma_block<NW>(pr.Q, pr.dO, row0, i * KB, len, sX + (i % NSTAGE) * STAGE_BYTES,
-                      sY + (i % NSTAGE) * STAGE_BYTES, w, ln, dvo);
+        dma_block<NW, !GATHERS>(pr.Q, pr.dO, row0, i * KB, len, sX + (i % NSTAGE) * STAGE_BYTES,
+                                sY + (i % NSTAGE) * STAGE_BYTES, w, ln, dvo, pr.once, 0);
     };
     issue(0);
     if (KB < len) issue(1);
@@ -1968,6 +1971,8 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
     __syncthreads();   // the walk's stages take the memory in front
 }
 
+// (STREAM in two instances: short ones lose 1.5 % to the test of pr.once at every load)
+template <bool STREAM>
 __global__ __launch_bounds__(512) void attn_fwd_direct_mfma_kernel(Geom g, AttnProblem pr)
 {
     extern __shared__ __attribute__((aligned(256))) char smem[];
@@ -1984,8 +1989,8 @@ __global__ __launch_bounds__(512) void attn_fwd_direct_mfma_kernel(Geom g, AttnP
     gather_state(pr.Bk, pr.Cv, ((size_t)grp * g.N + from) * ROWB, tok0 - from, 1.f, nullptr, base, false, smem, tid, w);
     const bool first = !g.W || tok0 == slot0;
     const int rb = w < 4 ? w : 11 - w;   // waves w and w+4 share a SIMD: row blocks s and 7-s
-    if (rb < 4) skew_walk<false, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
-    else skew_walk<true, false, false, true>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
+    if (rb < 4) skew_walk<false, false, false, true, STREAM>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
+    else skew_walk<true, false, false, true, STREAM>(g, pr, smem, tid, w, rb, grp, s, tok0, len, nullptr, ps, true, first);
 }
 
 // The same two with scalar decay: the three backward problems have a workgroup each, and the anti-causal ones (first in the
@@ -2110,6 +2115,11 @@ hipError_t launch_attn_skew(const Geom& g, const AttnProblem& p0, const AttnProb
 
 // Internal chunk of the fused pass: 256 rows (eight waves) unless no slot is longer than 128.
 bool wide_chunks(const Geom& g) { return g.L > 128; }
+
+// Whether two tensors of G x N rows fill the 256 MB cache: nothing of them is left there when they are read again, and loads
+// that are marked so (non-temporal) are faster, 5.6 instead of 5.2 TB/s in a walk.  Smaller ones do stay: forward, us, plain | marked,
+// tensors of 17 MB 41.7 | 43.3, 67 MB (64 x 4 096) 73.9 | 80.6, 98 MB 116.6 | 117.0, 134 MB (128 x 4 096) 125.6 | 124.2, 268 MB (256 x 4 096) 216 | 187.
+int streams_past_caches(const Geom& g) { return 2.0 * (double)g.G * (double)g.N * ROWB >= 256e6; }
 
 AttnProblem make_problem(const void* A, const void* Bk, const void* Cv, const float* state, int user_state,
                          void* out, int transpose_state, int anti)
@@ -2633,7 +2643,8 @@ hipError_t launch_attn_decay(const Geom& g, const AttnProblem& p0, const AttnPro
 hipError_t launch_attn_fwd_mfma(const Geom& g, const void* Q, const void* K, const void* V,
                                 const float* P, void* O, hipStream_t st)
 {
-    const AttnProblem p = make_problem(Q, K, V, P, 1, O, 0, 0);
+    AttnProblem p = make_problem(Q, K, V, P, 1, O, 0, 0);
+    p.once = streams_past_caches(g);
     if (g.decay) return launch_attn_decay(g, p, p, p, 1, st);
     if (wide_chunks(g)) return launch_attn_skew<false>(g, p, p, p, 1, st);
     return launch_attn_C<128>(g, p, p, p, 1, st);
@@ -2650,6 +2661,7 @@ hipError_t launch_attn_fwd_emit_mfma(const Geom& g, const void* Q, const void* K
     constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
     AttnProblem p = make_problem(Q, K, V, g.lone_slots ? nullptr : P, 1, O, 0, 0);
     p.emit = P;
+    p.once = streams_past_caches(g);
     auto kern = g.decay ? attn_fwd_emit_mfma_kernel<true> : attn_fwd_emit_mfma_kernel<false>;
     hipError_t e = g.decay ? allow_dynamic_lds<attn_fwd_emit_mfma_kernel<true>>(smem)
                            : allow_dynamic_lds<attn_fwd_emit_mfma_kernel<false>>(smem);
@@ -2664,9 +2676,11 @@ hipError_t launch_attn_fwd_direct_mfma(const Geom& g, const void* Q, const void*
     constexpr int smem = 2 * NSTAGE * STAGE_BYTES + D * ROWB + 8 * 4096;
     AttnProblem p = make_problem(Q, K, V, state, 1, O, 0, 0);
     p.emit = emit;
-    hipError_t e = g.decay ? allow_dynamic_lds<attn_decay_fwd_direct_kernel>(smem) : allow_dynamic_lds<attn_fwd_direct_mfma_kernel>(smem);
+    p.once = streams_past_caches(g);
+    hipError_t e = g.decay ? allow_dynamic_lds<attn_decay_fwd_direct_kernel>(smem)
+                   : p.once ? allow_dynamic_lds<attn_fwd_direct_mfma_kernel<true>>(smem) : allow_dynamic_lds<attn_fwd_direct_mfma_kernel<false>>(smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((g.decay ? attn_decay_fwd_direct_kernel : attn_fwd_direct_mfma_kernel), dim3((unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, p);
+    hipLaunchKernelGGL((g.decay ? attn_decay_fwd_direct_kernel : p.once ? attn_fwd_direct_mfma_kernel<true> : attn_fwd_direct_mfma_kernel<false>), dim3((unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, p);
     return hipGetLastError();
 }
 
@@ -2684,7 +2698,7 @@ hipError_t launch_attn_bwd_direct_mfma(const Geom& g, const void* Q, const void*
         return hipGetLastError();
     }
     const PairProblem pp = {static_cast<const char*>(Q), static_cast<const char*>(dO), static_cast<const char*>(K),
-                            static_cast<const char*>(V), dR, static_cast<char*>(dV), static_cast<char*>(dK), nullptr};
+                            static_cast<const char*>(V), dR, static_cast<char*>(dV), static_cast<char*>(dK), nullptr, 0};
     hipError_t e = allow_dynamic_lds<attn_bwd_direct_mfma_kernel>(smem);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(attn_bwd_direct_mfma_kernel, dim3(2u * (unsigned)g.T_s * (unsigned)g.G), dim3(512), smem, st, g, pq, pp,
@@ -2721,7 +2735,7 @@ hipError_t launch_attn_bwd_mfma(const Geom& g, const void* Q, const void* K, con
         }
         const PairProblem pp = {static_cast<const char*>(Q), static_cast<const char*>(dO),
                                 static_cast<const char*>(K), static_cast<const char*>(V), const_cast<float*>(dR),
-                                static_cast<char*>(dV), static_cast<char*>(dK), pace};
+                                static_cast<char*>(dV), static_cast<char*>(dK), pace, streams_past_caches(g)};
         dim3 grid(2u * ((units + 7u) & ~7u)), block(512);
         hipLaunchKernelGGL(attn_bwd_pair_mfma_kernel, grid, block, smem, st, g, pq2, pp);
         return hipGetLastError();

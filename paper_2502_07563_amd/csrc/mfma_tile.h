@@ -140,6 +140,14 @@ __device__ __forceinline__ void dma16_nt(const char* sbase, uint32_t voff, uint3
 {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_base), "v"(voff), "s"(sbase) : "memory", "m0");
 }
+
+// ... marked so if `nt` (uniform).  The branch lies inside the statement: one that the compiler sees, at every load, cost a walk 2 %.
+__device__ __forceinline__ void dma16_if_nt(const char* sbase, uint32_t voff, uint32_t lds_base, int nt)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_cmp_lg_u32 %3, 0\n\ts_cbranch_scc1 .Lnt%=\n\t"
+                 "global_load_lds_dwordx4 %1, %2\n\ts_branch .Ldone%=\n.Lnt%=:\n\tglobal_load_lds_dwordx4 %1, %2 nt\n.Ldone%=:"
+                 ::"s"(lds_base), "v"(voff), "s"(sbase), "s"(nt) : "memory", "m0", "scc");
+}
 #pragma clang diagnostic pop
 
 // Byte offset, inside a block of rows that starts at a multiple of 16, of the 16 bytes that lane
@@ -153,11 +161,12 @@ __device__ __forceinline__ uint32_t dma_lane_off(int k, int lane)
 // Issue the loads of one 64-token block (rows tok .. tok+63 of the slot) of X and Y into the
 // stage tiles tx, ty; dvo[u] = dma_lane_off(w * IPW + u, lane), computed once per kernel.
 // Rows past the slot's end are fetched from its last row (always in bounds) and zeroed
-// afterwards by zero_tail_rows().
-template <int NW, bool STREAM = false>
+// afterwards by zero_tail_rows().  MARK: x_nt, y_nt (uniform) say which
+// tensor's loads are marked non-temporal.
+template <int NW, bool MARK = false>
 __device__ __forceinline__ void dma_block(const char* X, const char* Y, size_t row0_bytes, int tok,
                                           int len, char* tx, char* ty, int w, int lane,
-                                          const uint32_t (&dvo)[16 / NW])
+                                          const uint32_t (&dvo)[16 / NW], int x_nt = 0, int y_nt = 0)
 {
     constexpr int IPW = 16 / NW;   // wave instructions per tensor per stage
     const size_t blk = row0_bytes + (size_t)tok * ROWB;
@@ -170,9 +179,9 @@ __device__ __forceinline__ void dma_block(const char* X, const char* Y, size_t r
             const int r = 4 * k + (lane >> 4);
             voff = (uint32_t)(min(r, len - 1 - tok) * ROWB + (int)(voff & (ROWB - 1)));
         }
-        if (STREAM) {
-            dma16_nt(X + blk, voff, lds_addr_of(tx + 4 * k * ROWB));
-            dma16_nt(Y + blk, voff, lds_addr_of(ty + 4 * k * ROWB));
+        if (MARK) {
+            dma16_if_nt(X + blk, voff, lds_addr_of(tx + 4 * k * ROWB), x_nt);
+            dma16_if_nt(Y + blk, voff, lds_addr_of(ty + 4 * k * ROWB), y_nt);
         } else {
             dma16(X + blk, voff, lds_addr_of(tx + 4 * k * ROWB));
             dma16(Y + blk, voff, lds_addr_of(ty + 4 * k * ROWB));

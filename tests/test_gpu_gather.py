@@ -1,0 +1,78 @@
+"""Linear attention, bf16 heads of 128: walks that gather the state they start from, with as many rows before (and, in the backward,
+behind) them as fill the ring of stages partly, exactly and several times, with ragged last stages and sums of 512 rows on both
+sides; and tensors that fill the last cache, whose rows are then loaded past it.  Against the definition in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_07563_amd import binding as bd
+
+
+def _problem(G, N, L, lam=None, device="cuda"):
+    f = None if lam is None else np.full(G, lam, np.float32)
+    return bd.Problem(1, G, N, 128, 64, L, "bf16", decay=f, device=device)
+
+
+def _want(x, lam):
+    q, k, v, w = (t.double() for t in x)
+    i = torch.arange(q.shape[0], device="cuda")
+    m = torch.tril(lam ** (i[:, None] - i[None]).clamp(min=0).double())
+    s, g = m * (q @ k.T.contiguous()), m * (w @ v.T.contiguous())
+    return s @ v, g @ k, g.T.contiguous() @ q, s.T.contiguous() @ w
+
+
+def _check(G, N, L, lam, heads, rows):
+    p = _problem(G, N, L, lam)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    x = [torch.randn(1, G, N, 128, generator=gen, device="cuda").mul_(128 ** -0.5).to(torch.bfloat16) for _ in range(4)]
+    O, P = bd.forward(p, *x[:3])
+    alone = torch.empty_like(O)
+    bd.lasp2_attn_fwd(p, *x[:3], P, alone)
+    got = (O,) + bd.backward(p, *x, P)[:3]
+    for h in heads:
+        want = _want([t[0, h] for t in x], 1.0 if lam is None else lam)
+        for name, a, b in list(zip(("O", "dQ", "dK", "dV"), got, want)) + [("attn_fwd", alone, want[0])]:
+            a = a[0, h].double()
+            # results, scores, the state's snapshot and, with decay, the weighted rows are rounded to bf16 (2^-9 each at most,
+            # half of that in the mean); every 64 rows on their own, so that a wrong block does not drown in the others
+            for r in range(0, N, rows):
+                err = ((a[r:r + rows] - b[r:r + rows]).norm() / b[r:r + rows].norm()).item()
+                assert err <= 2.0 ** -7, (name, G, N, L, lam, h, r, err)
+
+
+# rows of the sequence; walks of 128 or 256 gather 0, 64 .. 2 560 rows from its start and to its end
+LENGTHS = (129, 191, 320, 321, 383, 449, 512, 575, 769, 1024, 1025, 1087, 1531, 2111, 2700)
+
+
+def test_the_lengths_gather():
+    """(256 CUs assumed where no device answers)"""
+    for N in LENGTHS[2:]:
+        assert bd.lasp2_walk_plan(_problem(2, N, 4096, device="cpu"), "forward")[1] == "gather", N
+    assert any(bd.lasp2_walk_plan(_problem(2, N, 4096, device="cpu"), "attn_bwd")[1] == "gather" for N in LENGTHS)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lam", [None, 0.99])
+@pytest.mark.parametrize("N", LENGTHS)
+def test_rows_gathered(N, lam):
+    for L in (64, 256, 4096):
+        _check(2, N, L, lam, (0, 1), 64)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("G,N,L,lam", [(128, 4096, 512, None), (2048, 250, 256, None), (128, 4096, 512, 0.99), (16, 32768, 4096, None)])
+def test_tensors_that_fill_the_cache(G, N, L, lam):
+    """Two tensors of 128 MiB.  (Long sequences: the first walks' rows only, by the rows that follow them.)"""
+    if N <= 4096:
+        _check(G, N, L, lam, (0, 77, G - 1), 64)
+        return
+    p, n = _problem(G, N, L, lam), 4096 + 300
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    x = [torch.randn(1, G, N, 128, generator=gen, device="cuda").mul_(128 ** -0.5).to(torch.bfloat16) for _ in range(4)]
+    O, P = bd.forward(p, *x[:3])
+    dQ = bd.backward(p, *x, P)[0]
+    for h in (0, G - 1):
+        want = _want([t[0, h, :n] for t in x], 1.0)
+        for name, a, b in (("O", O, want[0]), ("dQ", dQ, want[1])):
+            err = ((a[0, h, :n].double() - b).norm() / b.norm()).item()
+            assert err <= 2.0 ** -7, (name, h, err)
