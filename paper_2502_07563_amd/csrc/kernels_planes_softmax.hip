@@ -8,7 +8,13 @@
 // stand.  The waves of a workgroup are QW row tiles times KW shares of the partner rows, whose results are
 // merged at the end: 4 x 1 when such workgroups fill the device; 2 x 4 otherwise, where the longest causal
 // row sets the time.  The two row tiles are then mirrored (tile i with the i-th from the end), and a SIMD
-// has one wave of each, so that every workgroup has the same number of tiles.
+// has one wave of each, so that every workgroup has the same number of tiles.  In the forward and in dQ the shorter tile's waves,
+// once they are done, fill the stages for the longer one's (HELP): filling takes as long as a tile's scores and products, and a
+// workgroup of the longest and the shortest tile is nearly all such stages.  (A middle one has half as many stages with two tiles
+// each and ends first: the longest row still sets the time.)  A stage of theirs then takes 5200 clocks instead of 6700; forward,
+// us, causal: fp32 8 x 2003 x 64 52 -> 50, 8 x 1500 x 128 108 -> 79, 4 x 4000 x 16 49 -> 33; bf16 16 x 2500 x 64 88 -> 70; dQ of the first
+// 59 -> 55.  dK and dV read both their partners in both of their products, and own rows fill what LDS there is: not there.
+// Masks are applied to tiles at the border alone.
 // Bounds: vector instructions - in fp32 the splits of the stages (five and a half per element) and of the scores -
 // and the matrix products beside them (six bf16 ones per fp32 one).
 #include "planes.h"
@@ -25,6 +31,7 @@ struct SmCfg {
     static constexpr int NP = planes_of<T>::n, DP = D < 32 ? 32 : D, NT = DP / 32, KS = D / 16, QW = QW_, KW = KW_, THR = 64 * QW * KW;
     static constexpr int ROWS = 32 * KW < 64 && !(NP == 3 && D == 128) ? 64 : 32 * KW;   // partner rows per stage
     typedef PairStage<T, D, DP, ROWS, THR> Stage;
+    static constexpr bool help = QW == 2 && ROWS == 32 * KW;   // waves whose tile is done fill the stages
     static constexpr bool own_lds = NP == 3 && D == 64 && KW == 4;   // dK, dV: own rows in LDS
     static constexpr int MERGE = (KW - 1) * QW * 64 * 4;      // bytes per merged register
     static constexpr int lds(int merged, int extra)            // stage, or the merge of `merged` registers per lane
@@ -49,6 +56,15 @@ __device__ __forceinline__ void wg_rows(int bx, int rows, bool mirrored, int& r0
     const bool m = QW == 2 && mirrored;
     r0 = m ? 32 * bx : 32 * QW * bx;
     r1 = min(rows, m ? 32 * ((rows + 31) / 32 - bx) : 32 * QW * (bx + 1));
+}
+
+// Mirrored tiles of one causal sequence: where the stages end that the shorter one (the second) takes part in, and one more.
+template <int QW>
+__device__ __forceinline__ int shared_end(const Geom& g, int bx, int klo, int khi, int rows)
+{
+    const int wr = tile_row<QW>(bx, 1, g.qn, true);
+    const int end = wr < g.qn ? g.q0 + min(wr + 32, g.qn) : klo;
+    return min(khi, klo + (max(end - klo, 0) + 2 * rows - 1) / rows * rows);
 }
 
 // Document of token i: [lo, hi).
@@ -357,8 +373,9 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_pl
     typedef SmCfg<T, D, QW, KW> Cf;
     typedef typename Cf::Stage Stage;
     constexpr int NP = Cf::NP, DP = Cf::DP, NT = Cf::NT, KS = Cf::KS, ROWS = Cf::ROWS;
+    constexpr bool HELP = Cf::help;
     extern __shared__ __align__(16) char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int qw = w / KW, kw = w % KW, grp = blockIdx.y;
     const bool mirrored = causal && g.n_seqs == 0;
     // Order of the workgroups within a group.  Mirrored ones are alike.  Else documents start with their last rows,
@@ -374,15 +391,17 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_pl
     int lo = 0, hi = 0;
     if (valid) keys_of(g, g.q0 + row, causal, lo, hi);
     // the wave's and the workgroup's key ranges: both ends grow with the query
-    int wlo = 0, whi = 0, klo, khi, t;
+    int wlo = 0, whi = 0, alo = 0, ahi = 0, klo, khi, t;   // [alo, ahi): the keys that every row has
     if (wr < g.qn) {
-        keys_of(g, g.q0 + wr, causal, wlo, t);
-        keys_of(g, g.q0 + min(wr + 31, g.qn - 1), causal, t, whi);
+        keys_of(g, g.q0 + wr, causal, wlo, ahi);
+        keys_of(g, g.q0 + min(wr + 31, g.qn - 1), causal, alo, whi);
     }
     keys_of(g, g.q0 + r0, causal, klo, t);
     keys_of(g, g.q0 + r1 - 1, causal, t, khi);
 
     const unsigned span = (unsigned)max(hi - lo, 0);   // a partner row x counts if (unsigned)(x - lo) < span
+    Stage st;
+    st.fetch(K + kbase, V + kbase, klo, khi, tid);
     bf16x8 q[KS][NP];
     load_rows<T, D>(q, Q + qbase + (size_t)row * D, valid, h);
     const float c = rsqrtf((float)D) * kLog2e;
@@ -390,13 +409,37 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_pl
     f32x16 acc[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[nt] = zero16();
+    // scores of the 32 keys at t0 -> probabilities, row statistics
+    auto softmax = [&](f32x16& s, int t0) __attribute__((always_inline)) {
+        if (t0 < alo || t0 + 32 > ahi) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s[v] = (unsigned)(t0 + 4 * h - lo + acc_row(v)) < span ? s[v] : -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+        mx = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)) * c);
+        const float mu = mx == -INFINITY ? 0.f : mx;
+        const float alpha = __builtin_amdgcn_exp2f(m - mu);
+        m = mx;
+        float ps = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c, -mu));
+            ps += s[v];
+        }
+        l = fmaf(l, alpha, ps);
+        if (__any(alpha != 1.f)) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[nt] *= alpha;
+        }
+    };
 
-    Stage st;
-    st.fetch(K + kbase, V + kbase, klo, khi, tid);
-    for (int k0 = klo; k0 < khi; k0 += ROWS) {
+    const int kshared = HELP && mirrored ? shared_end<QW>(g, bx, klo, khi, ROWS) : khi;
+    for (int k0 = klo; k0 < kshared; k0 += ROWS) {
         if (k0 > klo) __syncthreads();
         st.put(smem, tid);
-        if (k0 + ROWS < khi) st.fetch(K + kbase, V + kbase, k0 + ROWS, khi, tid);
+        if (k0 + ROWS < kshared) st.fetch(K + kbase, V + kbase, k0 + ROWS, khi, tid);
         __syncthreads();
 #pragma unroll 1
         for (int u = kw; u < ROWS / 32; u += KW) {
@@ -404,28 +447,51 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_fwd_pl
             if (t0 >= whi || t0 + 32 <= wlo) continue;
             const char* kt = smem + u * 64 * DP;
             f32x16 s = scores<DP, KS, NP>(kt, Stage::PLANE, q, l32, h);
-            float mx = -INFINITY;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                s[v] = (unsigned)(t0 + 4 * h - lo + acc_row(v)) < span ? s[v] * c : -INFINITY;
-                mx = fmaxf(mx, s[v]);
-            }
-            mx = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)));
-            const float mu = mx == -INFINITY ? 0.f : mx;
-            const float alpha = __builtin_amdgcn_exp2f(m - mu);
-            m = mx;
-            float ps = 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                s[v] = __builtin_amdgcn_exp2f(s[v] - mu);
-                ps += s[v];
-            }
-            l = fmaf(l, alpha, ps);
-            if (__any(alpha != 1.f)) {
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) acc[nt] *= alpha;
-            }
+            softmax(s, t0);
             accumulate<DP, NP>(acc, kt + Stage::TENSOR, Stage::PLANE, s, lane);
+        }
+    }
+    if constexpr (HELP) {
+        // The shorter tile is done (a stage ago): its waves fill the stages from here on.  V has two places, and half of the next one
+        // is put beside the scores, the other half and K beside the products, which take twice as long.  (V whole beside the scores,
+        // in one place: they waited for it, 5800 clocks a stage.)
+        if (kshared < khi) {
+            int vbuf = 2 * Stage::TENSOR;
+            if (qw == 0) {
+                __syncthreads();
+                for (int k0 = kshared; k0 < khi; k0 += ROWS) {
+                    const int t0 = k0 + 32 * kw;
+                    f32x16 s;
+                    __syncthreads();   // K and V are there
+                    if (t0 < whi) s = scores<DP, KS, NP>(smem + kw * 64 * DP, Stage::PLANE, q, l32, h);
+                    __syncthreads();   // K has been read
+                    if (t0 < whi) {
+                        softmax(s, t0);
+                        accumulate<DP, NP>(acc, smem + kw * 64 * DP + vbuf, Stage::PLANE, s, lane);
+                    }
+                    vbuf = 3 * Stage::TENSOR - vbuf;
+                }
+            } else {
+                typedef PairStage<T, D, DP, ROWS, 64 * KW> Half;
+                const int t = tid - 64 * KW;
+                Half hs;
+                Half::fetch_one(hs.x, K + kbase, kshared, khi, t);
+                Half::fetch_one(hs.y, V + kbase, kshared, khi, t);
+                Half::put_one(hs.y, smem + vbuf, t);
+                Half::fetch_one(hs.y, V + kbase, kshared + ROWS, khi, t);
+                __syncthreads();
+                Half::put_one(hs.x, smem, t);
+                for (int k0 = kshared; k0 < khi; k0 += ROWS) {
+                    Half::fetch_one(hs.x, K + kbase, k0 + ROWS, khi, t);   // (after the last stage too: see fetch_one)
+                    vbuf = 3 * Stage::TENSOR - vbuf;
+                    __syncthreads();
+                    Half::template put_one<0, Half::NU / 2>(hs.y, smem + vbuf, t);
+                    __syncthreads();
+                    Half::template put_one<Half::NU / 2, Half::NU>(hs.y, smem + vbuf, t);
+                    Half::fetch_one(hs.y, V + kbase, k0 + 2 * ROWS, khi, t);
+                    Half::put_one(hs.x, smem, t);
+                }
+            }
         }
     }
     l += __shfl_xor(l, 32, 64);
@@ -479,8 +545,9 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
     typedef SmCfg<T, D, QW, KW> Cf;
     typedef typename Cf::Stage Stage;
     constexpr int NP = Cf::NP, DP = Cf::DP, NT = Cf::NT, KS = Cf::KS, ROWS = Cf::ROWS;
+    constexpr bool HELP = Cf::help;
     extern __shared__ __align__(16) char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int qw = w / KW, kw = w % KW, grp = blockIdx.y;
     const bool mirrored = causal && g.n_seqs == 0;
     const int bx = mirrored ? blockIdx.x : gridDim.x - 1 - blockIdx.x;   // as in the forward
@@ -489,7 +556,7 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
     wg_rows<QW>(bx, g.qn, mirrored, r0, r1);
     const size_t kbase = (size_t)grp * (size_t)g.N * D, qbase = (size_t)grp * (size_t)g.qn * D;
     const bool valid = row < g.qn;
-    int lo = 0, hi = 0, wlo = 0, whi = 0, klo, khi, t;
+    int lo = 0, hi = 0, wlo = 0, whi = 0, alo = 0, ahi = 0, klo, khi, t;   // [alo, ahi): the keys that every row has
     float lse2 = 0.f, dlt = 0.f;
     if (valid) {
         keys_of(g, g.q0 + row, causal, lo, hi);
@@ -497,13 +564,15 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
         dlt = delta[(size_t)grp * g.qn + row];
     }
     if (wr < g.qn) {
-        keys_of(g, g.q0 + wr, causal, wlo, t);
-        keys_of(g, g.q0 + min(wr + 31, g.qn - 1), causal, t, whi);
+        keys_of(g, g.q0 + wr, causal, wlo, ahi);
+        keys_of(g, g.q0 + min(wr + 31, g.qn - 1), causal, alo, whi);
     }
     keys_of(g, g.q0 + r0, causal, klo, t);
     keys_of(g, g.q0 + r1 - 1, causal, t, khi);
 
     const unsigned span = (unsigned)max(hi - lo, 0);
+    Stage st;
+    st.fetch(K + kbase, V + kbase, klo, khi, tid);
     bf16x8 q[KS][NP], d[KS][NP];
     load_rows<T, D>(q, Q + qbase + (size_t)row * D, valid, h);
     load_rows<T, D>(d, dO + qbase + (size_t)row * D, valid, h);
@@ -511,13 +580,21 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
     f32x16 acc[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[nt] = zero16();
+    // scores and dO.v of the 32 keys at t0 -> dS
+    auto gradient = [&](f32x16& s, const f32x16& dp, int t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c, -lse2)) * (dp[v] - dlt);
+        if (t0 < alo || t0 + 32 > ahi) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s[v] = (unsigned)(t0 + 4 * h - lo + acc_row(v)) < span ? s[v] : 0.f;
+        }
+    };
 
-    Stage st;
-    st.fetch(K + kbase, V + kbase, klo, khi, tid);
-    for (int k0 = klo; k0 < khi; k0 += ROWS) {
+    const int kshared = HELP && mirrored ? shared_end<QW>(g, bx, klo, khi, ROWS) : khi;
+    for (int k0 = klo; k0 < kshared; k0 += ROWS) {
         if (k0 > klo) __syncthreads();
         st.put(smem, tid);
-        if (k0 + ROWS < khi) st.fetch(K + kbase, V + kbase, k0 + ROWS, khi, tid);
+        if (k0 + ROWS < kshared) st.fetch(K + kbase, V + kbase, k0 + ROWS, khi, tid);
         __syncthreads();
 #pragma unroll 1
         for (int u = kw; u < ROWS / 32; u += KW) {
@@ -526,12 +603,52 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
             const char* kt = smem + u * 64 * DP;
             f32x16 s = scores<DP, KS, NP>(kt, Stage::PLANE, q, l32, h);
             const f32x16 dp = scores<DP, KS, NP>(kt + Stage::TENSOR, Stage::PLANE, d, l32, h);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(s[v], c, -lse2)), ds = p * (dp[v] - dlt);
-                s[v] = (unsigned)(t0 + 4 * h - lo + acc_row(v)) < span ? ds : 0.f;
-            }
+            gradient(s, dp, t0);
             accumulate<DP, NP>(acc, kt, Stage::PLANE, s, lane);
+        }
+    }
+    if constexpr (HELP) {
+        // (as in the forward; here K has two places, as it is what the second product reads)
+        if (kshared < khi) {
+            int kbuf = 2 * Stage::TENSOR;
+            if (qw == 0) {
+                __syncthreads();
+                for (int k0 = kshared; k0 < khi; k0 += ROWS) {
+                    const int t0 = k0 + 32 * kw;
+                    const char* kt = smem + kw * 64 * DP;
+                    f32x16 s, dp;
+                    __syncthreads();   // K and V are there
+                    if (t0 < whi) {
+                        s = scores<DP, KS, NP>(kt + kbuf, Stage::PLANE, q, l32, h);
+                        dp = scores<DP, KS, NP>(kt + Stage::TENSOR, Stage::PLANE, d, l32, h);
+                    }
+                    __syncthreads();   // V has been read
+                    if (t0 < whi) {
+                        gradient(s, dp, t0);
+                        accumulate<DP, NP>(acc, kt + kbuf, Stage::PLANE, s, lane);
+                    }
+                    kbuf = 2 * Stage::TENSOR - kbuf;
+                }
+            } else {
+                typedef PairStage<T, D, DP, ROWS, 64 * KW> Half;
+                const int t = tid - 64 * KW;
+                Half hs;
+                Half::fetch_one(hs.x, K + kbase, kshared, khi, t);
+                Half::fetch_one(hs.y, V + kbase, kshared, khi, t);
+                Half::put_one(hs.x, smem + kbuf, t);
+                Half::fetch_one(hs.x, K + kbase, kshared + ROWS, khi, t);
+                __syncthreads();
+                Half::put_one(hs.y, smem + Half::TENSOR, t);
+                for (int k0 = kshared; k0 < khi; k0 += ROWS) {
+                    Half::fetch_one(hs.y, V + kbase, k0 + ROWS, khi, t);
+                    kbuf = 2 * Stage::TENSOR - kbuf;
+                    __syncthreads();
+                    Half::put_one(hs.x, smem + kbuf, t);
+                    Half::fetch_one(hs.x, K + kbase, k0 + 2 * ROWS, khi, t);
+                    __syncthreads();
+                    Half::put_one(hs.y, smem + Half::TENSOR, t);
+                }
+            }
         }
     }
     if constexpr (KW > 1) {
@@ -556,7 +673,7 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
     }
     const int ln = lane_again(), first = __builtin_amdgcn_readfirstlane(row);
     uint32_t odd = odd_rows<D>(acc, 0.f, valid, h);
-    if (valid && !((odd >> (ln & 31)) & 1u)) store_row<T, D>(dQ + qbase + (size_t)row * D, acc, scale, h);
+    if (valid && !((odd >> (ln & 31)) & 1u)) store_row<T, D>(dQ + qbase + (size_t)(wr + (ln & 31)) * D, acc, scale, ln >> 5);
     for (; odd; odd &= odd - 1) {
         const int r = first + __builtin_ctz(odd);
         const size_t o = qbase + (size_t)r * D, i = (size_t)grp * g.qn + r;
@@ -567,9 +684,9 @@ __global__ __launch_bounds__(64 * QW * KW, D == 128 ? 1 : 2) void softmax_bwd_dq
 
 // dV = sum_i P_i dO_i and dK = scale * sum_i dS_i q_i: a key per lane, the share's queries pass through LDS with
 // their log-sum-exp (base 2) and delta.  fp32, d = 64: with two accumulators the own rows' planes (96 registers)
-// do not fit beside the rest at two waves per SIMD.  Eight waves keep them in LDS (158 -> 84 us at
+// do not fit beside the rest at two waves per SIMD.  Eight waves keep them in LDS (158 -> 76 us at
 // 8 x 2003, against spills of 72 registers), four run at one wave per SIMD.  fp32, d = 128, spills at one wave per SIMD too
-// (111 registers with two row tiles, 62 with four); against scalar products, 16 x 4096 causal, backward: 16.5 -> 3.1 ms.
+// (107 registers with two row tiles, 55 with four); against scalar products, 16 x 4096 causal, backward: 16.5 -> 3.1 ms.
 template <typename T, int D, int QW, int KW>
 __global__ __launch_bounds__(64 * QW * KW, D == 128 || (D == 64 && planes_of<T>::n == 3 && KW == 1) ? 1 : 2)
 void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
@@ -583,7 +700,7 @@ void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __r
     constexpr bool OWN_LDS = Cf::own_lds;
     constexpr int OPLANE = 64 * DP, OTENSOR = NP * OPLANE;        // 32 own rows
     float* stat = reinterpret_cast<float*>(smem + Stage::BYTES);   // [2][ROWS]
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int qw = w / KW, kw = w % KW, grp = blockIdx.y;
     const bool mirrored = causal && g.n_seqs == 0;
     const int wr = tile_row<QW>(blockIdx.x, qw, g.N, mirrored), row = wr + l32;   // (causal: the first keys have the most queries)
@@ -591,11 +708,11 @@ void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __r
     wg_rows<QW>(blockIdx.x, g.N, mirrored, r0, r1);
     const size_t kbase = (size_t)grp * (size_t)g.N * D, qbase = (size_t)grp * (size_t)g.qn * D;
     const bool valid = row < g.N;
-    int lo = 0, hi = 0, wlo = 0, whi = 0, ilo, ihi, t;
+    int lo = 0, hi = 0, wlo = 0, whi = 0, alo = 0, ahi = 0, ilo, ihi, t;   // [alo, ahi): the queries that every row has
     if (valid) queries_of(g, row, causal, lo, hi);
     if (wr < g.N) {
-        queries_of(g, wr, causal, wlo, t);
-        queries_of(g, min(wr + 31, g.N - 1), causal, t, whi);
+        queries_of(g, wr, causal, wlo, ahi);
+        queries_of(g, min(wr + 31, g.N - 1), causal, alo, whi);
     }
     queries_of(g, r0, causal, ilo, t);
     queries_of(g, r1 - 1, causal, t, ihi);
@@ -662,10 +779,16 @@ void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __r
                 const f32x4 dl = *reinterpret_cast<const f32x4*>(stat + ROWS + 32 * u + acc_row(v) + 4 * h);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const bool keep = (unsigned)(t0 + 4 * h - lo + acc_row(v + e)) < span;
-                    const float p = __builtin_amdgcn_exp2f(fmaf(s[v + e], c, -ls[e])), ds = p * (dp[v + e] - dl[e]);
-                    s[v + e] = keep ? p : 0.f;
-                    dp[v + e] = keep ? ds : 0.f;
+                    s[v + e] = __builtin_amdgcn_exp2f(fmaf(s[v + e], c, -ls[e]));
+                    dp[v + e] = s[v + e] * (dp[v + e] - dl[e]);
+                }
+            }
+            if (t0 < alo || t0 + 32 > ahi) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const bool keep = (unsigned)(t0 + 4 * h - lo + acc_row(v)) < span;
+                    s[v] = keep ? s[v] : 0.f;
+                    dp[v] = keep ? dp[v] : 0.f;
                 }
             }
             accumulate<DP, NP>(av, qt + Stage::TENSOR, Stage::PLANE, s, lane);
@@ -698,10 +821,11 @@ void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __r
                 }
         }
     }
-    const int ln = lane_again(), first = __builtin_amdgcn_readfirstlane(row);
-    const uint32_t oddk = odd_rows<D>(ak, 0.f, valid, h), oddv = odd_rows<D>(av, 0.f, valid, h);
-    if (valid && !((oddk >> (ln & 31)) & 1u)) store_row<T, D>(dK + kbase + (size_t)row * D, ak, scale, h);
-    if (valid && !((oddv >> (ln & 31)) & 1u)) store_row<T, D>(dV + kbase + (size_t)row * D, av, 1.f, h);
+    const int ln = lane_again(), first = wr, own_row = wr + (ln & 31);   // (row and what hangs on it are not kept through the walk)
+    const bool there = own_row < g.N;
+    const uint32_t oddk = odd_rows<D>(ak, 0.f, there, ln >> 5), oddv = odd_rows<D>(av, 0.f, there, ln >> 5);
+    if (there && !((oddk >> (ln & 31)) & 1u)) store_row<T, D>(dK + kbase + (size_t)own_row * D, ak, scale, ln >> 5);
+    if (there && !((oddv >> (ln & 31)) & 1u)) store_row<T, D>(dV + kbase + (size_t)own_row * D, av, 1.f, ln >> 5);
     for (uint32_t odd = oddk | oddv; odd; odd &= odd - 1) {
         const int b = __builtin_ctz(odd), r = first + b;
         const size_t o = kbase + (size_t)r * D, i = (size_t)grp * g.qn;
@@ -713,14 +837,14 @@ void softmax_bwd_dkv_planes_kernel(Geom g, const T* __restrict__ Q, const T* __r
 
 // Workgroups of four row tiles, unless they fill less than the device twice over: then two tiles and four (fp32
 // with d = 128, whose rows take too many registers for eight waves: two) shares of the partner rows.
-// (fp32, 8 x 2003 x 64, causal, forward: 1 x 4 115 us, 2 x 4 mirrored 57 us.)
+// (fp32, 8 x 2003 x 64, causal, forward: 1 x 4 115 us, 2 x 4 mirrored 50 us.)
 bool split_partners(const Geom& g, int rows) { return (int64_t)g.G * ((rows + 127) / 128) < 2 * (int64_t)cu_count(); }
 
 template <typename T, int D, int QW, int KW>
 hipError_t fwd_TD(const Geom& g, const T* Q, const T* K, const T* V, T* O, float* LSE, int causal, hipStream_t st)
 {
     typedef SmCfg<T, D, QW, KW> Cf;
-    constexpr int lds = Cf::lds(16 * Cf::NT + 2, 0), R = 32 * Cf::QW;
+    constexpr int lds = Cf::lds(16 * Cf::NT + 2, Cf::help ? Cf::Stage::TENSOR : 0), R = 32 * Cf::QW;
     hipError_t e = allow_dynamic_lds<softmax_fwd_planes_kernel<T, D, QW, KW>>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((softmax_fwd_planes_kernel<T, D, QW, KW>), dim3((g.qn + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K, V,
@@ -733,7 +857,7 @@ hipError_t dq_TD(const Geom& g, const T* Q, const T* K, const T* V, const T* dO,
                  int causal, hipStream_t st)
 {
     typedef SmCfg<T, D, QW, KW> Cf;
-    constexpr int lds = Cf::lds(16 * Cf::NT, 0), R = 32 * Cf::QW;
+    constexpr int lds = Cf::lds(16 * Cf::NT, Cf::help ? Cf::Stage::TENSOR : 0), R = 32 * Cf::QW;
     hipError_t e = allow_dynamic_lds<softmax_bwd_dq_planes_kernel<T, D, QW, KW>>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((softmax_bwd_dq_planes_kernel<T, D, QW, KW>), dim3((g.qn + R - 1) / R, g.G), dim3(Cf::THR), lds, st, g, Q, K,

@@ -216,6 +216,30 @@ struct PairStage {
             }
         }
     }
+    // One of the two tensors (x, at buf, or y, at buf + TENSOR).  Rows past the end are the last one: loads without a condition, or the
+    // next put waits for all of them, the other tensor's too.
+    __device__ __forceinline__ static void fetch_one(raw8<T> (&z)[NU], const T* Z, int tok0, int end, int tid)
+    {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int unit = tid + u * NTHR;
+            z[u] = load8(Z + (size_t)min(tok0 + unit / CPR, end - 1) * D + (unit % CPR) * 8, true);
+        }
+    }
+    template <int U0 = 0, int U1 = NU>
+    __device__ __forceinline__ static void put_one(const raw8<T> (&z)[NU], char* buf, int tid)
+    {
+#pragma unroll
+        for (int u = U0; u < U1; ++u) {
+            const int unit = tid + u * NTHR;
+            if (UNITS % NTHR != 0 && unit >= UNITS) continue;
+            const int off = plane_off<DP>(unit / CPR, unit % CPR);
+            bf16x8 p[NP];
+            to_planes(z[u], p);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) *reinterpret_cast<bf16x8*>(buf + i * PLANE + off) = p[i];
+        }
+    }
 };
 
 }  // namespace
