@@ -158,7 +158,6 @@ struct PlanesProblem {
     void* out;
     int transpose, reverse;
     int of_walks;   // the states are one per walk, not one per slot of the caller's
-    int later;      // (of_walks, reverse, heads of 64) each walk's own sum: a walk starts from those of the walks behind it
 };
 struct PlanesProblems { PlanesProblem p[3]; };
 
@@ -223,13 +222,6 @@ __device__ __forceinline__ size_t state_index(const Geom& g, const PlanesProblem
     return pb.of_walks ? (size_t)grp * g.T_s + s : (size_t)grp * g.P_Ts + ps;
 }
 
-// How many states a walk's first one is the sum of, and the first of them
-__device__ __forceinline__ int first_states(const Geom& g, const PlanesProblem& pb, int grp, int s, int ps, const float*& at, int dd)
-{
-    at = pb.state + (state_index(g, pb, grp, s, ps) + (pb.later ? 1 : 0)) * (size_t)dd;
-    return pb.later ? g.T_s - 1 - s : 1;
-}
-
 // Tokens of the caller's slots
 __device__ __forceinline__ int slot_tokens(const Geom& g)
 {
@@ -256,19 +248,13 @@ __device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems&
     const T* Bk = static_cast<const T*>(pb.Bk) + base;
     const T* Cv = static_cast<const T*>(pb.Cv) + base;
     T* out = static_cast<T*>(pb.out) + base;
-    const float* state = nullptr;
-    const int nstates = pb.state ? first_states(g, pb, grp, s, ps, state, D * D) : 0;
-    const float l2 = decay_log2(g, grp), wwalk = exp2f((float)g.L * l2);
+    const float* state = pb.state ? pb.state + state_index(g, pb, grp, s, ps) * (size_t)(D * D) : nullptr;
+    const float l2 = decay_log2(g, grp);
     const int transpose = pb.transpose, last = min((len + CHUNK - 1) / CHUNK, (seg + 1) * pg.cps);
     constexpr int NB = D > 64 ? 2 : 1;
     const int lane = tid & 63, nch = (len + CHUNK - 1) / CHUNK;
 #pragma unroll 1
-    for (int e = tid; e < D * D; e += kThr) {
-        float m = 0.f;
-#pragma unroll 1
-        for (int k = nstates - 1; k >= 0; --k) m = fmaf(wwalk, m, state[(size_t)k * (D * D) + (transpose ? (e % D) * D + e / D : e)]);
-        M[e] = m;
-    }
+    for (int e = tid; e < D * D; e += kThr) M[e] = state ? state[transpose ? (e % D) * D + e / D : e] : 0.f;
 #pragma unroll 1
     for (int ci = 0; ci < last; ++ci) {
         const int c0 = (rev ? nch - 1 - ci : ci) * CHUNK, clen = min(CHUNK, len - c0);
@@ -647,32 +633,20 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
     Stage st;
     st.fetch(Bk, Cv, (rev ? nch - 1 : 0) * kRows64, len, tid);
     f32x16 S[1] = {zero16()};
-    const float* st0 = nullptr;
-    const int nstates = pb.state ? first_states(g, pb, grp, s, ps, st0, D * D) : 0;
-    bool have_state = nstates > 0;
+    bool have_state = pb.state != nullptr;
     if (have_state) {
-        auto load = [&](f32x16& m, const float* st) __attribute__((always_inline)) {
+        const float* st0 = pb.state + state_index(g, pb, grp, s, ps) * (size_t)(D * D);
 #pragma unroll
-            for (int v = 0; v < 16; v += 4) {
-                const int a = 32 * rt + acc_row(v) + 4 * h, b = 32 * ct + l32;
-                if (pb.transpose) {
-                    const f32x4 q4 = *reinterpret_cast<const f32x4*>(st + b * D + a);
+        for (int v = 0; v < 16; v += 4) {
+            const int a = 32 * rt + acc_row(v) + 4 * h, b = 32 * ct + l32;
+            if (pb.transpose) {
+                const f32x4 q4 = *reinterpret_cast<const f32x4*>(st0 + b * D + a);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) m[v + e] = q4[e];
-                } else {
+                for (int e = 0; e < 4; ++e) S[0][v + e] = q4[e];
+            } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) m[v + e] = st[(a + e) * D + b];
-                }
+                for (int e = 0; e < 4; ++e) S[0][v + e] = st0[(a + e) * D + b];
             }
-        };
-        // (the last walk's first, as in the prefix kernel; four of them on their way at a time were no faster)
-        load(S[0], st0 + (size_t)(nstates - 1) * (D * D));
-        const float wwalk = DECAY ? exp2f((float)g.L * l2) : 1.f;
-        for (int k = nstates - 2; k >= 0; --k) {
-            f32x16 m;
-            load(m, st0 + (size_t)k * (D * D));
-#pragma unroll
-            for (int v = 0; v < 16; ++v) S[0][v] = DECAY ? fmaf(wwalk, S[0][v], m[v]) : S[0][v] + m[v];
         }
     }
 
@@ -936,36 +910,27 @@ hipError_t launch_states_planes(const Geom& g, int dtype, const void* K, const v
     LASP2_FOR_TYPE_AND_SIZE(states_T, g, K, V, M, anchor_start, of_slots, st)
 }
 
-// Whether the backward's walks add up the states of the walks behind them themselves (one load after another, G T_s^2 / 2 states
-// in each of two problems) instead of a launch before them that does: few states (packed batches aside, which would look for their
-// documents' ends).  Backward, us, with the launch | without: fp32, 2 x 1024 in walks of 128 22.3 | 20.4, 4 x 500 of 64 22.8 | 20.0;
-// 8 x 1000 of 128 25.0 | 24.8, 16 x 1000 31.0 | 31.7; 4 x 4000 34 | 41.
-bool planes_sum_later(const Geom& g)
-{
-    return g.d == 64 && g.n_seqs == 0 && (int64_t)g.G * g.T_s * g.T_s <= 512;
-}
-
 bool planes_emit(const Geom& g) { return g.d == 64 && (g.L / g.wslots) % kRows64 == 0 && (g.wslots > 1 || g.lone_slots); }
 
 hipError_t launch_attn_fwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V, const float* P,
                                   float* emit, void* O, hipStream_t st)
 {
     PlanesProblems p = {};
-    p.p[0] = {Q, K, V, P, O, 0, 0, 0, 0};
+    p.p[0] = {Q, K, V, P, O, 0, 0, 0};
     return attn_any(g, dtype, p, 1, emit, st);
 }
 
 hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V, const void* dO,
-                                  const float* P, const float* dR, int later, void* dQ, void* dK, void* dV, hipStream_t st)
+                                  const float* P, const float* dR, void* dQ, void* dK, void* dV, hipStream_t st)
 {
     PlanesProblems p = {};
     // dQ: the forward problem with (dO, V, K) in the roles of (Q, K, V); its state is
     // V^T K = (K^T V)^T, i.e. the cached prefix read transposed.
-    p.p[0] = {dO, V, K, P, dQ, 1, 0, 0, 0};
+    p.p[0] = {dO, V, K, P, dQ, 1, 0, 0};
     // dV: anti-causal problem with (K, Q, dO); state dM_{t+1:T} = sum Q^T dO.
-    p.p[1] = {K, Q, dO, dR, dV, 0, 1, 1, later};
+    p.p[1] = {K, Q, dO, dR, dV, 0, 1, 1};
     // dK: anti-causal problem with (V, dO, Q); state dO^T Q = dM^T.
-    p.p[2] = {V, dO, Q, dR, dK, 1, 1, 1, later};
+    p.p[2] = {V, dO, Q, dR, dK, 1, 1, 1};
     return attn_any(g, dtype, p, 3, nullptr, st);
 }
 

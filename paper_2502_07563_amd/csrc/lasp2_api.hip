@@ -679,14 +679,13 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const void* Q, const void* K, con
         e = run_states(g, dtype, Q, dO, dR, 1, st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     }
-    const bool later = !pl.fast && pl.need_states_w && planes_sum_later(g);
-    if (!pl.lone_w && !later) {
+    if (!pl.lone_w) {
         e = launch_state_prefix(g, dR, dR, 1, pl.inclusive ? 1 : 0, 0, clear ? pace : nullptr, (unsigned)(g.T_s * g.G), st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     }
     if (pl.fast)
         return from_hip(launch_attn_bwd_mfma(g, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, pace, clear ? 0 : 1, dQ, dK, dV, st));
-    return from_hip(launch_attn_bwd_planes(g, dtype, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, later, dQ, dK, dV, st));
+    return from_hip(launch_attn_bwd_planes(g, dtype, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, dQ, dK, dV, st));
 }
 
 // Scratch of lasp2_attn_bwd_noalloc: device memory that belongs to the loaded library itself, one

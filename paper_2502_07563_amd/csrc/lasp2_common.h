@@ -205,9 +205,8 @@ hipError_t launch_attn_fwd_planes(const Geom& g, int dtype, const void* Q, const
                                   const float* P, float* emit, void* O, hipStream_t st);
 // dR: EXCLUSIVE suffix states of Q^T dO, one per walk of g; P, dR NULL: zero (every document a single walk)
 hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V,
-                                  const void* dO, const float* P, const float* dR, int later, void* dQ, void* dK,
-                                  void* dV, hipStream_t st);   // later: dR holds each walk's own state (planes_sum_later)
-bool planes_sum_later(const Geom& g);
+                                  const void* dO, const float* P, const float* dR, void* dQ, void* dK,
+                                  void* dV, hipStream_t st);
 // inclusive = 0: P[s] excludes M[s] (the public entry point); 1: P[s] includes it.
 // user_slots: the states of g's walks lie in arrays with one entry per slot of the caller's, each walk's
 // where its first slot is; otherwise the arrays have one entry per walk.

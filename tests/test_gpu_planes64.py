@@ -91,27 +91,3 @@ def test_states_of_slots_behind_an_infinity(monkeypatch, dtype, lam, value):
                 ok = torch.isfinite(b)
                 assert ((a[ok].double() - b[ok].double()).norm() / b[ok].double().norm()).item() <= 4 * LIMIT[dtype], j
         assert torch.isfinite(got[1][1][0, 0]).all()
-
-
-@pytest.mark.parametrize("lam", [None, 0.9])
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_states_behind_a_walk(monkeypatch, dtype, lam):
-    """The backward from states that its walks add up themselves (few of them) and that a launch has added up: one walk behind
-    the first, several, a short last one, walks of one slot and of more, on both sides of the choice; a NaN in a later walk."""
-    for walk, G, N, L in (("1", 1, 65, 64), ("1", 2, 1024, 128), ("1", 3, 640, 50), ("2", 2, 513, 64), ("1", 8, 500, 64), ("1", 8, 513, 64),
-                          ("1", 1, 22 * 64, 64), ("1", 1, 23 * 64, 64)):
-        monkeypatch.setenv("LASP2_WALK_SLOTS", walk)
-        _check(dtype, G, N, L, lam=lam)
-    monkeypatch.setenv("LASP2_WALK_SLOTS", "1")
-    f = None if lam is None else np.array([lam, 1.0], dtype=np.float32)
-    p = bd.Problem(1, 2, 700, 64, 64, 64, dtype, decay=f)
-    x = _inputs(2, 700, dtype, 5)
-    P = bd.forward(p, *x[:3])[1]
-    want = bd.backward(p, *x, P)[:3]
-    x[0][0, 0, 300, 7] = float("nan")
-    got = bd.backward(p, *x, P)[:3]
-    assert torch.equal(got[0], want[0])
-    for a, b in zip(got[1:], want[1:]):   # row 300 enters dK and dV of the rows up to it alone
-        assert torch.equal(a[0, 1], b[0, 1]) and not torch.isfinite(a[0, 0, :301]).all(dim=1).any()
-        err = (a[0, 0, 320:].double() - b[0, 0, 320:].double()).norm() / b[0, 0, 320:].double().norm()
-        assert err <= LIMIT[dtype], err
