@@ -172,7 +172,8 @@ int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_
  *       (lasp2_attn_fwd), or what lasp2_forward and lasp2_attn_bwd compute in
  *       launches before the attention launch (none where no walk needs one);
  *   LASP2_START_GATHER  the rows of its document before it (backward: from it to
- *       the end), which the walk adds up itself: one launch;
+ *       the end), which the walk adds up itself: one launch (of lasp2_forward
+ *       perhaps in parts of 128 rows, where these all run at once);
  *   LASP2_START_SLOTS   a state per slot, given or computed as above, and the
  *       rows of the slot on that side of the walk.
  * (Of lasp2_attn_bwd's dQ, whose states are the given P, this is said of the

@@ -486,6 +486,18 @@ WalkPlan pick_forward_walks(const Geom& g, const int32_t* cu_host)
     return {pick_walk_slots(g, cu_host, cu_count(), kWalkTargetFwd), 0, Start::states};
 }
 
+// Walks of 128 rows where lasp2_forward's gather anyway and all of these run at once: the last one then gathers half a walk more and walks
+// half as many rows (skew_walk ends after half a chunk there).  Forward, us, walks of 256 | 128: 16 heads x 300 16.5 | 12.5, x 1 024 21.1 | 17.7, x
+// 2 048 (256 workgroups) 28.5 | 26.0; 32 x 1 200 (320) 22.7 | 22.9; slots of 64, whose states take longer to write, 16 x 1 500 26.1 | 26.8.
+WalkPlan in_halves(const Geom& g, const int32_t* cu_host, const WalkPlan& p)
+{
+    const int64_t longest = longest_sequence(g, cu_host);
+    if (p.start != Start::gather || g.n_seqs || g.decay || g.L < 128 || longest <= 128 || forced_walk_slots(g) ||
+        (int64_t)g.G * slots_of(longest, 128) > cu_count())
+        return p;
+    return g.L > 128 ? WalkPlan{1, 128, Start::gather} : WalkPlan{1, 0, Start::gather};
+}
+
 // Slots per walk of the split-plane kernels, `nprob` workgroups per walk.  They work on chunks of 128
 // rows: slots that leave chunks partly empty (one state per 64 tokens, say) are taken two, four or
 // eight at a time while that still gives every CU a workgroup, and P is read at the first only.  (d = 32, fp32,
@@ -820,7 +832,7 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     hipStream_t st = (hipStream_t)stream;
     const int32_t* cu = desc->cu_seqlens_host;
     const bool fast = mfma_path_supported(g, desc->dtype);
-    const WalkPlan wp = fast ? plan_of(g, cu, desc->dtype, LASP2_CALL_FORWARD) : WalkPlan{planes_slots(g, cu, desc->dtype, false), 0, Start::states};
+    const WalkPlan wp = fast ? in_halves(g, cu, plan_of(g, cu, desc->dtype, LASP2_CALL_FORWARD)) : WalkPlan{planes_slots(g, cu, desc->dtype, false), 0, Start::states};
     const Geom gw = regroup(g, cu, wp);
     hipError_t e;
     if (wp.start == Start::gather) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, nullptr, P, O, st));

@@ -29,6 +29,12 @@ def _check(G, N, L, lam, heads, rows):
     alone = torch.empty_like(O)
     bd.lasp2_attn_fwd(p, *x[:3], P, alone)
     got = (O,) + bd.backward(p, *x, P)[:3]
+    for s in range(0, N, L):   # sums of at most N rows in fp32; with decay a row is rounded to bf16 when it has been weighted
+        w = (1.0 if lam is None else lam) ** torch.arange(s - 1, -1, -1, device="cuda").double()[:, None]
+        for h in heads:
+            want = (x[1][0, h, :s].double() * w).T.contiguous() @ x[2][0, h, :s].double()
+            err = (P[0, h, s // L].double() - want).norm().item()
+            assert err <= (4096 * 2.0 ** -24 if lam is None else 2.0 ** -8) * want.norm().item(), ("P", G, N, L, lam, h, s, err)
     for h in heads:
         want = _want([t[0, h] for t in x], 1.0 if lam is None else lam)
         for name, a, b in list(zip(("O", "dQ", "dK", "dV"), got, want)) + [("attn_fwd", alone, want[0])]:
@@ -55,8 +61,15 @@ def test_the_lengths_gather():
 @pytest.mark.parametrize("lam", [None, 0.99])
 @pytest.mark.parametrize("N", LENGTHS)
 def test_rows_gathered(N, lam):
-    for L in (64, 256, 4096):
+    for L in (64, 128, 256, 4096):
         _check(2, N, L, lam, (0, 1), 64)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("G,N,L", [(16, 2048, 128), (16, 2049, 128), (32, 1024, 512), (33, 1024, 512), (256, 129, 256), (40, 385, 4096)])
+def test_walks_of_128_rows_and_of_256(G, N, L):
+    """Both sides of 256 workgroups of 128 rows."""
+    _check(G, N, L, None, (0, G - 1), 64)
 
 
 @pytest.mark.gpu
