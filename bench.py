@@ -395,7 +395,7 @@ def main():
                      "launches": {"fwd": dict(lf, kernel=kern_fwd),
                                   "bwd": dict(lb, kernel=kern_bwd,
                                               **({"note": "priced against HBM as the contract asks; what limits this launch "
-                                                          "is the LDS instruction rate inside its fused dV/dK workgroups"}
+                                                          "are the chains of dependent steps inside its fused dV/dK workgroups, at a power-limited clock"}
                                                  if pair_kernel else {}))},
                      "device_copy_GBps": copy_gbps},
     }

@@ -1840,7 +1840,7 @@ __global__ __launch_bounds__(512) void attn_bwd_pair_mfma_kernel(Geom g, AttnPro
 // two); a ring of four stages.  A stage cannot take less than 512 clk of matrix instructions, about as many of LDS (its fill
 // and the reads) and as many of the requests' addresses, and the eight waves come to each at the same time: 1 420 clk with the
 // reads before the products and all requests behind the barrier, 1 160 as it stands (160 of them the sum of sums, every eighth
-// stage).  32 heads x 1 531, forward, us: 26.1 -> 24.2; 4 x 4 000, slots of 2 048, 47.7 -> 42.3, backward 55.0 -> 49.4.
+// stage).  16 heads x 1 531, forward, us: 26.1 -> 24.2; 4 x 4 000, slots of 2 048, 47.7 -> 42.3, backward 55.0 -> 49.4.
 // The halves are added through LDS at the end.
 // With decay (l2: log2 of the factor) row r counts lam^(ntok - 1 - r), or lam^r if anchor_start, and base lam^ntok: the rows of a stage
 // are weighted among themselves (and rounded), the stage's sum in fp32, as in states_body.
