@@ -227,6 +227,9 @@ int lasp2_state_prefix(const lasp2_desc_t* desc, const float* M, float* P,
  * P may be NULL when every sequence (document) is a single slot: its prefix is
  * zero, the slot starts from a zero state (serial-carry schedule).  With more
  * than one slot in some sequence a NULL P is LASP2_ERR_NULL.
+ * The split-plane kernels take a given P as it is where a sequence starts too
+ * (not zero where it continues another one); those for bf16, d = 128 take it as
+ * zero there if every sequence is walked whole.
  */
 int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K,
                    const void* V, const float* P, void* O, void* stream);

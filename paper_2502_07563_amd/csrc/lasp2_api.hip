@@ -677,7 +677,7 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const void* Q, const void* K, con
                  const float* P, void* dQ, void* dK, void* dV, float* dR, hipStream_t st)
 {
     const Geom& g = pl.gw;
-    if (pl.lone_w) P = nullptr;
+    if (pl.fast ? pl.lone_w : pl.lone) P = nullptr;   // (the split-plane kernels take a walk's first state as it is given, zero or not)
     hipError_t e = hipSuccess;
     if (pl.start == Start::gather) return from_hip(launch_attn_bwd_direct_mfma(g, Q, K, V, dO, P, dR, 0, dQ, dK, dV, st));
     if (pl.start == Start::both) {   // suffix states per slot
@@ -817,7 +817,7 @@ int lasp2_attn_fwd(const lasp2_desc_t* desc, const void* Q, const void* K, const
     if (wp.W) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, g.lone_slots ? nullptr : P, nullptr, O, st));
     if (mfma_path_supported(g, desc->dtype))
         return from_hip(launch_attn_fwd_mfma(gw, Q, K, V, gw.lone_slots ? nullptr : P, O, st));
-    return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, gw.lone_slots ? nullptr : P, nullptr, O, st));
+    return from_hip(launch_attn_fwd_planes(gw, desc->dtype, Q, K, V, P, nullptr, O, st));
 }
 
 int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const void* V,

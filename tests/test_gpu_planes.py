@@ -83,6 +83,40 @@ def test_forced_walk_lengths(oracle, monkeypatch, dtype, d, lam, slots):
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     _run(oracle, dtype, 1, 2, int(cu[-1]), d, 32, 96, cu=cu, lam=f)
 
+@pytest.mark.parametrize("lam", [None, 0.97])
+@pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 64), ("f32", 128), ("bf16", 32), ("bf16", 64)])
+def test_a_sequence_that_continues_another(dtype, d, lam):
+    """P that is not zero where the sequence starts: what a program that holds a later part of a sequence has (the states of the
+    parts before it are in its prefixes).  One slot and several, lengths that are walked whole and others: O and dQ have its share."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    G, f = 2, None if lam is None else np.array([lam, 1.0], dtype=np.float32)
+    lams = torch.ones(G, device="cuda").double() if lam is None else torch.from_numpy(f).cuda().double()
+    for N, L in ((200, 256), (1000, 1024), (300, 128), (500, 64), (700, 96), (2000, 512)):
+        x = {n: to_device(v, 1, G, dtype) for n, v in host_inputs(31, G, N, d, dtype).items()}
+        p = bd.Problem(1, G, N, d, L if L < 128 else 128, L, dtype, decay=f)
+        own, T = bd.alloc_states(p), -(-N // L)
+        bd.lasp2_chunk_states(p, x["K"], x["V"], own)
+        bd.lasp2_state_prefix(p, own, own)
+        X = torch.randn(G, d, d, generator=torch.Generator(device="cuda").manual_seed(N), device="cuda")
+        age = lams[:, None] ** (L * torch.arange(T, device="cuda"))
+        P = (own.double() + (age[:, :, None, None] * X.double()[:, None])[None]).float()
+        O, dQ = torch.full_like(x["Q"], float("nan")), torch.full_like(x["Q"], float("nan"))
+        dK, dV = torch.empty_like(x["K"]), torch.empty_like(x["V"])
+        bd.lasp2_attn_fwd(p, x["Q"], x["K"], x["V"], P, O)
+        bd.lasp2_attn_bwd(p, x["Q"], x["K"], x["V"], x["dO"], P, dQ, dK, dV, bd.alloc_workspace(p))
+        Q, K, V, dO = (x[n][0].double() for n in ("Q", "K", "V", "dO"))
+        i = torch.arange(N, device="cuda")
+        w = (lams[:, None, None] ** (i[:, None] - i[None]).clamp(min=0)) * (i[:, None] >= i[None])
+        from_X = (lams[:, None] ** (i + 1))[..., None]
+        want = (w * (Q @ K.transpose(1, 2).contiguous())) @ V + from_X * (Q @ X.double())
+        err = ((O[0].double() - want).norm() / want.norm()).item()
+        assert err <= LIMIT[dtype], ("O", dtype, d, lam, N, L, err)
+        if T > 1:      # (lasp2_attn_bwd does not read P where every sequence is a single slot)
+            want = (w * (dO @ V.transpose(1, 2).contiguous())) @ K + from_X * (dO @ X.double().transpose(1, 2).contiguous())
+            err = ((dQ[0].double() - want).norm() / want.norm()).item()
+            assert err <= LIMIT[dtype], ("dQ", dtype, d, lam, N, L, err)
+
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 32), ("f32", 128)])
 def test_rows_that_the_mask_keeps_from_a_nan_stay_finite(dtype, d):
