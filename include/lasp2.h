@@ -155,10 +155,9 @@ int lasp2_num_slots(const lasp2_desc_t* desc, int64_t* T_s);
  *     two apart.
  *   Everything else: only where L is not a multiple of the kernels' 128-row
  *     chunk, so that single slots would leave chunks partly empty; 1 otherwise.
- *     lasp2_attn_bwd builds its dM states per walk.  With d = 64 this (and
- *     lasp2_walk_plan) is what lasp2_attn_fwd does, and the least that
- *     lasp2_forward and lasp2_attn_bwd take: theirs are up to 1024 tokens
- *     long, or whole sequences.
+ *     With d = 64 this (and lasp2_walk_plan) is what lasp2_attn_fwd does, and
+ *     the least that lasp2_forward and lasp2_attn_bwd take.  lasp2_attn_bwd
+ *     gives dM_{t+1:T} of every slot (see there).
  * The environment variable LASP2_WALK_SLOTS (a positive integer, read at every
  * call) overrides the choice where there is one; 1 gives one walk per slot.
  */
@@ -184,8 +183,8 @@ typedef enum { LASP2_START_STATES = 0, LASP2_START_GATHER = 1, LASP2_START_SLOTS
 int lasp2_walk_plan(const lasp2_desc_t* desc, int call, int64_t* walk_tokens, int* start);
 
 /* Bytes of device scratch lasp2_attn_bwd and lasp2_nomask_bwd need: room for one fp32 state
- * array [B,H,T_s,d,d] that holds dM_t and then, in place, its suffix combine (lasp2_attn_bwd
- * may build fewer states than that: one per walk, see lasp2_walk_slots), followed by one 32-bit
+ * array [B,H,T_s,d,d] that holds dM_t and then, in place, its suffix combine (the kernels for
+ * bf16, d = 128 may build fewer states than that: one per walk, see lasp2_walk_slots), followed by one 32-bit
  * counter per (b,h,slot) with which the backward's workgroups that read the same tokens keep in
  * step (a matter of speed only: no result depends on a counter). */
 int lasp2_workspace_size(const lasp2_desc_t* desc, size_t* bytes);
@@ -256,8 +255,10 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K,
  * In: Q,K,V,dO [B,H,N,d]; P = the forward's cached prefix array (the paper
  * keeps M_{1:t-1} in HBM for this purpose).  Out: dQ,dK,dV [B,H,N,d].
  * `workspace`: device scratch of at least lasp2_workspace_size() bytes,
- * 16-byte aligned; its contents on return are unspecified (suffix states in
- * the form the kernels that ran wanted them).
+ * 16-byte aligned; on return the split-plane kernels leave the exclusive suffix
+ * states dM_{t+1:T} of all slots in its state array (nothing is written where every
+ * sequence is a single slot); otherwise its contents are unspecified (suffix states
+ * in the form the kernels that ran wanted them).
  * When every sequence (document) is a single slot, all prefixes and suffixes
  * are zero: P is not read and may be NULL, and the combine is skipped.  The
  * split-plane kernels and the decayed ones for bf16, d = 128 then need no

@@ -344,7 +344,8 @@ def _head(p, ws, T_s):
 
 
 def workspace_states(p: Problem, ws):
-    """The fp32 [B,H,T_s,d,d] state array at the head of a workspace."""
+    """The fp32 [B,H,T_s,d,d] state array at the head of a workspace.  After attn_bwd on the split-plane kernels it holds each
+    slot's exclusive suffix of Q^T dO, unless every sequence is a single slot."""
     return _head(p, ws, lasp2_num_slots(p))
 
 

@@ -20,7 +20,8 @@ __device__ __forceinline__ void st(__hip_bfloat16* p, float v) { *p = __float2bf
 // One thread owns four adjacent state elements and walks the slots in order; loads are
 // batched ahead of the stores so that in-place use (P == M) stays correct and the
 // memory system sees several requests in flight.  The exclusive form does not touch the last slot's own state.
-// user_slots: entry per slot of the caller's, walks of g.wslots of them (see launch_state_prefix).
+// user_slots: entry per slot of the caller's, walks of g.wslots of them (see launch_state_prefix): a walk's is its first, or
+// reversed its last.
 // PACKED, a kernel of its own: what the marks and divisions of packed batches take before the first load shows where
 // a sequence has few slots (1 280 sequences of one slot: 25.1 us with them, 17.4 without).
 constexpr int kScanBatch = 8;
@@ -41,7 +42,6 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
     const int entries = user_slots ? g.P_Ts : g.T_s;
     const size_t base = (size_t)blockIdx.y * (size_t)entries * dd + e;
     const float l2 = decay_log2(g, blockIdx.y);
-    const int step = reverse ? -stride : stride;
     // a packed batch's documents of one mark, or all of them (documents are independent of each other)
     const uint32_t L = (uint32_t)min(g.L, (int64_t)INT32_MAX);
     const uint32_t Lp = PACKED && user_slots ? L / (uint32_t)g.wslots : L;   // tokens per walk, array entry
@@ -51,8 +51,9 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
     for (int k = k0; k < k1; ++k) {
         const int dlen = PACKED ? (g.cu[k + 1] - g.cu[k]) : g.N;
         const int ns = PACKED ? (int)(((uint32_t)dlen + (L - 1u)) / L) : g.T_s;
-        const int ne = PACKED ? (int)(((uint32_t)dlen + (Lp - 1u)) / Lp) : 0;
-        int s = first + (reverse ? (ns - 1) * stride : 0);
+        const int ne = PACKED ? (int)(((uint32_t)dlen + (Lp - 1u)) / Lp) : entries;
+        const size_t doc = base + (size_t)first * dd;
+        auto entry = [&](int r) { return (size_t)(reverse ? min((ns - r) * stride, ne) - 1 : r * stride) * dd; };
         first += ne;
         const int nm = inclusive ? ns : ns - 1;   // states that enter a result
         float4 run = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -64,11 +65,11 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u)
                 if (r + u < nm)
-                    m[u] = *reinterpret_cast<const float4*>(M + base + (size_t)(s + step * u) * dd);
+                    m[u] = *reinterpret_cast<const float4*>(M + doc + entry(r + u));
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u)
                 if (r + u < ns) {
-                    float4* dst = reinterpret_cast<float4*>(P + base + (size_t)(s + step * u) * dd);
+                    float4* dst = reinterpret_cast<float4*>(P + doc + entry(r + u));
                     if (!inclusive) *dst = run;
                     // decay: the carried state ages by the length of the slot it crosses
                     // (slot index inside the document: r+u counted from the walk's start)
@@ -79,7 +80,6 @@ __global__ __launch_bounds__(kThreads) void state_prefix_kernel(Geom g, const fl
                     run.z = fmaf(w, run.z, m[u].z); run.w = fmaf(w, run.w, m[u].w);
                     if (inclusive) *dst = run;
                 }
-            s += step * kScanBatch;
         }
     }
 }

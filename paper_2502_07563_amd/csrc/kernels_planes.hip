@@ -83,6 +83,12 @@ __device__ __forceinline__ float state_element(const T* x, const T* y, int D, in
     return acc;
 }
 
+// Tokens of the caller's slots
+__device__ __forceinline__ int slot_tokens(const Geom& g)
+{
+    return g.wslots > 1 ? (int)((uint32_t)g.L / (uint32_t)g.wslots) : (int)min(g.L, (int64_t)INT32_MAX);
+}
+
 // M[slot] = sum over the slot's tokens of (weighted) k^T v; one workgroup per slot.
 template <typename T, int D, bool DECAY>
 __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __restrict__ K, const T* __restrict__ V,
@@ -96,7 +102,7 @@ __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __
     const int s = blockIdx.x, grp = blockIdx.y;
     int tok0, len, ps, doc0, doc1, slot0, slot1;
     slot_range<false>(g, s, tok0, len, ps, doc0, doc1, slot0, slot1);
-    if (of_slots && tok0 + len == doc1) return;   // (no exclusive prefix contains a document's last walk)
+    if (of_slots && (anchor_start ? tok0 == doc0 : tok0 + len == doc1)) return;   // (in no exclusive sum)
     const size_t base = ((size_t)grp * (size_t)g.N + tok0) * D;
     const float l2 = decay_log2(g, grp);
     const int e0 = anchor_start ? 0 : len - 1, de = anchor_start ? 1 : -1;
@@ -120,6 +126,7 @@ __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __
             state_step<T, D, DP, Stage::PLANE, DECAY, 1>(S, buf, Stage::TENSOR, 16 * w, w, lane, e0 + de * i * ROWS, de, l2);
         }
     }
+    if (of_slots && anchor_start) ps += (len - 1) / slot_tokens(g);
     float* m = M + (of_slots ? (size_t)grp * g.P_Ts + ps : (size_t)grp * g.T_s + s) * (size_t)(D * D);
     // Planes make NaN of an infinity and of what rounds to one (planes.h): such a slot is summed again in fp32.
     float odd = 0.f;
@@ -157,7 +164,7 @@ struct PlanesProblem {
     const float* state;
     void* out;
     int transpose, reverse;
-    int of_walks;   // the states are one per walk, not one per slot of the caller's
+    float* emit;   // NULL, or the array of such states whose entries of the other slots the walks write (heads of 64)
 };
 struct PlanesProblems { PlanesProblem p[3]; };
 
@@ -216,24 +223,17 @@ struct AttnLds {
     static constexpr int FLAG = Stage::BYTES + 3 * SPLANE, BYTES = FLAG + 16;
 };
 
-// Where a problem's state lies, in states: ps is the caller's slot (the walk's first), s the walk.
-__device__ __forceinline__ size_t state_index(const Geom& g, const PlanesProblem& pb, int grp, int s, int ps)
+// Where the state that a walk starts from lies, in states: the entry of its first slot (ps), reversed of its last.
+__device__ __forceinline__ size_t state_index(const Geom& g, const PlanesProblem& pb, int grp, int ps, int len)
 {
-    return pb.of_walks ? (size_t)grp * g.T_s + s : (size_t)grp * g.P_Ts + ps;
-}
-
-// Tokens of the caller's slots
-__device__ __forceinline__ int slot_tokens(const Geom& g)
-{
-    return g.wslots > 1 ? (int)((uint32_t)g.L / (uint32_t)g.wslots) : (int)min(g.L, (int64_t)INT32_MAX);
+    return (size_t)grp * g.P_Ts + ps + (pb.reverse && g.wslots > 1 ? (len - 1) / slot_tokens(g) : 0);
 }
 
 // What attn_planes_kernel computes, in fp32 from the elements as they are, for a workgroup's chunks from `first`
 // on: a row of out per wave, the running state M [D][D] in LDS.  For inputs whose planes are not finite: slow, as scalar
 // products are (fp32, 8 x 2003 x 64 with a NaN in every head's V, forward + backward: 1760 us).
 template <typename T, int D, int CHUNK>
-__device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems& probs, PlanesGrid pg, int first, float* M,
-                                            float* emit)
+__device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems& probs, PlanesGrid pg, int first, float* M)
 {
     asm volatile("" : "+s"(pg.nseg));   // (all of this worked out anew, so that none of it stays in registers through the walk)
     int s, seg, prob, grp;
@@ -248,7 +248,7 @@ __device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems&
     const T* Bk = static_cast<const T*>(pb.Bk) + base;
     const T* Cv = static_cast<const T*>(pb.Cv) + base;
     T* out = static_cast<T*>(pb.out) + base;
-    const float* state = pb.state ? pb.state + state_index(g, pb, grp, s, ps) * (size_t)(D * D) : nullptr;
+    const float* state = pb.state ? pb.state + state_index(g, pb, grp, ps, len) * (size_t)(D * D) : nullptr;
     const float l2 = decay_log2(g, grp);
     const int transpose = pb.transpose, last = min((len + CHUNK - 1) / CHUNK, (seg + 1) * pg.cps);
     constexpr int NB = D > 64 ? 2 : 1;
@@ -259,8 +259,9 @@ __device__ __forceinline__ void attn_scalar(const Geom& g, const PlanesProblems&
     for (int ci = 0; ci < last; ++ci) {
         const int c0 = (rev ? nch - 1 - ci : ci) * CHUNK, clen = min(CHUNK, len - c0);
         __syncthreads();   // M is written
-        if (emit && ci >= first && (c0 > 0 || !pb.state) && c0 % slot_tokens(g) == 0) {
-            float* at = emit + ((size_t)grp * g.P_Ts + ps + c0 / slot_tokens(g)) * (size_t)(D * D);
+        const int edge = rev ? c0 + clen : c0, slot = slot_tokens(g);
+        if (pb.emit && ci >= first && (ci > 0 || !pb.state) && (edge % slot == 0 || (rev && ci == 0))) {
+            float* at = pb.emit + ((size_t)grp * g.P_Ts + ps + (rev ? (edge - 1) / slot : edge / slot)) * (size_t)(D * D);
 #pragma unroll 1
             for (int e = tid; e < D * D; e += kThr) at[e] = M[e];
         }
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
 #pragma unroll
     for (int t = 0; t < NTL; ++t) S[t] = zero16();
     if (have_state && owner) {
-        const float* st0 = pb.state + state_index(g, pb, grp, s, ps) * (size_t)(D * D);
+        const float* st0 = pb.state + state_index(g, pb, grp, ps, len) * (size_t)(D * D);
 #pragma unroll
         for (int t = 0; t < NTL; ++t)
 #pragma unroll
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geo
         }
         have_state = true;
     }
-    if (redo < ci1) attn_scalar<T, D, kChunk>(g, probs, pg, redo, reinterpret_cast<float*>(snap), nullptr);
+    if (redo < ci1) attn_scalar<T, D, kChunk>(g, probs, pg, redo, reinterpret_cast<float*>(snap));
 }
 
 // 8 consecutive elements of a row in all its planes
@@ -599,8 +600,7 @@ struct Attn64Lds {
 constexpr int kRows64 = 64;
 
 template <typename T, bool DECAY>
-__global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void attn64_planes_kernel(Geom g, PlanesProblems probs, PlanesGrid pg,
-                                                                                                      float* emit)
+__global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void attn64_planes_kernel(Geom g, PlanesProblems probs, PlanesGrid pg)
 {
     typedef Attn64Lds<T> LD;
     typedef typename LD::Stage Stage;
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
     f32x16 S[1] = {zero16()};
     bool have_state = pb.state != nullptr;
     if (have_state) {
-        const float* st0 = pb.state + state_index(g, pb, grp, s, ps) * (size_t)(D * D);
+        const float* st0 = pb.state + state_index(g, pb, grp, ps, len) * (size_t)(D * D);
 #pragma unroll
         for (int v = 0; v < 16; v += 4) {
             const int a = 32 * rt + acc_row(v) + 4 * h, b = 32 * ct + l32;
@@ -650,13 +650,20 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
         }
     }
 
-    // the next slot of the caller's whose state goes to `emit`: its first row, and ps, its number
-    int slot = 0, to_emit = -1;
-    if (emit) {
+    // the next slot of the caller's whose state is written: its number in the walk, and its first row (reversed: the row behind it)
+    int slot = 0, at_slot = 0, to_emit = -1;
+    if (pb.emit) {
         slot = slot_tokens(g);
-        const int k = (int)(((uint32_t)(ci0 * kRows64) + (uint32_t)slot - 1u) / (uint32_t)slot);
-        to_emit = k * slot;
-        ps += k;
+        if (!rev) {
+            at_slot = (int)(((uint32_t)(ci0 * kRows64) + (uint32_t)slot - 1u) / (uint32_t)slot);
+            to_emit = at_slot * slot;
+        } else if (ci0 == 0) {
+            at_slot = (len - 1) / slot;
+            to_emit = len;
+        } else {
+            to_emit = (nch - ci0) * kRows64 / slot * slot;
+            at_slot = to_emit / slot - 1;
+        }
     }
     // offset of a lane's first piece of its row in a tile; the next ones differ in bits 5 and 6 alone
     uint32_t row_at = (uint32_t)plane_off<D>(l32, h);
@@ -672,14 +679,14 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
             const T* row = A + (size_t)min(c0 + 32 * rt + l32, len - 1) * D + 8 * h;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) to_planes(load8(row + 16 * ks, true), q[ks]);
-            if (c0 == to_emit) {   // a slot of the caller's starts here (a walk's first has its state, unless there is none)
-                if (c0 > 0 || !pb.state) {
-                    float* at = emit + ((size_t)grp * g.P_Ts + ps) * (size_t)(D * D) + (32 * rt + 4 * h) * D + 32 * ct + l32;
+            if ((rev ? c0 + clen : c0) == to_emit) {   // a slot of the caller's starts here (the state that the walk started from is there)
+                if (ci > 0 || !pb.state) {
+                    float* at = pb.emit + ((size_t)grp * g.P_Ts + ps + at_slot) * (size_t)(D * D) + (32 * rt + 4 * h) * D + 32 * ct + l32;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) at[acc_row(v) * D] = S[0][v];
                 }
-                ++ps;
-                to_emit += slot;
+                at_slot += rev ? -1 : 1;
+                to_emit = (at_slot + (rev ? 1 : 0)) * slot;
             }
             // snapshot of the running state, rows = its second index
             if (have_state) {
@@ -816,7 +823,7 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
             }
         }
     }
-    if (redo < ci1) attn_scalar<T, D, kRows64>(g, probs, pg, redo, reinterpret_cast<float*>(snap), emit);
+    if (redo < ci1) attn_scalar<T, D, kRows64>(g, probs, pg, redo, reinterpret_cast<float*>(snap));
 }
 
 template <typename T, int D, bool DECAY>
@@ -831,7 +838,7 @@ hipError_t states_TD(const Geom& g, const T* K, const T* V, float* M, int anchor
 }
 
 template <typename T, int D, bool DECAY>
-hipError_t attn_TD(const Geom& g, const PlanesProblems& p, int n, float* emit, hipStream_t st)
+hipError_t attn_TD(const Geom& g, const PlanesProblems& p, int n, hipStream_t st)
 {
     constexpr int lds = D == 64 ? Attn64Lds<T>::BYTES : AttnLds<T, D, DECAY>::BYTES, rows = D == 64 ? kRows64 : kChunk;
     hipError_t e;
@@ -852,7 +859,7 @@ hipError_t attn_TD(const Geom& g, const PlanesProblems& p, int n, float* emit, h
         const uint32_t in_group = (uint32_t)(g.T_s * nseg);
         const PlanesGrid pg = {per, (int)nseg, (int)cps, flat, in_group, (uint32_t)(((uint64_t)1 << 32) / std::max(2u, in_group)),
                                (uint32_t)(((uint64_t)1 << 32) / std::max<int64_t>(2, nseg))};
-        if constexpr (D == 64) hipLaunchKernelGGL((attn64_planes_kernel<T, DECAY>), grid, dim3(kThr), lds, st, g, q, pg, emit);
+        if constexpr (D == 64) hipLaunchKernelGGL((attn64_planes_kernel<T, DECAY>), grid, dim3(kThr), lds, st, g, q, pg);
         else hipLaunchKernelGGL((attn_planes_kernel<T, D, DECAY>), grid, dim3(kThr), lds, st, g, q, pg);
         return hipGetLastError();
     };
@@ -877,9 +884,9 @@ hipError_t states_T(const Geom& g, const void* K, const void* V, float* M, int a
 }
 
 template <typename T, int D>
-hipError_t attn_T(const Geom& g, const PlanesProblems& p, int n, float* emit, hipStream_t st)
+hipError_t attn_T(const Geom& g, const PlanesProblems& p, int n, hipStream_t st)
 {
-    return g.decay ? attn_TD<T, D, true>(g, p, n, emit, st) : attn_TD<T, D, false>(g, p, n, emit, st);
+    return g.decay ? attn_TD<T, D, true>(g, p, n, st) : attn_TD<T, D, false>(g, p, n, st);
 }
 
 // one instance per (type, head size)
@@ -897,9 +904,9 @@ hipError_t attn_T(const Geom& g, const PlanesProblems& p, int n, float* emit, hi
         default: return CALL<__hip_bfloat16, 128>(__VA_ARGS__);                    \
     }
 
-hipError_t attn_any(const Geom& g, int dtype, const PlanesProblems& p, int n, float* emit, hipStream_t st)
+hipError_t attn_any(const Geom& g, int dtype, const PlanesProblems& p, int n, hipStream_t st)
 {
-    LASP2_FOR_TYPE_AND_SIZE(attn_T, g, p, n, emit, st)
+    LASP2_FOR_TYPE_AND_SIZE(attn_T, g, p, n, st)
 }
 
 }  // namespace
@@ -916,22 +923,22 @@ hipError_t launch_attn_fwd_planes(const Geom& g, int dtype, const void* Q, const
                                   float* emit, void* O, hipStream_t st)
 {
     PlanesProblems p = {};
-    p.p[0] = {Q, K, V, P, O, 0, 0, 0};
-    return attn_any(g, dtype, p, 1, emit, st);
+    p.p[0] = {Q, K, V, P, O, 0, 0, emit};
+    return attn_any(g, dtype, p, 1, st);
 }
 
 hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V, const void* dO,
-                                  const float* P, const float* dR, void* dQ, void* dK, void* dV, hipStream_t st)
+                                  const float* P, const float* dR, float* emit, void* dQ, void* dK, void* dV, hipStream_t st)
 {
     PlanesProblems p = {};
     // dQ: the forward problem with (dO, V, K) in the roles of (Q, K, V); its state is
     // V^T K = (K^T V)^T, i.e. the cached prefix read transposed.
-    p.p[0] = {dO, V, K, P, dQ, 1, 0, 0};
+    p.p[0] = {dO, V, K, P, dQ, 1, 0, nullptr};
     // dV: anti-causal problem with (K, Q, dO); state dM_{t+1:T} = sum Q^T dO.
-    p.p[1] = {K, Q, dO, dR, dV, 0, 1, 1};
+    p.p[1] = {K, Q, dO, dR, dV, 0, 1, emit};
     // dK: anti-causal problem with (V, dO, Q); state dO^T Q = dM^T.
-    p.p[2] = {V, dO, Q, dR, dK, 1, 1, 1};
-    return attn_any(g, dtype, p, 3, nullptr, st);
+    p.p[2] = {V, dO, Q, dR, dK, 1, 1, nullptr};
+    return attn_any(g, dtype, p, 3, st);
 }
 
 }  // namespace lasp2

@@ -630,7 +630,7 @@ struct BwdPlan {
     bool need_states;   // dM_t go through a state array of `need` bytes
     size_t need;
     bool lone_w;        // every document a single walk
-    bool need_states_w;
+    bool need_states_w; // (matrix-core kernels)
     Start start;        // what the walks start from (matrix-core kernels)
 };
 
@@ -660,8 +660,8 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     rc = check_ptrs({Q, K, V, dO, dQ, dK, dV});
     if (rc != LASP2_OK) return rc;
     if ((!pl->lone && !aligned16(P)) || (ws && !aligned16(*workspace))) return LASP2_ERR_ALIGN;
-    // The kernels' own walks.  The backward's dM states live in the workspace only, so they are
-    // built per walk, not per slot of the caller: fewer of them, never more bytes than `need`.
+    // The kernels' own walks.  The matrix-core kernels' dM states are built per walk, not per slot of the caller: fewer
+    // of them, never more bytes than `need`.
     pl->gw = g;
     pl->start = Start::states;
     const int32_t* cu = desc->cu_seqlens_host;
@@ -673,11 +673,27 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     return LASP2_OK;
 }
 
+// Split planes.  dR holds the exclusive suffix of every slot of the caller's afterwards, however long the walks are.  Where the walks
+// write the entries of the slots inside them, the launches before make those at the walks' ends only.
+// (P: a walk's first state is taken as it is given, zero or not.)
+int run_attn_bwd_planes(const BwdPlan& pl, int dtype, const void* Q, const void* K, const void* V, const void* dO, const float* P,
+                        void* dQ, void* dK, void* dV, float* dR, hipStream_t st)
+{
+    const bool emit = dR && planes_emit(pl.gw);
+    const Geom& g = emit ? pl.gw : pl.g;
+    if (dR && !(emit && pl.lone_w)) {
+        if (launch_states_planes(g, dtype, Q, dO, dR, 1, emit ? 1 : 0, st) != hipSuccess) return LASP2_ERR_LAUNCH;
+        if (launch_state_prefix(g, dR, dR, 1, 0, emit ? 1 : 0, nullptr, 0, st) != hipSuccess) return LASP2_ERR_LAUNCH;
+    }
+    return from_hip(launch_attn_bwd_planes(pl.gw, dtype, Q, K, V, dO, P, emit && pl.lone_w ? nullptr : dR, emit ? dR : nullptr, dQ, dK, dV, st));
+}
+
 int run_attn_bwd(const BwdPlan& pl, int dtype, const void* Q, const void* K, const void* V, const void* dO,
                  const float* P, void* dQ, void* dK, void* dV, float* dR, hipStream_t st)
 {
     const Geom& g = pl.gw;
-    if (pl.fast ? pl.lone_w : pl.lone) P = nullptr;   // (the split-plane kernels take a walk's first state as it is given, zero or not)
+    if (!pl.fast) return run_attn_bwd_planes(pl, dtype, Q, K, V, dO, pl.lone ? nullptr : P, dQ, dK, dV, dR, st);
+    if (pl.lone_w) P = nullptr;
     hipError_t e = hipSuccess;
     if (pl.start == Start::gather) return from_hip(launch_attn_bwd_direct_mfma(g, Q, K, V, dO, P, dR, 0, dQ, dK, dV, st));
     if (pl.start == Start::both) {   // suffix states per slot
@@ -696,9 +712,7 @@ int run_attn_bwd(const BwdPlan& pl, int dtype, const void* Q, const void* K, con
         e = launch_state_prefix(g, dR, dR, 1, pl.inclusive ? 1 : 0, 0, clear ? pace : nullptr, (unsigned)(g.T_s * g.G), st);
         if (e != hipSuccess) return LASP2_ERR_LAUNCH;
     }
-    if (pl.fast)
-        return from_hip(launch_attn_bwd_mfma(g, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, pace, clear ? 0 : 1, dQ, dK, dV, st));
-    return from_hip(launch_attn_bwd_planes(g, dtype, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, dQ, dK, dV, st));
+    return from_hip(launch_attn_bwd_mfma(g, Q, K, V, dO, P, pl.need_states_w ? dR : nullptr, pace, clear ? 0 : 1, dQ, dK, dV, st));
 }
 
 // Scratch of lasp2_attn_bwd_noalloc: device memory that belongs to the loaded library itself, one

@@ -194,8 +194,8 @@ inline int cu_count()
 
 // Split-plane matrix-core kernels (kernels_planes.hip), any supported (dtype, d, C).
 // anchor_start (decay only): weights lam^(token - slot start) instead of lam^(slot end - token).
-// of_slots: M has one entry per slot of the caller's, and the state of each of g's walks goes where its first slot is (not that
-// of a document's last walk, which no exclusive prefix contains); otherwise one entry per walk.
+// of_slots: M has one entry per slot of the caller's, and the state of each of g's walks goes where its first slot is (anchor_start:
+// its last), but for the one of a document that no exclusive prefix (suffix) contains; otherwise one entry per walk.
 hipError_t launch_states_planes(const Geom& g, int dtype, const void* K, const void* V,
                                 float* M, int anchor_start, int of_slots, hipStream_t st);
 // emit (where planes_emit(g)): NULL, or the prefix states, which the walks write for every slot but a walk's first (and
@@ -203,13 +203,15 @@ hipError_t launch_states_planes(const Geom& g, int dtype, const void* K, const v
 bool planes_emit(const Geom& g);
 hipError_t launch_attn_fwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V,
                                   const float* P, float* emit, void* O, hipStream_t st);
-// dR: EXCLUSIVE suffix states of Q^T dO, one per walk of g; P, dR NULL: zero (every document a single walk)
+// dR: EXCLUSIVE suffix states of Q^T dO, an entry per slot of the caller's, of which a walk reads its last slot's; P, dR NULL: zero
+// (every document a single walk).  emit (where planes_emit(g)): NULL, or the array dR, whose other entries the walks write
+// (all of them where dR is NULL).
 hipError_t launch_attn_bwd_planes(const Geom& g, int dtype, const void* Q, const void* K, const void* V,
-                                  const void* dO, const float* P, const float* dR, void* dQ, void* dK,
+                                  const void* dO, const float* P, const float* dR, float* emit, void* dQ, void* dK,
                                   void* dV, hipStream_t st);
 // inclusive = 0: P[s] excludes M[s] (the public entry point); 1: P[s] includes it.
 // user_slots: the states of g's walks lie in arrays with one entry per slot of the caller's, each walk's
-// where its first slot is; otherwise the arrays have one entry per walk.
+// where its first slot is (reversed: its last); otherwise the arrays have one entry per walk.
 // clear: NULL, or nclear counters set to zero.
 hipError_t launch_state_prefix(const Geom& g, const float* M, float* P, int reverse, int inclusive,
                                int user_slots, unsigned* clear, unsigned nclear, hipStream_t st);

@@ -91,3 +91,66 @@ def test_states_of_slots_behind_an_infinity(monkeypatch, dtype, lam, value):
                 ok = torch.isfinite(b)
                 assert ((a[ok].double() - b[ok].double()).norm() / b[ok].double().norm()).item() <= 4 * LIMIT[dtype], j
         assert torch.isfinite(got[1][1][0, 0]).all()
+
+
+def _suffix(x, cu, L, lam):
+    """What follows each slot of its document, Q^T dO in 64 bits as the slot's end sees it; lam: [G]"""
+    out = []
+    for a, b in zip(cu[:-1], cu[1:]):
+        Q, dO = x[0][0, :, a:b].double(), x[3][0, :, a:b].double()
+        for end in range(L, b - a + L, L):
+            i = torch.arange(max(b - a - end, 0), device="cuda")
+            out.append((Q[:, end:] * (lam[:, None] ** i)[..., None]).transpose(1, 2).contiguous() @ dO[:, end:])
+    return torch.stack(out, 1)
+
+
+@pytest.mark.parametrize("walk", ["", "1", "3", "100"])
+@pytest.mark.parametrize("lam", [None, 0.9])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("f32", 16), ("bf16", 32), ("f32", 128)])
+def test_the_workspace_holds_the_suffix_of_every_slot(monkeypatch, dtype, d, lam, walk):
+    """lasp2_attn_bwd on the split-plane kernels, whatever its walks are: slots that the walks write in passing and others, whole
+    sequences in one walk, segments of a walk, documents.  (Sums of at most 4 001 products in fp32: as P in _check.)"""
+    monkeypatch.setenv("LASP2_WALK_SLOTS", walk)
+    docs = [64, 1, 200, 129, 63, 500]
+    for G, N, L, lens in ((2, 65, 64, None), (2, 191, 64, None), (16, 1000, 64, None), (4, 500, 128, None), (2, 4001, 128, None), (64, 900, 128, None),
+                          (2, 700, 192, None), (3, 300, 50, None), (40, 640, 64, None), (2, 900, 512, None),
+                          (3, sum(docs), 64, docs), (3, sum(docs), 128, docs), (3, sum(docs), 96, docs)):
+        cu = np.concatenate([[0], np.cumsum(lens or [N])]).astype(np.int32)
+        x = [t[..., :d].contiguous() if d <= 64 else torch.cat([t, t.flip(-1)], -1) for t in _inputs(G, N, dtype, N)]
+        f = None if lam is None else np.linspace(lam, 1.0, G).astype(np.float32)
+        p = bd.Problem(1, G, N, d, L if L < 64 else 64 if L % 64 == 0 else L, L, dtype, cu if lens else None, decay=f)
+        lams = torch.ones(G, dtype=torch.float64, device="cuda") if f is None else torch.from_numpy(f).cuda().double()
+        P, ws = bd.forward(p, *x[:3])[1], bd.alloc_workspace(p).fill_(float("nan"))
+        grads = [torch.empty_like(t) for t in x[:3]]
+        bd.lasp2_attn_bwd(p, *x, P, *grads, ws)
+        want = _suffix(x, cu, L, lams)
+        got = bd.workspace_states(p, ws)[0].double()
+        err = ((got - want).norm() / want.norm()).item()
+        assert err <= LIMIT["f32"], (dtype, d, lam, walk, G, N, L, lens, err)
+        for a, b in zip((-1,) if lens is None else np.cumsum([-(-n // L) for n in lens]) - 1, (-1,) if lens is None else range(len(lens))):
+            assert not got[:, a].any(), (dtype, d, lam, walk, G, N, L, lens, b)   # nothing follows a document's last slot
+
+
+@pytest.mark.parametrize("lam", [None, 0.9])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_suffixes_of_slots_before_an_infinity(monkeypatch, dtype, lam, value):
+    """The same for an element of dO that is not finite and the suffixes that the backward's walks write."""
+    N, L = 500, 64
+    f = None if lam is None else np.array([lam, 1.0], dtype=np.float32)
+    p = bd.Problem(1, 2, N, 64, 64, L, dtype, decay=f)
+    for j in (0, 130, 191, 499):
+        Q, K, V, dO = _inputs(2, N, dtype, j)
+        P = bd.forward(p, Q, K, V)[1]
+        dO[0, 1, j, 3] = value
+        got = []
+        for walk in ("1", "3", "100"):
+            monkeypatch.setenv("LASP2_WALK_SLOTS", walk)
+            got.append(bd.backward(p, Q, K, V, dO, P))
+        for other in got[1:]:
+            for a, b in zip(other, got[0]):
+                assert torch.equal(torch.isfinite(a), torch.isfinite(b)), j
+                assert torch.equal(torch.isnan(a), torch.isnan(b)), j
+                ok = torch.isfinite(b)
+                assert ((a[ok].double() - b[ok].double()).norm() / b[ok].double().norm()).item() <= 4 * LIMIT[dtype], j
+        assert torch.isfinite(got[1][3][0, 0]).all()
