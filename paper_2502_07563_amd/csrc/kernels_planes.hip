@@ -105,27 +105,44 @@ __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __
     if (of_slots && (anchor_start ? tok0 == doc0 : tok0 + len == doc1)) return;   // (in no exclusive sum)
     const size_t base = ((size_t)grp * (size_t)g.N + tok0) * D;
     const float l2 = decay_log2(g, grp);
-    const int e0 = anchor_start ? 0 : len - 1, de = anchor_start ? 1 : -1;
+    const int de = anchor_start ? 1 : -1;
 
     f32x16 S[Tiles<NT>::n];
 #pragma unroll
     for (int t = 0; t < Tiles<NT>::n; ++t) S[t] = zero16();
+    // Walks of several slots (of_slots: heads of 64, slots of whole stages): a slot's rows are weighted and summed among themselves, then
+    // the sum before (anchor_start: behind) them is aged and added, as it is where each slot has a state.
+    constexpr bool SPLIT = D == 64;
+    const bool back = SPLIT && of_slots && anchor_start;
+    const int slot = SPLIT && of_slots ? slot_tokens(g) : len;
+    int slot_at = back ? (len - 1) / slot * slot : 0;
+    f32x16 sum = zero16();
     Stage st;
     const int nst = (len + ROWS - 1) / ROWS;
-    st.fetch(K + base, V + base, 0, len, tid);
+    auto row_of = [&](int i) { return (back ? nst - 1 - i : i) * ROWS; };
+    st.fetch(K + base, V + base, row_of(0), len, tid);
     for (int i = 0; i < nst; ++i) {
         char* buf = smem + (i & 1) * Stage::BYTES;
         st.put(buf, tid);
-        if (i + 1 < nst) st.fetch(K + base, V + base, (i + 1) * ROWS, len, tid);
+        if (i + 1 < nst) st.fetch(K + base, V + base, row_of(i + 1), len, tid);
         __syncthreads();   // (two buffers: the one written next was last read before this barrier)
+        const int row = row_of(i), end = min(slot_at + slot, len), e = anchor_start ? row - slot_at : end - 1 - row;
         if (NT > 1) {
 #pragma unroll
             for (int r0 = 0; r0 < ROWS; r0 += 32)
-                state_step<T, D, DP, Stage::PLANE, DECAY, 2>(S, buf, Stage::TENSOR, r0, w, lane, e0 + de * i * ROWS, de, l2);
+                state_step<T, D, DP, Stage::PLANE, DECAY, 2>(S, buf, Stage::TENSOR, r0, w, lane, e, de, l2);
         } else {           // one tile: the waves share the tokens
-            state_step<T, D, DP, Stage::PLANE, DECAY, 1>(S, buf, Stage::TENSOR, 16 * w, w, lane, e0 + de * i * ROWS, de, l2);
+            state_step<T, D, DP, Stage::PLANE, DECAY, 1>(S, buf, Stage::TENSOR, 16 * w, w, lane, e, de, l2);
+        }
+        if (SPLIT && (back ? row == slot_at : row + ROWS >= end)) {
+            const float age = DECAY ? decay_pow((float)(end - slot_at), l2) : 1.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[v] = DECAY ? fmaf(age, sum[v], S[0][v]) : sum[v] + S[0][v];
+            S[0] = zero16();
+            slot_at += back ? -slot : slot;
         }
     }
+    if (SPLIT) S[0] = sum;
     if (of_slots && anchor_start) ps += (len - 1) / slot_tokens(g);
     float* m = M + (of_slots ? (size_t)grp * g.P_Ts + ps : (size_t)grp * g.T_s + s) * (size_t)(D * D);
     // Planes make NaN of an infinity and of what rounds to one (planes.h): such a slot is summed again in fp32.
@@ -137,7 +154,7 @@ __global__ __launch_bounds__(kThr) void states_planes_kernel(Geom g, const T* __
             odd = fmaf(D >= 32 || (acc_row(v) + 4 * (lane >> 5) < D && (lane & 31) < D) ? S[t][v] : 0.f, 0.f, odd);
     if (__syncthreads_or(odd != 0.f)) {
         for (int e = tid; e < D * D; e += kThr)
-            m[e] = state_element(K + base + e / D, V + base + e % D, D, len, l2, e0, de);
+            m[e] = state_element(K + base + e / D, V + base + e % D, D, len, l2, anchor_start ? 0 : len - 1, de);
         return;
     }
     if (NT == 1) {
@@ -605,7 +622,7 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
     typedef Attn64Lds<T> LD;
     typedef typename LD::Stage Stage;
     constexpr int D = 64, NP = planes_of<T>::n, KS = D / 16, SUB = 32 * D * 2;
-    constexpr bool TR = NP == 1;
+    constexpr bool TR = NP == 1, LOW = NP > 1;
     extern __shared__ __align__(16) char smem[];
     char* snap = smem + Stage::BYTES;
     char* patch = snap + 3 * LD::SPLANE;
@@ -632,7 +649,10 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
 
     Stage st;
     st.fetch(Bk, Cv, (rev ? nch - 1 : 0) * kRows64, len, tid);
-    f32x16 S[1] = {zero16()};
+    // The running state is the sum since the last edge of a slot, S, on top of that there, base, so that states are sums of slots' sums,
+    // as accurate as those of the states and prefix kernels: one running sum rounds all of it with every 16 rows (P of 130 x 1000
+    // in slots of 64, error 1.5e-7 instead of 7.6e-8).
+    f32x16 S[1] = {zero16()}, base_sum = zero16();
     bool have_state = pb.state != nullptr;
     if (have_state) {
         const float* st0 = pb.state + state_index(g, pb, grp, ps, len) * (size_t)(D * D);
@@ -642,36 +662,46 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
             if (pb.transpose) {
                 const f32x4 q4 = *reinterpret_cast<const f32x4*>(st0 + b * D + a);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) S[0][v + e] = q4[e];
+                for (int e = 0; e < 4; ++e) base_sum[v + e] = q4[e];
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) S[0][v + e] = st0[(a + e) * D + b];
+                for (int e = 0; e < 4; ++e) base_sum[v + e] = st0[(a + e) * D + b];
             }
         }
     }
 
-    // the next slot of the caller's whose state is written: its number in the walk, and its first row (reversed: the row behind it)
-    int slot = 0, at_slot = 0, to_emit = -1;
-    if (pb.emit) {
-        slot = slot_tokens(g);
-        if (!rev) {
-            at_slot = (int)(((uint32_t)(ci0 * kRows64) + (uint32_t)slot - 1u) / (uint32_t)slot);
-            to_emit = at_slot * slot;
-        } else if (ci0 == 0) {
-            at_slot = (len - 1) / slot;
-            to_emit = len;
-        } else {
-            to_emit = (nch - ci0) * kRows64 / slot * slot;
-            at_slot = to_emit / slot - 1;
-        }
-    }
+    // the next edge of a slot of the caller's (where edges lie inside chunks: every 128 rows), its number in the walk, and its row
+    const int tokens = slot_tokens(g), slot = tokens % kRows64 ? 2 * kRows64 : tokens;
+    int at_slot = rev ? (len - 1) / slot : 0, edge = rev ? len : 0, since = 0;   // since: rows in S
     // offset of a lane's first piece of its row in a tile; the next ones differ in bits 5 and 6 alone
     uint32_t row_at = (uint32_t)plane_off<D>(l32, h);
+    // ... and of its first piece of the state's snapshot, row 32 ct + l32, columns 32 rt + 4 h ..; the next ones are 8, 16 and 24 columns on
+    uint32_t snap_at = (uint32_t)plane_off<D>(32 * ct + l32, 4 * rt) + 8u * h;
+    auto running = [&](int v, float age) __attribute__((always_inline)) { return DECAY ? fmaf(age, base_sum[v], S[0][v]) : base_sum[v] + S[0][v]; };
     int redo = ci1;
     for (int ci = 0; ci < ci1; ++ci) {
         const int c0 = (rev ? nch - 1 - ci : ci) * kRows64, clen = min(kRows64, len - c0);
         const bool rows = ci >= ci0, update = ci + 1 < ci1;
-        f32x16 acc, low;   // (products of the higher orders have a sum of their own for the whole chunk)
+        float age = DECAY ? decay_pow((float)since, l2) : 1.f;
+        if ((rev ? c0 + clen : c0) == edge) {
+            if (ci > 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) base_sum[v] = running(v, age);
+                S[0] = zero16();
+                since = 0;
+                age = 1.f;
+            }
+            if (rows && pb.emit && (ci > 0 || !pb.state)) {   // (the state that the walk started from is there)
+                int t = threadIdx.x;
+                asm volatile("" : "+v"(t));   // (worked out anew, as below)
+                float* at = pb.emit + ((size_t)grp * g.P_Ts + ps + at_slot) * (size_t)(D * D) + (32 * rt + (t >> 3 & 4)) * D + 32 * ct + (t & 31);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) at[acc_row(v) * D] = base_sum[v];
+            }
+            at_slot += rev ? -1 : 1;
+            edge = (at_slot + (rev ? 1 : 0)) * slot;
+        }
+        f32x16 acc, low;   // (fp32: products of the higher orders have a sum of their own for the whole chunk)
         bf16x8 q[KS][NP];
         if (rows) {
             // (rows past the end: the last one once more, whose results nobody reads; a zero instead of it would be a select
@@ -679,27 +709,21 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
             const T* row = A + (size_t)min(c0 + 32 * rt + l32, len - 1) * D + 8 * h;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) to_planes(load8(row + 16 * ks, true), q[ks]);
-            if ((rev ? c0 + clen : c0) == to_emit) {   // a slot of the caller's starts here (the state that the walk started from is there)
-                if (ci > 0 || !pb.state) {
-                    float* at = pb.emit + ((size_t)grp * g.P_Ts + ps + at_slot) * (size_t)(D * D) + (32 * rt + 4 * h) * D + 32 * ct + l32;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) at[acc_row(v) * D] = S[0][v];
-                }
-                at_slot += rev ? -1 : 1;
-                to_emit = (at_slot + (rev ? 1 : 0)) * slot;
-            }
             // snapshot of the running state, rows = its second index
             if (have_state) {
+                pin_vgpr(snap_at);
 #pragma unroll
                 for (int v = 0; v < 16; v += 8) {
+                    float x[8];
                     bf16x8 p[3];
-                    acc_frag(S[0], v, p);
-                    const int b = 32 * ct + l32, a = 32 * rt + acc_row(v) + 4 * h;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = running(v + e, age);
+                    split8(x, p);
 #pragma unroll
                     for (int i = 0; i < 3; ++i) {
                         const bf16x4 lo = {p[i][0], p[i][1], p[i][2], p[i][3]}, hi = {p[i][4], p[i][5], p[i][6], p[i][7]};
-                        *reinterpret_cast<bf16x4*>(snap + i * LD::SPLANE + plane_off<D>(b, a >> 3) + (a & 7) * 2) = lo;
-                        *reinterpret_cast<bf16x4*>(snap + i * LD::SPLANE + plane_off<D>(b, (a >> 3) + 1) + (a & 7) * 2) = hi;
+                        *reinterpret_cast<bf16x4*>(snap + i * LD::SPLANE + (snap_at ^ (v << 2))) = lo;
+                        *reinterpret_cast<bf16x4*>(snap + i * LD::SPLANE + (snap_at ^ ((v << 2) + 16))) = hi;
                     }
                 }
             }
@@ -715,13 +739,14 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
         __syncthreads();
         if (rows) {
             acc = zero16();
-            low = zero16();
+            if constexpr (LOW) low = zero16();
             if (have_state) {
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     bf16x8 b[3];
                     frag_at<3>(snap + 32 * ct * 2 * D, LD::SPLANE, row_at ^ (32 * ks), b);
-                    low = mm_either<TR, 1, 2>(q[ks], b, low);
+                    if constexpr (LOW) low = mm_either<TR, 1, 2>(q[ks], b, low);
+                    else acc = mm_either<TR, 1, 2>(q[ks], b, acc);
                 }
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
@@ -736,7 +761,7 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
                         const int i = 32 * rt + (TR ? l32 : acc_row(v) + 4 * h);
                         const float f = decay_pow((float)(rev ? max(clen - i, 0) : i + 1), l2);
                         acc[v] *= f;
-                        low[v] *= f;
+                        if constexpr (LOW) low[v] *= f;
                     }
                 }
             }
@@ -769,7 +794,8 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
                 bf16x8 v[2][NP];
                 col_frag<D>(buf + Stage::TENSOR, Stage::PLANE, 0, 32 * ct, lane, v[0]);
                 col_frag<D>(buf + Stage::TENSOR, Stage::PLANE, 16, 32 * ct, lane, v[1]);
-                low = mm_either<TR, 1, 2>(p[1], v[1], mm_either<TR, 1, 2>(p[0], v[0], low));
+                if constexpr (LOW) low = mm_either<TR, 1, 2>(p[1], v[1], mm_either<TR, 1, 2>(p[0], v[0], low));
+                else acc += mm_either<TR, 1, 2>(p[1], v[1], mm_either<TR, 1, 2>(p[0], v[0], zero16()));
                 acc = mm_either<TR, 0, 0>(p[1], v[1], mm_either<TR, 0, 0>(p[0], v[0], acc));
             }
         }
@@ -780,10 +806,11 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
                                                             rev ? r0 : clen - 1 - r0, rev ? 1 : -1, l2);
         }
         have_state = true;
+        since += clen;
         if (!rows) continue;
 
         // (not finite: from this chunk on in fp32, as above)
-        acc += low;
+        if constexpr (LOW) acc += low;
         float odd = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) odd = fmaf(acc[v], 0.f, odd);
@@ -810,13 +837,15 @@ __global__ __launch_bounds__(kThr, planes_of<T>::n == 1 && !DECAY ? 3 : 2) void 
                 if (row < clen) *reinterpret_cast<u32x4*>(out + (size_t)(c0 + row) * D + 8 * ch) = piece;
             }
         } else {
-            T* o = out + (size_t)(c0 + 32 * rt + 4 * h) * D + 32 * ct + l32;
-            int left = clen - 32 * rt - 4 * h;
+            int t = threadIdx.x;
+            asm volatile("" : "+v"(t));   // (else the address and the answers for the rows are kept through the walk)
+            const int h4 = t >> 3 & 4;
+            T* o = out + (size_t)(c0 + 32 * rt + h4) * D + 32 * ct + (t & 31);
+            const int left = clen - 32 * rt - h4;
             if (clen >= 32 * rt + 32) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) store1(o + acc_row(v) * D, acc[v]);
             } else {
-                asm volatile("" : "+v"(left));   // (else the answers for the rows are kept through the walk)
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
                     if (acc_row(v) < left) store1(o + acc_row(v) * D, acc[v]);
