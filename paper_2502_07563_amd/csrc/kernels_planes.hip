@@ -26,17 +26,18 @@ struct Tiles {
 __device__ __forceinline__ float decay_pow(float e, float l2) { return __builtin_amdgcn_exp2f(e * l2); }
 
 // Rescales the elements of a transposed fetch (tokens r0 + 4h + .., planes.h) by lam^(e0 + de * token):
-// the planes add up to the exact value, the product is an fp32 one and is split again.
+// the planes add up to the exact value, which is multiplied and split again.
 template <int NP>
 __device__ __forceinline__ void weight_frag(const bf16x8 (&f)[NP], int r0, int lane, int e0, int de, float l2, bf16x8 (&out)[3])
 {
-    float x[8];
+    float x[8], y[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int t = r0 + 4 * (lane >> 5) + (e < 4 ? e : e + 4);
-        x[e] = frag_value(f, e) * decay_pow((float)max(e0 + de * t, 0), l2);   // (below 0: rows past the end, all zero)
+        x[e] = frag_value(f, e);
+        y[e] = decay_pow((float)max(e0 + de * t, 0), l2);   // (below 0: rows past the end, all zero)
     }
-    split8(x, out);
+    split8_products(x, y, out);
 }
 
 // S[t] += X^T Y over the tokens of NKS k-steps (16 rows each, from row r0) of one stage

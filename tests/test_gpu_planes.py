@@ -142,6 +142,32 @@ def test_rows_that_the_mask_keeps_from_a_nan_stay_finite(dtype, d):
     assert rel_l2(to_host(dV[:, :, j + 1:]), to_host(gv[:, :, j + 1:])) <= LIMIT[dtype]
 
 
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_weighted_rows_are_split_exactly(d):
+    """With decay a row is multiplied by its weight and split into planes, which hold more bits than fp32: the state of one row of
+    weight w < 1 is as close to w k^T v as that of a row of weight 1 to k^T v (the weight itself, the same for all elements, is fitted).
+    A product that is rounded to fp32 before it is split adds about as much as the state's own rounding: 1.24 of the error."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    G = 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    K, V = (torch.randn(1, G, 2, d, generator=gen, device="cuda") for _ in range(2))
+    K[:, :, 1] = 0
+
+    def error(lam):
+        p = bd.Problem(1, G, 2, d, 2, 2, "f32", decay=np.full(G, lam, dtype=np.float32))
+        M = bd.alloc_states(p)
+        bd.lasp2_chunk_states(p, K, V, M)
+        want = (K[0, :, 0, :, None].double() * V[0, :, 0, None].double()).flatten()
+        w = (M.double().flatten() / want).mean()
+        assert abs(w.item() / lam - 1) <= 1e-6
+        return ((M.double().flatten() - w * want) / (w * want)).square().mean().sqrt().item()
+    one = error(1.0)
+    for lam in (0.6, 0.9, 0.99, 0.999):
+        print(d, lam, error(lam) / one, flush=True)
+        assert error(lam) <= 1.15 * one, (d, lam, error(lam), one)
+
+
 def _positive_inputs(N, d, dtype, seed):
     import torch
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
