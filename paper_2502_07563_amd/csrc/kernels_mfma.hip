@@ -1882,16 +1882,26 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
             y[e] = lds_read_tr8_u((py ^ (e << 6)) + k * (16 * ROWB), (py ^ (e << 6) ^ 16) + (4 + 16 * k) * ROWB);
         }
     };
-    // sums of at most 512 rows, and the sum of those: as accurate as the sums of a slot and of slots that they replace.  With decay one
+    // Sums of at most 512 rows, and the sum of those: as accurate as the sums of a slot and of slots that they replace.  With decay one
     // sum, aged by a stage before the stage is added: its weighted rows are bf16, and the rounding of sums does not show (16 heads x 1 024,
-    // forward, 27.7 us with both sums, 22.7 so; errors of P and O against 64 bits the same to four digits)
+    // forward, 27.7 us with both sums, 22.7 so; errors of P and O against 64 bits the same to four digits).  Weights of a factor of 1 are
+    // exact, and there it would (P, 4 x 1 531 in slots of 128, 1.04e-7 -> 1.27e-7): such heads take sums of two stages (7.5e-8).
     f32x16 acc[2][2], tot[2][2];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { acc[a][b][v] = 0.f; tot[a][b][v] = 0.f; }
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+    const bool sums = !DECAY || uniform_f32(l2) == 0.f;   // (nobody touches tot otherwise)
+    if (sums) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) tot[a][b][v] = 0.f;
+    }
     auto flush = [&]() {
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -1973,9 +1983,14 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
         SCHED_FENCE();
         product(xB, yB, 1, 0);
         product(xB, yB, 1, 1);
-        if (!DECAY && (i & 7) == 7) flush();
+        if (DECAY ? sums && (i & 1) : (i & 7) == 7) flush();
     }
-    flush();
+    if (sums) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[a][b] += tot[a][b];
+    }
     __syncthreads();
     // this wave finishes row hf of its quadrant's tiles and hands the other to the wave with the other half
     f32x4* out = reinterpret_cast<f32x4*>(smem + w * 8192) + lane;
@@ -1986,7 +2001,7 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
         for (int q = 0; q < 4; ++q) {
             f32x4 p;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) p[e] = hf ? tot[0][b][4 * q + e] : tot[1][b][4 * q + e];
+            for (int e = 0; e < 4; ++e) p[e] = hf ? acc[0][b][4 * q + e] : acc[1][b][4 * q + e];
             out[(4 * b + q) * 64] = p;
         }
     __syncthreads();
@@ -1998,7 +2013,7 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
         for (int q = 0; q < 4; ++q) {
             f32x4 p = in[(4 * b + q) * 64];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) p[e] += hf ? tot[1][b][4 * q + e] : tot[0][b][4 * q + e];
+            for (int e = 0; e < 4; ++e) p[e] += hf ? acc[1][b][4 * q + e] : acc[0][b][4 * q + e];
             if (base) {
                 const int r = 32 * (w >> 1) + 8 * q + 4 * h, c = 64 * qb + 32 * b + (lane & 31);
 #pragma unroll
