@@ -259,8 +259,9 @@ def main():
         return sum(f * -(-Leff // w) + -(-(n - f * Leff) // w) for f, n in zip(full, doc_lens))
     (w_f, start_f), (w_b, start_b) = bd.lasp2_walk_plan(p, "attn_fwd"), bd.lasp2_walk_plan(p, "attn_bwd")
     ws_f, ws_b = bd.lasp2_walk_slots(p), bd.lasp2_walk_slots(p, backward=True)
-    # tokens per state that the backward builds before its attention launch (off the matrix-core kernels per slot, whatever the walk)
-    w_states = w_b if mfma and start_b == "states" else Leff
+    # tokens per state that the backward builds before its attention launch: per walk on the matrix-core kernels and, in slots of
+    # whole chunks, for heads of 64; else per slot, whatever the walk
+    w_states = w_b if start_b == "states" and (mfma or (d == 64 and Leff % 64 == 0)) else Leff
     lone_f, lone_b = walks(w_f if mfma else Leff) == len(doc_lens), walks(w_states) == len(doc_lens)
     n_states = lambda start, w, one: 0 if start == "gather" or one else walks(w) if start == "states" else T_s
     # What lasp2_attn_bwd spends before its attention launch: the dM_t = Q_t^T dO_t and their suffix

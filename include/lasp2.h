@@ -155,9 +155,9 @@ int lasp2_num_slots(const lasp2_desc_t* desc, int64_t* T_s);
  *     two apart.
  *   Everything else: only where L is not a multiple of the kernels' 128-row
  *     chunk, so that single slots would leave chunks partly empty; 1 otherwise.
- *     With d = 64 this (and lasp2_walk_plan) is what lasp2_attn_fwd does, and
- *     the least that lasp2_forward and lasp2_attn_bwd take.  lasp2_attn_bwd
- *     gives dM_{t+1:T} of every slot (see there).
+ *     With d = 64 lasp2_attn_bwd (and lasp2_forward) takes walks by the work
+ *     that a launch has, of 128 tokens and more, or short sequences whole.
+ *     lasp2_attn_bwd gives dM_{t+1:T} of every slot (see there).
  * The environment variable LASP2_WALK_SLOTS (a positive integer, read at every
  * call) overrides the choice where there is one; 1 gives one walk per slot.
  */
@@ -171,8 +171,7 @@ int lasp2_walk_slots(const lasp2_desc_t* desc, int backward, int64_t* slots_per_
  *       (lasp2_attn_fwd), or what lasp2_forward and lasp2_attn_bwd compute in
  *       launches before the attention launch (none where no walk needs one);
  *   LASP2_START_GATHER  the rows of its document before it (backward: from it to
- *       the end), which the walk adds up itself: one launch (of lasp2_forward
- *       perhaps in parts of 128 rows, where these all run at once);
+ *       the end), which the walk adds up itself: one launch;
  *   LASP2_START_SLOTS   a state per slot, given or computed as above, and the
  *       rows of the slot on that side of the walk.
  * (Of lasp2_attn_bwd's dQ, whose states are the given P, this is said of the

@@ -544,19 +544,16 @@ int pick_planes64_slots(const Geom& g, const int32_t* cu_host, int dtype, bool b
     return (int)ws;
 }
 
-// Slots per walk of what lasp2_forward and the backward launch on these kernels.  (lasp2_walk_slots and lasp2_walk_plan report
-// pick_planes_slots: the fewest a walk takes.)
-int planes_slots(const Geom& g, const int32_t* cu_host, int dtype, bool backward)
-{
-    return g.d == 64 ? pick_planes64_slots(g, cu_host, dtype, backward) : pick_planes_slots(g, cu_host, backward ? 3 : 1);
-}
-
-// What each call does with its descriptor (lasp2_walk_plan).
+// What each call does with its descriptor: what they launch by, and what lasp2_walk_slots and lasp2_walk_plan report.
 WalkPlan plan_of(const Geom& g, const int32_t* cu_host, int dtype, int call)
 {
-    if (!mfma_path_supported(g, dtype)) return {pick_planes_slots(g, cu_host, call == LASP2_CALL_ATTN_BWD ? 3 : 1), 0, Start::states};
-    if (call == LASP2_CALL_ATTN_BWD) return pick_bwd_walks(g, cu_host);
-    if (call == LASP2_CALL_FORWARD) return pick_forward_walks(g, cu_host);
+    const bool backward = call == LASP2_CALL_ATTN_BWD;
+    if (!mfma_path_supported(g, dtype)) {
+        const bool builds = call != LASP2_CALL_ATTN_FWD;   // (lasp2_attn_fwd is given the states)
+        return {g.d == 64 && builds ? pick_planes64_slots(g, cu_host, dtype, backward) : pick_planes_slots(g, cu_host, backward ? 3 : 1), 0, Start::states};
+    }
+    if (backward) return pick_bwd_walks(g, cu_host);
+    if (call == LASP2_CALL_FORWARD) return in_halves(g, cu_host, pick_forward_walks(g, cu_host));
     // long slots that leave CUs without work: walks of parts of them
     if (g.L >= 512) {
         const WalkPlan wp = pick_walks(g, cu_host, false, false);
@@ -665,7 +662,7 @@ int plan_attn_bwd(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     pl->gw = g;
     pl->start = Start::states;
     const int32_t* cu = desc->cu_seqlens_host;
-    const WalkPlan wp = pl->fast ? plan_of(g, cu, desc->dtype, LASP2_CALL_ATTN_BWD) : WalkPlan{planes_slots(g, cu, desc->dtype, true), 0, Start::states};
+    const WalkPlan wp = plan_of(g, cu, desc->dtype, LASP2_CALL_ATTN_BWD);
     pl->gw = regroup(g, cu, wp);
     pl->start = wp.start;
     pl->lone_w = pl->gw.lone_slots != 0;
@@ -847,7 +844,7 @@ int lasp2_forward(const lasp2_desc_t* desc, const void* Q, const void* K, const 
     hipStream_t st = (hipStream_t)stream;
     const int32_t* cu = desc->cu_seqlens_host;
     const bool fast = mfma_path_supported(g, desc->dtype);
-    const WalkPlan wp = fast ? in_halves(g, cu, plan_of(g, cu, desc->dtype, LASP2_CALL_FORWARD)) : WalkPlan{planes_slots(g, cu, desc->dtype, false), 0, Start::states};
+    const WalkPlan wp = plan_of(g, cu, desc->dtype, LASP2_CALL_FORWARD);
     const Geom gw = regroup(g, cu, wp);
     hipError_t e;
     if (wp.start == Start::gather) return from_hip(launch_attn_fwd_direct_mfma(gw, Q, K, V, nullptr, P, O, st));

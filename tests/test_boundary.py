@@ -126,12 +126,15 @@ def test_walk_plan_tells_the_calls_apart(monkeypatch):
     for kw, fwd, forward, bwd in (
             (dict(N=32768), (1024, "states"), (2048, "states"), (2048, "states")),
             (dict(N=262144, L=4096), (4096, "states"), (8192, "states"), (16384, "states")),
-            (dict(N=1531), (256, "states"), (256, "gather"), (256, "states")),
+            # gathering walks of lasp2_forward: of 128 rows while all of these run at once (256 workgroups)
+            (dict(N=1531), (256, "states"), (128, "gather"), (256, "states")),
+            (dict(N=2048), (256, "states"), (128, "gather"), (256, "states")),
+            (dict(H=17, N=1930, C=128), (128, "states"), (256, "gather"), (384, "states")),
             # one head in slots of 4 096: 25 of them, parts of a slot a walk
             (dict(H=1, N=100003, L=4096), (448, "slots"), (448, "slots"), (832, "slots")),
             # few heads: walks of 128 rows in the backward; more of them, and 256 are the shorter launch
-            (dict(H=4, N=1000, C=128), (128, "states"), (256, "gather"), (128, "states")),
-            (dict(H=32, N=1000, C=128), (128, "states"), (256, "gather"), (256, "states"))):
+            (dict(H=4, N=1000, C=128), (128, "states"), (128, "gather"), (128, "states")),
+            (dict(H=32, N=1000, C=128), (128, "states"), (128, "gather"), (256, "states"))):
         got = [_plan(_desc(**dict(bf, **kw)), c)[1:] for c in ("attn_fwd", "forward", "attn_bwd")]
         assert got == [fwd, forward, bwd], (kw, got)
     # with decay and one walk per document there is nothing to gather, and no launch that it would save
@@ -182,9 +185,10 @@ def test_planning_packed_batches_costs_a_few_passes_over_the_documents(monkeypat
 
 def test_walk_slots_off_the_bf16_d128_path(monkeypatch):
     """The kernels for fp32, d < 128 and strong decay take slots that leave their 128-row chunks partly empty two,
-    four or eight at a time while every CU gets a workgroup; the query says so, and the override reaches them."""
+    four or eight at a time while every CU gets a workgroup; the query says so, and the override reaches them.  (Heads of 64:
+    lasp2_attn_fwd; the other calls below.)"""
     monkeypatch.delenv("LASP2_WALK_SLOTS", raising=False)
-    many = dict(B=16, H=32, N=1000, d=64)
+    many = dict(B=16, H=32, N=1000, d=32)
     lam = (ctypes.c_float * 32)(*([0.2] * 32))
     decay = dict(decay_host=ctypes.addressof(lam), decay_dev=0x3000)
     for kw in (dict(), dict(dtype=B.LASP2_BF16), dict(dtype=B.LASP2_BF16, d=128, **decay)):
@@ -194,14 +198,40 @@ def test_walk_slots_off_the_bf16_d128_path(monkeypatch):
         assert _walk(_desc(C=128, **kw)) == (0, 1)                              # whole chunks
         assert _walk(_desc(C=64, **dict(kw, B=1, N=100), L=128)) == (0, 1)      # a slot holds the sequence
     # 2 heads x 400 tokens: 14 slots, 7 walks of two; three workgroups each (backward) do not fill 256 CUs either
-    few = dict(H=2, N=400, d=64, C=64)
+    few = dict(H=2, N=400, d=32, C=64)
     assert _walk(_desc(**few)) == (0, 1) and _walk(_desc(**few), 1) == (0, 1)
     # 200 groups x 64-token slots of 128 tokens: 200 walks of two are too few, 600 workgroups enough
-    assert _walk(_desc(B=10, H=20, N=128, d=64, C=64)) == (0, 1) and _walk(_desc(B=10, H=20, N=128, d=64, C=64), 1) == (0, 2)
+    assert _walk(_desc(B=10, H=20, N=128, d=32, C=64)) == (0, 1) and _walk(_desc(B=10, H=20, N=128, d=32, C=64), 1) == (0, 2)
+    for kw in (many, few):
+        assert _walk(_desc(**dict(kw, C=64, d=64))) == _walk(_desc(**dict(kw, C=64)))
     for forced, want in ((1, 1), (3, 3), (1 << 40, (1 << 30) // 64)):
         monkeypatch.setenv("LASP2_WALK_SLOTS", str(forced))
         assert _walk(_desc(C=64, **many)) == (0, want) and _walk(_desc(**few), 1) == (0, want)
         assert _walk(_desc(C=128, **many)) == (0, 1)
+
+
+def test_walks_of_heads_of_64(monkeypatch):
+    """lasp2_forward and lasp2_attn_bwd build the states themselves and take walks by the work of a launch (256 CUs assumed where no
+    device answers); both queries say what they launch."""
+    monkeypatch.delenv("LASP2_WALK_SLOTS", raising=False)
+    lam = (ctypes.c_float * 16)(*([0.9] * 16))
+    decay = dict(decay_host=ctypes.addressof(lam), decay_dev=0x3000)
+    bf = dict(d=64, dtype=B.LASP2_BF16)
+    for kw, fwd, forward, bwd in (
+            (dict(bf, B=4, H=16, N=4001), 1, 4, 8),              # 256 064 rows, two walks a CU forward, one backward
+            (dict(bf, H=16, N=1000), 1, 8, 8),                   # short sequences whole
+            (dict(bf, B=1, H=4, N=500, **decay), 1, 4, 4),
+            (dict(bf, B=1, H=16, N=1000, **decay), 1, 1, 1),     # ... not where rows have more work
+            (dict(H=2, N=1024, d=64), 1, 1, 1),
+            (dict(bf, B=4, H=16, N=8000, L=640), 1, 2, 2),       # the first number of slots that has 1 024 tokens or more
+            (dict(bf, B=4, H=16, N=8000, C=64), 2, 16, 16)):
+        desc = _desc(**kw)
+        L = desc.L or desc.C
+        assert _walk(desc) == (0, fwd) and _walk(desc, 1) == (0, bwd), kw
+        assert [_plan(desc, c)[1:] for c in ("attn_fwd", "forward", "attn_bwd")] == [(w * L, "states") for w in (fwd, forward, bwd)], kw
+    monkeypatch.setenv("LASP2_WALK_SLOTS", "3")
+    desc = _desc(**dict(bf, B=4, H=16, N=4001))
+    assert [_plan(desc, c)[1] for c in ("attn_fwd", "forward", "attn_bwd")] == [128, 384, 384]
 
 
 def test_workspace_size():

@@ -53,7 +53,7 @@ LENGTHS = (129, 191, 320, 321, 383, 449, 512, 575, 769, 1024, 1025, 1087, 1531, 
 def test_the_lengths_gather():
     """(256 CUs assumed where no device answers)"""
     for N in LENGTHS[2:]:
-        assert bd.lasp2_walk_plan(_problem(2, N, 4096, device="cpu"), "forward")[1] == "gather", N
+        assert bd.lasp2_walk_plan(_problem(2, N, 4096, device="cpu"), "forward") == (128, "gather"), N
     assert any(bd.lasp2_walk_plan(_problem(2, N, 4096, device="cpu"), "attn_bwd")[1] == "gather" for N in LENGTHS)
 
 
@@ -86,10 +86,19 @@ def test_heads_that_do_not_decay_are_summed_as_without_decay(G, N, L):
     assert err[1] <= 1.25 * err[0], (G, N, L, err)
 
 
+BOTH_SIDES = [(16, 2048, 128, 128), (17, 1930, 128, 256), (24, 1400, 128, 256), (32, 1024, 512, 128), (33, 1024, 512, 256), (40, 385, 4096, 128)]
+
+
+def test_the_sides_of_256_workgroups():
+    """(256 CUs assumed where no device answers)"""
+    for G, N, L, rows in BOTH_SIDES:
+        assert bd.lasp2_walk_plan(_problem(G, N, L, device="cpu"), "forward") == (rows, "gather"), (G, N, L)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("G,N,L", [(16, 2048, 128), (16, 2049, 128), (32, 1024, 512), (33, 1024, 512), (256, 129, 256), (40, 385, 4096)])
+@pytest.mark.parametrize("G,N,L", [c[:3] for c in BOTH_SIDES] + [(16, 2049, 128), (256, 129, 256)])
 def test_walks_of_128_rows_and_of_256(G, N, L):
-    """Both sides of 256 workgroups of 128 rows."""
+    """Both sides of 256 workgroups of 128 rows, and of the first choice, walks that gather."""
     _check(G, N, L, None, (0, G - 1), 64)
 
 
