@@ -489,14 +489,14 @@ WalkPlan pick_forward_walks(const Geom& g, const int32_t* cu_host)
 // Walks of 128 rows where lasp2_forward's gather anyway and all of these run at once: the last one then gathers half a walk more and walks
 // half as many rows (skew_walk ends after half a chunk there).  Forward, us, walks of 256 | 128: 16 heads x 300 16.5 | 12.5, x 1 024 21.1 | 17.7, x
 // 2 048 (256 workgroups) 28.5 | 26.0; 32 x 1 200 (320) 22.7 | 22.9; slots of 64, whose states take longer to write, 16 x 1 500 26.1 | 26.8;
-// with decay 8 x 500 20.6 | 16.8, 16 x 1 024 27.7 | 24.3, 16 x 2 048 41.0 | 38.3.
+// with decay 8 x 500 20.6 | 16.8, 16 x 1 024 27.7 | 24.3, 16 x 2 048 41.0 | 38.3.  Walks end with their slots, so the launch has its remainders too, and
+// these are counted: slots of 192 (there walks of 192) 16 x 1 000 (176) 19.6 | 16.2, 32 x 1 000 (352) 19.8 | 22.3, 16 x 1 920 (320) 27.1 | 25.6; slots
+// of 320 16 x 1 280 (240) 25.1 | 18.6, 16 x 2 048 (304) 25.8 | 24.9.
 WalkPlan in_halves(const Geom& g, const int32_t* cu_host, const WalkPlan& p)
 {
-    const int64_t longest = longest_sequence(g, cu_host);
-    if (p.start != Start::gather || g.n_seqs || g.L < 128 || longest <= 128 || forced_walk_slots(g) ||
-        (int64_t)g.G * slots_of(longest, 128) > cu_count())
-        return p;
-    return g.L > 128 ? WalkPlan{1, 128, Start::gather} : WalkPlan{1, 0, Start::gather};
+    if (p.start != Start::gather || g.n_seqs || g.L < 128 || g.N <= 128 || forced_walk_slots(g)) return p;
+    const WalkPlan half = {1, g.L > 128 ? 128 : 0, Start::gather};
+    return (int64_t)g.G * regroup(g, cu_host, half).T_s <= cu_count() ? half : p;   // (walks end with their slots)
 }
 
 // Slots per walk of the split-plane kernels, `nprob` workgroups per walk.  They work on chunks of 128

@@ -86,7 +86,9 @@ def test_heads_that_do_not_decay_are_summed_as_without_decay(G, N, L):
     assert err[1] <= 1.25 * err[0], (G, N, L, err)
 
 
-BOTH_SIDES = [(16, 2048, 128, 128), (17, 1930, 128, 256), (24, 1400, 128, 256), (32, 1024, 512, 128), (33, 1024, 512, 256), (40, 385, 4096, 128)]
+BOTH_SIDES = [(16, 2048, 128, 128), (17, 1930, 128, 256), (24, 1400, 128, 256), (32, 1024, 512, 128), (33, 1024, 512, 256), (40, 385, 4096, 128),
+              # walks end with their slots: 11 and 16 of a sequence's walks, not 8 and 12; 192 and 256 tokens are a slot, most of one
+              (16, 1000, 192, 128), (16, 1536, 192, 128), (16, 1600, 192, 192), (32, 1000, 192, 192), (16, 1600, 320, 128), (16, 2048, 320, 256)]
 
 
 def test_the_sides_of_256_workgroups():
