@@ -143,6 +143,31 @@ def test_rows_that_the_mask_keeps_from_a_nan_stay_finite(dtype, d):
 
 
 @pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_values_of_every_exponent_are_split(d):
+    """States of single rows, k^T v, with elements of one factor from 2^-126 to 2^126 and the other's so that the product is an
+    ordinary number.  Three planes hold all bits of a value above 2^-109, and of a smaller one those above 2^-133: half of
+    that lost, an error of 2^-134 / 2^e at most for values from 2^e on.  Products and sums: 2^-24 for the plane products that are
+    not formed, 2^-24 twice for the sum of the small ones and of all."""
+    import torch
+    from paper_2502_07563_amd import binding as bd
+    e = torch.arange(-126, 127)
+    N, gen = len(e), torch.Generator().manual_seed(d)
+    sign = lambda: torch.where(torch.rand(1, 2, N, d, generator=gen) < 0.5, -1.0, 1.0)
+    a, b = ((1 + torch.rand(1, 2, N, d, generator=gen)) * sign() for _ in range(2))
+    small = torch.ldexp(a, e[:, None])
+    other = torch.ldexp(b, (-e).clamp(-20, 100)[:, None])
+    limit = 3 * 2.0 ** -24 + 2.0 ** (-134.0 - e.double())
+    p = bd.Problem(1, 2, N, d, 1, 1, "f32")
+    M = bd.alloc_states(p)
+    for K, V in ((small, other), (other, small)):
+        bd.lasp2_chunk_states(p, K.cuda(), V.cuda(), M)
+        want = K.double()[..., :, None] * V.double()[..., None, :]
+        err = ((M.cpu().double() - want) / want).abs().amax((0, 1, 3, 4))
+        bad = torch.nonzero(err > limit).flatten()
+        assert not len(bad), [(int(e[i]), err[i].item(), limit[i].item()) for i in bad[:5]]
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
 def test_weighted_rows_are_split_exactly(d):
     """With decay a row is multiplied by its weight and split into planes, which hold more bits than fp32: the state of one row of
     weight w < 1 is as close to w k^T v as that of a row of weight 1 to k^T v (the weight itself, the same for all elements, is fitted).
