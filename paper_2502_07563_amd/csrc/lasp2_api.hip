@@ -517,17 +517,17 @@ int pick_planes_slots(const Geom& g, const int32_t* cu_host, int nprob)
     return ws;
 }
 
-// The same for heads of 64 in lasp2_forward and the backward, which build the states: one per walk (the forward writes the others in
+// The same for heads of 64 in lasp2_forward and the backward, which build the states: one per walk (the walks write the others in
 // passing, planes_emit).  A walk starts with the rows of its predecessors read once more and one state each written, combined
 // and read, and holds a third of a CU (half in fp32); so about two walks per CU, and not below the length under which states cost
 // more than CUs without work.
-//   - Layer forward | backward, us, tokens per walk: bf16, 64 x 4001 64 tokens 84 | 139, 128 75 | 119, 256 62 | 106, 512 57 | 97,
-//     1024 60 | 94, 2048 78 | 124; 16 x 4000 128 28 | 40, 256 27 | 35, 512 29 | 42; fp32, 64 x 4001 128 135 | 269, 256 130 | 259, 512
-//     125 | 255, 1024 140 | 262; 16 x 4000 64 54 | 81, 128 45 | 75, 256 46 | 77, 512 57 | 87.
+//   - Layer forward | backward, us, tokens per walk, slots of 64: bf16, 64 x 4001 64 tokens 82 | 140, 128 69 | 120, 256 60 | 110, 512 54 | 103,
+//     1024 60 | 104, 2048 84 | 150; 16 x 4000 64 36 | 46, 128 28 | 41, 256 27 | 36, 512 31 | 44; 16 x 2000 128 22 | 26, 256 22 | 28; fp32, 64 x 4001
+//     128 134 | 264, 256 124 | 255, 512 119 | 246, 1024 137 | 255; 16 x 4000 64 54 | 78, 128 43 | 73, 256 43 | 72, 512 53 | 85.
 //   - Short sequences whole, in one launch without states (in segments that add up the rows before them, where CUs are free),
-//     three launches | one, forward and backward: bf16, 16 x 1000 20 + 26 | 19 + 22, 32 x 500 20 + 27 | 15 + 21, 64 x 1000 25 + 33 | 29 + 35,
-//     128 x 500 25 + 33 | 19 + 30, 256 x 1000 52 + 96 | 42 + 78; with decay 16 x 1000 23 + 28 | 34 + 49; fp32 4 x 1000 21 + 27 | 36 + 37,
-//     128 x 500 40 + 71 | 38 + 66, 256 x 1000 124 + 253 | 104 + 228.
+//     three launches | one, forward and backward: bf16, 16 x 600 16 + 17 | 14 + 15, 40 x 768 19 + 24 | 17 + 22, 8 x 768 14 + 16 | 16 + 16, 16 x 1000
+//     17 + 20 | 19 + 22, 128 x 500 24 + 35 | 17 + 32, 256 x 1000 66 + 119 | 43 + 87; with decay 4 x 320 15 + 16 | 13 + 13, 16 x 384 15 + 17 | 15 + 17, 16 x 512
+//     16 + 17 | 18 + 21, 100 x 384 30 + 38 | 21 + 37; fp32 4 x 1000 19 + 19 | 37 + 37, 128 x 500 39 + 68 | 33 + 64, 256 x 1000 132 + 262 | 102 + 227.
 int pick_planes64_slots(const Geom& g, const int32_t* cu_host, int dtype, bool backward)
 {
     const int64_t longest = longest_sequence(g, cu_host);
@@ -536,9 +536,10 @@ int pick_planes64_slots(const Geom& g, const int32_t* cu_host, int dtype, bool b
     const bool light = dtype == LASP2_BF16 && !g.decay;
     const int64_t slots = slots_of(longest, g.L), cus = cu_count(), ws_max = std::min(slots, max_walk_slots(g));
     if (g.n_seqs == 0 && longest <= 1024 && slots == ws_max &&
-        (g.G >= cus / 2 || (light && g.G <= cus / 8) || (dtype == LASP2_BF16 && longest <= 512)))
+        (g.G >= cus / 2 || longest <= (light ? 768 : dtype == LASP2_BF16 ? 384 : 0)))
         return (int)slots;
-    const int64_t tokens = (int64_t)g.G * g.N, target = std::max<int64_t>(light ? 256 : 128, std::min<int64_t>(1024, tokens / (backward && light ? cus : 2 * cus)));
+    const int64_t tokens = (int64_t)g.G * g.N, least = light && tokens >= 160 * cus ? 256 : 128;
+    const int64_t target = std::max<int64_t>(least, std::min<int64_t>(1024, tokens / (backward && light ? cus : 2 * cus)));
     int64_t ws = 1;
     while (ws * g.L < target && 2 * ws <= ws_max && !(backward && tokens * 3 < 2 * ws * g.L * cus)) ws *= 2;
     return (int)ws;

@@ -219,9 +219,15 @@ def test_walks_of_heads_of_64(monkeypatch):
     bf = dict(d=64, dtype=B.LASP2_BF16)
     for kw, fwd, forward, bwd in (
             (dict(bf, B=4, H=16, N=4001), 1, 4, 8),              # 256 064 rows, two walks a CU forward, one backward
-            (dict(bf, H=16, N=1000), 1, 8, 8),                   # short sequences whole
-            (dict(bf, B=1, H=4, N=500, **decay), 1, 4, 4),
-            (dict(bf, B=1, H=16, N=1000, **decay), 1, 1, 1),     # ... not where rows have more work
+            (dict(bf, H=16, N=16000, C=64), 2, 8, 16),
+            (dict(bf, H=16, N=2000, C=64), 2, 2, 2),             # too little work to be worth fewer walks than CUs
+            (dict(bf, H=16, N=768), 1, 6, 6),                    # short sequences whole
+            (dict(bf, H=16, N=769), 1, 1, 1),
+            (dict(bf, B=1, H=4, N=384, **decay), 1, 3, 3),       # ... less long where rows have more work
+            (dict(bf, B=1, H=4, N=385, **decay), 1, 1, 1),
+            (dict(H=2, N=384, d=64), 1, 1, 1),
+            (dict(H=128, N=1024, d=64), 1, 8, 8),                # ... longer ones where there is one for two CUs
+            (dict(H=128, N=1025, d=64), 1, 2, 2),
             (dict(H=2, N=1024, d=64), 1, 1, 1),
             (dict(bf, B=4, H=16, N=8000, L=640), 1, 2, 2),       # the first number of slots that has 1 024 tokens or more
             (dict(bf, B=4, H=16, N=8000, C=64), 2, 16, 16)):

@@ -64,7 +64,7 @@ def test_walks(monkeypatch, dtype, lam, walk):
 def test_many_groups(dtype):
     """Both sides of the choice: whole sequences in one launch, walks of several slots, a launch per kind; two or one
     workgroups per CU, segments of one chunk and of more."""
-    for G, N, L in ((16, 1000, 64), (48, 512, 64), (48, 513, 64), (130, 300, 128), (60, 1030, 64), (16, 2000, 512), (130, 1025, 64)):
+    for G, N, L in ((16, 1000, 64), (48, 512, 64), (48, 513, 64), (48, 768, 64), (48, 769, 64), (130, 300, 128), (60, 1030, 64), (16, 2000, 512), (130, 1025, 64)):
         _check(dtype, G, N, L)
 
 
