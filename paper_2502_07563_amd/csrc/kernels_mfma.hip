@@ -1241,8 +1241,9 @@ __device__ __forceinline__ void skew_walk(const Geom& g, const AttnProblem& pr, 
     zero_out();
     using std::integral_constant;
     // CUT: a last chunk without rows in its second half, and with no state to write inside it, ends after block 1 (below): a walk
-    // of 128 rows that gathers 128 before it takes 12.5 us, with two blocks of zeros 15.  (Not in the kernels that walk whole slots, where it
-    // is rare and its code costs 3 %.)
+    // of 128 rows that gathers 128 before it takes 12.5 us, with two blocks of zeros 15.  (In the forward kernels whose walks are given their
+    // states it is rare and its code costs 3 %: not there.  In the pair's launch, for dQ, it neither costs nor gains that much: 64 x 1 200 in
+    // slots of 64 55.6 us with it, 55.8 without, 16 x 262 144, 32 x 131 072 in 40 documents and 256 x 8 192 within 0.1 %.)
     const bool cut = CUT && len - (nch - 1) * C <= C / 2 &&
                      !(EMIT && pr.emit && ((nch - 1) * BPC + 1) * KB < len && ((nch - 1) * BPC + 1) % eblk == 0);
     const int nwhole = cut ? nch - 1 : nch;

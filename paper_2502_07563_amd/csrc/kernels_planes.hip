@@ -376,17 +376,18 @@ __device__ __forceinline__ void store4(__hip_bfloat16* p, float a, float b, floa
 // are written to LDS once per chunk, as rows of the state's second index.
 // With d = 128 the result is formed transposed too: a lane stores four columns of its row at a time, and the 64 addresses and
 // bounds of single elements no longer compete for the registers (forward | backward launch, 16 x 1800 x 128 in fp32, us: 73 -> 63 |
-// 207 -> 179; scratch 416 -> 352 bytes).  Smaller heads lose by it (bf16, 64 x 4001 x 64: 50 -> 53 | 124 -> 128): their
-// stores, rows of 32 to 256 bytes, are better made by column.
+// 207 -> 179; scratch 416 -> 352 bytes).  Heads of 16 and 32 store by column (64 x 4001 x 32 by row, forward | backward, us: fp32 68 -> 68 |
+// 119 -> 114, bf16 43 -> 43 | 65 -> 64).
 // A slot may be cut into `nseg` segments of `cps` chunks, a workgroup each: a workgroup first adds up
 // the states of the chunks before its own (a fifth of a chunk's work), which is worth it while the
 // launch leaves CUs idle.
 // Bounds: the split's vector instructions next to the matrix products in fp32, latency and HBM in bf16.
-// Against one scalar fp32 product per element (and a load for each), layer forward + backward: bf16,
-// 64 groups x 4001 x 64: 4200 -> 230 us (the forward launch 50 us, 3.2 TB/s); fp32, 2 x 1024 x 64: 1190 -> 58 us.
+// Against one scalar fp32 product per element (and a load for each), layer forward + backward, when it took heads of 64 too: bf16,
+// 64 groups x 4001 x 64: 4200 -> 230 us; fp32, 2 x 1024 x 64: 1190 -> 58 us.  Now 64 x 4001 x 32: bf16 108 us, fp32 187.
 template <typename T, int D, bool DECAY>
 __global__ __launch_bounds__(kThr, D == 128 ? 1 : 2) void attn_planes_kernel(Geom g, PlanesProblems probs, PlanesGrid pg)
 {
+    static_assert(D != 64, "heads of 64: attn64_planes_kernel");
     typedef AttnLds<T, D, DECAY> LD;
     typedef typename LD::Stage Stage;
     constexpr int DP = LD::DP, NP = planes_of<T>::n, NT = DP / 32, KS = D / 16, NTL = Tiles<NT>::n;
@@ -602,13 +603,14 @@ __device__ __forceinline__ void frag_at(const char* tile, int plane_bytes, uint3
 // ---- The same for heads of 64 ----
 // Chunks of 64 rows; a wave has 32 of them and 32 of the 64 columns: the scores of its rows are formed by two waves, but a
 // chunk is three score tiles instead of ten per 128 rows, the longest of a wave two instead of four, and accumulators and
-// state take a third of the registers: three workgroups per CU in bf16 (48 KB of LDS and 168 registers each) where there were
-// two; fp32 and decay have two.  Walks of several slots write the states of the slots inside them (emit).  bf16 rows go out through
+// state take less than half of the registers: three workgroups per CU in bf16 (48 KB of LDS and 168 registers each) where there were
+// two; fp32 and decay have two.  Walks of several slots write the states of the slots inside them (emit: prefixes in the forward,
+// suffixes by the backward's dV).  bf16 rows go out through
 // LDS, 128 bytes at a time.  Bounds: the chain of a chunk (snapshot, stage, barrier, state product, two tiles, barrier: about
-// 8000 clocks, 3000 of them the tiles), of which a CU runs two or three side by side.  With walks as pick_planes_slots has
-// them, us, against 128-row chunks in four waves of 32 rows and all columns: bf16, 64 x 4001, layer forward 81 -> 57, backward
-// 149 -> 97 (the launches 47 -> 35 and 119 -> 80, 4.7 and 3.8 TB/s); 16 x 4000 29 -> 27, 48 -> 36; fp32, 64 x 4001 146 -> 122, 276
-// -> 257; 2 x 1024 25 -> 21, 29 -> 27.
+// 8000 clocks, 3000 of them the tiles), of which a CU runs two or three side by side.  With walks as pick_planes64_slots has
+// them and slots of 128, us, against 128-row chunks in four waves of 32 rows and all columns: bf16, 64 x 4001, layer forward 77 -> 51, backward
+// 147 -> 96 (the launches 47 -> 38 and 119 -> 87, 4.3 and 3.0 TB/s); 16 x 4000 28 -> 25, 46 -> 35; fp32, 64 x 4001 137 -> 113, 260
+// -> 241; 2 x 1024 25 -> 20, 25 -> 20.
 template <typename T>
 struct Attn64Lds {
     typedef PairStage<T, 64, 64, 64, kThr> Stage;
