@@ -523,7 +523,8 @@ int pick_planes_slots(const Geom& g, const int32_t* cu_host, int nprob)
 // more than CUs without work.
 //   - Layer forward | backward, us, tokens per walk, slots of 64: bf16, 64 x 4001 64 tokens 82 | 140, 128 69 | 120, 256 60 | 110, 512 54 | 103,
 //     1024 60 | 104, 2048 84 | 150; 16 x 4000 64 36 | 46, 128 28 | 41, 256 27 | 36, 512 31 | 44; 16 x 2000 128 22 | 26, 256 22 | 28; fp32, 64 x 4001
-//     128 134 | 264, 256 124 | 255, 512 119 | 246, 1024 137 | 255; 16 x 4000 64 54 | 78, 128 43 | 73, 256 43 | 72, 512 53 | 85.
+//     128 134 | 264, 256 124 | 255, 512 119 | 246, 1024 137 | 255; 16 x 4000 64 54 | 78, 128 43 | 73, 256 43 | 72, 512 53 | 85; 4 x 1000 64 19 | 19,
+//     128 20 | 21; with decay 16 x 512 64 16 | 17, 128 18 | 21.
 //   - Short sequences whole, in one launch without states (in segments that add up the rows before them, where CUs are free),
 //     three launches | one, forward and backward: bf16, 16 x 600 16 + 17 | 14 + 15, 40 x 768 19 + 24 | 17 + 22, 8 x 768 14 + 16 | 16 + 16, 16 x 1000
 //     17 + 20 | 19 + 22, 128 x 500 24 + 35 | 17 + 32, 256 x 1000 66 + 119 | 43 + 87; with decay 4 x 320 15 + 16 | 13 + 13, 16 x 384 15 + 17 | 15 + 17, 16 x 512
@@ -538,7 +539,7 @@ int pick_planes64_slots(const Geom& g, const int32_t* cu_host, int dtype, bool b
     if (g.n_seqs == 0 && longest <= 1024 && slots == ws_max &&
         (g.G >= cus / 2 || longest <= (light ? 768 : dtype == LASP2_BF16 ? 384 : 0)))
         return (int)slots;
-    const int64_t tokens = (int64_t)g.G * g.N, least = light && tokens >= 160 * cus ? 256 : 128;
+    const int64_t tokens = (int64_t)g.G * g.N, least = light ? (tokens >= 160 * cus ? 256 : 128) : tokens >= 64 * cus ? 128 : 64;
     const int64_t target = std::max<int64_t>(least, std::min<int64_t>(1024, tokens / (backward && light ? cus : 2 * cus)));
     int64_t ws = 1;
     while (ws * g.L < target && 2 * ws <= ws_max && !(backward && tokens * 3 < 2 * ws * g.L * cus)) ws *= 2;

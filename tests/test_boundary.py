@@ -225,6 +225,8 @@ def test_walks_of_heads_of_64(monkeypatch):
             (dict(bf, H=16, N=769), 1, 1, 1),
             (dict(bf, B=1, H=4, N=384, **decay), 1, 3, 3),       # ... less long where rows have more work
             (dict(bf, B=1, H=4, N=385, **decay), 1, 1, 1),
+            (dict(bf, B=1, H=16, N=512, C=64, **decay), 1, 1, 1),
+            (dict(bf, B=1, H=16, N=1024, C=64, **decay), 1, 2, 2),
             (dict(H=2, N=384, d=64), 1, 1, 1),
             (dict(H=128, N=1024, d=64), 1, 8, 8),                # ... longer ones where there is one for two CUs
             (dict(H=128, N=1025, d=64), 1, 2, 2),
