@@ -156,7 +156,7 @@ int lasp2_num_slots(const lasp2_desc_t* desc, int64_t* T_s);
  *   Everything else: only where L is not a multiple of the kernels' 128-row
  *     chunk, so that single slots would leave chunks partly empty; 1 otherwise.
  *     With d = 64 lasp2_attn_bwd (and lasp2_forward) takes walks by the work
- *     that a launch has, of 128 tokens and more, or short sequences whole.
+ *     that a launch has, whatever L is, or short sequences whole.
  *     lasp2_attn_bwd gives dM_{t+1:T} of every slot (see there).
  * The environment variable LASP2_WALK_SLOTS (a positive integer, read at every
  * call) overrides the choice where there is one; 1 gives one walk per slot.
