@@ -1957,35 +1957,41 @@ __device__ __forceinline__ void gather_state(const char* X, const char* Y, size_
         fetch(0, 0, xA, yA);
     }
     const float wfull = DECAY ? __builtin_amdgcn_exp2f((float)KB * l2) : 1.f;
-    for (int i = 0; i < nst; ++i) {
-        // (the last rows that count from the end may be fewer; nothing is there yet to age at the first stage)
-        if (DECAY && i) age(anchor_start || (i + 1) * KB <= ntok ? wfull : __builtin_amdgcn_exp2f((float)(ntok - i * KB) * l2));
-        product(xA, yA, 0, 0);
-        SCHED_FENCE();
-        fetch(i, 1, xB, yB);
-        SCHED_FENCE();
-        product(xA, yA, 0, 1);
-        SCHED_FENCE();
-        if (i && i + NST - 1 < nst) issue(i + NST - 1, 1);
-        SCHED_FENCE();
-        product(xA, yA, 1, 0);
-        product(xA, yA, 1, 1);
-        SCHED_FENCE();
-        if (i + 1 < nst) {
-            landed(i + 1, min(i + NST, nst) - 1);
-            __syncthreads();   // stage i + 1 complete in LDS; every wave has read stage i, whose place stage i + 4 takes
-            fetch(i + 1, 0, xA, yA);
+    // (a loop for either kind of head: what it does is not asked at every stage)
+    auto stages = [&](auto ages_c) __attribute__((always_inline)) {
+        constexpr bool ages = decltype(ages_c)::value;
+        for (int i = 0; i < nst; ++i) {
+            // (the last rows that count from the end may be fewer; nothing is there yet to age at the first stage)
+            if (ages && i) age(anchor_start || (i + 1) * KB <= ntok ? wfull : __builtin_amdgcn_exp2f((float)(ntok - i * KB) * l2));
+            product(xA, yA, 0, 0);
+            SCHED_FENCE();
+            fetch(i, 1, xB, yB);
+            SCHED_FENCE();
+            product(xA, yA, 0, 1);
+            SCHED_FENCE();
+            if (i && i + NST - 1 < nst) issue(i + NST - 1, 1);
+            SCHED_FENCE();
+            product(xA, yA, 1, 0);
+            product(xA, yA, 1, 1);
+            SCHED_FENCE();
+            if (i + 1 < nst) {
+                landed(i + 1, min(i + NST, nst) - 1);
+                __syncthreads();   // stage i + 1 complete in LDS; every wave has read stage i, whose place stage i + 4 takes
+                fetch(i + 1, 0, xA, yA);
+            }
+            SCHED_FENCE();
+            product(xB, yB, 0, 0);
+            product(xB, yB, 0, 1);
+            SCHED_FENCE();
+            if (i + NST < nst) issue(i + NST, 0);
+            SCHED_FENCE();
+            product(xB, yB, 1, 0);
+            product(xB, yB, 1, 1);
+            if (!ages && (DECAY ? i & 1 : (i & 7) == 7)) flush();
         }
-        SCHED_FENCE();
-        product(xB, yB, 0, 0);
-        product(xB, yB, 0, 1);
-        SCHED_FENCE();
-        if (i + NST < nst) issue(i + NST, 0);
-        SCHED_FENCE();
-        product(xB, yB, 1, 0);
-        product(xB, yB, 1, 1);
-        if (DECAY ? sums && (i & 1) : (i & 7) == 7) flush();
-    }
+    };
+    if (!sums) stages(std::integral_constant<bool, DECAY>{});
+    else stages(std::integral_constant<bool, false>{});
     if (sums) {
 #pragma unroll
         for (int a = 0; a < 2; ++a)

@@ -102,11 +102,11 @@ def test_no_compiler_placed_vmcnt_wait_in_the_walk(isa):
 # anti-causal pair's walk: dV / dK rows x early / late row blocks, plus the causal walk's two halves)
 SKEW = (("attn_skew_mfma_kernelILb0E", 4), ("attn_skew_mfma_kernelILb1E", 4), ("attn_bwd_pair_mfma_kernel", 6),
         ("attn_fwd_emit_mfma_kernelILb0E", 2), ("attn_fwd_emit_mfma_kernelILb1E", 2),
-        # one loop more for each place where rows are gathered before a walk
+        # one loop more for each place where rows are gathered before a walk, with decay two (heads whose factor is 1)
         ("attn_fwd_direct_mfma_kernel", 3), ("attn_bwd_direct_mfma_kernel", 8),
-        ("attn_decay_fwd_direct_kernel", 3), ("attn_decay_bwd_direct_kernel", 6))
+        ("attn_decay_fwd_direct_kernel", 4), ("attn_decay_bwd_direct_kernel", 8))
 GATHERS = {"attn_fwd_direct_mfma_kernel": 1, "attn_bwd_direct_mfma_kernel": 2,
-           "attn_decay_fwd_direct_kernel": 1, "attn_decay_bwd_direct_kernel": 2}   # ... of them
+           "attn_decay_fwd_direct_kernel": 2, "attn_decay_bwd_direct_kernel": 4}   # ... of them
 
 
 def _skew_blocks(lines, inst):
